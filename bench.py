@@ -444,8 +444,8 @@ def main():
             nbytes = rows * ROW_VISIT_BYTES
             gbs = nbytes / (avg_ms * 1e-3) / 1e9 if launches else None
             name = ROOFLINE_KERNELS[kind]
-            if top >= 0:  # the specialised engine's instance: <precision, top level k, last LDS level k>
-                name = f"{name[:-1]}, {levels[top]['k']}, {levels[eng['lds_level']]['k']}>"
+            if top >= 0:  # the specialised engine's instance: <precision, top level k>
+                name = f"{name[:-1]}, {levels[top]['k']}>"
             return {"bound": "hbm", "kernel": name, "achieved": gbs, "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": (gbs / HBM_PEAK_GBS) if gbs else None,
                     "traffic": traffic_from_profiles(kind, args.workload),

@@ -238,8 +238,8 @@ amg_status amg_kernel_timing_enable(amg_hierarchy *h, const char *name);
 amg_status amg_kernel_timing_read(amg_hierarchy *h, int64_t *launches, double *total_ms, double *bytes_per_launch);
 
 /* Configuration of the persistent small-level workgroup for a precision: the hierarchy level index of its top
- * (-1 = not used), the first level index whose operators live in LDS, the length of its step list and its dynamic
- * LDS bytes. */
+ * (-1 = not used), the first level index whose operators stay on chip for a launch (registers or LDS), the number of
+ * its steps and its dynamic LDS bytes. */
 amg_status amg_engine_info(const amg_hierarchy *h, int32_t precision, int32_t *top_level, int32_t *lds_level,
                            int32_t *steps, size_t *lds_bytes);
 

@@ -7,19 +7,38 @@
 // constant:
 //  - the coarsest level is the 64-cell level k = 3, one smoothing sweep, two inner steps of Algorithm 2.1;
 //  - on the engine's levels no coupling reaches beyond one cell, so no two cells of one color are coupled;
-//  - the top level is k = KT (4, 5 or 6); the levels k <= KL keep their operators and vectors in LDS. A top level
-//    above them is held in registers: each thread owns TR rows of every color block of it (k = 6 in FP32: 512
-//    threads, two rows each; k = 5 in FP64: 256 threads, one row each) and keeps their nine operator entries and
-//    their entries of g, e, r and q0 for the whole launch; only p0 and p1, whose neighbours every color phase
-//    gathers, are in LDS. The engine then reads global memory once, in its prologue.
-// A step on level k runs on the threads j < 4^(k-1): thread j owns row j of each of the four color blocks, so the
-// color of every row a thread touches is a compile-time constant and the neighbour indices of Section 4.4 fold to a
-// few integer operations; no level table, no loop over a run-time row count. The whole of B~ on the 256-cell level
-// k = 4, with the coarsest solve below it, runs in a single wavefront: its sub-steps (one row per lane per color
-// block) are ordered by the wavefront's in-order LDS accesses, with no workgroup barrier between them.
+//  - the top level is k = KT (4, 5 or 6).
 //
-// The arithmetic of every value is that of the interpreter (same expressions, same order of the nine slot terms);
-// only inner products use a different fixed reduction tree.
+// What bounds it is the latency of its chain of steps on one CU, so a step is kept to an LDS round trip, the nine
+// products of a row and a barrier:
+//  - a thread owns whole super-cells (the four cells of one parent, one per color) of a level, two on the 4,096-cell
+//    level and one below, and keeps their operator rows, the reciprocals of their diagonals and their entries of
+//    f, q0, p0 and the current B^ output u in registers for the whole launch. Global memory is read once, in the
+//    prologue. The 1,024-cell level belongs to wavefronts 4 to 7 and the 256-cell level to wavefront 0 of the
+//    512-thread workgroup (k = 6), so the two share one set of registers;
+//  - LDS holds only what neighbours read: u, one plane per color over the super-cells in row-major order with a ring
+//    of zeros around the grid. A neighbour is then a compile-time distance from the super-cell's own place, an
+//    immediate offset of the LDS load: no index arithmetic and no test for the grid's edge (an absent slot holds 0
+//    and reads the ring or a cell of the ring's row padding). The row stride is 8 mod 16 super-cells, so that a
+//    wavefront's 8 x 8 Morton block of super-cells touches every bank alike;
+//  - the presmoothing sweep starts from zero, so a phase skips the slots of colors not yet relaxed (their products
+//    are zero); the prolongation is folded into the first post-smoothing phase, which reads u + P e_c of its
+//    neighbours formed from the presmoothing planes and the coarse correction's plane and writes a second set of
+//    planes; quotients by the diagonal take Markstein's correction of numerator x reciprocal (the correctly rounded
+//    quotient for a correctly rounded reciprocal) in three instructions;
+//  - A p1 is formed for the second inner step instead of A (p1 + beta p0): with (p0, q0), (g, p0), (p1, q0),
+//    (p1, A p1), (r, p1) and (r, p0) Algorithm 2.1's beta and alpha1 follow, so a level needs one reduction per inner
+//    step. The error of one FP32 preconditioner application against FP64, geometric mean over 120 systems of 256 to
+//    1,044,484 unknowns, is 1.39e-6 this way and 1.43e-6 with A (p1 + beta p0);
+//  - the whole of B~ on the 256-cell level k = 4, with the coarsest solve below it, runs in a single wavefront: its
+//    steps are ordered by the wavefront's in-order LDS accesses, with no workgroup barrier between them.
+//  - the FP64 coarsest solve is shared by four wavefronts, the three others holding their columns of the inverse in
+//    registers that no level of theirs uses.
+// Before, with operators and vectors of the levels below the top in LDS, neighbours by index arithmetic, two
+// reductions per second inner step and the coarsest solve in one wavefront, a launch took 71.6 us (FP32, k = 6) and
+// 27.3 us (FP64, k = 5); now 31.3 and 15.1 us. Of the FP32 launch's 39 us with a clock read after every step, the
+// prologue takes 4, the 4,096-cell level 9, the 1,024-cell level 9 and the eight B^ of the 256-cell level 17, where a
+// color phase is 0.1 us (one LDS round trip, nine products), the coarsest solve 0.45 and a reduction 0.25 us.
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
@@ -36,94 +55,70 @@ namespace qa {
 
 namespace {
 
-constexpr int kFeMaxThreads = 1024;
-constexpr int kFeMaxWaves = kFeMaxThreads / 64;
-constexpr int kFeMaxOps = 256;
 constexpr int kFeCoarse = 64;                 // cells of the coarsest level k = 3
-constexpr int kFeAinvBytes = kFeCoarse * kFeCoarse * 8;
-
-enum FeType : int { FE_FIRST2 = 0, FE_GS, FE_RES, FE_PROLONG, FE_SPMV0, FE_SPMV1, FE_UPDATE2, FE_BTILDE_W };
-// step word: type | level << 3 | color << 5 | (second B^ of B~) << 7
-constexpr int fe_code(int type, int lvl, int color, int b2) { return type | (lvl << 3) | (color << 5) | (b2 << 7); }
-
-// work vectors of a level: Algorithm 2.1's right-hand side g, result e, residual r, directions p0, p1 (the B^
-// outputs) and q0 = A p0
-enum FeVec : int { V_G = 0, V_E, V_R, V_P0, V_Q0, V_P1, V_COUNT };
-// scalars of a level (LDS, written by thread 0 after a reduction). Algorithm 2.1's stop condition (p0, q0) <= 0 is
-// tested on d0 = (p0, q0) itself wherever it is needed rather than stored as a flag: the flag's store, a boolean
-// materialised under a one-lane branch, was compiled to a select on a stale scalar condition code.
-enum FeScalar : int { S_D0 = 0, S_A0, S_BETA, S_A1 };
-
-constexpr int popc(unsigned v) { return v ? static_cast<int>(v & 1u) + popc(v >> 1) : 0; }
-
-// LDS layout of one configuration. Byte 0: the coarsest inverse (64 x 64 FP64). Then, in units of T: for every LDS
-// level down to k = 4 its operator (9 x n, slot-major, color-major rows) and its six vectors; the coarsest level's
-// g and e; and, for a top level held in registers, its p0 and p1.
-template <class T, int KT, int KL>
-struct FeLayout {
-  static constexpr int lw = KT - 4;            // level index of k = 4 (B~ in one wavefront)
-  static constexpr int first_lds = KT - KL;    // first level index in LDS
-  __host__ __device__ static constexpr int n(int i) { return 1 << (2 * (KT - i)); }
-  __host__ __device__ static constexpr bool lds(int i) { return i >= first_lds; }
-  // top level in registers (TR rows of each color block per thread), else 256 threads
-  static constexpr bool reg_top = !lds(0);
-  static constexpr int TR = (reg_top && n(0) > 1024) ? 2 : 1;
-  static constexpr int threads = reg_top ? n(0) / 4 / TR : 256;
-  // vectors of a register top level held in LDS: the B^ outputs p0, p1, whose nine neighbours every color phase
-  // gathers
-  static constexpr unsigned lvec_mask = reg_top ? ((1u << V_P0) | (1u << V_P1)) : 0u;
-  __host__ __device__ static constexpr int ax_off(int i) {
-    int o = 0;
-    for (int j = first_lds; j < i; j++) o += 15 * n(j);
-    return o;
-  }
-  __host__ __device__ static constexpr int vec_off(int i) { return ax_off(i) + 9 * n(i); }
-  static constexpr int c3_off = ax_off(lw + 1);
-  static constexpr int lvec_off = c3_off + 2 * kFeCoarse;
-  static constexpr int t_units = lvec_off + popc(lvec_mask) * n(0);
-  static constexpr size_t bytes = kFeAinvBytes + sizeof(T) * static_cast<size_t>(t_units);
-};
-
-// registers of a top level: thread t's rows j + c 4^(k-1) (c = 0..3, j = t + i NT for i < TR), their nine operator
-// entries (slot order) and their entries of g, e, r, q0
-template <class T, int TR>
-struct FeTop {
-  T a[TR][4][9];
-  T v[TR][4][4];
-};
-__host__ __device__ constexpr int fe_rv(int v) { return v == V_G ? 0 : v == V_E ? 1 : v == V_R ? 2 : 3; }
-
-template <class T>
-struct FeArgs {
-  int nops;
-  const int32_t *ops;
-  const double *ainv;        // coarsest inverse, 64 x 64, storage numbering (bitwise symmetric: Y^t Y in one order)
-  const T *ax[4];            // 9 x n operator of each engine level (global)
-  T *gv[V_COUNT];            // the top level's work vectors in global memory (g and e are read and written there)
-};
+constexpr int kFeRedWaves = 8;                // wavefronts of the largest level
 
 template <int C>
 using IC = std::integral_constant<int, C>;
 
-// the thread index, opaque to the optimiser: row and neighbour indices derived from it are formed inside each step
-// rather than hoisted out of the step loop, where they would stay live across the whole launch
-__device__ __forceinline__ int fe_tid() {
-  int t;
-  asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(static_cast<int>(threadIdx.x)));
-  return t;
-}
+// neighbour offsets of Section 4.4 as constants: self, E, NE, N, NW, W, SW, S, SE
+constexpr int fe_dx(int s) { return (s == 1 || s == 2 || s == 8) ? 1 : ((s == 4 || s == 5 || s == 6) ? -1 : 0); }
+constexpr int fe_dy(int s) { return (s == 2 || s == 3 || s == 4) ? 1 : ((s == 6 || s == 7 || s == 8) ? -1 : 0); }
 
-// f(j) for the rows j < N4 of a color block, thread j owning j, j + NT, ... (compile-time trip count)
-template <int N4, int NT, class F>
-__device__ __forceinline__ void for_rows(F f) {
-  constexpr int trips = (N4 + NT - 1) / NT;
-  const int t0 = fe_tid();
-#pragma unroll 1
-  for (int it = 0; it < trips; it++) {
-    const int j = t0 + it * NT;
-    if (N4 % NT == 0 || j < N4) f(j);
+// the slot S neighbour of the color-C cell of a super-cell: its color and the offset of its super-cell
+template <int C, int S>
+struct FeNbr {
+  static constexpr int ux = (C & 1) + fe_dx(S), uy = (C >> 1) + fe_dy(S);
+  static constexpr int color = (ux & 1) | ((uy & 1) << 1);
+  static constexpr int ox = ux < 0 ? -1 : (ux > 1 ? 1 : 0), oy = uy < 0 ? -1 : (uy > 1 ? 1 : 0);
+};
+
+// geometry of level k: S x S super-cells, padded row stride P, cells per plane PP
+template <int K>
+struct FeGeo {
+  static constexpr int S = 1 << (K - 1), N4 = S * S, N = 4 * N4;
+  static constexpr int P = K == 6 ? 40 : 24;
+  static constexpr int PP = (S + 2) * P;
+};
+
+// LDS of one configuration. In doubles: the first 16 columns of the coarsest inverse (pairs of entries of a lane's row
+// side by side), the coarsest right-hand side, the helpers' partial sums and the wavefront sums of the reductions. Then
+// in units of T, for every level k = KT .. 4: the presmoothing planes (4), the post-smoothing planes (4) and the plane
+// of the next level's correction, and the right-hand side handed to the next level (k > 4; color-major).
+template <int KT>
+struct FeLayout {
+  static constexpr int kAinv = 0, kG3 = 16 * kFeCoarse, kPart = kG3 + kFeCoarse, kRed = kPart + 4 * kFeCoarse,
+                       kDoubles = kRed + 2 * 4 * kFeRedWaves;
+  __host__ __device__ static constexpr int planes(int k) {  // offset of level k's planes
+    int o = 0;
+    if (k < 6 && KT >= 6) o += 9 * FeGeo<6>::PP + FeGeo<5>::N;
+    if (k < 5 && KT >= 5) o += 9 * FeGeo<5>::PP + FeGeo<4>::N;
+    return o;
   }
-}
+  static constexpr int t_units = planes(4) + 9 * FeGeo<4>::PP;
+  static constexpr int TR = KT == 6 ? 2 : 1;               // super-cells per thread of the top level
+  static constexpr int threads = KT == 6 ? 512 : KT == 5 ? 320 : 256;
+  template <class T>
+  static constexpr size_t bytes() {
+    return sizeof(double) * kDoubles + sizeof(T) * static_cast<size_t>(t_units);
+  }
+};
+
+// a thread's super-cells of one level
+template <class T, int TR>
+struct FeRows {
+  T a[TR][4][9];   // operator rows by color, slot order
+  T rd[TR][4];     // 1 / diagonal
+  T f[TR][4], q0[TR][4], p0[TR][4], u[TR][4];
+};
+
+template <class T>
+struct FeArgs {
+  const double *ainv;        // coarsest inverse, 64 x 64, storage numbering (bitwise symmetric: Y^t Y in one order)
+  const T *ax[3];            // 9 x n operator of each engine level from the top down (global)
+  const T *g;                // the top level's right-hand side and result (global)
+  T *e;
+};
 
 template <class F>
 __device__ __forceinline__ void for_slots(F f) {
@@ -138,25 +133,29 @@ __device__ __forceinline__ void for_colors(F f) {
   f(IC<3>{});
 }
 
-// (A x)_q for row q = C 4^(k-1) + j of level k (slots in order 0..8; an absent slot holds 0 and its product is taken
-// with x[q])
-template <class T, int K, int C, class XV>
-__device__ __forceinline__ T fe_row(const T *ax, uint32_t j, XV xv) {
-  constexpr int sh = 2 * K - 2;
-  constexpr uint32_t n = 1u << (2 * K);
-  const uint32_t q = (static_cast<uint32_t>(C) << sh) | j;
-  uint32_t nb[9];
-  stencil_q(q, j, C, sh, nb);
-  T acc = 0;
-#pragma unroll
-  for (int s = 0; s < 9; s++) acc += ax[s * n + q] * xv(nb[s]);
-  return acc;
+template <class F>
+__device__ __forceinline__ void for_16(F f) {
+  f(IC<0>{}); f(IC<1>{}); f(IC<2>{}); f(IC<3>{}); f(IC<4>{}); f(IC<5>{}); f(IC<6>{}); f(IC<7>{});
+  f(IC<8>{}); f(IC<9>{}); f(IC<10>{}); f(IC<11>{}); f(IC<12>{}); f(IC<13>{}); f(IC<14>{}); f(IC<15>{});
 }
 
-// r = g - a0 q0, the first inner update of Algorithm 2.1 (the interpreter's expression)
+__device__ __forceinline__ float fe_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fe_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// the thread index, opaque to the optimiser: places derived from it on the lower levels are formed when such a level
+// begins rather than kept in registers across the launch
+__device__ __forceinline__ int fe_tid() {
+  int t;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(static_cast<int>(threadIdx.x)));
+  return t;
+}
+
+// n / d from rd = 1 / d rounded to nearest: q = n rd, then q + (n - q d) rd with fused multiply-adds (Markstein, IBM
+// Journal of Research and Development 34, 1990)
 template <class T>
-__device__ __forceinline__ T fe_upd1_r(T g, T a0, T q0) {
-  return g - a0 * q0;
+__device__ __forceinline__ T fe_div(T n, T d, T rd) {
+  const T q = n * rd;
+  return fe_fma(fe_fma(-q, d, n), rd, q);
 }
 
 // a lane's double moved by a DPP lane pattern (two 32-bit moves)
@@ -175,44 +174,43 @@ __device__ __forceinline__ double fe_readlane(double x, int lane) {
   return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
 }
 
-// sum over one wavefront, the same value in every lane: within each row of 16 lanes a butterfly over DPP lane
-// patterns (pairs, quads, half-row mirror, row mirror: every lane of the row ends with the row sum, added in an
-// order that gives the same value in each), then the four row sums (R0 + R1) + (R2 + R3) read from lanes 0, 16, 32,
-// 48. A fixed tree: the result depends only on the lanes' values.
-template <int ND>
-__device__ __forceinline__ void fe_wave_allreduce(double (&v)[ND]) {
-#pragma unroll
-  for (int j = 0; j < ND; j++) {
-    double x = v[j];
-    x += fe_dpp<0xb1>(x);   // quad_perm [1, 0, 3, 2]
-    x += fe_dpp<0x4e>(x);   // quad_perm [2, 3, 0, 1]
-    x += fe_dpp<0x141>(x);  // row_half_mirror
-    x += fe_dpp<0x140>(x);  // row_mirror
-    v[j] = (fe_readlane(x, 0) + fe_readlane(x, 16)) + (fe_readlane(x, 32) + fe_readlane(x, 48));
-  }
+// the sum of x over the lanes i, i + 16, i + 32, i + 48 of a wavefront, in every one of them: rows of 16 lanes added in
+// pairs, then the two halves
+__device__ __forceinline__ double fe_rows_sum(double x) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const auto l0 = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(u), static_cast<unsigned>(u), false, false);
+  const auto h0 =
+      __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(u >> 32), static_cast<unsigned>(u >> 32), false, false);
+  x = __builtin_bit_cast(double, (static_cast<unsigned long long>(h0[0]) << 32) | l0[0]) +
+      __builtin_bit_cast(double, (static_cast<unsigned long long>(h0[1]) << 32) | l0[1]);
+  const unsigned long long w = __builtin_bit_cast(unsigned long long, x);
+  const auto l1 = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(w), static_cast<unsigned>(w), false, false);
+  const auto h1 =
+      __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(w >> 32), static_cast<unsigned>(w >> 32), false, false);
+  return __builtin_bit_cast(double, (static_cast<unsigned long long>(h1[0]) << 32) | l1[0]) +
+         __builtin_bit_cast(double, (static_cast<unsigned long long>(h1[1]) << 32) | l1[1]);
 }
 
-// sum over the first W wavefronts, delivered to thread 0 (fixed tree: each wavefront's sum as above, then the
-// wavefront sums in order). Every thread calls it.
-template <int ND, int W>
-__device__ __forceinline__ void fe_reduce_t0(double (&v)[ND], double *red) {
-  if (static_cast<int>(threadIdx.x >> 6) < W) {
-    fe_wave_allreduce<ND>(v);
-    if (W > 1 && (threadIdx.x & 63) == 0)
-#pragma unroll
-      for (int j = 0; j < ND; j++) red[j * kFeMaxWaves + (threadIdx.x >> 6)] = v[j];
-  }
-  if constexpr (W > 1) {
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-      for (int j = 0; j < ND; j++) {
-        double acc = 0.0;
-#pragma unroll
-        for (int w = 0; w < W; w++) acc += red[j * kFeMaxWaves + w];
-        v[j] = acc;
-      }
-  }
+// lane n's double in every lane of each row of 16 lanes (row_newbcast)
+template <int N>
+__device__ __forceinline__ double fe_bcast(double x) {
+  const long u = __builtin_bit_cast(long, x);
+  const long r = __builtin_amdgcn_update_dpp(0L, u, 0x150 + N, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, r);
+}
+
+// four sums over one wavefront at once: in two steps of pairs each lane hands over the half of its values that its
+// partner keeps, so that one value per lane is left (lane i holds a part of sum fe_sum_of(i & 3)), which is then added
+// over the lanes of equal i & 3. A fixed tree: the result depends only on the lanes' values.
+__device__ __forceinline__ constexpr int fe_sum_of(int i) { return (i & 1) * 2 + (i >> 1); }
+__device__ __forceinline__ double fe_wave_sum4(const double (&v)[4]) {
+  const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
+  const double k0 = (b0 ? v[2] : v[0]) + fe_dpp<0xb1>(b0 ? v[0] : v[2]);  // quad_perm [1, 0, 3, 2]
+  const double k1 = (b0 ? v[3] : v[1]) + fe_dpp<0xb1>(b0 ? v[1] : v[3]);
+  double k = (b1 ? k1 : k0) + fe_dpp<0x4e>(b1 ? k0 : k1);                 // quad_perm [2, 3, 0, 1]
+  k += fe_dpp<0x124>(k);                                                  // row_ror 4
+  k += fe_dpp<0x128>(k);                                                  // row_ror 8
+  return fe_rows_sum(k);
 }
 
 // Order between the sub-steps of the one-wavefront B~: a wavefront's LDS accesses are performed in issue order, so
@@ -224,627 +222,489 @@ __device__ __forceinline__ void fe_wsync() {
   asm volatile("" ::: "memory");
 }
 
-template <class T, int KT, int KL>
-struct FeEngine {
-  using Lay = FeLayout<T, KT, KL>;
-  static constexpr int lw = Lay::lw;
-  static constexpr int NT = Lay::threads;
-  static constexpr int TR = Lay::TR;
+template <bool WAVE>
+__device__ __forceinline__ void fe_sync() {
+  if constexpr (WAVE) fe_wsync();
+  else __syncthreads();
+}
 
-  T *S;                 // T arrays in LDS
-  const double *Ainv;   // LDS
-  const FeArgs<T> &A;
-  double (*sc)[8];
-  double *red;
-  FeTop<T, TR> &R;      // the top level's registers (unused unless Lay::reg_top)
-
-  template <int I>
-  static constexpr bool reg() {
-    return Lay::reg_top && I == 0;
-  }
-
-  template <int I, int V>
-  __device__ __forceinline__ T *vec() const {
-    static_assert(!reg<I>() || V == V_P0 || V == V_P1, "register vector of the top level");
-    if constexpr (Lay::lds(I)) {
-      return S + Lay::vec_off(I) + V * Lay::n(I);
-    } else if constexpr ((Lay::lvec_mask >> V) & 1u) {
-      return S + Lay::lvec_off + popc(Lay::lvec_mask & ((1u << V) - 1u)) * Lay::n(I);
-    } else {
-      return A.gv[V];
-    }
-  }
-  template <int I>
-  __device__ __forceinline__ const T *ax() const {
-    if constexpr (Lay::lds(I)) return S + Lay::ax_off(I);
-    else return A.ax[I];
-  }
-
-  // f(j, t) for the rows j < 4^(k-1) of a color block of level I: on the register top level the thread's TR rows
-  // (t = IC<i> for the i-th, unrolled), elsewhere a loop with t = IC<0>
-  template <int I, class F>
-  __device__ __forceinline__ void rows(F f) const {
-    if constexpr (reg<I>()) {
-      const int t = fe_tid();
-      f(t, IC<0>{});
-      if constexpr (TR > 1) f(t + NT, IC<1>{});
-    } else {
-      for_rows<Lay::n(I) / 4, NT>([&](int j) { f(j, IC<0>{}); });
-    }
-  }
-
-  // entry V of row C 4^(k-1) + j of level I (a register of the top level, else LDS or global memory)
-  template <int I, int V, int C, int Tr>
-  __device__ __forceinline__ T &own(int j, IC<Tr>) const {
-    if constexpr (reg<I>() && V != V_P0 && V != V_P1) return R.v[Tr][fe_rv(V)][C];
-    else return vec<I, V>()[C * (Lay::n(I) / 4) + j];
-  }
-  // operator entry in slot Sl of that row
-  template <int I, int C, int Sl, int Tr>
-  __device__ __forceinline__ T aop(int j, IC<Tr>) const {
-    if constexpr (reg<I>()) return R.a[Tr][C][Sl];
-    else return ax<I>()[Sl * Lay::n(I) + C * (Lay::n(I) / 4) + j];
-  }
-
-  // (A x)_q for row q = C 4^(k-1) + j of level I (slots in order 0..8; an absent slot holds 0 and its product is
-  // taken with x[q])
-  template <int I, int C, int Tr, class XV>
-  __device__ __forceinline__ T row(int j, IC<Tr> tr, XV xv) const {
-    constexpr int K = KT - I, sh = 2 * K - 2;
-    const uint32_t ju = static_cast<uint32_t>(j);
-    const uint32_t q = (static_cast<uint32_t>(C) << sh) | ju;
-    uint32_t nb[9];
-    stencil_q(q, ju, C, sh, nb);
-    T acc = 0;
-    for_slots([&](auto ss) {
-      constexpr int sl = decltype(ss)::value;
-      acc += aop<I, C, sl>(j, tr) * xv(nb[sl]);
-    });
-    return acc;
-  }
-
-  // ---- steps on a level run by the workgroup (k >= 5) ----
-
-  // the first two color phases of B^ from zero: color 0 takes f / diag, the color-1 rows read those values (their
-  // color-0 neighbours are E and W; every other neighbour is still 0), colors 2 and 3 are 0. For the second B^ of B~
-  // the right-hand side is r = g - a0 q0, and e = a0 p0 and r are stored here. On an LDS level the color-1 rows form
-  // their neighbours' values on the fly (one step); on a register top level the color-0 values go through LDS first.
-  template <int I, int B2>
-  __device__ __forceinline__ void first2() const {
-    constexpr int K = KT - I, N = Lay::n(I), N4 = N / 4, SH = 2 * K - 2;
-    T *u = vec<I, B2 ? V_P1 : V_P0>();
-    const T *p0 = vec<I, V_P0>();
-    const T a0 = B2 ? static_cast<T>(sc[I][S_A0]) : T(0);
-    if constexpr (reg<I>()) {
-      auto fo = [&](auto cc, auto tr) -> T {
-        constexpr int c = decltype(cc)::value, t = decltype(tr)::value;
-        if constexpr (B2) return fe_upd1_r(R.v[t][0][c], a0, R.v[t][3][c]);
-        else return R.v[t][0][c];
-      };
-      rows<I>([&](int j, auto tr) {
-        constexpr int t = decltype(tr)::value;
-        u[j] = fo(IC<0>{}, tr) / R.a[t][0][0];
-        u[2 * N4 + j] = T(0);
-        u[3 * N4 + j] = T(0);
-        if constexpr (B2) {
-          for_colors([&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            R.v[t][1][c] = a0 * p0[c * N4 + j];
-            R.v[t][2][c] = fe_upd1_r(R.v[t][0][c], a0, R.v[t][3][c]);
-          });
-        }
-      });
-      __syncthreads();
-      rows<I>([&](int j, auto tr) {
-        constexpr int t = decltype(tr)::value;
-        const uint32_t q1 = static_cast<uint32_t>(N4 + j);
-        uint32_t nb[9];
-        stencil_q(q1, static_cast<uint32_t>(j), 1, SH, nb);
-        auto first = [=](uint32_t i) -> T { return i < static_cast<uint32_t>(N4) ? u[i] : T(0); };
-        T acc = R.a[t][1][1] * first(nb[1]);
-        acc += R.a[t][1][5] * first(nb[5]);
-        u[q1] = T(0) + (fo(IC<1>{}, tr) - acc) / R.a[t][1][0];
-      });
-    } else {
-      const T *a = ax<I>();
-      const T *g = vec<I, V_G>(), *q0 = vec<I, V_Q0>();
-      T *e = vec<I, V_E>(), *r = vec<I, V_R>();
-      auto fv = [=](uint32_t i) -> T {
-        if constexpr (B2) return fe_upd1_r(g[i], a0, q0[i]);
-        else return g[i];
-      };
-      for_rows<N4, NT>([&](int j) {
-        const uint32_t q1 = static_cast<uint32_t>(N4 + j);
-        uint32_t nb[9];
-        stencil_q(q1, static_cast<uint32_t>(j), 1, SH, nb);
-        auto first = [=](uint32_t i) -> T { return i < static_cast<uint32_t>(N4) ? fv(i) / a[i] : T(0); };
-        T acc = a[1 * N + q1] * first(nb[1]);
-        acc += a[5 * N + q1] * first(nb[5]);
-        const T u1 = T(0) + (fv(q1) - acc) / a[q1];
-        u[j] = fv(static_cast<uint32_t>(j)) / a[j];
-        u[q1] = u1;
-        u[2 * N4 + j] = T(0);
-        u[3 * N4 + j] = T(0);
-        if constexpr (B2) {
-          for_colors([&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            const int q = c * N4 + j;
-            e[q] = a0 * p0[q];
-            r[q] = fe_upd1_r(g[q], a0, q0[q]);
-          });
-        }
-      });
-    }
-  }
-
-  // one color phase of the pointwise Gauss-Seidel (Section 4.5): x += (f - A x) / diag on the rows of color C; for
-  // the second B^'s last phase also beta = -(p1, q0) / d0 of Algorithm 2.1
-  template <int I, int C, int B2>
-  __device__ __forceinline__ void gs() const {
-    constexpr int N4 = Lay::n(I) / 4;
-    T *u = vec<I, B2 ? V_P1 : V_P0>();
-    rows<I>([&](int j, auto tr) {
-      const T f = own<I, B2 ? V_R : V_G, C>(j, tr);
-      const T dl = (f - row<I, C>(j, tr, [u](uint32_t i) { return u[i]; })) / aop<I, C, 0>(j, tr);
-      u[C * N4 + j] += dl;
-    });
-    if constexpr (B2 && C == 0) {
-      __syncthreads();
-      dot_beta<I>();
-    }
-  }
-
-  template <int I>
-  __device__ __forceinline__ void dot_beta() const {
-    constexpr int N4 = Lay::n(I) / 4;
-    const T *p1 = vec<I, V_P1>();
-    double t[1] = {0.0};
-    rows<I>([&](int j, auto tr) {
-      for_colors([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        t[0] += static_cast<double>(p1[c * N4 + j]) * static_cast<double>(own<I, V_Q0, c>(j, tr));
-      });
-    });
-    fe_reduce_t0<1, (N4 < NT ? N4 : NT) / 64>(t, red);
-    if (threadIdx.x == 0) {
-      const double d0 = sc[I][S_D0];
-      sc[I][S_BETA] = (d0 > 0.0) ? -t[0] / d0 : 0.0;
-    }
-  }
-
-  // residual f - A u of the four children of each parent cell, summed in the order 0, 1, 3, 2 (Section 4.3's
-  // explicit restriction) into the parent's g
-  template <int I, int B2>
-  __device__ __forceinline__ void res_restrict() const {
-    constexpr int K = KT - I;
-    constexpr int F = B2 ? V_R : V_G;
-    const T *u = vec<I, B2 ? V_P1 : V_P0>();
-    T *gc = vec<I + 1, V_G>();
-    auto uv = [u](uint32_t i) { return u[i]; };
-    rows<I>([&](int m, auto tr) {
-      const T r0 = own<I, F, 0>(m, tr) - row<I, 0>(m, tr, uv);
-      const T r1 = own<I, F, 1>(m, tr) - row<I, 1>(m, tr, uv);
-      const T r3 = own<I, F, 3>(m, tr) - row<I, 3>(m, tr, uv);
-      const T r2 = own<I, F, 2>(m, tr) - row<I, 2>(m, tr, uv);
-      T acc = 0;
-      acc += r0;
-      acc += r1;
-      acc += r3;
-      acc += r2;
-      gc[q_of_m(static_cast<uint32_t>(m), K - 1)] = acc;
-    });
-  }
-
-  // u += P e_c; when the child's B~ ran as steps, its last update e_c + a1 (p1 + beta p0) is formed here
-  template <int I, int B2>
-  __device__ __forceinline__ void prolong() const {
-    constexpr int K = KT - I, N4 = Lay::n(I) / 4;
-    constexpr bool defer = (K - 1) >= 5;
-    T *u = vec<I, B2 ? V_P1 : V_P0>();
-    const T *ec = vec<I + 1, V_E>();
-    const T *p1c = vec<I + 1, V_P1>(), *p0c = vec<I + 1, V_P0>();
-    const T a1 = defer ? static_cast<T>(sc[I + 1][S_A1]) : T(0);
-    const T beta = defer ? static_cast<T>(sc[I + 1][S_BETA]) : T(0);
-    rows<I>([&](int j, auto) {
-      const uint32_t m = q_of_m(static_cast<uint32_t>(j), K - 1);
-      T ecm = ec[m];
-      if constexpr (defer) ecm = ec[m] + a1 * (p1c[m] + beta * p0c[m]);
-      for_colors([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        u[c * N4 + j] += ecm;
-      });
-    });
-  }
-
-  // q0 = A p0 with (p0, q0) and (g, p0); alpha0 of Algorithm 2.1
-  template <int I>
-  __device__ __forceinline__ void spmv0() const {
-    constexpr int N4 = Lay::n(I) / 4;
-    const T *x = vec<I, V_P0>();
-    double v[2] = {0.0, 0.0};
-    rows<I>([&](int j, auto tr) {
-      for_colors([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        const int q = c * N4 + j;
-        const T yq = row<I, c>(j, tr, [x](uint32_t i) { return x[i]; });
-        own<I, V_Q0, c>(j, tr) = yq;
-        v[0] += static_cast<double>(x[q]) * static_cast<double>(yq);
-        v[1] += static_cast<double>(own<I, V_G, c>(j, tr)) * static_cast<double>(x[q]);
-      });
-    });
-    fe_reduce_t0<2, (N4 < NT ? N4 : NT) / 64>(v, red);
-    if (threadIdx.x == 0) {
-      sc[I][S_D0] = v[0];
-      sc[I][S_A0] = (v[0] > 0.0) ? v[1] / v[0] : 0.0;
-    }
-  }
-
-  // A d for the direction d = p1 + beta p0 formed on the fly, with (d, A d) and (r, d); alpha1
-  template <int I>
-  __device__ __forceinline__ void spmv1() const {
-    constexpr int N4 = Lay::n(I) / 4;
-    const T beta = static_cast<T>(sc[I][S_BETA]);
-    const T *p1 = vec<I, V_P1>(), *p0 = vec<I, V_P0>();
-    auto dir = [p1, p0, beta](uint32_t i) { return p1[i] + beta * p0[i]; };
-    double v[2] = {0.0, 0.0};
-    rows<I>([&](int j, auto tr) {
-      for_colors([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        const uint32_t q = static_cast<uint32_t>(c * N4 + j);
-        const T yq = row<I, c>(j, tr, dir);
-        const T xq = dir(q);
-        v[0] += static_cast<double>(xq) * static_cast<double>(yq);
-        v[1] += static_cast<double>(own<I, V_R, c>(j, tr)) * static_cast<double>(xq);
-      });
-    });
-    fe_reduce_t0<2, (N4 < NT ? N4 : NT) / 64>(v, red);
-    if (threadIdx.x == 0) sc[I][S_A1] = (sc[I][S_D0] > 0.0 && v[0] > 0.0) ? v[1] / v[0] : 0.0;
-  }
-
-  // e += a1 (p1 + beta p0)
-  template <int I>
-  __device__ __forceinline__ void update2() const {
-    constexpr int N4 = Lay::n(I) / 4;
-    const T a1 = static_cast<T>(sc[I][S_A1]), beta = static_cast<T>(sc[I][S_BETA]);
-    const T *p1 = vec<I, V_P1>(), *p0 = vec<I, V_P0>();
-    rows<I>([&](int j, auto tr) {
-      for_colors([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        const int q = c * N4 + j;
-        own<I, V_E, c>(j, tr) += a1 * (p1[q] + beta * p0[q]);
-      });
-    });
-  }
-
-  // ---- B~ on level k = 4 (256 cells) in one wavefront: lane j owns row j of each color block ----
-
-  template <int B2>
-  __device__ __forceinline__ void bhat_w(T a0) const {
-    constexpr int I = lw, N = 256, N4 = 64, SH = 6;
-    const T *a = ax<I>();
-    const T *g = vec<I, V_G>(), *q0 = vec<I, V_Q0>(), *p0 = vec<I, V_P0>();
-    T *e = vec<I, V_E>(), *r = vec<I, V_R>();
-    T *u = vec<I, B2 ? V_P1 : V_P0>();
-    const T *f = B2 ? r : g;
-    T *g3 = S + Lay::c3_off, *e3 = g3 + kFeCoarse;
-    const int j = static_cast<int>(threadIdx.x);
-    const uint32_t ju = static_cast<uint32_t>(j);
-    auto uv = [u](uint32_t i) { return u[i]; };
-    auto fv = [=](uint32_t i) -> T {
-      if constexpr (B2) return fe_upd1_r(g[i], a0, q0[i]);
-      else return g[i];
-    };
-    {  // first two phases from zero (and, for the second B^, the first inner update)
-      const uint32_t q1 = static_cast<uint32_t>(N4 + j);
-      uint32_t nb[9];
-      stencil_q(q1, ju, 1, SH, nb);
-      auto first = [=](uint32_t i) -> T { return i < static_cast<uint32_t>(N4) ? fv(i) / a[i] : T(0); };
-      T acc = a[1 * N + q1] * first(nb[1]);
-      acc += a[5 * N + q1] * first(nb[5]);
-      const T u1 = T(0) + (fv(q1) - acc) / a[q1];
-      const T u0 = fv(ju) / a[j];
-      if constexpr (B2) {
-        for_colors([&](auto cc) {
-          constexpr int c = decltype(cc)::value;
-          const int q = c * N4 + j;
-          e[q] = a0 * p0[q];
-          r[q] = fe_upd1_r(g[q], a0, q0[q]);
-        });
-      }
-      u[j] = u0;
-      u[q1] = u1;
-      u[2 * N4 + j] = T(0);
-      u[3 * N4 + j] = T(0);
-    }
-    fe_wsync();
-    auto phase = [&](auto cc) {
-      constexpr int c = decltype(cc)::value;
-      const int q = c * N4 + j;
-      const T dl = (f[q] - fe_row<T, 4, c>(a, ju, uv)) / a[q];
-      u[q] += dl;
-      fe_wsync();
-    };
-    phase(IC<2>{});
-    phase(IC<3>{});
-    {  // residual and restriction to the coarsest level (lane m = parent)
-      const T r0 = f[0 * N4 + j] - fe_row<T, 4, 0>(a, ju, uv);
-      const T r1 = f[1 * N4 + j] - fe_row<T, 4, 1>(a, ju, uv);
-      const T r3 = f[3 * N4 + j] - fe_row<T, 4, 3>(a, ju, uv);
-      const T r2 = f[2 * N4 + j] - fe_row<T, 4, 2>(a, ju, uv);
-      T acc = 0;
-      acc += r0;
-      acc += r1;
-      acc += r3;
-      acc += r2;
-      g3[q_of_m(ju, 3)] = acc;
-    }
-    fe_wsync();
-    {  // coarsest solve e3 = A_3^{-1} g3 in FP64 (row j of the symmetric inverse read as column j), four partial
-       // sums over i mod 4 (independent FMA chains), added pairwise
-      double acc[4] = {0.0, 0.0, 0.0, 0.0};
+// four sums over the level's W wavefronts, the same in every thread: each wavefront's sums as above, then the
+// wavefronts' sums added in pairs
+template <int W, bool WAVE>
+__device__ __forceinline__ void fe_reduce4(double (&v)[4], double *red, bool act, int wl) {
+  const int lane = static_cast<int>(threadIdx.x & 63);
+  if constexpr (WAVE) {
+    const double k = fe_wave_sum4(v);
 #pragma unroll
-      for (int i = 0; i < kFeCoarse; i += 4)
+    for (int j = 0; j < 4; j++) v[fe_sum_of(j)] = fe_readlane(k, j);
+  } else {
+    if (act) {
+      const double k = fe_wave_sum4(v);
+      if (lane < 4) red[fe_sum_of(lane) * kFeRedWaves + wl] = k;
+    }
+    __syncthreads();
+    if (act) {  // lanes 8 j .. 8 j + 7 hold the wavefronts' sums of v[j]
+      double r = (lane & 7) < W ? red[((lane >> 3) & 3) * kFeRedWaves + (lane & 7)] : 0.0;
+      r += fe_dpp<0xb1>(r);
+      r += fe_dpp<0x4e>(r);
+      if constexpr (W > 4) r += fe_dpp<0x141>(r);  // row_half_mirror
 #pragma unroll
-        for (int k = 0; k < 4; k++) acc[k] += Ainv[(i + k) * kFeCoarse + j] * static_cast<double>(g3[i + k]);
-      e3[j] = static_cast<T>((acc[0] + acc[1]) + (acc[2] + acc[3]));
-    }
-    fe_wsync();
-    {  // prolongation
-      const T ecm = e3[q_of_m(ju, 3)];
-      for_colors([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        u[c * N4 + j] += ecm;
-      });
-    }
-    fe_wsync();
-    phase(IC<3>{});
-    phase(IC<2>{});
-    phase(IC<1>{});
-    phase(IC<0>{});
-  }
-
-  __device__ __forceinline__ void btilde_w() const {
-    constexpr int I = lw, N4 = 64;
-    if (threadIdx.x >= 64) return;
-    const T *a = ax<I>();
-    const T *g = vec<I, V_G>();
-    T *e = vec<I, V_E>(), *r = vec<I, V_R>(), *p0 = vec<I, V_P0>(), *q0 = vec<I, V_Q0>(), *p1 = vec<I, V_P1>();
-    const int j = static_cast<int>(threadIdx.x);
-    const uint32_t ju = static_cast<uint32_t>(j);
-    bhat_w<0>(T(0));
-    double v[2] = {0.0, 0.0};
-    for_colors([&](auto cc) {
-      constexpr int c = decltype(cc)::value;
-      const int q = c * N4 + j;
-      const T yq = fe_row<T, 4, c>(a, ju, [p0](uint32_t i) { return p0[i]; });
-      q0[q] = yq;
-      v[0] += static_cast<double>(p0[q]) * static_cast<double>(yq);
-      v[1] += static_cast<double>(g[q]) * static_cast<double>(p0[q]);
-    });
-    fe_wave_allreduce<2>(v);
-    const double d0 = v[0];
-    const bool stop = !(d0 > 0.0);
-    const double a0 = stop ? 0.0 : v[1] / d0;
-    fe_wsync();
-    bhat_w<1>(static_cast<T>(a0));
-    double t[1] = {0.0};
-    for_colors([&](auto cc) {
-      constexpr int c = decltype(cc)::value;
-      const int q = c * N4 + j;
-      t[0] += static_cast<double>(p1[q]) * static_cast<double>(q0[q]);
-    });
-    fe_wave_allreduce<1>(t);
-    const double beta = stop ? 0.0 : -t[0] / d0;
-    const T bt = static_cast<T>(beta);
-    auto dir = [p1, p0, bt](uint32_t i) { return p1[i] + bt * p0[i]; };
-    double w[2] = {0.0, 0.0};
-    for_colors([&](auto cc) {
-      constexpr int c = decltype(cc)::value;
-      const uint32_t q = static_cast<uint32_t>(c * N4 + j);
-      const T yq = fe_row<T, 4, c>(a, ju, dir);
-      const T xq = dir(q);
-      w[0] += static_cast<double>(xq) * static_cast<double>(yq);
-      w[1] += static_cast<double>(r[q]) * static_cast<double>(xq);
-    });
-    fe_wave_allreduce<2>(w);
-    const T a1 = static_cast<T>((stop || !(w[0] > 0.0)) ? 0.0 : w[1] / w[0]);
-    for_colors([&](auto cc) {
-      constexpr int c = decltype(cc)::value;
-      const int q = c * N4 + j;
-      e[q] += a1 * (p1[q] + bt * p0[q]);
-    });
-  }
-
-  // ---- dispatch ----
-
-  template <int I>
-  __device__ __forceinline__ bool level_steps(int code) const {
-    if constexpr (I < lw) {
-      switch (code) {
-        case fe_code(FE_FIRST2, I, 0, 0): first2<I, 0>(); return true;
-        case fe_code(FE_FIRST2, I, 0, 1): first2<I, 1>(); return true;
-        case fe_code(FE_GS, I, 0, 0): gs<I, 0, 0>(); return true;
-        case fe_code(FE_GS, I, 1, 0): gs<I, 1, 0>(); return true;
-        case fe_code(FE_GS, I, 2, 0): gs<I, 2, 0>(); return true;
-        case fe_code(FE_GS, I, 3, 0): gs<I, 3, 0>(); return true;
-        case fe_code(FE_GS, I, 0, 1): gs<I, 0, 1>(); return true;
-        case fe_code(FE_GS, I, 1, 1): gs<I, 1, 1>(); return true;
-        case fe_code(FE_GS, I, 2, 1): gs<I, 2, 1>(); return true;
-        case fe_code(FE_GS, I, 3, 1): gs<I, 3, 1>(); return true;
-        case fe_code(FE_RES, I, 0, 0): res_restrict<I, 0>(); return true;
-        case fe_code(FE_RES, I, 0, 1): res_restrict<I, 1>(); return true;
-        case fe_code(FE_PROLONG, I, 0, 0): prolong<I, 0>(); return true;
-        case fe_code(FE_PROLONG, I, 0, 1): prolong<I, 1>(); return true;
-        case fe_code(FE_SPMV0, I, 0, 0): spmv0<I>(); return true;
-        case fe_code(FE_SPMV1, I, 0, 0): spmv1<I>(); return true;
-        case fe_code(FE_UPDATE2, I, 0, 0): update2<I>(); return true;
-        default: return false;
-      }
-    } else {
-      return false;
-    }
-  }
-
-  __device__ __forceinline__ void step(int code) const {
-    if (code == fe_code(FE_BTILDE_W, lw, 0, 0)) {
-      btilde_w();
-      return;
-    }
-    if (level_steps<0>(code)) return;
-    level_steps<1>(code);
-  }
-};
-
-// dst[i] = src[i] for i < N: a thread's loads issued in rounds of eight before any of them is stored (a plain copy
-// loop waits for each load before the next)
-template <class V, int N, int NT>
-__device__ __forceinline__ void fe_stage(V *dst, const V *__restrict__ src, int tid) {
-  constexpr int per = (N + NT - 1) / NT, R = 8;
-#pragma unroll
-  for (int k0 = 0; k0 < per; k0 += R) {
-    V tmp[R];
-#pragma unroll
-    for (int k = 0; k < R; k++) {
-      const int i = tid + (k0 + k) * NT;
-      if (k0 + k < per) tmp[k] = src[i < N ? i : N - 1];
-    }
-#pragma unroll
-    for (int k = 0; k < R; k++) {
-      const int i = tid + (k0 + k) * NT;
-      if (k0 + k < per && i < N) dst[i] = tmp[k];
+      for (int j = 0; j < 4; j++) v[j] = fe_readlane(r, 8 * j);
     }
   }
 }
 
-template <class T, int KT, int KL>
-__global__ void __launch_bounds__((FeLayout<T, KT, KL>::threads)) k_engine_fast(FeArgs<T> A) {
-  using Lay = FeLayout<T, KT, KL>;
-  constexpr int NT = Lay::threads;
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double sc[4][8];
-  __shared__ double red[2 * kFeMaxWaves];
-  __shared__ int32_t ops[kFeMaxOps];
-  double *ainv = reinterpret_cast<double *>(smem);
-  T *S = reinterpret_cast<T *>(smem + kFeAinvBytes);
-  const int tid = static_cast<int>(threadIdx.x);
-  FeTop<T, Lay::TR> R;
-  if constexpr (Lay::reg_top) {  // the top level's rows of this thread
-    constexpr int N = Lay::n(0), N4 = N / 4;
+// sum over the nine slots of the color-C row: own values from registers, the others from the planes at `pl` (the
+// super-cell's place less one row and one column). PRE: in a sweep from zero, the slots of colors not relaxed yet
+// (and the row itself) hold zero and are left out.
+template <class T, int K, int C, bool PRE>
+__device__ __forceinline__ T fe_row(const T (&a)[9], const T (&own)[4], const T *pl) {
+  using G = FeGeo<K>;
+  T acc = 0;
+  for_slots([&](auto ss) {
+    constexpr int s = decltype(ss)::value;
+    using Nb = FeNbr<C, s>;
+    if constexpr (!PRE || Nb::color < C) {
+      T x;
+      if constexpr (Nb::ox == 0 && Nb::oy == 0) x = own[Nb::color];
+      else x = pl[Nb::color * G::PP + (Nb::oy + 1) * G::P + Nb::ox + 1];
+      acc += a[s] * x;
+    }
+  });
+  return acc;
+}
+
+// B~ of Algorithm 2.1 (n = 2) on level k = K, its B^ (Algorithm 2.2, one sweep) around the next level's child(). R.f
+// holds the right-hand side; out(t, c, e) takes the result's entry of color c of the thread's super-cell t. A, B, E:
+// the level's pre- and post-smoothing planes and the correction's plane at the thread's place (less one row and one
+// column); a thread's second super-cell lies 16 rows on. `act`: the thread belongs to the level (all threads call,
+// or, for a level of one wavefront, its threads). TOP: the reciprocals of the diagonals are formed on the way, each
+// when its rows are first needed. put(t, g) hands the restricted residual to the next level, child(half) runs that.
+template <class T, int K, int TR, int W, bool WAVE, bool TOP, class Put, class Child, class Out>
+__device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T *E, bool act, int wl, double *red,
+                                          Put put, Child child, Out out) {
+  using G = FeGeo<K>;
+  constexpr int own = G::P + 1, second = 16 * G::P;
+  double d0 = 0.0, rd0 = 0.0;
+  T a0 = 0;
+  auto relax = [&](auto cc, auto pre, T *pl, int half) {  // x += (f - A x) / diag on the color's rows
+    constexpr int c = decltype(cc)::value;
+    constexpr bool p = decltype(pre)::value != 0;
+    if (act)
 #pragma unroll
-    for (int t = 0; t < Lay::TR; t++)
-      for_colors([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        const int j = tid + t * NT;
-        for_slots([&](auto ss) {
-          constexpr int sl = decltype(ss)::value;
-          R.a[t][c][sl] = A.ax[0][sl * N + c * N4 + j];
-        });
-        R.v[t][0][c] = A.gv[V_G][c * N4 + j];
-      });
-  }
-  for (int i = tid; i < A.nops; i += NT) ops[i] = A.ops[i];
-  fe_stage<double, kFeCoarse * kFeCoarse, NT>(ainv, A.ainv, tid);
-  // operators of the LDS levels
-  auto stage_level = [&](auto ll) {
-    constexpr int l = decltype(ll)::value;
-    if constexpr (l >= Lay::first_lds && l <= Lay::lw)
-      fe_stage<T, 9 * Lay::n(l), NT>(S + Lay::ax_off(l), A.ax[l], tid);
+      for (int t = 0; t < TR; t++) {
+        if constexpr (TOP && p)
+          if (half == 0) R.rd[t][c] = T(1) / R.a[t][c][0];
+        const T acc = fe_row<T, K, c, p>(R.a[t][c], R.u[t], pl + t * second);
+        const T dl = fe_div(R.f[t][c] - acc, R.a[t][c][0], R.rd[t][c]);
+        if constexpr (p) R.u[t][c] = dl;
+        else R.u[t][c] += dl;
+        pl[t * second + c * G::PP + own] = R.u[t][c];
+      }
+    fe_sync<WAVE>();
   };
-  stage_level(IC<0>{});
-  stage_level(IC<1>{});
-  stage_level(IC<2>{});
-  if constexpr (Lay::lds(0)) fe_stage<T, Lay::n(0), NT>(S + Lay::vec_off(0) + V_G * Lay::n(0), A.gv[V_G], tid);
-  __syncthreads();
-  const FeEngine<T, KT, KL> E{S, ainv, A, sc, red, R};
-  for (int oi = 0; oi < A.nops; oi++) {
-    E.step(__builtin_amdgcn_readfirstlane(ops[oi]));
-    __syncthreads();
-  }
-  if constexpr (Lay::reg_top) {
-    constexpr int N4 = Lay::n(0) / 4;
+#pragma unroll 1
+  for (int half = 0; half < 2; half++) {
+    if (act)
 #pragma unroll
-    for (int t = 0; t < Lay::TR; t++)
+      for (int t = 0; t < TR; t++) {
+        if constexpr (TOP)
+          if (half == 0) R.rd[t][0] = T(1) / R.a[t][0][0];
+        R.u[t][0] = fe_div(R.f[t][0], R.a[t][0][0], R.rd[t][0]);
+        A[t * second + own] = R.u[t][0];
+      }
+    fe_sync<WAVE>();
+    relax(IC<1>{}, IC<1>{}, A, half);
+    relax(IC<2>{}, IC<1>{}, A, half);
+    relax(IC<3>{}, IC<1>{}, A, half);
+    if (act)
+#pragma unroll
+      for (int t = 0; t < TR; t++) {  // residual, summed over the children in the order 0, 1, 3, 2 (Section 4.3)
+        const T *pl = A + t * second;
+        const T r0 = R.f[t][0] - fe_row<T, K, 0, false>(R.a[t][0], R.u[t], pl);
+        const T r1 = R.f[t][1] - fe_row<T, K, 1, false>(R.a[t][1], R.u[t], pl);
+        const T r3 = R.f[t][3] - fe_row<T, K, 3, false>(R.a[t][3], R.u[t], pl);
+        const T r2 = R.f[t][2] - fe_row<T, K, 2, false>(R.a[t][2], R.u[t], pl);
+        T acc = 0;
+        acc += r0;
+        acc += r1;
+        acc += r3;
+        acc += r2;
+        put(t, acc);
+      }
+    fe_sync<WAVE>();
+    child(half);
+    if (act)
+#pragma unroll
+      for (int t = 0; t < TR; t++) {  // u += P e_c, and color 3 relaxed against its neighbours' u + P e_c
+        const T *pl = A + t * second, *el = E + t * second;
+        const T em = el[own];
+        for_colors([&](auto cc) { R.u[t][decltype(cc)::value] += em; });
+        T acc = 0;
+        for_slots([&](auto ss) {
+          constexpr int s = decltype(ss)::value;
+          using Nb = FeNbr<3, s>;
+          T x;
+          if constexpr (Nb::ox == 0 && Nb::oy == 0) {
+            x = R.u[t][Nb::color];
+          } else {
+            constexpr int o = (Nb::oy + 1) * G::P + Nb::ox + 1;
+            x = pl[Nb::color * G::PP + o] + el[o];
+          }
+          acc += R.a[t][3][s] * x;
+        });
+        R.u[t][3] += fe_div(R.f[t][3] - acc, R.a[t][3][0], R.rd[t][3]);
+        T *ql = B + t * second + own;
+        for_colors([&](auto cc) {
+          constexpr int c = decltype(cc)::value;
+          ql[c * G::PP] = R.u[t][c];
+        });
+      }
+    fe_sync<WAVE>();
+    relax(IC<2>{}, IC<0>{}, B, half);
+    relax(IC<1>{}, IC<0>{}, B, half);
+    relax(IC<0>{}, IC<0>{}, B, half);
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (act)
+#pragma unroll
+      for (int t = 0; t < TR; t++) {  // A u with (u, A u), (f, u) and, in the second step, (u, q0), (f, p0)
+        if (t > 0) __builtin_amdgcn_sched_barrier(0);  // one super-cell at a time (register pressure)
+        T y[4];
+        const T *pl = B + t * second;
+        for_colors([&](auto cc) {
+          constexpr int c = decltype(cc)::value;
+          y[c] = fe_row<T, K, c, false>(R.a[t][c], R.u[t], pl);
+        });
+        for_colors([&](auto cc) {
+          constexpr int c = decltype(cc)::value;
+          const double ud = static_cast<double>(R.u[t][c]), fd = static_cast<double>(R.f[t][c]);
+          v[0] += ud * static_cast<double>(y[c]);
+          v[1] += fd * ud;
+          if (half) {
+            v[2] += ud * static_cast<double>(R.q0[t][c]);
+            v[3] += fd * static_cast<double>(R.p0[t][c]);
+          }
+        });
+        if (!half)
+          for_colors([&](auto cc) {
+            constexpr int c = decltype(cc)::value;
+            R.q0[t][c] = y[c];
+            R.p0[t][c] = R.u[t][c];
+          });
+      }
+    fe_reduce4<W, WAVE>(v, red, act, wl);
+    if (act) {
+      const bool first = half == 0;
+      if (first) {  // alpha0, r = g - alpha0 q0
+        d0 = v[0];
+        a0 = static_cast<T>(fe_readlane((d0 > 0.0) ? v[1] / d0 : 0.0, 0));  // uniform: kept in scalar registers
+        rd0 = fe_readlane(1.0 / d0, 0);  // ready before the second step's beta waits for it
+#pragma unroll
+        for (int t = 0; t < TR; t++)
+          for_colors([&](auto cc) {
+            constexpr int c = decltype(cc)::value;
+            R.f[t][c] = R.f[t][c] - a0 * R.q0[t][c];
+          });
+      } else {  // direction d = p1 + beta p0: (d, A d) and (r, d) from the inner products at hand
+        const bool stop = !(d0 > 0.0);
+        double bd = -v[2] * rd0;
+        if (d0 < 1e-290) bd = -v[2] / d0;  // 1 / d0 may overflow
+        const T bt = static_cast<T>(stop ? 0.0 : bd);
+        const double b = static_cast<double>(bt);
+        const double d1 = v[0] + b * (2.0 * v[2] + b * d0);
+        const T a1 = static_cast<T>((stop || !(d1 > 0.0)) ? 0.0 : (v[1] + b * v[3]) / d1);
+#pragma unroll
+        for (int t = 0; t < TR; t++)
+          for_colors([&](auto cc) {
+            constexpr int c = decltype(cc)::value;
+            T e = a0 * R.p0[t][c];
+            e += a1 * (R.u[t][c] + bt * R.p0[t][c]);
+            out(t, cc, e);
+          });
+      }
+    }
+  }
+}
+
+// operator rows of the level's super-cells j, j + step, ... into registers, in the order the presmoothing sweep and the
+// residual need them: color 0's diagonal, the rows of colors 1 to 3, the rest of color 0
+template <class T, int K, int TR>
+__device__ __forceinline__ void fe_load_rows(FeRows<T, TR> &R, const T *__restrict__ ax, int j, int step) {
+  using G = FeGeo<K>;
+  auto load = [&](auto cc, auto ss) {
+    constexpr int c = decltype(cc)::value, s = decltype(ss)::value;
+#pragma unroll
+    for (int t = 0; t < TR; t++) R.a[t][c][s] = ax[s * G::N + c * G::N4 + j + t * step];
+  };
+  load(IC<0>{}, IC<0>{});
+  for_slots([&](auto ss) { load(IC<1>{}, ss); });
+  for_slots([&](auto ss) { load(IC<2>{}, ss); });
+  for_slots([&](auto ss) { load(IC<3>{}, ss); });
+  for_slots([&](auto ss) {
+    if constexpr (decltype(ss)::value > 0) load(IC<0>{}, ss);
+  });
+}
+template <class T, int TR>
+__device__ __forceinline__ void fe_recip(FeRows<T, TR> &R) {
+#pragma unroll
+  for (int t = 0; t < TR; t++)
+    for_colors([&](auto cc) {
+      constexpr int c = decltype(cc)::value;
+      R.rd[t][c] = T(1) / R.a[t][c][0];
+    });
+}
+
+template <class T, int KT>
+__global__ void __launch_bounds__(FeLayout<KT>::threads) k_engine_fast(FeArgs<T> A) {
+  using Lay = FeLayout<KT>;
+  constexpr int NT = Lay::threads, TR = Lay::TR;
+  // wavefronts of the levels: the top level from wavefront 0; k = 5 below it from 4; k = 4 below those in one; the
+  // coarsest solve in that one and three others from wh on
+  constexpr int w5 = KT == 6 ? 4 : 0, w4 = KT == 5 ? 4 : 0, wh = KT == 5 ? 0 : 1;
+  extern __shared__ __align__(16) unsigned char smem[];
+  double *D = reinterpret_cast<double *>(smem);
+  T *S = reinterpret_cast<T *>(smem + sizeof(double) * Lay::kDoubles);
+  const int tid = static_cast<int>(threadIdx.x), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // R: the top level's rows. X: those of the levels below it (k = 5 and k = 4 belong to different wavefronts; below a
+  // top level k = 5, which leaves wavefront 4 free, X is R).
+  FeRows<T, TR> R;
+  FeRows<T, 1> below;
+  auto &X = [&]() -> FeRows<T, 1> & {
+    if constexpr (KT == 5) return R;
+    else return below;
+  }();
+  const bool act_top = KT == 5 ? wave < 4 : (KT == 4 ? wave == 0 : true);
+  const bool act5 = KT == 6 && wave >= w5, act4 = KT > 4 && wave == w4;
+  const int part = (wave >= wh && wave < wh + 3) ? wave - wh + 1 : 0;  // helper of the coarsest solve (1 to 3) or 0
+  const int jt = tid, j5 = tid - 64 * w5, j4 = lane;
+  constexpr int step = KT == 6 ? 512 : 0;
+  // a helper's 16 entries of its lane's row of the coarsest inverse; k = 6: in the registers of X, which its
+  // wavefronts do not use otherwise
+  double hrow[KT == 6 ? 1 : 16];
+  static_assert(KT != 6 || sizeof(T) == 4, "two registers of X to a double");
+  auto hset = [&](auto ii, double v) {
+    constexpr int i = decltype(ii)::value;
+    if constexpr (KT == 6) {
+      const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+      X.a[0][i / 9][i % 9] = __builtin_bit_cast(float, static_cast<unsigned>(u));
+      X.a[0][2 + i / 9][i % 9] = __builtin_bit_cast(float, static_cast<unsigned>(u >> 32));
+    } else {
+      hrow[i] = v;
+    }
+  };
+  auto hget = [&](auto ii) -> double {
+    constexpr int i = decltype(ii)::value;
+    if constexpr (KT == 6) {
+      const unsigned lo = __builtin_bit_cast(unsigned, static_cast<float>(X.a[0][i / 9][i % 9]));
+      const unsigned hi = __builtin_bit_cast(unsigned, static_cast<float>(X.a[0][2 + i / 9][i % 9]));
+      return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
+    } else {
+      return hrow[i];
+    }
+  };
+  const int q3 = static_cast<int>(q_of_m(static_cast<uint32_t>(lane), 3));  // lane's cell of the coarsest level
+  // Loads in the order of their first use; each is waited for only there. The entries of the coarsest inverse for LDS
+  // come first, as they pass through registers.
+  double a16[16];
+  if (wave == w4)
+#pragma unroll
+    for (int i = 0; i < 16; i++) a16[i] = A.ainv[i * kFeCoarse + q3];
+  if (act_top) {
+#pragma unroll
+    for (int t = 0; t < TR; t++)
       for_colors([&](auto cc) {
         constexpr int c = decltype(cc)::value;
-        A.gv[V_E][c * N4 + tid + t * NT] = R.v[t][1][c];
+        R.f[t][c] = A.g[c * FeGeo<KT>::N4 + jt + t * step];
       });
+    fe_load_rows<T, KT, TR>(R, A.ax[0], jt, step);
+  }
+  if constexpr (KT == 6) {
+    if (act5) fe_load_rows<T, 5, 1>(X, A.ax[1], j5, 0);
+  }
+  if constexpr (KT > 4) {
+    if (act4) fe_load_rows<T, 4, 1>(X, A.ax[KT - 4], j4, 0);
+  }
+  if (part)  // row q3 of the symmetric inverse read as a column
+    for_16([&](auto ii) { hset(ii, A.ainv[(16 * part + decltype(ii)::value) * kFeCoarse + q3]); });
+  {
+    constexpr int nz = Lay::t_units * static_cast<int>(sizeof(T)) / 16;
+    static_assert(Lay::t_units * sizeof(T) % 16 == 0, "whole 16-byte stores");
+    float4 *Z = reinterpret_cast<float4 *>(S);  // the planes' rings are read and never written
+    for (int i = tid; i < nz; i += NT) Z[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  if (wave == w4)
+#pragma unroll
+    for (int p = 0; p < 8; p++)
+      reinterpret_cast<double2 *>(D + Lay::kAinv)[p * 64 + lane] = make_double2(a16[2 * p], a16[2 * p + 1]);
+  __syncthreads();
+
+  // the thread's place in the planes of level k, for its super-cell of Morton index j
+  auto place = [](int j, int p) {
+    return static_cast<int>(compact_bits(static_cast<uint32_t>(j) >> 1)) * p +
+           static_cast<int>(compact_bits(static_cast<uint32_t>(j)));
+  };
+  // where a cell (2 X + cx, 2 Y + cy) of level k lies in the parent's correction plane: the place of (X, Y)'s first
+  // cell, then cy rows and cx columns on
+  auto parent_place = [](int j, int p) {
+    return (2 * static_cast<int>(compact_bits(static_cast<uint32_t>(j) >> 1)) + 1) * p +
+           2 * static_cast<int>(compact_bits(static_cast<uint32_t>(j))) + 1;
+  };
+
+  // the 256-cell level in one wavefront (act), e to the caller's out. Its coarsest solve e3 = A_3^{-1} g3 in FP64
+  // takes a quarter of the columns in each of four wavefronts: one FMA chain per i mod 4, added pairwise, then the
+  // four wavefronts' sums.
+  auto level4 = [&](FeRows<T, 1> &Y, bool act, auto top, auto out) {
+    using G = FeGeo<4>;
+    T *S4 = S + Lay::planes(4);
+    const int lane = fe_tid() & 63, q3 = static_cast<int>(q_of_m(static_cast<uint32_t>(lane), 3));
+    const int pl = place(lane, G::P);
+    double *g3 = D + Lay::kG3, *ps = D + Lay::kPart;
+    if (act) {
+      fe_btilde<T, 4, 1, 1, true, decltype(top)::value != 0>(
+          Y, S4 + pl, S4 + 4 * G::PP + pl, S4 + 8 * G::PP + pl, true, 0, nullptr,
+          [&](int, T acc) { g3[q3] = static_cast<double>(acc); },
+          [&](int) {
+            __syncthreads();
+            const double2 *Ai = reinterpret_cast<const double2 *>(D + Lay::kAinv) + lane;
+            const double gr = g3[lane & 15];
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            for_16([&](auto nn) {
+              constexpr int n = decltype(nn)::value;
+              if constexpr (n % 2 == 0) {
+                const double2 x = Ai[(n / 2) * 64];
+                acc[n % 4] += x.x * fe_bcast<n>(gr);
+                acc[n % 4 + 1] += x.y * fe_bcast<n + 1>(gr);
+              }
+            });
+            const double mine = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+            __syncthreads();
+            S4[8 * G::PP + pl + G::P + 1] =
+                static_cast<T>((mine + ps[64 + lane]) + (ps[128 + lane] + ps[192 + lane]));
+            fe_wsync();
+          },
+          out);
+    } else {
+#pragma unroll 1
+      for (int half = 0; half < 2; half++) {
+        __syncthreads();
+        if (part) {
+          const double gr = g3[16 * part + (lane & 15)];
+          double acc[4] = {0.0, 0.0, 0.0, 0.0};
+          for_16([&](auto nn) {
+            constexpr int n = decltype(nn)::value;
+            acc[n % 4] += hget(nn) * fe_bcast<n>(gr);
+          });
+          ps[64 * part + lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        }
+        __syncthreads();
+      }
+    }
+  };
+  // result entries of the top level to global memory
+  auto to_global = [&](int t, auto cc, T e) {
+    A.e[decltype(cc)::value * FeGeo<KT>::N4 + jt + t * step] = e;
+  };
+
+  if constexpr (KT == 4) {
+    level4(R, act_top, IC<1>{}, to_global);
   } else {
-    const T *e = S + Lay::vec_off(0) + V_E * Lay::n(0);
-    for (int i = tid; i < Lay::n(0); i += NT) A.gv[V_E][i] = e[i];
+    // the right-hand side handed to the next level lies behind this level's planes (color-major)
+    auto level5 = [&](auto &Y, bool act, auto top, auto out) {
+      using G = FeGeo<5>;
+      const int t5 = fe_tid(), j = t5 - 64 * w5, j4 = t5 & 63;
+      T *S5 = S + Lay::planes(5);
+      T *g4 = S5 + 9 * G::PP;
+      const int pl = place(j & (G::N4 - 1), G::P), e4 = parent_place(j4, G::P);
+      fe_btilde<T, 5, 1, 4, false, decltype(top)::value != 0>(
+          Y, S5 + pl, S5 + 4 * G::PP + pl, S5 + 8 * G::PP + pl, act, wave - w5, D + Lay::kRed,
+          [&](int, T acc) { g4[(j & 3) * FeGeo<4>::N4 + (j >> 2)] = acc; },
+          [&](int half) {
+            if constexpr (decltype(top)::value != 0)
+              if (act4 && half == 0) fe_recip(X);
+            if (act4)
+              for_colors([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                X.f[0][c] = g4[c * FeGeo<4>::N4 + j4];
+              });
+            level4(X, act4, IC<0>{}, [&](int, auto cc, T e) {
+              constexpr int c = decltype(cc)::value;
+              S5[8 * G::PP + e4 + (c >> 1) * G::P + (c & 1)] = e;
+            });
+            __syncthreads();
+          },
+          out);
+    };
+    if constexpr (KT == 5) {
+      level5(R, act_top, IC<1>{}, to_global);
+    } else {
+      using G = FeGeo<6>;
+      T *S6 = S + Lay::planes(6);
+      T *g5 = S6 + 9 * G::PP;
+      const int pl = place(jt, G::P);
+      fe_btilde<T, 6, 2, 8, false, true>(
+          R, S6 + pl, S6 + 4 * G::PP + pl, S6 + 8 * G::PP + pl, true, wave, D + Lay::kRed + 4 * kFeRedWaves,
+          [&](int t, T acc) { g5[(jt & 3) * FeGeo<5>::N4 + (jt >> 2) + t * (step / 4)] = acc; },
+          [&](int half) {
+            if (half == 0 && (act5 || act4)) fe_recip(X);
+            const int j5 = (fe_tid() - 64 * w5) & (FeGeo<5>::N4 - 1), e5 = parent_place(j5, G::P);
+            if (act5)
+              for_colors([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                X.f[0][c] = g5[c * FeGeo<5>::N4 + j5];
+              });
+            level5(X, act5, IC<0>{}, [&, e5](int, auto cc, T e) {
+              constexpr int c = decltype(cc)::value;
+              S6[8 * G::PP + e5 + (c >> 1) * G::P + (c & 1)] = e;
+            });
+            __syncthreads();
+          },
+          to_global);
+    }
   }
 }
 
 // ---- host side ----
 
-void fe_emit_btilde(std::vector<int32_t> &ops, int kt, int l, bool defer);
+// steps of one launch (a step ends with a barrier; B~ of the 256-cell level is one): per inner step of a level four
+// presmoothing phases, the restriction, the next level's steps, four post-smoothing phases and the reduction
+constexpr int fe_steps(int kt) { return kt == 4 ? 1 : 2 * (10 + fe_steps(kt - 1)); }
 
-// B^ of Algorithm 2.2 on engine level l (k >= 5), one sweep: the first two phases from zero as one step, then
-// colors 2 and 3, residual and restriction, the coarse B~, prolongation, colors 3..0
-void fe_emit_bhat(std::vector<int32_t> &ops, int kt, int l, int b2) {
-  ops.push_back(fe_code(FE_FIRST2, l, 0, b2));
-  ops.push_back(fe_code(FE_GS, l, 2, b2));
-  ops.push_back(fe_code(FE_GS, l, 3, b2));
-  ops.push_back(fe_code(FE_RES, l, 0, b2));
-  fe_emit_btilde(ops, kt, l + 1, kt - (l + 1) >= 5);
-  ops.push_back(fe_code(FE_PROLONG, l, 0, b2));
-  for (int c = 3; c >= 0; c--) ops.push_back(fe_code(FE_GS, l, c, b2));
-}
-
-// B~ of Algorithm 2.1 (n = 2) on engine level l; on k = 4 one step for the whole of it. defer: the last update is
-// formed by the parent's prolongation.
-void fe_emit_btilde(std::vector<int32_t> &ops, int kt, int l, bool defer) {
-  if (kt - l == 4) {
-    ops.push_back(fe_code(FE_BTILDE_W, l, 0, 0));
-    return;
-  }
-  fe_emit_bhat(ops, kt, l, 0);
-  ops.push_back(fe_code(FE_SPMV0, l, 0, 0));
-  fe_emit_bhat(ops, kt, l, 1);
-  ops.push_back(fe_code(FE_SPMV1, l, 0, 0));
-  if (!defer) ops.push_back(fe_code(FE_UPDATE2, l, 0, 0));
-}
-
-// configuration ids: FP32 (6,5), (5,5), (4,4); FP64 (5,4), (4,4)
+// configuration ids: FP32 k = 6, 5, 4; FP64 k = 5, 4 (the operators of the 4,096-cell level in FP64 alone are 288 KB,
+// and with its vectors exceed the registers and LDS of a CU)
 struct FeCfg {
-  int pi, kt, kl;
+  int pi, kt;
 };
-constexpr FeCfg kFeCfgs[] = {{1, 6, 5}, {1, 5, 5}, {1, 4, 4}, {0, 5, 4}, {0, 4, 4}};
-
-template <class T, int KT, int KL>
-size_t fe_bytes() {
-  return FeLayout<T, KT, KL>::bytes;
-}
+constexpr FeCfg kFeCfgs[] = {{1, 6}, {1, 5}, {1, 4}, {0, 5}, {0, 4}};
 
 size_t fe_cfg_bytes(int id) {
   switch (id) {
-    case 0: return fe_bytes<float, 6, 5>();
-    case 1: return fe_bytes<float, 5, 5>();
-    case 2: return fe_bytes<float, 4, 4>();
-    case 3: return fe_bytes<double, 5, 4>();
-    default: return fe_bytes<double, 4, 4>();
+    case 0: return FeLayout<6>::bytes<float>();
+    case 1: return FeLayout<5>::bytes<float>();
+    case 2: return FeLayout<4>::bytes<float>();
+    case 3: return FeLayout<5>::bytes<double>();
+    default: return FeLayout<4>::bytes<double>();
   }
 }
 
 const void *fe_kernel(int id) {
   switch (id) {
-    case 0: return reinterpret_cast<const void *>(k_engine_fast<float, 6, 5>);
-    case 1: return reinterpret_cast<const void *>(k_engine_fast<float, 5, 5>);
-    case 2: return reinterpret_cast<const void *>(k_engine_fast<float, 4, 4>);
-    case 3: return reinterpret_cast<const void *>(k_engine_fast<double, 5, 4>);
-    default: return reinterpret_cast<const void *>(k_engine_fast<double, 4, 4>);
+    case 0: return reinterpret_cast<const void *>(k_engine_fast<float, 6>);
+    case 1: return reinterpret_cast<const void *>(k_engine_fast<float, 5>);
+    case 2: return reinterpret_cast<const void *>(k_engine_fast<float, 4>);
+    case 3: return reinterpret_cast<const void *>(k_engine_fast<double, 5>);
+    default: return reinterpret_cast<const void *>(k_engine_fast<double, 4>);
   }
 }
-
-constexpr size_t kFeStatic = sizeof(double) * 4 * 8 + sizeof(double) * 2 * kFeMaxWaves + sizeof(int32_t) * kFeMaxOps;
 
 amg_status fe_lds_limits(int device, size_t lds_max) {
   static std::once_flag once[64];
   if (device < 0 || device >= 64) return AMG_ERR_DEVICE;
   amg_status st = AMG_OK;
   std::call_once(once[device], [&]() {
-    const int dyn = static_cast<int>(lds_max - kFeStatic);
     for (int id = 0; id < 5; id++)
-      if (hipFuncSetAttribute(fe_kernel(id), hipFuncAttributeMaxDynamicSharedMemorySize, dyn) != hipSuccess)
+      if (hipFuncSetAttribute(fe_kernel(id), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              static_cast<int>(lds_max)) != hipSuccess)
         st = AMG_ERR_DEVICE;
   });
   return st;
@@ -861,39 +721,24 @@ const T *fe_level_ax(const QuadLevel &Q) {
   else return Q.ax64;
 }
 
-template <class T>
-void fe_fill(amg_hierarchy *h, int pi, FeArgs<T> &A) {
-  const int top = h->engine_top[pi];
-  A.nops = h->fe_nops[pi];
-  A.ops = static_cast<const int32_t *>(h->fe_ops[pi]);
-  A.ainv = h->ainv;
-  for (int i = 0; i < 4; i++) {
-    const int l = top + i;
-    A.ax[i] = l < h->nlev ? fe_level_ax<T>(h->lev[l]) : nullptr;
-  }
-  const LevelWork<T> &w = fe_work<T>(h)[top];
-  A.gv[V_G] = w.g;
-  A.gv[V_E] = w.e;
-  A.gv[V_R] = w.r;
-  A.gv[V_P0] = w.p0;
-  A.gv[V_Q0] = w.q0;
-  A.gv[V_P1] = w.p1;
-}
-
-template <class T, int KT, int KL>
+template <class T, int KT>
 void fe_launch(amg_hierarchy *h, int pi) {
   FeArgs<T> A{};
-  fe_fill<T>(h, pi, A);
-  const size_t lds = FeLayout<T, KT, KL>::bytes;
+  const int top = h->engine_top[pi];
+  A.ainv = h->ainv;
+  for (int i = 0; i < 3; i++) A.ax[i] = top + i < h->nlev ? fe_level_ax<T>(h->lev[top + i]) : nullptr;
+  const LevelWork<T> &w = fe_work<T>(h)[top];
+  A.g = w.g;
+  A.e = w.e;
+  const size_t lds = FeLayout<KT>::template bytes<T>();
   Timing &t = h->timing;
   const int kind = pi ? KK_ENGINE32 : KK_ENGINE64;
   if (t.kind == kind && t.used + 2 <= t.ev.size()) {  // dispatch-stamped start / stop
-    hipExtLaunchKernelGGL(k_engine_fast<T, KT, KL>, dim3(1), dim3(FeLayout<T, KT, KL>::threads), lds, h->stream,
-                          t.ev[t.used],
+    hipExtLaunchKernelGGL(k_engine_fast<T, KT>, dim3(1), dim3(FeLayout<KT>::threads), lds, h->stream, t.ev[t.used],
                           t.ev[t.used + 1], 0, A);
     t.used += 2;
   } else {
-    k_engine_fast<T, KT, KL><<<1, FeLayout<T, KT, KL>::threads, lds, h->stream>>>(A);
+    k_engine_fast<T, KT><<<1, FeLayout<KT>::threads, lds, h->stream>>>(A);
   }
 }
 
@@ -911,30 +756,18 @@ amg_status plan_engine_fast(amg_hierarchy *h) {
   }
   for (int id = 0; id < 5; id++) {
     const FeCfg c = kFeCfgs[id];
-    // the top is the largest level the count allows (k = min(L, 6) in FP32, min(L, 5) in FP64); LDS holds k <= 5 in
-    // FP32 and k <= 4 in FP64
-    const int kt = std::min(h->L, c.pi ? 6 : 5);
-    const int kl = std::min(kt, c.pi ? 5 : 4);
-    if (kt != c.kt || kl != c.kl) continue;
+    // the top is the largest level the count allows: k = min(L, 6) in FP32, min(L, 5) in FP64
+    if (std::min(h->L, c.pi ? 6 : 5) != c.kt) continue;
     const int top = 1 + (h->L - c.kt);  // hierarchy index of level k = kt
-    bool ok = fe_cfg_bytes(id) + kFeStatic <= h->lds_max;
+    bool ok = fe_cfg_bytes(id) <= h->lds_max;
     for (int l = top; l + 1 < h->nlev && ok; l++)
       if (h->lev[l].ovf_nnz != 0 || h->lev[l].same_color_ovf) ok = false;
     if (!ok) continue;
-    std::vector<int32_t> ops;
-    fe_emit_btilde(ops, c.kt, 0, false);
-    if (ops.size() > static_cast<size_t>(kFeMaxOps)) continue;
-    int32_t *d = static_cast<int32_t *>(dalloc(h, sizeof(int32_t) * ops.size()));
-    if (!d) return AMG_ERR_NOMEM;
-    QA_HIP(hipMemcpyAsync(d, ops.data(), sizeof(int32_t) * ops.size(), hipMemcpyHostToDevice, h->stream));
-    QA_HIP(hipStreamSynchronize(h->stream));
     h->fe_cfg[c.pi] = id;
-    h->fe_ops[c.pi] = d;
-    h->fe_nops[c.pi] = static_cast<int>(ops.size());
     h->engine_top[c.pi] = top;
-    h->engine_lds_top[c.pi] = top + (c.kt - c.kl);
+    h->engine_lds_top[c.pi] = top;
     h->engine_lds[c.pi] = fe_cfg_bytes(id);
-    h->engine_nops[c.pi] = static_cast<int>(ops.size());
+    h->engine_nops[c.pi] = fe_steps(c.kt);
   }
   if (h->fe_cfg[0] >= 0 || h->fe_cfg[1] >= 0) QA_TRY(fe_lds_limits(h->device, h->lds_max));
   return AMG_OK;
@@ -942,11 +775,11 @@ amg_status plan_engine_fast(amg_hierarchy *h) {
 
 void launch_engine_fast(amg_hierarchy *h, int pi) {
   switch (h->fe_cfg[pi]) {
-    case 0: fe_launch<float, 6, 5>(h, pi); break;
-    case 1: fe_launch<float, 5, 5>(h, pi); break;
-    case 2: fe_launch<float, 4, 4>(h, pi); break;
-    case 3: fe_launch<double, 5, 4>(h, pi); break;
-    case 4: fe_launch<double, 4, 4>(h, pi); break;
+    case 0: fe_launch<float, 6>(h, pi); break;
+    case 1: fe_launch<float, 5>(h, pi); break;
+    case 2: fe_launch<float, 4>(h, pi); break;
+    case 3: fe_launch<double, 5>(h, pi); break;
+    case 4: fe_launch<double, 4>(h, pi); break;
     default: break;
   }
 }

@@ -297,10 +297,8 @@ struct amg_hierarchy {
   size_t engine_lds[2] = {0, 0};
   size_t lds_max = 0;
   int use_engine = 1;                 // 0 off, 1 on (specialised engine where eligible), 2 the step interpreter only
-  // specialised engine (qa_engine.hip): configuration id per precision (-1 = the interpreter), its step list
+  // specialised engine (qa_engine.hip): configuration id per precision (-1 = the interpreter)
   int fe_cfg[2] = {-1, -1};
-  void *fe_ops[2] = {nullptr, nullptr};
-  int fe_nops[2] = {0, 0};
   int use_batch = 1;
   // whole-solve workgroup (batched serving of small systems), per precision
   void *wg_ops[2] = {nullptr, nullptr};
