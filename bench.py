@@ -106,7 +106,7 @@ def kernel_source_hash(kernel="resid_fine32"):
     csrc = os.path.join(ROOT, "paper_1209_5421_amd", "csrc")
     h = hashlib.sha256()
     if kernel.startswith("engine"):
-        names = ("qa_engine.hip", "qa_internal.hpp")
+        names = ("qa_engine.hip", "qa_internal.hpp", "qa_wave.hpp")
     else:
         with open(os.path.join(csrc, "qa_solve.hip")) as f:
             text = f.read()

@@ -50,6 +50,7 @@
 #include <vector>
 
 #include "qa_internal.hpp"
+#include "qa_wave.hpp"
 
 namespace qa {
 
@@ -158,59 +159,12 @@ __device__ __forceinline__ T fe_div(T n, T d, T rd) {
   return fe_fma(fe_fma(-q, d, n), rd, q);
 }
 
-// a lane's double moved by a DPP lane pattern (two 32-bit moves)
-template <int Ctrl>
-__device__ __forceinline__ double fe_dpp(double x) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), Ctrl, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), Ctrl, 0xf, 0xf, false);
-  return __builtin_bit_cast(double, (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) |
-                                        static_cast<unsigned>(lo));
-}
-__device__ __forceinline__ double fe_readlane(double x, int lane) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-  const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(u & 0xffffffffu), lane));
-  const unsigned hi = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane));
-  return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
-}
-
-// the sum of x over the lanes i, i + 16, i + 32, i + 48 of a wavefront, in every one of them: rows of 16 lanes added in
-// pairs, then the two halves
-__device__ __forceinline__ double fe_rows_sum(double x) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-  const auto l0 = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(u), static_cast<unsigned>(u), false, false);
-  const auto h0 =
-      __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(u >> 32), static_cast<unsigned>(u >> 32), false, false);
-  x = __builtin_bit_cast(double, (static_cast<unsigned long long>(h0[0]) << 32) | l0[0]) +
-      __builtin_bit_cast(double, (static_cast<unsigned long long>(h0[1]) << 32) | l0[1]);
-  const unsigned long long w = __builtin_bit_cast(unsigned long long, x);
-  const auto l1 = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(w), static_cast<unsigned>(w), false, false);
-  const auto h1 =
-      __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(w >> 32), static_cast<unsigned>(w >> 32), false, false);
-  return __builtin_bit_cast(double, (static_cast<unsigned long long>(h1[0]) << 32) | l1[0]) +
-         __builtin_bit_cast(double, (static_cast<unsigned long long>(h1[1]) << 32) | l1[1]);
-}
-
 // lane n's double in every lane of each row of 16 lanes (row_newbcast)
 template <int N>
 __device__ __forceinline__ double fe_bcast(double x) {
   const long u = __builtin_bit_cast(long, x);
   const long r = __builtin_amdgcn_update_dpp(0L, u, 0x150 + N, 0xf, 0xf, true);
   return __builtin_bit_cast(double, r);
-}
-
-// four sums over one wavefront at once: in two steps of pairs each lane hands over the half of its values that its
-// partner keeps, so that one value per lane is left (lane i holds a part of sum fe_sum_of(i & 3)), which is then added
-// over the lanes of equal i & 3. A fixed tree: the result depends only on the lanes' values.
-__device__ __forceinline__ constexpr int fe_sum_of(int i) { return (i & 1) * 2 + (i >> 1); }
-__device__ __forceinline__ double fe_wave_sum4(const double (&v)[4]) {
-  const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
-  const double k0 = (b0 ? v[2] : v[0]) + fe_dpp<0xb1>(b0 ? v[0] : v[2]);  // quad_perm [1, 0, 3, 2]
-  const double k1 = (b0 ? v[3] : v[1]) + fe_dpp<0xb1>(b0 ? v[1] : v[3]);
-  double k = (b1 ? k1 : k0) + fe_dpp<0x4e>(b1 ? k0 : k1);                 // quad_perm [2, 3, 0, 1]
-  k += fe_dpp<0x124>(k);                                                  // row_ror 4
-  k += fe_dpp<0x128>(k);                                                  // row_ror 8
-  return fe_rows_sum(k);
 }
 
 // Order between the sub-steps of the one-wavefront B~: a wavefront's LDS accesses are performed in issue order, so
@@ -234,22 +188,22 @@ template <int W, bool WAVE>
 __device__ __forceinline__ void fe_reduce4(double (&v)[4], double *red, bool act, int wl) {
   const int lane = static_cast<int>(threadIdx.x & 63);
   if constexpr (WAVE) {
-    const double k = fe_wave_sum4(v);
+    const double k = wave_sum4(v);
 #pragma unroll
-    for (int j = 0; j < 4; j++) v[fe_sum_of(j)] = fe_readlane(k, j);
+    for (int j = 0; j < 4; j++) v[sum4_of(j)] = readlane_f64(k, j);
   } else {
     if (act) {
-      const double k = fe_wave_sum4(v);
-      if (lane < 4) red[fe_sum_of(lane) * kFeRedWaves + wl] = k;
+      const double k = wave_sum4(v);
+      if (lane < 4) red[sum4_of(lane) * kFeRedWaves + wl] = k;
     }
     __syncthreads();
     if (act) {  // lanes 8 j .. 8 j + 7 hold the wavefronts' sums of v[j]
       double r = (lane & 7) < W ? red[((lane >> 3) & 3) * kFeRedWaves + (lane & 7)] : 0.0;
-      r += fe_dpp<0xb1>(r);
-      r += fe_dpp<0x4e>(r);
-      if constexpr (W > 4) r += fe_dpp<0x141>(r);  // row_half_mirror
+      r += dpp_f64<0xb1>(r);
+      r += dpp_f64<0x4e>(r);
+      if constexpr (W > 4) r += dpp_f64<0x141>(r);  // row_half_mirror
 #pragma unroll
-      for (int j = 0; j < 4; j++) v[j] = fe_readlane(r, 8 * j);
+      for (int j = 0; j < 4; j++) v[j] = readlane_f64(r, 8 * j);
     }
   }
 }
@@ -397,8 +351,8 @@ __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T 
       const bool first = half == 0;
       if (first) {  // alpha0, r = g - alpha0 q0
         d0 = v[0];
-        a0 = static_cast<T>(fe_readlane((d0 > 0.0) ? v[1] / d0 : 0.0, 0));  // uniform: kept in scalar registers
-        rd0 = fe_readlane(1.0 / d0, 0);  // ready before the second step's beta waits for it
+        a0 = static_cast<T>(readlane_f64((d0 > 0.0) ? v[1] / d0 : 0.0, 0));  // uniform: kept in scalar registers
+        rd0 = readlane_f64(1.0 / d0, 0);  // ready before the second step's beta waits for it
 #pragma unroll
         for (int t = 0; t < TR; t++)
           for_colors([&](auto cc) {

@@ -25,6 +25,7 @@
 #include <hip/hip_ext.h>
 
 #include "qa_internal.hpp"
+#include "qa_wave.hpp"
 
 namespace qa {
 
@@ -35,7 +36,7 @@ enum {
   S_D0 = 0, S_S0 = 1, S_A0 = 2, S_STOP = 3, S_T = 4, S_BETA = 5, S_D1 = 6, S_S1 = 7, S_A1 = 8,
   O_D = 0, O_S = 1, O_ALPHA = 2, O_BREAK = 3, O_ZQ = 4, O_BETA = 5, O_RR = 6, O_TT = 7, O_BB = 8
 };
-enum Epi { EPI_ALPHA0, EPI_BETA, EPI_ALPHA1, EPI_OUT_ALPHA, EPI_OUT_BETA, EPI_STORE };
+enum Epi { EPI_ALPHA0, EPI_BETA, EPI_ALPHA1, EPI_PAIR32, EPI_PAIR64, EPI_OUT_ALPHA, EPI_OUT_BETA, EPI_STORE };
 
 struct Red {
   double *partials;
@@ -62,6 +63,16 @@ __device__ inline void block_sum(double (&v)[ND]) {
     for (int j = 0; j < ND; j++) v[j] = (s[j][0] + s[j][1]) + (s[j][2] + s[j][3]);
 }
 
+// beta and alpha1 of Algorithm 2.1 from v = (p1, A p1), (r, p1), (p1, q0), (r, p0) and d0 = (p0, q0): with
+// d = p1 + beta p0 (beta rounded to T, as it is applied), (d, A d) and (r, d) are sums of these, so A d is never formed
+template <class T>
+__device__ inline void pair_scalars(const double *v, double d0, bool stop, double &beta, double &a1) {
+  const double b = static_cast<double>(static_cast<T>(stop ? 0.0 : -v[2] / d0));
+  const double d1 = v[0] + b * (2.0 * v[2] + b * d0);
+  beta = b;
+  a1 = (stop || !(d1 > 0.0)) ? 0.0 : (v[1] + b * v[3]) / d1;
+}
+
 __device__ inline void epilogue(const double *acc, const Red &R) {
   double *sc = R.sc;
   switch (R.epi) {
@@ -79,6 +90,18 @@ __device__ inline void epilogue(const double *acc, const Red &R) {
       const double d = acc[0], s = acc[1];
       sc[S_D1] = d; sc[S_S1] = s;
       sc[S_A1] = (sc[S_STOP] != 0.0 || !(d > 0.0)) ? 0.0 : s / d;
+      break;
+    }
+    case EPI_PAIR32: {
+      double b, a;
+      pair_scalars<float>(acc, sc[S_D0], sc[S_STOP] != 0.0, b, a);
+      sc[S_T] = acc[2]; sc[S_BETA] = b; sc[S_S1] = acc[1]; sc[S_A1] = a;
+      break;
+    }
+    case EPI_PAIR64: {
+      double b, a;
+      pair_scalars<double>(acc, sc[S_D0], sc[S_STOP] != 0.0, b, a);
+      sc[S_T] = acc[2]; sc[S_BETA] = b; sc[S_S1] = acc[1]; sc[S_A1] = a;
       break;
     }
     case EPI_OUT_ALPHA: {
@@ -136,10 +159,19 @@ __device__ __forceinline__ T upd1_r(T g, T a0, T q0) {
 // that kernel writes e and r and reads its right-hand side r formed on the fly
 template <class T>
 struct Upd1 {
-  const double *sc;
+  double *sc;
   const T *g, *q0, *p0;
   T *e, *r;
+  const double *part;  // partial sums (p0, q0), (g, p0) not yet added up (tiled levels), four doubles to a workgroup
+  int nb;              // of nb workgroups; null: the scalars hold alpha0
   __device__ T a0() const { return static_cast<T>(sc[S_A0]); }
+  // alpha0 from the sums v; `store`: this thread keeps the scalars for the kernels behind
+  __device__ double alpha0(const double (&v)[4], bool store) const {
+    const bool stop = !(v[0] > 0.0);
+    const double a = stop ? 0.0 : v[1] / v[0];
+    if (store) sc[S_D0] = v[0], sc[S_S0] = v[1], sc[S_STOP] = stop ? 1.0 : 0.0, sc[S_A0] = a;
+    return a;
+  }
   __device__ T rv(T a, uint32_t i) const { return upd1_r(g[i], a, q0[i]); }
   __device__ void store(T a, int64_t i) const {
     e[i] = a * p0[i];
@@ -149,10 +181,18 @@ struct Upd1 {
 
 // the child's pending last update e_c + a1 (p1 + beta p0) of Algorithm 2.1, formed where the prolongation reads e_c
 // (null sc: nothing pending)
+// With `part`, beta and alpha1 come from partial sums that a tiled level left (nb workgroups, four doubles each).
 template <class T>
 struct Pending {
   const double *sc;
   const T *p1, *p0;
+  const double *part;
+  int nb;
+  __device__ void pair(const double (&v)[4], T &a1, T &beta) const {
+    double b, a;
+    pair_scalars<T>(v, sc[S_D0], sc[S_STOP] != 0.0, b, a);
+    beta = static_cast<T>(b), a1 = static_cast<T>(a);
+  }
   __device__ T mix(T em, T p1m, T p0m) const {
     const T a1 = static_cast<T>(sc[S_A1]), beta = static_cast<T>(sc[S_BETA]);
     return em + a1 * (p1m + beta * p0m);
@@ -1049,103 +1089,92 @@ __global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__rest
   if constexpr (BETA) reduce_finish<1>(v, R);
 }
 
-// Tiles of the per-step path. Workgroup b owns the 16 x 16 super-cells j in [256 b, 256 b + 256), a Morton-aligned
-// square, and stages the values of the square and four rings of super-cells around it in LDS. A stencil reaches one
-// super-cell further, so a chain of color phases runs on shrinking rings: each phase relaxes the rows that the later
-// phases of the square's rows read (ring rows again in the neighbouring workgroups, from the same values). Each row
-// takes the values, slot order and arithmetic of the one-launch-per-phase kernels, so the square's rows equal
-// theirs bit for bit.
-constexpr int kTileSide = 16;                          // super-cells per side of a workgroup's square
-constexpr int kTileRings = 4;                          // rings staged around it
-constexpr int kTileStage = kTileSide + 2 * kTileRings;  // 24
-constexpr int kTileCells = kTileSide * kTileSide;       // 256: thread t < 256 holds super-cell 256 b + t
-constexpr int kTileThreads = 512;                      // threads of a tile workgroup: one row slot per thread and
-                                                       // phase, so a wavefront's prologue loads stay in flight together
-static_assert(kTileCells == kBlock, "the square's partial sums are those of a kBlock-thread per-phase launch");
-static_assert(kTileStage == 24 && kTileRings == 4, "the staged square is 6 x 6 blocks of 4 x 4 super-cells");
-
-template <int RG>
-struct RingRows {  // row slots per thread of a phase over the square and its RG innermost rings
-  static constexpr int side = kTileSide + 2 * RG;
-  static constexpr int count = side * side;
-  static constexpr int slots = (count + kTileThreads - 1) / kTileThreads;
+// Tiles of the per-step path. Workgroup b owns a Morton-aligned square of TS x TS super-cells, j in
+// [TS^2 b, TS^2 (b + 1)), and stages the values of the square and RS rings of super-cells around it in LDS. A stencil
+// reaches one super-cell further, so a chain of color phases runs on shrinking rings: each phase relaxes the rows that
+// the later phases of the square's rows read (ring rows again in the neighbouring workgroups, from the same values).
+// Each row takes the values, slot order and arithmetic of the one-launch-per-phase kernels, so the square's rows equal
+// theirs bit for bit. Cells outside the grid are staged as zeros (their slots hold 0), so a row needs no edge tests.
+//
+// A launch is bound by its latency: dispatch, one round of loads, four LDS phases, the stores. B~ of a level takes four
+// launches (two tiles per B^, A u and the inner products in the second, their partial sums added up by the kernel that
+// needs them) where tiles, products and reductions of their own took nine: 47 -> 22 us per visit of the 16,384-cell
+// level in FP32 (4.9 / 5.4 us per presmoothing tile, 5.7 / 5.9 us with the products, against 6.2 + 4.7 + 4.3 us), 8.92
+// instead of 10.41 ms per FP32-preconditioned solve of 1,044,484 unknowns, 8.95 instead of 11.58 ms in FP64 on 301,401.
+template <int TS, int RS>
+struct Tile {
+  static constexpr int NT = TS == 16 ? 512 : 256;  // threads: at most two row slots per thread and phase, so that a
+                                                   // wavefront's prologue loads stay in flight together
+  static constexpr int W = TS + 2 * RS;            // staged super-cells per side
+  static constexpr int cells = TS * TS;
+  static constexpr int stage_slots = (W * W + NT - 1) / NT;
 };
 
-constexpr int kStageSlots = (kTileStage * kTileStage + kTileThreads - 1) / kTileThreads;  // 2
-
-// staging slot i of this thread (the 6 x 6 blocks of 4 x 4 super-cells in turn, Morton order inside a block, so a
-// wavefront reads four contiguous runs): its staged index, -1 outside the grid, and its super-cell's Morton index
-__device__ inline int stage_slot(int i, int px0, int py0, int np, uint32_t &jm) {
-  const int e = static_cast<int>(threadIdx.x) + i * kTileThreads;
-  const int blk = e >> 4, w = e & 15;
-  const int lx = 4 * (blk % 6) + static_cast<int>(compact_bits(static_cast<uint32_t>(w)));
-  const int ly = 4 * (blk / 6) + static_cast<int>(compact_bits(static_cast<uint32_t>(w) >> 1));
-  const int px = px0 + lx, py = py0 + ly;
-  const bool ok = e < kTileStage * kTileStage && px >= 0 && px < np && py >= 0 && py < np;
-  jm = ok ? morton(static_cast<uint32_t>(px), static_cast<uint32_t>(py)) : 0u;
-  return ok ? ly * kTileStage + lx : -1;
-}
-
-template <class T, int RG>
-struct RingData {
-  T a[RingRows<RG>::slots][9];
-  T f[RingRows<RG>::slots];
-  T f2[RingRows<RG>::slots];  // with a pending first inner update: q0 of the row (f holds g until rhs_upd)
-  int l[RingRows<RG>::slots];  // staged index of the row's super-cell, -1 when the slot has no row
-};
-
-// staged super-cell (lx, ly) of slot i. The staged square is 6 x 6 Morton-contiguous blocks of 4 x 4 super-cells;
-// the rows of a region are taken block by block (bands of block rows, blocks across a band, row-major inside the
-// part of a block in the region), so that a wavefront's loads touch a few blocks. For the square alone (RG = 0):
-// its Morton order, so that thread t holds super-cell 256 b + t (threads from 256 on hold no row).
-template <int RG>
-__device__ inline void ring_slot_xy(int i, int &lx, int &ly) {
-  const int r = static_cast<int>(threadIdx.x) + i * kTileThreads;
-  if constexpr (RG == 0) {
-    lx = static_cast<int>(compact_bits(static_cast<uint32_t>(r))) + kTileRings;
-    ly = static_cast<int>(compact_bits(static_cast<uint32_t>(r) >> 1)) + kTileRings;
-  } else {
-    constexpr int W = RingRows<RG>::side;
-    constexpr int band0 = W * RG, bandm = W * 4;  // rows of the outer and of an inner band of blocks
-    int by, rb, h;
-    if (r < band0) {
-      by = 0, rb = r, h = RG;
-    } else if (r < band0 + 4 * bandm) {
-      const int t = r - band0;
-      by = 1 + t / bandm, rb = t % bandm, h = 4;
-    } else {
-      by = 5, rb = r - band0 - 4 * bandm, h = RG;
-    }
-    int bx, rs, w;
+// staged place (lx, ly) of entry r of the square and its RG innermost rings. The entries are taken by the
+// Morton-contiguous 4 x 4 blocks of super-cells that the square is made of (bands of blocks, an outer band on each
+// side as wide as the rings; blocks across a band; row-major inside a block), so that a wavefront's loads touch few
+// blocks.
+template <int TS, int RS, int RG>
+__device__ __forceinline__ void ring_place(int r, int &lx, int &ly) {
+  constexpr int W = TS + 2 * RG, nb = TS / 4, band0 = W * RG, bandm = W * 4;
+  // position inside a block of width w: (x, y) = (rs mod w, rs div w) with w = 4 or RG
+  auto in_band = [&](int rb, auto hh, int by) {
+    constexpr int h = decltype(hh)::value, hd = h > 0 ? h : 1;
+    int bx, rs;
+    bool outer = true;
     if (rb < RG * h) {
-      bx = 0, rs = rb, w = RG;
-    } else if (rb < RG * h + 16 * h) {
+      bx = 0, rs = rb;
+    } else if (rb < RG * h + nb * 4 * h) {
       const int t = rb - RG * h;
-      bx = 1 + t / (4 * h), rs = t % (4 * h), w = 4;
+      bx = 1 + t / (4 * hd), rs = t % (4 * hd), outer = false;
     } else {
-      bx = 5, rs = rb - RG * h - 16 * h, w = RG;
+      bx = nb + 1, rs = rb - RG * h - nb * 4 * h;
     }
-    lx = (bx == 0 ? kTileRings - RG : 4 * bx) + rs % w;
-    ly = (by == 0 ? kTileRings - RG : 4 * by) + rs / w;
+    constexpr int wo = RG > 0 ? RG : 1;
+    lx = RS + (bx == 0 ? -RG : 4 * (bx - 1)) + (outer ? rs % wo : rs & 3);
+    ly = RS + (by == 0 ? -RG : 4 * (by - 1)) + (outer ? rs / wo : rs >> 2);
+  };
+  if (r < band0) {
+    in_band(r, std::integral_constant<int, RG>{}, 0);
+  } else if (r < band0 + nb * bandm) {
+    const int t = r - band0;
+    in_band(t % bandm, std::integral_constant<int, 4>{}, 1 + t / bandm);
+  } else {
+    in_band(r - band0 - nb * bandm, std::integral_constant<int, RG>{}, nb + 1);
   }
 }
 
+// a region's row slots of this thread (region: the square and its RG innermost rings)
+template <class T, int TS, int RS, int RG>
+struct RingRows {
+  static constexpr int count = (TS + 2 * RG) * (TS + 2 * RG);
+  static constexpr int slots = (count + Tile<TS, RS>::NT - 1) / Tile<TS, RS>::NT;
+  T a[slots][9];
+  T f[slots];
+  T f2[slots];       // with a pending first inner update: q0 of the row (f holds g until rhs_upd)
+  int l[slots];      // staged place of the row's super-cell, -1 when the slot has no row
+  uint32_t j[slots]; // its Morton index
+  bool sq[slots];    // it lies in the square
+};
+
 // the operator rows and right-hand sides of the color-C rows of the region. UPD: f and f2 take g and q0 of the
 // pending first inner update, combined by rhs_upd once every load has been issued.
-template <class T, int RG, int C, bool UPD>
-__device__ inline void ring_load(const QView<T> &Q, const T *__restrict__ f, const Upd1<T> &U, int px0, int py0,
-                                 int np, uint32_t n4, RingData<T, RG> &D) {
+template <int C, bool UPD, class T, int TS, int RS, int RG>
+__device__ __forceinline__ void ring_load(const QView<T> &Q, const T *__restrict__ f, const Upd1<T> &U, int px0,
+                                          int py0, int np, uint32_t n4, RingRows<T, TS, RS, RG> &D) {
+  using R = RingRows<T, TS, RS, RG>;
 #pragma unroll
-  for (int i = 0; i < RingRows<RG>::slots; i++) {
+  for (int i = 0; i < R::slots; i++) {
+    const int r = static_cast<int>(threadIdx.x) + i * Tile<TS, RS>::NT;
     int lx, ly;
-    ring_slot_xy<RG>(i, lx, ly);
-    const int r = static_cast<int>(threadIdx.x) + i * kTileThreads;
+    ring_place<TS, RS, RG>(r, lx, ly);
     const int px = px0 + lx, py = py0 + ly;
-    const bool ok = r < RingRows<RG>::count && px >= 0 && px < np && py >= 0 && py < np;
-    D.l[i] = ok ? ly * kTileStage + lx : -1;
+    const bool ok = r < R::count && px >= 0 && px < np && py >= 0 && py < np;
+    D.l[i] = ok ? ly * Tile<TS, RS>::W + lx : -1;
+    D.sq[i] = ok && lx >= RS && lx < RS + TS && ly >= RS && ly < RS + TS;
     // loads without branches (a slot without a row reads row C n/4 and ignores it), so that none waits for another
-    const uint32_t jm = ok ? morton(static_cast<uint32_t>(px), static_cast<uint32_t>(py)) : 0u;
-    const uint32_t q = static_cast<uint32_t>(C) * n4 + jm;
+    D.j[i] = ok ? morton(static_cast<uint32_t>(px), static_cast<uint32_t>(py)) : 0u;
+    const uint32_t q = static_cast<uint32_t>(C) * n4 + D.j[i];
 #pragma unroll
     for (int s = 0; s < 9; s++) D.a[i][s] = Q.ax[s * Q.n + q];
     if constexpr (UPD) {
@@ -1158,99 +1187,105 @@ __device__ inline void ring_load(const QView<T> &Q, const T *__restrict__ f, con
 }
 
 // r = g - a0 q0 of the pending first inner update as the right-hand side of the region's rows
-template <class T, int RG>
-__device__ inline void rhs_upd(RingData<T, RG> &D, T a0) {
+template <class T, int TS, int RS, int RG>
+__device__ __forceinline__ void rhs_upd(RingRows<T, TS, RS, RG> &D, T a0) {
 #pragma unroll
-  for (int i = 0; i < RingRows<RG>::slots; i++)
+  for (int i = 0; i < RingRows<T, TS, RS, RG>::slots; i++)
     if (D.l[i] >= 0) D.f[i] = upd1_r(D.f[i], a0, D.f2[i]);
 }
 
-// sum over the nine slots of a color-C row at staged index l (a slot outside the grid holds 0: its product is taken
-// with the row's own value, as the per-phase kernels do)
-template <class T, int C>
-__device__ inline T ring_row(const T (&a)[9], int l, int px0, int py0, int np, const T (*sv)[kTileStage * kTileStage]) {
-  constexpr int cx = C & 1, cy = C >> 1;
-  const int lx = l % kTileStage, ly = l / kTileStage;
+// sum over the nine slots of a color-C row at staged place l
+template <int C, int W, class T>
+__device__ __forceinline__ T ring_row(const T (&a)[9], int l, const T (*sv)[W * W]) {
   T acc = 0;
 #pragma unroll
   for (int s = 0; s < 9; s++) {
-    const int ux = cx + slot_dx(s), uy = cy + slot_dy(s);
+    const int ux = (C & 1) + slot_dx(s), uy = (C >> 1) + slot_dy(s);
     const int cn = (ux & 1) | ((uy & 1) << 1);
-    const int nx = lx + (ux >> 1), ny = ly + (uy >> 1);
-    const int gx = px0 + nx, gy = py0 + ny;
-    const bool in = gx >= 0 && gx < np && gy >= 0 && gy < np;
-    acc += a[s] * (in ? sv[cn][ny * kTileStage + nx] : sv[C][l]);
+    acc += a[s] * sv[cn][l + (uy >> 1) * W + (ux >> 1)];
   }
   return acc;
 }
 
 // one color phase: x_q + (f_q - (A x)_q) / a_qq for the color-C rows of the region
-template <class T, int RG, int C>
-__device__ inline void ring_phase(const RingData<T, RG> &D, int px0, int py0, int np, T (*sv)[kTileStage * kTileStage]) {
+template <int C, class T, int TS, int RS, int RG>
+__device__ __forceinline__ void ring_phase(const RingRows<T, TS, RS, RG> &D,
+                                           T (*sv)[Tile<TS, RS>::W * Tile<TS, RS>::W]) {
 #pragma unroll
-  for (int i = 0; i < RingRows<RG>::slots; i++) {
+  for (int i = 0; i < RingRows<T, TS, RS, RG>::slots; i++) {
     const int l = D.l[i];
     if (l < 0) continue;
-    const T acc = ring_row<T, C>(D.a[i], l, px0, py0, np, sv);
-    const T xq = sv[C][l];
-    sv[C][l] = xq + (D.f[i] - acc) / D.a[i][0];
+    const T acc = ring_row<C, Tile<TS, RS>::W>(D.a[i], l, sv);
+    sv[C][l] += (D.f[i] - acc) / D.a[i][0];
   }
 }
 
-// residuals f_q - (A x)_q of the square's color-C rows among the region's rows, by the square's Morton index
-template <class T, int RG, int C>
-__device__ inline void ring_resid(const RingData<T, RG> &D, int px0, int py0, int np,
-                                  const T (*sv)[kTileStage * kTileStage], T *res) {
-#pragma unroll
-  for (int i = 0; i < RingRows<RG>::slots; i++) {
-    const int l = D.l[i];
-    if (l < 0) continue;
-    const int tx = l % kTileStage - kTileRings, ty = l / kTileStage - kTileRings;
-    if (tx < 0 || tx >= kTileSide || ty < 0 || ty >= kTileSide) continue;
-    const T acc = ring_row<T, C>(D.a[i], l, px0, py0, np, sv);
-    res[morton(static_cast<uint32_t>(tx), static_cast<uint32_t>(ty))] = D.f[i] - acc;
-  }
+// the four sums of a launch's workgroups (part: four doubles each, nb <= 256 of them), the same in every thread of every
+// workgroup that asks: the loads, to be issued with the caller's others, and the sums (all threads call both)
+__device__ __forceinline__ void fold_load(const double *__restrict__ part, int nb, double (&v)[4]) {
+  const int t = static_cast<int>(threadIdx.x);
+  const double2 *p = reinterpret_cast<const double2 *>(part) + 2 * (t < nb ? t : 0);
+  const double2 x = p[0], y = p[1];
+  const bool in = t < nb;
+  v[0] = in ? x.x : 0.0, v[1] = in ? x.y : 0.0, v[2] = in ? y.x : 0.0, v[3] = in ? y.y : 0.0;
 }
-
-// (p1, q0) partial of the square: the sum over threads 0..255 in block_sum's order, stored as reduce_finish stores
-// it (every thread of the workgroup calls this)
-__device__ inline void tile_reduce_finish(double v, const Red &R) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  __shared__ double s[kTileThreads / 64];
-  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+template <int NT>
+__device__ __forceinline__ void block_sum4(double (&v)[4], double (*red)[8]) {  // red[4][8] in LDS
+  const int lane = static_cast<int>(threadIdx.x & 63), w = static_cast<int>(threadIdx.x >> 6);
+  const double k = wave_sum4(v);
+  if (lane < 4) red[sum4_of(lane)][w] = k;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double acc[1] = {(s[0] + s[1]) + (s[2] + s[3])};
-    if (gridDim.x == 1) epilogue(acc, R);
-    else R.partials[blockIdx.x] = acc[0];
-  }
+  double r = (lane & 7) < NT / 64 ? red[(lane >> 3) & 3][lane & 7] : 0.0;  // lanes 8 j .. 8 j + 7: the waves' v[j]
+  r += dpp_f64<0xb1>(r);
+  r += dpp_f64<0x4e>(r);
+  r += dpp_f64<0x141>(r);
+#pragma unroll
+  for (int j = 0; j < 4; j++) v[j] = readlane_f64(r, 8 * j);
 }
 
 // The whole first post-smoothing sweep (color phases 3, 2, 1, 0, the prolongation folded in as in k_cgs_post) of a
-// level without same-color couplings or overflow entries, in one launch: u + P e_c staged over the square and its
-// rings, phase C on the color-C rows of the square and its C innermost rings. With BETA thread t forms (p1, q0) over
-// rows j + c n/4 of super-cell j = 256 b + t, as k_cgs_post<T, 0, true> does, so the partials are the same.
-template <class T, bool BETA>
-__global__ void __launch_bounds__(kTileThreads) k_cgs_post4(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
-                                                      const T *__restrict__ ec, Pending<T> pend,
-                                                      const T *__restrict__ q0, Red R) {
-  __shared__ T sv[4][kTileStage * kTileStage];
+// level without same-color couplings or overflow entries, in one launch: x + P e_c (x: the presmoothed values) staged
+// over the square and its rings, each phase on one ring less, the result to u (another vector: the neighbouring
+// workgroups read x around their squares at any time). SP > 0: the last sweep of a B^ of Algorithm 2.1; one more ring gives the final
+// values around the square, and y = A u of the square's rows is formed here too, with the square's partial sums of
+// (u, y), (f, u) and
+//   SP 1, the first inner step (u = p0): y is stored as q0;
+//   SP 2, the second (u = p1): of (u, q0) and (f, p0) as well, from which pair_scalars has beta and alpha1.
+// This replaces a pass over the level per inner step (k_cspmv_dot, k_cspmv_dir) and two reductions. (In the first inner
+// step u is p0 itself, which is not read then.)
+template <class T, int SP, int TS>
+__global__ void __launch_bounds__((Tile<TS, SP ? 5 : 4>::NT))
+    k_cgs_post4(QView<T> Q, const T *__restrict__ f, const T *__restrict__ x, T *u, const T *__restrict__ ec,
+                Pending<T> pend, T *q0, const T *p0, double *__restrict__ part) {
+  constexpr int RS = SP ? 5 : 4, G = RS - 4;  // G: rings of the last phase
+  using TL = Tile<TS, RS>;
+  constexpr int NT = TL::NT, W = TL::W;
+  __shared__ T sv[4][W * W];
+  __shared__ double red[4][8];
   const int kc = Q.k - 1;
   const int np = 1 << kc;
   const uint32_t n4 = static_cast<uint32_t>(Q.n >> 2);
-  const uint32_t j0 = blockIdx.x * static_cast<uint32_t>(kTileCells);
-  const int px0 = static_cast<int>(compact_bits(j0)) - kTileRings;
-  const int py0 = static_cast<int>(compact_bits(j0 >> 1)) - kTileRings;
+  const uint32_t j0 = blockIdx.x * static_cast<uint32_t>(TL::cells);
+  const int px0 = static_cast<int>(compact_bits(j0)) - RS;
+  const int py0 = static_cast<int>(compact_bits(j0 >> 1)) - RS;
+  const int t = static_cast<int>(threadIdx.x);
   // every load of the prologue is issued before the first value is formed
-  // (branch-free: a slot outside the grid reads super-cell 0 and ignores it)
-  int sl[kStageSlots];
-  T sx[kStageSlots][4], se[kStageSlots], s1[kStageSlots], s0[kStageSlots];
+  // (branch-free: a slot outside the grid reads super-cell 0 and stages zero)
+  double pv[4];
+  if (pend.part) fold_load(pend.part, pend.nb, pv);
+  int sl[TL::stage_slots];
+  bool sin[TL::stage_slots];
+  T sx[TL::stage_slots][4], se[TL::stage_slots], s1[TL::stage_slots], s0[TL::stage_slots];
   const T *p1p = pend.sc ? pend.p1 : ec, *p0p = pend.sc ? pend.p0 : ec;
 #pragma unroll
-  for (int i = 0; i < kStageSlots; i++) {
-    uint32_t jm;
-    sl[i] = stage_slot(i, px0, py0, np, jm);
+  for (int i = 0; i < TL::stage_slots; i++) {
+    const int r = t + i * NT;
+    int lx, ly;
+    ring_place<TS, RS, RS>(r, lx, ly);
+    const int px = px0 + lx, py = py0 + ly;
+    sl[i] = r < W * W ? ly * W + lx : -1;
+    sin[i] = r < W * W && px >= 0 && px < np && py >= 0 && py < np;
+    const uint32_t jm = sin[i] ? morton(static_cast<uint32_t>(px), static_cast<uint32_t>(py)) : 0u;
 #pragma unroll
     for (int c = 0; c < 4; c++) sx[i][c] = x[c * n4 + jm];
     const uint32_t m = q_of_m(jm, kc);
@@ -1258,76 +1293,136 @@ __global__ void __launch_bounds__(kTileThreads) k_cgs_post4(QView<T> Q, const T 
     s1[i] = p1p[m];
     s0[i] = p0p[m];
   }
-  T q0v[4];
-  const int t = static_cast<int>(threadIdx.x);
-  const uint32_t jt = j0 + static_cast<uint32_t>(t & (kTileCells - 1));  // clamped for threads without a super-cell
-  if constexpr (BETA) {
-#pragma unroll
-    for (int c = 0; c < 4; c++) q0v[c] = q0[c * n4 + jt];
-  }
   const Upd1<T> none{};
-  RingData<T, 3> D3;
-  RingData<T, 2> D2;
-  RingData<T, 1> D1;
-  RingData<T, 0> D0;
-  ring_load<T, 3, 3, false>(Q, f, none, px0, py0, np, n4, D3);
-  ring_load<T, 2, 2, false>(Q, f, none, px0, py0, np, n4, D2);
-  ring_load<T, 1, 1, false>(Q, f, none, px0, py0, np, n4, D1);
-  ring_load<T, 0, 0, false>(Q, f, none, px0, py0, np, n4, D0);
+  RingRows<T, TS, RS, 3 + G> D3;
+  RingRows<T, TS, RS, 2 + G> D2;
+  RingRows<T, TS, RS, 1 + G> D1;
+  RingRows<T, TS, RS, G> D0;
+  ring_load<3, false>(Q, f, none, px0, py0, np, n4, D3);
+  ring_load<2, false>(Q, f, none, px0, py0, np, n4, D2);
+  ring_load<1, false>(Q, f, none, px0, py0, np, n4, D1);
+  ring_load<0, false>(Q, f, none, px0, py0, np, n4, D0);
+  // SP 2: q0 and p0 of the rows, for the inner products
+  T xq[4][2], xp[4][2];
+  if constexpr (SP == 2) {
+    auto extra = [&](auto &D, auto cc) {
+      constexpr int c = decltype(cc)::value;
+#pragma unroll
+      for (int i = 0; i < std::remove_reference_t<decltype(D)>::slots; i++) {
+        const uint32_t q = static_cast<uint32_t>(c) * n4 + D.j[i];
+        xq[c][i] = q0[q];
+        xp[c][i] = p0[q];
+      }
+    };
+    extra(D0, std::integral_constant<int, 0>{});
+    extra(D1, std::integral_constant<int, 1>{});
+    extra(D2, std::integral_constant<int, 2>{});
+    extra(D3, std::integral_constant<int, 3>{});
+  }
+  T a1 = 0, beta = 0;
+  if (pend.part) {
+    block_sum4<NT>(pv, red);
+    pend.pair(pv, a1, beta);
+  } else if (pend.sc) {
+    a1 = static_cast<T>(pend.sc[S_A1]), beta = static_cast<T>(pend.sc[S_BETA]);
+  }
   // u + P e_c as k_cgs_post forms it
 #pragma unroll
-  for (int i = 0; i < kStageSlots; i++)
+  for (int i = 0; i < TL::stage_slots; i++)
     if (sl[i] >= 0) {
-      const T em = pend.sc ? pend.mix(se[i], s1[i], s0[i]) : se[i];
+      const T em = pend.sc ? se[i] + a1 * (s1[i] + beta * s0[i]) : se[i];
 #pragma unroll
-      for (int c = 0; c < 4; c++) sv[c][sl[i]] = sx[i][c] + em;
+      for (int c = 0; c < 4; c++) sv[c][sl[i]] = sin[i] ? sx[i][c] + em : T(0);
     }
   __syncthreads();
-  ring_phase<T, 3, 3>(D3, px0, py0, np, sv);
+  ring_phase<3>(D3, sv);
   __syncthreads();
-  ring_phase<T, 2, 2>(D2, px0, py0, np, sv);
+  ring_phase<2>(D2, sv);
   __syncthreads();
-  ring_phase<T, 1, 1>(D1, px0, py0, np, sv);
+  ring_phase<1>(D1, sv);
   __syncthreads();
-  ring_phase<T, 0, 0>(D0, px0, py0, np, sv);  // thread t's own row: read back below by thread t alone
-  const int lj = D0.l[0];
-  double v = 0.0;
-  if (t < kTileCells) {
+  ring_phase<0>(D0, sv);
+  __syncthreads();
+  if constexpr (SP > 0) {
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    auto rows = [&](auto &D, auto cc) {
+      constexpr int c = decltype(cc)::value;
 #pragma unroll
-    for (int c = 0; c < 4; c++) x[c * n4 + jt] = sv[c][lj];
-    if constexpr (BETA) {
-      v = static_cast<double>(sv[0][lj]) * static_cast<double>(q0v[0]);
+      for (int i = 0; i < std::remove_reference_t<decltype(D)>::slots; i++) {
+        if (!D.sq[i]) continue;
+        const T y = ring_row<c, W>(D.a[i], D.l[i], sv);
+        const double ud = static_cast<double>(sv[c][D.l[i]]), fd = static_cast<double>(D.f[i]);
+        v[0] += ud * static_cast<double>(y);
+        v[1] += fd * ud;
+        if constexpr (SP == 1) {
+          q0[static_cast<uint32_t>(c) * n4 + D.j[i]] = y;
+        } else {
+          v[2] += ud * static_cast<double>(xq[c][i]);
+          v[3] += fd * static_cast<double>(xp[c][i]);
+        }
+      }
+    };
+    rows(D0, std::integral_constant<int, 0>{});
+    rows(D1, std::integral_constant<int, 1>{});
+    rows(D2, std::integral_constant<int, 2>{});
+    rows(D3, std::integral_constant<int, 3>{});
+    const double k = wave_sum4(v);
+    if ((t & 63) < 4) red[sum4_of(t & 3)][t >> 6] = k;
+    __syncthreads();
+    if (t < 4) {
+      double acc = 0.0;
 #pragma unroll
-      for (int c = 1; c < 4; c++) v += static_cast<double>(sv[c][lj]) * static_cast<double>(q0v[c]);
+      for (int w = 0; w < NT / 64; w++) acc += red[t][w];
+      part[static_cast<size_t>(blockIdx.x) * 4 + t] = acc;
     }
   }
-  if constexpr (BETA) tile_reduce_finish(v, R);
+  // the square's values (colors in turn, Morton order)
+#pragma unroll
+  for (int i = t; i < 4 * TL::cells; i += NT) {
+    const int c = i / TL::cells, w = i % TL::cells;
+    const int lx = static_cast<int>(compact_bits(static_cast<uint32_t>(w))) + RS;
+    const int ly = static_cast<int>(compact_bits(static_cast<uint32_t>(w) >> 1)) + RS;
+    u[c * n4 + j0 + static_cast<uint32_t>(w)] = sv[c][ly * W + lx];
+  }
 }
 
 // The whole presmoothing sweep from zero and the restriction (k_cgs_first2, the color phases 2 and 3, k_cres_restrict)
 // of a level without same-color couplings or overflow entries, in one launch: color 0 = f / diag staged over the
 // square and its rings (colors 1 to 3 zero), then color 1 on three rings, color 2 on two, color 3 on one, and the
 // square's residuals summed over the four children in the order 0, 1, 3, 2 into the parent's slot. UPD: the right-hand
-// side is the pending first inner update's r, formed on the fly, and the update's e and r are stored for the square.
-template <class T, bool UPD>
-__global__ void __launch_bounds__(kTileThreads) k_cgs_pre4(QView<T> Q, const T *__restrict__ f, T *__restrict__ x, Upd1<T> U,
-                                                     T *__restrict__ gc) {
-  __shared__ T sv[4][kTileStage * kTileStage];
-  __shared__ T res[4][kTileCells];
+// side is the pending first inner update's r, formed on the fly, and the update's e and r are stored for the square;
+// alpha0 comes from the scalars or, where the update names partial sums, from those (workgroup 0 stores the scalars).
+template <class T, bool UPD, int TS>
+__global__ void __launch_bounds__((Tile<TS, 4>::NT))
+    k_cgs_pre4(QView<T> Q, const T *__restrict__ f, T *__restrict__ x, Upd1<T> U, T *__restrict__ gc) {
+  constexpr int RS = 4;
+  using TL = Tile<TS, RS>;
+  constexpr int NT = TL::NT, W = TL::W;
+  __shared__ T sv[4][W * W];
+  __shared__ T res[4][TL::cells];
+  __shared__ double red[4][8];
   const int kc = Q.k - 1;
   const int np = 1 << kc;
   const uint32_t n4 = static_cast<uint32_t>(Q.n >> 2);
-  const uint32_t j0 = blockIdx.x * static_cast<uint32_t>(kTileCells);
-  const int px0 = static_cast<int>(compact_bits(j0)) - kTileRings;
-  const int py0 = static_cast<int>(compact_bits(j0 >> 1)) - kTileRings;
-  const T a0 = UPD ? U.a0() : T(0);
+  const uint32_t j0 = blockIdx.x * static_cast<uint32_t>(TL::cells);
+  const int px0 = static_cast<int>(compact_bits(j0)) - RS;
+  const int py0 = static_cast<int>(compact_bits(j0 >> 1)) - RS;
+  const int t = static_cast<int>(threadIdx.x);
   // every load of the prologue is issued before the first value is formed
-  int sl[kStageSlots];
-  T sf[kStageSlots], sq[kStageSlots], sd[kStageSlots];
+  double pv[4];
+  if (UPD && U.part) fold_load(U.part, U.nb, pv);
+  int sl[TL::stage_slots];
+  bool sin[TL::stage_slots];
+  T sf[TL::stage_slots], sq[TL::stage_slots], sd[TL::stage_slots];
 #pragma unroll
-  for (int i = 0; i < kStageSlots; i++) {  // branch-free, as in k_cgs_post4
-    uint32_t jm;
-    sl[i] = stage_slot(i, px0, py0, np, jm);
+  for (int i = 0; i < TL::stage_slots; i++) {  // branch-free, as in k_cgs_post4
+    const int r = t + i * NT;
+    int lx, ly;
+    ring_place<TS, RS, RS>(r, lx, ly);
+    const int px = px0 + lx, py = py0 + ly;
+    sl[i] = r < W * W ? ly * W + lx : -1;
+    sin[i] = r < W * W && px >= 0 && px < np && py >= 0 && py < np;
+    const uint32_t jm = sin[i] ? morton(static_cast<uint32_t>(px), static_cast<uint32_t>(py)) : 0u;
     if constexpr (UPD) {
       sf[i] = U.g[jm];
       sq[i] = U.q0[jm];
@@ -1336,72 +1431,93 @@ __global__ void __launch_bounds__(kTileThreads) k_cgs_pre4(QView<T> Q, const T *
     }
     sd[i] = Q.ax[jm];
   }
-  T up[4], ug[4], uq[4];  // p0, g, q0 of the square's rows for the update's e and r
-  const int t = static_cast<int>(threadIdx.x);
-  const uint32_t jt = j0 + static_cast<uint32_t>(t & (kTileCells - 1));  // clamped for threads without a super-cell
+  constexpr int own = 4 * TL::cells / NT;  // the square's values of this thread (colors in turn, Morton order)
+  T up[own], ug[own], uq[own];             // p0, g, q0 of them for the update's e and r
   if constexpr (UPD) {
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-      up[c] = U.p0[c * n4 + jt];
-      ug[c] = U.g[c * n4 + jt];
-      uq[c] = U.q0[c * n4 + jt];
+    for (int i = 0; i < own; i++) {
+      const int k = t + i * NT;
+      const uint32_t q = static_cast<uint32_t>(k / TL::cells) * n4 + j0 + static_cast<uint32_t>(k % TL::cells);
+      up[i] = U.p0[q];
+      ug[i] = U.g[q];
+      uq[i] = U.q0[q];
     }
   }
-  RingData<T, 3> D1;
-  RingData<T, 2> D2;
-  RingData<T, 1> D3;
-  RingData<T, 0> D0;
-  ring_load<T, 3, 1, UPD>(Q, f, U, px0, py0, np, n4, D1);
-  ring_load<T, 2, 2, UPD>(Q, f, U, px0, py0, np, n4, D2);
-  ring_load<T, 1, 3, UPD>(Q, f, U, px0, py0, np, n4, D3);
-  ring_load<T, 0, 0, UPD>(Q, f, U, px0, py0, np, n4, D0);
+  RingRows<T, TS, RS, 3> D1;
+  RingRows<T, TS, RS, 2> D2;
+  RingRows<T, TS, RS, 1> D3;
+  RingRows<T, TS, RS, 0> D0;
+  ring_load<1, UPD>(Q, f, U, px0, py0, np, n4, D1);
+  ring_load<2, UPD>(Q, f, U, px0, py0, np, n4, D2);
+  ring_load<3, UPD>(Q, f, U, px0, py0, np, n4, D3);
+  ring_load<0, UPD>(Q, f, U, px0, py0, np, n4, D0);
+  T a0 = 0;
   if constexpr (UPD) {
-    rhs_upd<T, 3>(D1, a0);
-    rhs_upd<T, 2>(D2, a0);
-    rhs_upd<T, 1>(D3, a0);
-    rhs_upd<T, 0>(D0, a0);
+    if (U.part) {
+      block_sum4<NT>(pv, red);
+      a0 = static_cast<T>(U.alpha0(pv, blockIdx.x == 0 && t == 0));
+    } else {
+      a0 = U.a0();
+    }
+    rhs_upd(D1, a0);
+    rhs_upd(D2, a0);
+    rhs_upd(D3, a0);
+    rhs_upd(D0, a0);
   }
   // color 0 = f / diag as k_cgs_first2 forms it, colors 1 to 3 zero
 #pragma unroll
-  for (int i = 0; i < kStageSlots; i++)
+  for (int i = 0; i < TL::stage_slots; i++)
     if (sl[i] >= 0) {
       T fi;
       if constexpr (UPD) fi = upd1_r(sf[i], a0, sq[i]);
       else fi = sf[i];
-      sv[0][sl[i]] = fi / sd[i];
+      sv[0][sl[i]] = sin[i] ? fi / sd[i] : T(0);
       sv[1][sl[i]] = T(0);
       sv[2][sl[i]] = T(0);
       sv[3][sl[i]] = T(0);
     }
-  if (UPD && t < kTileCells) {  // the update's e and r of the square's rows as Upd1::store forms them (independent
-                                // of the sweep)
+  if constexpr (UPD) {  // the update's e and r of the square's rows as Upd1::store forms them (independent of the sweep)
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-      U.e[c * n4 + jt] = a0 * up[c];
-      U.r[c * n4 + jt] = upd1_r(ug[c], a0, uq[c]);
+    for (int i = 0; i < own; i++) {
+      const int k = t + i * NT;
+      const uint32_t q = static_cast<uint32_t>(k / TL::cells) * n4 + j0 + static_cast<uint32_t>(k % TL::cells);
+      U.e[q] = a0 * up[i];
+      U.r[q] = upd1_r(ug[i], a0, uq[i]);
     }
   }
   __syncthreads();
-  ring_phase<T, 3, 1>(D1, px0, py0, np, sv);
+  ring_phase<1>(D1, sv);
   __syncthreads();
-  ring_phase<T, 2, 2>(D2, px0, py0, np, sv);
+  ring_phase<2>(D2, sv);
   __syncthreads();
-  ring_phase<T, 1, 3>(D3, px0, py0, np, sv);
+  ring_phase<3>(D3, sv);
   __syncthreads();
-  ring_resid<T, 0, 0>(D0, px0, py0, np, sv, res[0]);
-  ring_resid<T, 3, 1>(D1, px0, py0, np, sv, res[1]);
-  ring_resid<T, 2, 2>(D2, px0, py0, np, sv, res[2]);
-  ring_resid<T, 1, 3>(D3, px0, py0, np, sv, res[3]);
-  __syncthreads();
-  if (t >= kTileCells) return;
-  const int lj = D0.l[0];
-  const int order[4] = {0, 1, 3, 2};
-  T acc = 0;
+  // residuals f_q - (A x)_q of the square's rows, by the square's Morton index
+  auto resid = [&](auto &D, auto cc) {
+    constexpr int c = decltype(cc)::value;
 #pragma unroll
-  for (int oi = 0; oi < 4; oi++) acc += res[order[oi]][t];
-  gc[q_of_m(jt, kc)] = acc;
+    for (int i = 0; i < std::remove_reference_t<decltype(D)>::slots; i++)
+      if (D.sq[i]) res[c][D.j[i] - j0] = D.f[i] - ring_row<c, W>(D.a[i], D.l[i], sv);
+  };
+  resid(D0, std::integral_constant<int, 0>{});
+  resid(D1, std::integral_constant<int, 1>{});
+  resid(D2, std::integral_constant<int, 2>{});
+  resid(D3, std::integral_constant<int, 3>{});
+  __syncthreads();
+  if (t < TL::cells) {
+    const int order[4] = {0, 1, 3, 2};
+    T acc = 0;
 #pragma unroll
-  for (int c = 0; c < 4; c++) x[c * n4 + jt] = sv[c][lj];
+    for (int oi = 0; oi < 4; oi++) acc += res[order[oi]][t];
+    gc[q_of_m(j0 + static_cast<uint32_t>(t), kc)] = acc;
+  }
+#pragma unroll
+  for (int i = 0; i < own; i++) {
+    const int k = t + i * NT, c = k / TL::cells, w = k % TL::cells;
+    const int lx = static_cast<int>(compact_bits(static_cast<uint32_t>(w))) + RS;
+    const int ly = static_cast<int>(compact_bits(static_cast<uint32_t>(w) >> 1)) + RS;
+    x[c * n4 + j0 + static_cast<uint32_t>(w)] = sv[c][ly * W + lx];
+  }
 }
 
 template <class T>
@@ -3168,13 +3284,35 @@ amg_status plan_wg(amg_hierarchy *h) {
   return engine_lds_limits(h);
 }
 
-template <class T> static void btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2);
+template <class T> static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2, bool fold);
 template <class T> static void btilde_oct(amg_hierarchy *h, int l, const T *g, T *e);
 
-// Solve or cycle on level l for the correction of level l - 1. Returns the pending last update of B~ on level l when
-// it was left for the parent's prolongation (only levels that run per step, with two inner iterations).
+// Levels whose sweeps run as tiles: no same-color couplings or overflow entries, and at least 256 super-cells. The
+// per-step path (engine off) keeps one launch per color phase.
+static bool level_tiled(const amg_hierarchy *h, int l) {
+  const QuadLevel &Q = h->lev[l];
+  return h->use_engine != 0 && !Q.same_color_ovf && Q.ovf_nnz == 0 && (Q.n >> 2) >= 256;
+}
+// Super-cells of a level up to which its tiles have 8 instead of 16 to a side. Small squares spread a level over more
+// CUs but stage and relax more ring rows (2.7 rows relaxed per row kept with the products, against 1.7). Measured in
+// FP32: 6.5 us instead of 7.6 per post-smoothing tile on 16,384 super-cells (256 workgroups), but 15.6 instead of
+// 10.5 us on 65,536.
+constexpr int64_t kTileSmall = 16384;
+static int64_t tile_grid(const QuadLevel &Q) { return (Q.n >> 2) / ((Q.n >> 2) <= kTileSmall ? 64 : 256); }
+// B~ of a tiled level with one sweep forms A u and its inner products in the last tile of each B^; the partial sums of
+// a level, four doubles to a workgroup, lie in its spare vector q1. Up to kFoldBlocks workgroups' sums are added up by
+// the kernel that needs them (8 KB read by each workgroup, in its first round of loads); more take a k_finish launch.
+constexpr int64_t kFoldBlocks = 256;
 template <class T>
-static Pending<T> coarse_solve_or_cycle(amg_hierarchy *h, int l) {
+static double *tile_part(amg_hierarchy *h, int l) {
+  return reinterpret_cast<double *>(P<T>::W(h)[l].q1);
+}
+
+// Solve or cycle on level l for the correction of level l - 1. Returns the pending last update of B~ on level l when
+// it was left for the parent's prolongation (only levels that run per step, with two inner iterations). `fold`: the
+// parent can add up the pending update's partial sums.
+template <class T>
+static Pending<T> coarse_solve_or_cycle(amg_hierarchy *h, int l, bool fold) {
   LevelWork<T> &w = P<T>::W(h)[l];
   const int pi = std::is_same<T, float>::value ? 1 : 0;
   if (l == h->nlev - 1) {
@@ -3185,10 +3323,12 @@ static Pending<T> coarse_solve_or_cycle(amg_hierarchy *h, int l) {
     launch_engine<T>(h, l);
   } else {
     const bool defer = h->opt.inner_iters >= 2;
-    btilde<T>(h, l, w.g, w.e, defer);
-    if (defer) return Pending<T>{h->scal + static_cast<size_t>(l) * kScalars, w.p1, w.p0};
+    const bool folded = btilde<T>(h, l, w.g, w.e, defer, fold);
+    if (defer)
+      return Pending<T>{h->scal + static_cast<size_t>(l) * kScalars, w.p1, w.p0, folded ? tile_part<T>(h, l) : nullptr,
+                        folded ? static_cast<int>(tile_grid(h->lev[l])) : 0};
   }
-  return Pending<T>{nullptr, nullptr, nullptr};
+  return Pending<T>{nullptr, nullptr, nullptr, nullptr, 0};
 }
 
 template <class T>
@@ -3206,56 +3346,68 @@ static void gs_phase_coarse(amg_hierarchy *h, int l, const T *f, T *u, int c) {
 
 // B^_l for a quadtree level l (not the coarsest): Algorithm 2.2. `upd` (sc non-null): the pending first inner update
 // of the caller, done by the first relaxation (needs sweeps >= 1). `beta` (non-null): the last color phase also
-// forms (p1, q0) for beta (needs sweeps >= 1 and no same-color couplings).
+// forms (p1, q0) for beta (needs sweeps >= 1 and no same-color couplings). `sp` (a tiled level, one sweep): the inner
+// step whose A u and partial sums the last tile forms (k_cgs_post4), or 0.
 template <class T>
 static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T> &upd = Upd1<T>{},
-                        const T *beta_q0 = nullptr) {
+                        const T *beta_q0 = nullptr, int sp = 0) {
   const QuadLevel &Q = h->lev[l];
   hipStream_t s = h->stream;
   const int sweeps = h->opt.sweeps;
   const bool U = upd.sc != nullptr;
   const int64_t n4 = Q.n >> 2;
-  LevelWork<T> &wc = P<T>::W(h)[l + 1];
-  // the per-step path keeps one launch per color phase; with tiles the presmoothing sweep and the restriction take
-  // one launch, and so does the first post-smoothing sweep
-  const bool tiles = h->use_engine != 0 && !Q.same_color_ovf && Q.ovf_nnz == 0 && n4 >= kTileCells;
+  LevelWork<T> &w = P<T>::W(h)[l], &wc = P<T>::W(h)[l + 1];
+  // with tiles the presmoothing sweep and the restriction take one launch, and so does the first post-smoothing sweep;
+  // neighbouring workgroups read the presmoothed values around their squares, so the latter writes another vector
+  const bool tiles = level_tiled(h, l) && sweeps >= 1;
   const bool tiled_pre = tiles && sweeps == 1;
+  const bool small = n4 <= kTileSmall;
+  const unsigned grid = static_cast<unsigned>(tile_grid(Q));
+  T *v = tiles ? w.d : u;  // presmoothed values
   if (tiled_pre) {
-    const unsigned grid = static_cast<unsigned>(n4 / kTileCells);
-    if (U) k_cgs_pre4<T, true><<<grid, kTileThreads, 0, s>>>(qview<T>(Q), f, u, upd, wc.g);
-    else k_cgs_pre4<T, false><<<grid, kTileThreads, 0, s>>>(qview<T>(Q), f, u, upd, wc.g);
+    const QView<T> V = qview<T>(Q);
+    if (U) {
+      if (small) k_cgs_pre4<T, true, 8><<<grid, Tile<8, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
+      else k_cgs_pre4<T, true, 16><<<grid, Tile<16, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
+    } else {
+      if (small) k_cgs_pre4<T, false, 8><<<grid, Tile<8, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
+      else k_cgs_pre4<T, false, 16><<<grid, Tile<16, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
+    }
   }
   for (int sw = 0; sw < (tiled_pre ? 0 : sweeps); sw++)
     for (int c = 0; c < 4; c++) {
       if (sw == 0 && c == 0 && !Q.same_color_ovf) {
-        if (U) k_cgs_first2<T, true><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, u, upd);
-        else k_cgs_first2<T, false><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, u, upd);
+        if (U) k_cgs_first2<T, true><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
+        else k_cgs_first2<T, false><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
         c = 1;
       } else if (sw == 0 && c == 0) {
-        if (U) k_cgs_first<T, true><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, u, upd);
-        else k_cgs_first<T, false><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, u, upd);
+        if (U) k_cgs_first<T, true><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
+        else k_cgs_first<T, false><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
       } else {
-        gs_phase_coarse<T>(h, l, f, u, c);
+        gs_phase_coarse<T>(h, l, f, v, c);
       }
     }
-  if (!tiled_pre) k_cres_restrict<T><<<nblk(Q.n >> 2), kBlock, 0, s>>>(qview<T>(Q), f, u, wc.g);
-  const Pending<T> pend = coarse_solve_or_cycle<T>(h, l + 1);
+  if (!tiled_pre) k_cres_restrict<T><<<nblk(Q.n >> 2), kBlock, 0, s>>>(qview<T>(Q), f, v, wc.g);
+  const Pending<T> pend = coarse_solve_or_cycle<T>(h, l + 1, tiles);
   // without same-color couplings the prolongation folds into the first post-smoothing sweep
   const bool fold_prolong = !Q.same_color_ovf && sweeps >= 1;
   if (!fold_prolong) k_cprolong<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, wc.e, pend, u);
   const Red rb = red(h, l, EPI_BETA);
-  const bool tiled = tiles && fold_prolong;
-  if (tiled) {
+  if (tiles) {
     const QView<T> V = qview<T>(Q);
-    const unsigned grid = static_cast<unsigned>(n4 / kTileCells);
-    if (beta_q0 && sweeps == 1) {
-      k_cgs_post4<T, true><<<grid, kTileThreads, 0, s>>>(V, f, u, wc.e, pend, beta_q0, rb);
-      finish<1>(h, nblk(n4), rb);
-    } else {
-      k_cgs_post4<T, false><<<grid, kTileThreads, 0, s>>>(V, f, u, wc.e, pend, beta_q0, rb);
-    }
+    double *part = tile_part<T>(h, l);
+    auto post = [&](auto spc) {
+      constexpr int SP = decltype(spc)::value;
+      if (small)
+        k_cgs_post4<T, SP, 8><<<grid, Tile<8, SP ? 5 : 4>::NT, 0, s>>>(V, f, v, u, wc.e, pend, w.q0, w.p0, part);
+      else
+        k_cgs_post4<T, SP, 16><<<grid, Tile<16, SP ? 5 : 4>::NT, 0, s>>>(V, f, v, u, wc.e, pend, w.q0, w.p0, part);
+    };
+    if (sp == 1) post(std::integral_constant<int, 1>{});
+    else if (sp == 2) post(std::integral_constant<int, 2>{});
+    else post(std::integral_constant<int, 0>{});
   }
-  for (int sw = tiled ? 1 : 0; sw < sweeps; sw++)
+  for (int sw = tiles ? 1 : 0; sw < sweeps; sw++)
     for (int c = 3; c >= 0; c--) {
       const bool beta_here = beta_q0 && sw == sweeps - 1 && c == 0;
       if (fold_prolong && sw == 0) {
@@ -3383,36 +3535,49 @@ static void bhat_fine(amg_hierarchy *h, const T *f, T *u) {
   const int big = h->opt.smoother ? kBlockMax : kBigCell;  // the big-cell list's threshold
   k_fine_restrict<T><<<nblk(nL), kBlock, 0, s>>>(nL, F.crow, w.d, wc.g, F.nbig ? big : INT32_MAX);
   if (F.nbig) k_fine_restrict_big<T><<<static_cast<unsigned>(F.nbig), 64, 0, s>>>(F.big_cells, F.crow, w.d, wc.g);
-  const Pending<T> pend = coarse_solve_or_cycle<T>(h, 1);
+  const Pending<T> pend = coarse_solve_or_cycle<T>(h, 1, false);
   k_fine_prolong<T><<<nblk(F.n), kBlock, 0, s>>>(F.n, F.agg_q, wc.e, pend, u, one ? w.r : nullptr);
   for (int sw = 0; sw < sweeps; sw++)
     for (int c = nc - 1; c >= 0; c--) fine_phase<T>(h, f, u, w.d, c, false, false, one ? kOldSnap : kOldNone);
 }
 
+// B~_l: Algorithm 2.1 with n = inner_iters (1 or 2) steps and B^_l as preconditioner. True: the last update is left to
+// the caller (defer_update2) with its beta and alpha1 still in partial sums (`fold`, see tile_part).
 template <class T>
-static void bhat(amg_hierarchy *h, int l, const T *f, T *u) {
-  if (l == 0) bhat_fine<T>(h, f, u);
-  else bhat_coarse<T>(h, l, f, u);
-}
-
-// B~_l: Algorithm 2.1 with n = inner_iters (1 or 2) steps and B^_l as preconditioner
-template <class T>
-static void btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2) {
+static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2, bool fold) {
   const QuadLevel &Q = h->lev[l];
   LevelWork<T> &w = P<T>::W(h)[l];
   hipStream_t s = h->stream;
-  const double *sc = h->scal + static_cast<size_t>(l) * kScalars;
-  bhat<T>(h, l, g, w.p0);
+  double *sc = h->scal + static_cast<size_t>(l) * kScalars;
+  const bool two = h->opt.inner_iters >= 2;
+  if (level_tiled(h, l) && h->opt.sweeps == 1) {  // two launches per B^
+    double *part = tile_part<T>(h, l);
+    const unsigned nb = static_cast<unsigned>(tile_grid(Q));
+    const bool few = nb <= kFoldBlocks;
+    bhat_coarse<T>(h, l, g, w.p0, Upd1<T>{}, nullptr, 1);
+    if (!two || !few) k_finish<4><<<1, kBlock, 0, s>>>(nb, Red{part, sc, EPI_ALPHA0, 0});
+    if (!two) {
+      k_update1<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p0, w.q0, g, e, w.r);
+      return false;
+    }
+    bhat_coarse<T>(h, l, w.r, w.p1,
+                   Upd1<T>{sc, g, w.q0, w.p0, e, w.r, few ? part : nullptr, few ? static_cast<int>(nb) : 0}, nullptr, 2);
+    if (few && fold && defer_update2) return true;
+    k_finish<4><<<1, kBlock, 0, s>>>(
+        nb, Red{part, sc, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64, 0});
+    if (!defer_update2) k_update2<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p1, w.p0, e);
+    return false;
+  }
+  bhat_coarse<T>(h, l, g, w.p0);
   k_cspmv_dot<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p0, w.q0, g, red(h, l, EPI_ALPHA0));
   finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA0));
   // with two inner steps the update below and the inner product for beta fold into the second B^ (first and last
   // relaxation) where its sweeps allow
-  const bool two = h->opt.inner_iters >= 2;
   const bool fold_upd = two && h->opt.sweeps >= 1;
   const bool fold_beta = two && h->opt.sweeps >= 1 && !Q.same_color_ovf;
   if (!fold_upd) k_update1<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p0, w.q0, g, e, w.r);
-  if (!two) return;
-  bhat_coarse<T>(h, l, w.r, w.p1, fold_upd ? Upd1<T>{sc, g, w.q0, w.p0, e, w.r} : Upd1<T>{},
+  if (!two) return false;
+  bhat_coarse<T>(h, l, w.r, w.p1, fold_upd ? Upd1<T>{sc, g, w.q0, w.p0, e, w.r, nullptr, 0} : Upd1<T>{},
                  fold_beta ? w.q0 : nullptr);
   if (!fold_beta) {
     k_dot<T><<<nred(Q.n), kBlock, 0, s>>>(Q.n, w.p1, w.q0, red(h, l, EPI_BETA));
@@ -3421,6 +3586,7 @@ static void btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
   k_cspmv_dir<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, EPI_ALPHA1));
   finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA1));
   if (!defer_update2) k_update2<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p1, w.p0, e);
+  return false;
 }
 
 // Octree levels (per-step launches): one color phase, B^ (Algorithm 2.2) and B~ (Algorithm 2.1 with n = inner

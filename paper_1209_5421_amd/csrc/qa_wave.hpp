@@ -1,0 +1,56 @@
+// Wavefront reductions of doubles (gfx950, 64 lanes), shared by the engine and the tree-level kernels. Fixed trees: a
+// sum depends only on the lanes' values.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace qa {
+
+// a lane's double moved by a DPP lane pattern (two 32-bit moves)
+template <int Ctrl>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), Ctrl, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), Ctrl, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) |
+                                        static_cast<unsigned>(lo));
+}
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(u & 0xffffffffu), lane));
+  const unsigned hi = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane));
+  return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
+}
+
+// the sum of x over the lanes i, i + 16, i + 32, i + 48 of a wavefront, in every one of them: rows of 16 lanes added in
+// pairs, then the two halves
+__device__ __forceinline__ double rows_sum(double x) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const auto l0 = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(u), static_cast<unsigned>(u), false, false);
+  const auto h0 =
+      __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(u >> 32), static_cast<unsigned>(u >> 32), false, false);
+  x = __builtin_bit_cast(double, (static_cast<unsigned long long>(h0[0]) << 32) | l0[0]) +
+      __builtin_bit_cast(double, (static_cast<unsigned long long>(h0[1]) << 32) | l0[1]);
+  const unsigned long long w = __builtin_bit_cast(unsigned long long, x);
+  const auto l1 = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(w), static_cast<unsigned>(w), false, false);
+  const auto h1 =
+      __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(w >> 32), static_cast<unsigned>(w >> 32), false, false);
+  return __builtin_bit_cast(double, (static_cast<unsigned long long>(h1[0]) << 32) | l1[0]) +
+         __builtin_bit_cast(double, (static_cast<unsigned long long>(h1[1]) << 32) | l1[1]);
+}
+
+// four sums over one wavefront at once: in two steps of pairs each lane hands over the half of its values that its
+// partner keeps, so that one value per lane is left (lane i holds a part of sum sum4_of(i & 3)), which is then added
+// over the lanes of equal i & 3. A fixed tree: the result depends only on the lanes' values.
+__device__ __forceinline__ constexpr int sum4_of(int i) { return (i & 1) * 2 + (i >> 1); }
+__device__ __forceinline__ double wave_sum4(const double (&v)[4]) {
+  const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
+  const double k0 = (b0 ? v[2] : v[0]) + dpp_f64<0xb1>(b0 ? v[0] : v[2]);  // quad_perm [1, 0, 3, 2]
+  const double k1 = (b0 ? v[3] : v[1]) + dpp_f64<0xb1>(b0 ? v[1] : v[3]);
+  double k = (b1 ? k1 : k0) + dpp_f64<0x4e>(b1 ? k0 : k1);                 // quad_perm [2, 3, 0, 1]
+  k += dpp_f64<0x124>(k);                                                  // row_ror 4
+  k += dpp_f64<0x128>(k);                                                  // row_ror 8
+  return rows_sum(k);
+}
+
+}  // namespace qa
