@@ -965,23 +965,9 @@ __device__ inline int row_color(uint32_t q, int sh) {
   return sh >= 6 ? __builtin_amdgcn_readfirstlane(c) : c;
 }
 
-// first phase of a sweep from zero: x = f / diag on color 0, zero elsewhere (UPD: f is the pending update's r)
-template <class T, bool UPD>
-__global__ void __launch_bounds__(kBlock) k_cgs_first(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
-                                                       Upd1<T> U) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (q >= Q.n) return;
-  if constexpr (UPD) {
-    const T a = U.a0();
-    x[q] = (q < (Q.n >> 2)) ? U.rv(a, static_cast<uint32_t>(q)) / Q.ax[q] : T(0);
-    U.store(a, q);
-  } else {
-    x[q] = (q < (Q.n >> 2)) ? f[q] / Q.ax[q] : T(0);
-  }
-}
-
-// the first two phases of a sweep from zero (levels without same-color couplings): x = f / diag on color 0, zero on
-// colors 2 and 3, and the color-1 rows relaxed against the color-0 values formed on the fly (nothing reads x here)
+// the first two phases of a sweep from zero: x = f / diag on color 0, zero on colors 2 and 3, and the color-1 rows
+// relaxed against the color-0 values formed on the fly (nothing reads x here; every other value, those of coupled
+// color-1 rows among them, is still zero)
 template <class T, class FV>
 __device__ inline void cgs_first2_row(const QView<T> &Q, int64_t q, FV fv, T *__restrict__ x) {
   const int64_t n4 = Q.n >> 2;
@@ -1013,16 +999,24 @@ __global__ void __launch_bounds__(kBlock) k_cgs_first2(QView<T> Q, const T *__re
 
 // one color phase of the pointwise 4-color Gauss-Seidel: rows q = c n/4 + j, Morton m = 4 j + c.
 // delta == nullptr: update in place (valid when no coupling joins two cells of color c); else write delta only.
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_cgs(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
-                                                T *__restrict__ delta, int c) {
+// ZERO: the phase of a sweep from zero, where the color's rows hold zero before it: the values of coupled rows of the
+// color are not read, so the update is in place whatever the couplings.
+template <class T, bool ZERO>
+__global__ void __launch_bounds__(kBlock) k_cgs(QView<T> Q, const T *__restrict__ f, T *x, T *__restrict__ delta,
+                                                int c) {
   const int64_t n4 = Q.n >> 2;
   const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (j >= n4) return;
   const uint32_t q = static_cast<uint32_t>(c * n4 + j);
-  const T dl = (f[q] - row_apply(Q, q, c, x)) / Q.ax[q];
-  if (delta) delta[q] = dl;
-  else x[q] += dl;
+  if constexpr (ZERO) {
+    const int sh = 2 * Q.k - 2;
+    const T acc = row_apply_f<T>(Q, q, c, [=](uint32_t i) { return static_cast<int>(i >> sh) == c ? T(0) : x[i]; });
+    x[q] = T(0) + (f[q] - acc) / Q.ax[q];
+  } else {
+    const T dl = (f[q] - row_apply(Q, q, c, x)) / Q.ax[q];
+    if (delta) delta[q] = dl;
+    else x[q] += dl;
+  }
 }
 
 // the last color phase (c = 0) of the second B^ with the inner product (p1, q0) of Algorithm 2.1 for beta: thread j
@@ -1044,13 +1038,13 @@ __global__ void __launch_bounds__(kBlock) k_cgs0_beta(QView<T> Q, const T *__res
   reduce_finish<1>(v, R);
 }
 
-// A color phase of the first post-smoothing sweep (no same-color couplings) with the prolongation u += P e_c folded
-// in: the rows of colors <= C have not been corrected yet (the backward sweep has only passed colors > C), so their
-// values are read as u + (P e_c) formed on the fly, each equal to what the separate prolongation stores; the phase
-// stores the corrected and relaxed values of its own rows. With BETA (C = 0, the last phase of the second B^) it also
-// forms (p1, q0) for beta over the rows j + c n/4 of the four colors.
+// A color phase of the first post-smoothing sweep with the prolongation u = x + P e_c folded in (x: the presmoothed
+// values): the backward sweep has only passed colors > C, so those are read from u and the others as x + (P e_c) formed
+// on the fly, each equal to what a separate prolongation would store; the phase stores the corrected and relaxed values
+// of its own rows to u. As x is not written, coupled rows of one color all see the values from before the phase. With
+// BETA (C = 0, the last phase of the second B^) it also forms (p1, q0) for beta over the rows j + c n/4 of the colors.
 template <class T, int C, bool BETA>
-__global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
+__global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__restrict__ f, const T *__restrict__ x, T *u,
                                                      const T *__restrict__ ec, Pending<T> pend,
                                                      const T *__restrict__ q0, Red R) {
   const int64_t n4 = Q.n >> 2;
@@ -1068,22 +1062,21 @@ __global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__rest
 #pragma unroll
     for (int s = 0; s < 9; s++) {
       const int cn = (((C & 1) + slot_dx(s)) & 1) | ((((C >> 1) + slot_dy(s)) & 1) << 1);
-      const T xn = x[nb[s]];
-      acc += Q.ax[s * Q.n + q] * (cn <= C ? xn + pe(nb[s]) : xn);
+      // an absent neighbour is the row itself, whose color is C
+      acc += Q.ax[s * Q.n + q] * (cn <= C || nb[s] == q ? x[nb[s]] + pe(nb[s]) : u[nb[s]]);
     }
     if (Q.optr)
       for (int32_t e = Q.optr[q]; e < Q.optr[q + 1]; e++) {
         const uint32_t i = static_cast<uint32_t>(Q.ocol[e]);
-        const T xn = x[i];
-        acc += Q.oval[e] * (static_cast<int>(i >> sh) <= C ? xn + pe(i) : xn);
+        acc += Q.oval[e] * (static_cast<int>(i >> sh) <= C ? x[i] + pe(i) : u[i]);
       }
     const T xq = x[q] + pe(q);
     const T xr = xq + (f[q] - acc) / Q.ax[q];
-    x[q] = xr;
+    u[q] = xr;
     if constexpr (BETA) {
       v[0] = static_cast<double>(xr) * static_cast<double>(q0[q]);
 #pragma unroll
-      for (int c = 1; c < 4; c++) v[0] += static_cast<double>(x[c * n4 + j]) * static_cast<double>(q0[c * n4 + j]);
+      for (int c = 1; c < 4; c++) v[0] += static_cast<double>(u[c * n4 + j]) * static_cast<double>(q0[c * n4 + j]);
     }
   }
   if constexpr (BETA) reduce_finish<1>(v, R);
@@ -1546,17 +1539,6 @@ __global__ void __launch_bounds__(kBlock) k_cres_restrict(QView<T> Q, const T *_
   g[q_of_m(static_cast<uint32_t>(M), Q.k - 1)] = acc;
 }
 
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_cprolong(int k, int64_t n, const T *__restrict__ e, Pending<T> pend,
-                                                      T *__restrict__ u) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  // children of M are q = c n/4 + M: the parent's Morton index is q mod n/4
-  const uint32_t M = static_cast<uint32_t>(q & ((n >> 2) - 1));
-  const T em = pend.apply(e, q_of_m(M, k - 1));
-  u[q] += em;
-}
-
 // y = A x on a quadtree level with two inner products (x, y) and (w, x); grid-stride, fixed grid
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_cspmv_dot(QView<T> Q, const T *__restrict__ x, T *__restrict__ y,
@@ -1571,6 +1553,24 @@ __global__ void __launch_bounds__(kBlock) k_cspmv_dot(QView<T> Q, const T *__res
     v[1] += static_cast<double>(w[q]) * xq;
   }
   reduce_finish<2>(v, R);
+}
+
+// the second inner step of Algorithm 2.1 from p1 alone: A p1 (not stored) with (p1, A p1), (r, p1), (p1, q0) and
+// (r, p0), from which pair_scalars has beta and alpha1: one reduction instead of one for beta and one for alpha1
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_cspmv_pair(QView<T> Q, const T *__restrict__ p1, const T *__restrict__ r,
+                                                        const T *__restrict__ q0, const T *__restrict__ p0, Red R) {
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < Q.n;
+       q += static_cast<int64_t>(gridDim.x) * kBlock) {
+    const T yq = row_apply(Q, static_cast<uint32_t>(q), row_color(static_cast<uint32_t>(q), 2 * Q.k - 2), p1);
+    const double u = static_cast<double>(p1[q]), f = static_cast<double>(r[q]);
+    v[0] += u * static_cast<double>(yq);
+    v[1] += f * u;
+    v[2] += u * static_cast<double>(q0[q]);
+    v[3] += f * static_cast<double>(p0[q]);
+  }
+  reduce_finish<4>(v, R);
 }
 
 // the second inner step of Algorithm 2.1: A d with the direction d = p1 + beta p0 formed on the fly (never stored),
@@ -3331,22 +3331,25 @@ static Pending<T> coarse_solve_or_cycle(amg_hierarchy *h, int l, bool fold) {
   return Pending<T>{nullptr, nullptr, nullptr, nullptr, 0};
 }
 
+// one color phase; `zero`: of a sweep from zero
 template <class T>
-static void gs_phase_coarse(amg_hierarchy *h, int l, const T *f, T *u, int c) {
+static void gs_phase_coarse(amg_hierarchy *h, int l, const T *f, T *u, int c, bool zero) {
   const QuadLevel &Q = h->lev[l];
   const int64_t n4 = Q.n >> 2;
-  if (Q.same_color_ovf) {
+  if (Q.same_color_ovf && zero) {
+    k_cgs<T, true><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, nullptr, c);
+  } else if (Q.same_color_ovf) {
     T *dl = P<T>::W(h)[l].d;
-    k_cgs<T><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, dl, c);
+    k_cgs<T, false><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, dl, c);
     k_add_range<T><<<nblk(n4), kBlock, 0, h->stream>>>(c * n4, n4, dl, u);
   } else {
-    k_cgs<T><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, nullptr, c);
+    k_cgs<T, false><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, nullptr, c);
   }
 }
 
 // B^_l for a quadtree level l (not the coarsest): Algorithm 2.2. `upd` (sc non-null): the pending first inner update
-// of the caller, done by the first relaxation (needs sweeps >= 1). `beta` (non-null): the last color phase also
-// forms (p1, q0) for beta (needs sweeps >= 1 and no same-color couplings). `sp` (a tiled level, one sweep): the inner
+// of the caller, done by the first relaxation. `beta` (non-null): the last color phase also
+// forms (p1, q0) for beta (needs one sweep, or no same-color couplings). `sp` (a tiled level, one sweep): the inner
 // step whose A u and partial sums the last tile forms (k_cgs_post4), or 0.
 template <class T>
 static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T> &upd = Upd1<T>{},
@@ -3357,13 +3360,14 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
   const bool U = upd.sc != nullptr;
   const int64_t n4 = Q.n >> 2;
   LevelWork<T> &w = P<T>::W(h)[l], &wc = P<T>::W(h)[l + 1];
-  // with tiles the presmoothing sweep and the restriction take one launch, and so does the first post-smoothing sweep;
-  // neighbouring workgroups read the presmoothed values around their squares, so the latter writes another vector
-  const bool tiles = level_tiled(h, l) && sweeps >= 1;
+  // with tiles the presmoothing sweep and the restriction take one launch, and so does the first post-smoothing sweep.
+  // Either way that sweep reads the presmoothed values (of neighbouring rows and squares) while it writes, so they lie
+  // in another vector.
+  const bool tiles = level_tiled(h, l);
   const bool tiled_pre = tiles && sweeps == 1;
   const bool small = n4 <= kTileSmall;
   const unsigned grid = static_cast<unsigned>(tile_grid(Q));
-  T *v = tiles ? w.d : u;  // presmoothed values
+  T *v = tiles ? w.d : w.q1;  // presmoothed values
   if (tiled_pre) {
     const QView<T> V = qview<T>(Q);
     if (U) {
@@ -3376,22 +3380,16 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
   }
   for (int sw = 0; sw < (tiled_pre ? 0 : sweeps); sw++)
     for (int c = 0; c < 4; c++) {
-      if (sw == 0 && c == 0 && !Q.same_color_ovf) {
+      if (sw == 0 && c == 0) {
         if (U) k_cgs_first2<T, true><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
         else k_cgs_first2<T, false><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
         c = 1;
-      } else if (sw == 0 && c == 0) {
-        if (U) k_cgs_first<T, true><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
-        else k_cgs_first<T, false><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
       } else {
-        gs_phase_coarse<T>(h, l, f, v, c);
+        gs_phase_coarse<T>(h, l, f, v, c, sw == 0);
       }
     }
   if (!tiled_pre) k_cres_restrict<T><<<nblk(Q.n >> 2), kBlock, 0, s>>>(qview<T>(Q), f, v, wc.g);
   const Pending<T> pend = coarse_solve_or_cycle<T>(h, l + 1, tiles);
-  // without same-color couplings the prolongation folds into the first post-smoothing sweep
-  const bool fold_prolong = !Q.same_color_ovf && sweeps >= 1;
-  if (!fold_prolong) k_cprolong<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, wc.e, pend, u);
   const Red rb = red(h, l, EPI_BETA);
   if (tiles) {
     const QView<T> V = qview<T>(Q);
@@ -3410,20 +3408,20 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
   for (int sw = tiles ? 1 : 0; sw < sweeps; sw++)
     for (int c = 3; c >= 0; c--) {
       const bool beta_here = beta_q0 && sw == sweeps - 1 && c == 0;
-      if (fold_prolong && sw == 0) {
+      if (sw == 0) {
         const QView<T> V = qview<T>(Q);
         switch (c) {
-          case 3: k_cgs_post<T, 3, false><<<nblk(n4), kBlock, 0, s>>>(V, f, u, wc.e, pend, beta_q0, rb); break;
-          case 2: k_cgs_post<T, 2, false><<<nblk(n4), kBlock, 0, s>>>(V, f, u, wc.e, pend, beta_q0, rb); break;
-          case 1: k_cgs_post<T, 1, false><<<nblk(n4), kBlock, 0, s>>>(V, f, u, wc.e, pend, beta_q0, rb); break;
+          case 3: k_cgs_post<T, 3, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb); break;
+          case 2: k_cgs_post<T, 2, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb); break;
+          case 1: k_cgs_post<T, 1, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb); break;
           default:
-            if (beta_here) k_cgs_post<T, 0, true><<<nblk(n4), kBlock, 0, s>>>(V, f, u, wc.e, pend, beta_q0, rb);
-            else k_cgs_post<T, 0, false><<<nblk(n4), kBlock, 0, s>>>(V, f, u, wc.e, pend, beta_q0, rb);
+            if (beta_here) k_cgs_post<T, 0, true><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb);
+            else k_cgs_post<T, 0, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb);
         }
       } else if (beta_here) {
         k_cgs0_beta<T><<<nblk(n4), kBlock, 0, s>>>(qview<T>(Q), f, u, beta_q0, rb);
       } else {
-        gs_phase_coarse<T>(h, l, f, u, c);
+        gs_phase_coarse<T>(h, l, f, u, c, false);
       }
       if (beta_here) finish<1>(h, nblk(n4), rb);
     }
@@ -3571,20 +3569,29 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
   bhat_coarse<T>(h, l, g, w.p0);
   k_cspmv_dot<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p0, w.q0, g, red(h, l, EPI_ALPHA0));
   finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA0));
-  // with two inner steps the update below and the inner product for beta fold into the second B^ (first and last
-  // relaxation) where its sweeps allow
-  const bool fold_upd = two && h->opt.sweeps >= 1;
-  const bool fold_beta = two && h->opt.sweeps >= 1 && !Q.same_color_ovf;
-  if (!fold_upd) k_update1<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p0, w.q0, g, e, w.r);
-  if (!two) return false;
-  bhat_coarse<T>(h, l, w.r, w.p1, fold_upd ? Upd1<T>{sc, g, w.q0, w.p0, e, w.r, nullptr, 0} : Upd1<T>{},
-                 fold_beta ? w.q0 : nullptr);
-  if (!fold_beta) {
-    k_dot<T><<<nred(Q.n), kBlock, 0, s>>>(Q.n, w.p1, w.q0, red(h, l, EPI_BETA));
-    finish<1>(h, nred(Q.n), red(h, l, EPI_BETA));
+  if (!two) {
+    k_update1<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p0, w.q0, g, e, w.r);
+    return false;
   }
-  k_cspmv_dir<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, EPI_ALPHA1));
-  finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA1));
+  // the first inner update folds into the second B^'s first relaxation. With the engine on, beta and alpha1 come from
+  // one reduction behind A p1; the per-step path keeps Algorithm 2.1's steps apart, (p1, q0) folded into the last
+  // relaxation where its sweeps allow, then A d.
+  const Upd1<T> upd{sc, g, w.q0, w.p0, e, w.r, nullptr, 0};
+  if (h->use_engine != 0) {
+    const Red rp = red(h, l, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64);
+    bhat_coarse<T>(h, l, w.r, w.p1, upd);
+    k_cspmv_pair<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p1, w.r, w.q0, w.p0, rp);
+    finish<4>(h, nred(Q.n), rp);
+  } else {
+    const bool fold_beta = !Q.same_color_ovf || h->opt.sweeps == 1;
+    bhat_coarse<T>(h, l, w.r, w.p1, upd, fold_beta ? w.q0 : nullptr);
+    if (!fold_beta) {
+      k_dot<T><<<nred(Q.n), kBlock, 0, s>>>(Q.n, w.p1, w.q0, red(h, l, EPI_BETA));
+      finish<1>(h, nred(Q.n), red(h, l, EPI_BETA));
+    }
+    k_cspmv_dir<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, EPI_ALPHA1));
+    finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA1));
+  }
   if (!defer_update2) k_update2<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p1, w.p0, e);
   return false;
 }
@@ -3722,8 +3729,8 @@ amg_status alloc_workspaces(amg_hierarchy *h) {
     if (!*v) return AMG_ERR_NOMEM;
   }
   h->scal = dalloc_n<double>(h, (h->nlev + 1) * kScalars);
-  // two values per workgroup of the largest reduction launch (a scheduled pass over all slices)
-  h->partials_cap = std::max<int64_t>(kRedBlocksMax, sched_grid(slice_sched(h->fine, 0, h->fine.ncolor)) + 1) * 2;
+  // two values per workgroup of the largest reduction launch (a scheduled pass over all slices), or four of a level's
+  h->partials_cap = std::max<int64_t>(2 * kRedBlocksMax, sched_grid(slice_sched(h->fine, 0, h->fine.ncolor)) + 1) * 2;
   h->partials = dalloc_n<double>(h, h->partials_cap);
   if (!h->scal || !h->partials) return AMG_ERR_NOMEM;
   QA_HIP(hipMemsetAsync(h->scal, 0, sizeof(double) * (h->nlev + 1) * kScalars, h->stream));
@@ -3911,7 +3918,7 @@ static amg_status level_smooth_t(amg_hierarchy *h, int level, const double *f, d
     k_lex_to_q<double, T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, x, xx, 0, dim);
     for (int c = 0; c < nc; c++) {
       if (dim == 3) gs_phase_oct<T>(h, level, ff, xx, forward ? c : nc - 1 - c);
-      else gs_phase_coarse<T>(h, level, ff, xx, forward ? c : nc - 1 - c);
+      else gs_phase_coarse<T>(h, level, ff, xx, forward ? c : nc - 1 - c, false);
     }
     k_lex_to_q<T, double><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, xx, x, 1, dim);
   }
