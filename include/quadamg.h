@@ -108,8 +108,9 @@ amg_status amg_setup(int64_t n, const double *coords, const int64_t *row_ptr, co
  * Section 4.4 at dz = 0, +1, -1, self first) plus an overflow list, an 8-coloring (t1 & 1) + 2 (t2 & 1) + 4 (t3 & 1)
  * for the Gauss-Seidel smoother, and the same cycle and outer iteration as amg_setup. The coarsest level is the first
  * k with 8^k <= coarse_max. coords: device, n x 3 interleaved (x, y, z). opt may be NULL; opt->box must be NULL (the
- * box argument replaces it). Octree levels always run one kernel launch per step (options engine and batch have no
- * effect). amg_solve, amg_apply_precond, amg_update_values, amg_export_level (27 slots per row, lexicographic id
+ * box argument replaces it). With options.engine on, the octree levels from 4,096 cells down run inside one persistent
+ * workgroup (default coarse_max, sweeps and inner_iters); the others, and all with it off, run one kernel launch per step
+ * (option batch has no effect). amg_solve, amg_apply_precond, amg_update_values, amg_export_level (27 slots per row, lexicographic id
  * t1 + 2^k t2 + 4^k t3), amg_level_smooth, amg_level_spmv and amg_free take the hierarchy as for amg_setup. Errors
  * as amg_setup. */
 amg_status amg_setup3d(int64_t n, const double *coords, const int64_t *row_ptr, const int32_t *col_idx,

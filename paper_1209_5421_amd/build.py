@@ -26,6 +26,7 @@ SOURCES = {
     "qa_setup.hip": ["-ffp-contract=off"],
     "qa_solve.hip": [],
     "qa_engine.hip": [],
+    "qa_engine3.hip": [],
     # element entries and their sums in a fixed IEEE order
     "qa_assemble.hip": ["-ffp-contract=off"],
 }

@@ -1,0 +1,488 @@
+// Persistent engine of the small octree levels (gfx950): B~ (Algorithm 2.1 with n = 2) of the 4,096-cell level k = 4, or
+// of the 512-cell level k = 3 where that is the finest tree level, and everything below it in one launch of one
+// 512-thread workgroup. The coarsest level is the 64-cell level k = 2; one smoothing sweep.
+//
+// Like the quadtree's engine it is bound by the latency of its chain of steps on one CU; in 3D by the operator as well,
+// which at 27 entries a row (432 KB on the 4,096-cell level in FP32) exceeds the registers and LDS of a CU:
+//  - u lies in LDS as the plain lattice of the level's cells with a ring of zeros around it, so that every neighbour of
+//    every color is the same compile-time distance away: an immediate offset of the LDS load, no index arithmetic (the
+//    Morton rule for 27 neighbours is about 700 instructions a row) and no edge tests. The strides let a wavefront's
+//    4 x 4 x 4 block of cells of one color touch every second bank twice;
+//  - on level 4 a thread owns a super-cell (the eight cells of one parent, one per color): its f, q0 and p0 stay in
+//    registers, and the rows stream from L2, each row's entries loaded one or two rows ahead of their use and across the
+//    barriers (kAhead); the presmoothing sweep starts from zero, so it neither loads nor reads the slots of colors not
+//    relaxed yet;
+//  - on level 3 a thread owns a row, wavefront c those of color c, its entries in registers;
+//  - A p1 with (p1, A p1), (r, p1), (p1, q0) and (r, p0) replaces A (p1 + beta p0), as in the quadtree's engine: one
+//    reduction per inner step;
+//  - the FP64 coarsest solve takes eight columns per wavefront.
+// On the top level couplings beyond one cell are allowed (OVF): rows that have some are marked once, and coupled rows of
+// one color see the values from before their phase.
+// One launch takes 87 us (FP32) and 157 us (FP64) on level 4, where B~ of that level took 30 launches and about 390 us:
+// 28.0 -> 15.5 ms per FP32-preconditioned solve of the heat step with 1,020,100 unknowns, 6.1 -> 3.8 ms in FP64 with
+// 8,820.
+
+#include <hip/hip_runtime.h>
+
+#include <mutex>
+#include <type_traits>
+#include <utility>
+#include <vector>
+
+#include "qa_internal.hpp"
+#include "qa_wave.hpp"
+
+namespace qa {
+
+namespace {
+
+constexpr int kO3Threads = 512;
+
+template <int C>
+using IC = std::integral_constant<int, C>;
+
+template <int... I, class F>
+__device__ __forceinline__ void o3_each(std::integer_sequence<int, I...>, F f) {
+  (f(IC<I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void o3_for(F f) {
+  o3_each(std::make_integer_sequence<int, N>{}, f);
+}
+
+// offsets of slot s: the nine plane offsets of Section 4.4 (self, E, NE, N, NW, W, SW, S, SE) at dz = 0, +1, -1
+constexpr int o3_dx(int s) {
+  const int p = s % 9;
+  return (p == 1 || p == 2 || p == 8) ? 1 : ((p == 4 || p == 5 || p == 6) ? -1 : 0);
+}
+constexpr int o3_dy(int s) {
+  const int p = s % 9;
+  return (p == 2 || p == 3 || p == 4) ? 1 : ((p == 6 || p == 7 || p == 8) ? -1 : 0);
+}
+constexpr int o3_dz(int s) { return s < 9 ? 0 : (s < 18 ? 1 : -1); }
+// color of the slot's neighbour of a color-c cell
+constexpr int o3_color(int c, int s) {
+  return c ^ ((o3_dx(s) & 1) | ((o3_dy(s) & 1) << 1) | ((o3_dz(s) & 1) << 2));
+}
+// restriction order of the children: (0, 1, 3, 2) on either layer
+constexpr int o3_child(int i) { return (i & 4) | ((i & 3) == 2 ? 3 : ((i & 3) == 3 ? 2 : (i & 3))); }
+
+// lattice of level k: side 2^k with a ring around it
+template <int K>
+struct O3Geo {
+  static constexpr int S = 1 << K, n = S * S * S, N8 = n / 8;
+  static constexpr int SY = K == 4 ? 20 : 12, SZ = SY * (S + 2), cells = SZ * (S + 2);
+  // distance of a slot's neighbour from the cell's corner place (one row, column and layer back)
+  static constexpr int off(int s) { return (1 + o3_dz(s)) * SZ + (1 + o3_dy(s)) * SY + 1 + o3_dx(s); }
+  static constexpr int own = SZ + SY + 1;
+  static constexpr int child(int c) { return (c >> 2) * SZ + ((c >> 1) & 1) * SY + (c & 1); }
+};
+
+// LDS. In doubles: the coarsest inverse, its right-hand side, the wavefronts' partial solutions, the wavefront sums of
+// the reductions. In units of T: the lattices, the right-hand side of level 3 and its result (both 512), the residuals
+// of level 3 and, in FP64, p0 of level 4.
+struct O3Lay {
+  static constexpr int kAinv = 0, kG2 = 4096, kPart = kG2 + 64, kRed = kPart + 512, kDoubles = kRed + 32;
+  static constexpr int kLat4 = 0, kLat3 = O3Geo<4>::cells, kG3 = kLat3 + O3Geo<3>::cells, kE3 = kG3 + 512,
+                       kRes = kE3 + 512, kP0 = kRes + 512;
+  template <class T>
+  static constexpr int units() {
+    return kP0 + (sizeof(T) == 8 ? O3Geo<4>::n : 0);
+  }
+  template <class T>
+  static constexpr size_t bytes() {
+    return sizeof(double) * kDoubles + sizeof(T) * units<T>();
+  }
+};
+
+template <class T>
+struct O3Args {
+  const double *ainv;             // coarsest inverse, 64 x 64, storage numbering (bitwise symmetric)
+  const T *ax4, *ax3;             // 27 x n operators
+  const T *g;                     // the top level's right-hand side and result
+  T *e;
+  const int32_t *optr, *ocol;     // the top level's overflow couplings (OVF)
+  const T *oval;
+};
+
+// place of the cell with color-major index q on level k's lattice (its corner)
+template <int K>
+__device__ __forceinline__ int o3_place(uint32_t q) {
+  using G = O3Geo<K>;
+  const uint32_t m = m_of_q3(q, K);
+  return static_cast<int>(compact3(m >> 2)) * G::SZ + static_cast<int>(compact3(m >> 1)) * G::SY +
+         static_cast<int>(compact3(m));
+}
+
+// sum of a row's overflow couplings times u (added behind its 27 slots). ZERO: in the sweep from zero, entries of colors
+// not relaxed yet (the row's own among them) hold zero.
+template <class T, int K, bool ZERO>
+__device__ __forceinline__ T o3_ovf(const O3Args<T> &A, T acc, uint32_t q, int c, const T *lat) {
+  for (int32_t e = A.optr[q]; e < A.optr[q + 1]; e++) {
+    const uint32_t i = static_cast<uint32_t>(A.ocol[e]);
+    if (ZERO && static_cast<int>(i / O3Geo<K>::N8) >= c) continue;
+    acc += A.oval[e] * lat[o3_place<K>(i) + O3Geo<K>::own];
+  }
+  return acc;
+}
+
+// between two rows: nothing is loaded further ahead, and no lattice value is kept for the next (either would spill)
+__device__ __forceinline__ void o3_next() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// a uniform address that the optimiser cannot identify: it would hoist the loads out of the loop over the inner steps, or
+// keep one step's entries for the next, and spill them
+template <class T>
+using Global = const __attribute__((address_space(1))) T *;
+template <class T>
+__device__ __forceinline__ Global<T> o3_opaque(const T *p) {
+  Global<T> g = (Global<T>)p;
+  asm volatile("" : "+s"(g));
+  return g;
+}
+
+template <class T>
+struct O3Row {
+  T a[27];
+};
+
+// Algorithm 2.1's scalars of one level between its two steps
+template <class T>
+struct O3Scal {
+  double d0 = 0.0;
+  T a0 = 0;
+};
+
+template <class T>
+struct O3 {
+  const O3Args<T> &A;
+  double *D;
+  T *S;
+  int tid, wave, lane;
+
+  // (u, A u), (f, u), (u, q0), (f, p0) over the workgroup -> alpha0 (first) or beta and alpha1, uniform
+  __device__ __forceinline__ void first_scalars(double (&v)[4], O3Scal<T> &Z) const {
+    block_sum4<kO3Threads>(v, reinterpret_cast<double(*)[8]>(D + O3Lay::kRed));
+    Z.d0 = v[0];
+    Z.a0 = static_cast<T>(readlane_f64((v[0] > 0.0) ? v[1] / v[0] : 0.0, 0));
+  }
+  __device__ __forceinline__ void second_scalars(double (&v)[4], const O3Scal<T> &Z, T &bt, T &a1) const {
+    block_sum4<kO3Threads>(v, reinterpret_cast<double(*)[8]>(D + O3Lay::kRed));
+    const bool stop = !(Z.d0 > 0.0);
+    bt = static_cast<T>(stop ? 0.0 : -v[2] / Z.d0);
+    const double b = static_cast<double>(bt);
+    const double d1 = v[0] + b * (2.0 * v[2] + b * Z.d0);
+    a1 = static_cast<T>((stop || !(d1 > 0.0)) ? 0.0 : (v[1] + b * v[3]) / d1);
+  }
+
+  // ---- level 3: thread = row c 64 + j ----
+
+  // B~ with right-hand side f of the thread's row; returns the row's result
+  template <bool TOP, bool OVF>
+  __device__ __forceinline__ T level3(T f) const {
+    using G = O3Geo<3>;
+    const int c = wave, j = lane;
+    const uint32_t q = static_cast<uint32_t>(tid);
+    T a[27];
+    const Global<T> ax = o3_opaque(A.ax3);
+    o3_for<27>([&](auto ss) {
+      constexpr int s = decltype(ss)::value;
+      a[s] = (ax + s * G::n)[tid];
+    });
+    T *lat = S + O3Lay::kLat3 + o3_place<3>(q);
+    const T *lat0 = S + O3Lay::kLat3;
+    bool far = false;
+    if constexpr (TOP && OVF) far = A.optr[q + 1] > A.optr[q];
+    T *res = S + O3Lay::kRes;
+    double *g2 = D + O3Lay::kG2, *part = D + O3Lay::kPart;
+    const int q2 = static_cast<int>(q_of_m3(static_cast<uint32_t>(j), 2));
+    auto sum = [&]() -> T {
+      T acc = 0;
+      o3_for<27>([&](auto ss) {
+        constexpr int s = decltype(ss)::value;
+        acc += a[s] * lat[G::off(s)];
+      });
+      if constexpr (TOP && OVF)
+        if (far) acc = o3_ovf<T, 3, false>(A, acc, q, 0, lat0);
+      return acc;
+    };
+    O3Scal<T> Z;
+    T q0 = 0, p0 = 0, e = 0;
+#pragma unroll 1
+    for (int half = 0; half < 2; half++) {
+      T u = 0;
+      lat[G::own] = T(0);
+      __syncthreads();
+#pragma unroll 1
+      for (int cc = 0; cc < 8; cc++) {  // from zero: colors not relaxed yet (and coupled rows of this one) hold zero
+        if (c == cc) u = T(0) + (f - sum()) / a[0];
+        if constexpr (TOP && OVF) __syncthreads();
+        if (c == cc) lat[G::own] = u;
+        __syncthreads();
+      }
+      res[tid] = f - sum();
+      __syncthreads();
+      if (c == 0) {
+        T acc = 0;
+        o3_for<8>([&](auto ii) { acc += res[o3_child(decltype(ii)::value) * 64 + j]; });
+        g2[q2] = static_cast<double>(acc);
+      }
+      __syncthreads();
+      {  // e2 = A_2^{-1} g2: wavefront w takes the columns 8 w .. 8 w + 7 of row `lane` (symmetric: read as a column)
+        double acc[2] = {0.0, 0.0};
+        o3_for<8>([&](auto ii) {
+          constexpr int i = decltype(ii)::value;
+          acc[i & 1] += D[O3Lay::kAinv + (8 * c + i) * 64 + j] * g2[8 * c + i];
+        });
+        part[c * 64 + j] = acc[0] + acc[1];
+      }
+      __syncthreads();
+      {
+        double acc[2] = {0.0, 0.0};
+        o3_for<8>([&](auto ii) { acc[decltype(ii)::value & 1] += part[decltype(ii)::value * 64 + q2]; });
+        u += static_cast<T>(acc[0] + acc[1]);
+        lat[G::own] = u;
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (int cc = 7; cc >= 0; cc--) {
+        if (c == cc) u += (f - sum()) / a[0];
+        if constexpr (TOP && OVF) __syncthreads();
+        if (c == cc) lat[G::own] = u;
+        __syncthreads();
+      }
+      const T y = sum();
+      const double ud = static_cast<double>(u), fd = static_cast<double>(f);
+      double v[4] = {ud * static_cast<double>(y), fd * ud, 0.0, 0.0};
+      if (half == 0) {
+        first_scalars(v, Z);
+        q0 = y, p0 = u;
+        f = f - Z.a0 * q0;
+      } else {
+        v[2] = ud * static_cast<double>(q0);
+        v[3] = fd * static_cast<double>(p0);
+        T bt, a1;
+        second_scalars(v, Z, bt, a1);
+        e = Z.a0 * p0;
+        e += a1 * (u + bt * p0);
+      }
+    }
+    return e;
+  }
+
+  // ---- level 4: thread = super-cell j, rows c 512 + j ----
+
+  // jobs of the two stages between which the next level runs. Stage 0: the presmoothing phases of colors 0 .. 7, then
+  // the residuals of the children in restriction order; stage 1: the post-smoothing phases of colors 7 .. 0, then A u.
+  static constexpr int job_color(int stage, int i) {
+    return stage == 0 ? (i < 8 ? i : o3_child(i - 8)) : (i < 8 ? 7 - i : i - 8);
+  }
+  // entries of the job's row: in the sweep from zero the diagonal and the slots of colors relaxed already
+  template <int STAGE, int I>
+  __device__ __forceinline__ void job_load(O3Row<T> &b) const {
+    constexpr int c = job_color(STAGE, I);
+    constexpr bool pre = STAGE == 0 && I < 8;
+    const Global<T> ax = o3_opaque(A.ax4);
+    o3_for<27>([&](auto ss) {
+      constexpr int s = decltype(ss)::value;
+      if constexpr (!pre || s == 0 || o3_color(c, s) < c) b.a[s] = (ax + (s * O3Geo<4>::n + c * O3Geo<4>::N8))[tid];
+    });
+  }
+  template <int STAGE, int I, bool OVF>
+  __device__ __forceinline__ T job_sum(const O3Row<T> &b, const T *lat, const T *lat0, unsigned far) const {
+    using G = O3Geo<4>;
+    constexpr int c = job_color(STAGE, I);
+    constexpr bool pre = STAGE == 0 && I < 8;
+    T acc = 0;
+    o3_for<27>([&](auto ss) {
+      constexpr int s = decltype(ss)::value;
+      if constexpr (!pre || o3_color(c, s) < c) acc += b.a[s] * lat[G::child(c) + G::off(s)];
+    });
+    if constexpr (OVF)
+      if ((far >> c) & 1u) acc = o3_ovf<T, 4, pre>(A, acc, static_cast<uint32_t>(c * G::N8 + tid), c, lat0);
+    return acc;
+  }
+
+  template <bool OVF>
+  __device__ __forceinline__ void level4() const {
+    using G = O3Geo<4>;
+    constexpr int kAhead = sizeof(T) == 4 ? 2 : 1;  // rows loaded ahead (FP64: two would exceed the registers)
+    constexpr int NB = kAhead + 1;
+    const int corner = o3_place<4>(static_cast<uint32_t>(tid));  // color 0's
+    T *lat0 = S + O3Lay::kLat4, *lat = lat0 + corner;
+    T *g3 = S + O3Lay::kG3, *e3 = S + O3Lay::kE3;
+    T f[8], q0[8], p0r[sizeof(T) == 4 ? 8 : 1];
+    auto p0 = [&](int c) -> T & {  // FP64: in LDS, to save registers
+      if constexpr (sizeof(T) == 4) return p0r[c];
+      else return S[O3Lay::kP0 + c * G::N8 + tid];
+    };
+    unsigned far = 0;
+    o3_for<8>([&](auto cc) {
+      constexpr int c = decltype(cc)::value;
+      f[c] = A.g[c * G::N8 + tid];
+      q0[c] = p0(c) = T(0);
+      if constexpr (OVF)
+        if (A.optr[c * G::N8 + tid + 1] > A.optr[c * G::N8 + tid]) far |= 1u << c;
+    });
+    O3Scal<T> Z;
+#pragma unroll 1
+    for (int half = 0; half < 2; half++) {
+      O3Row<T> b[NB];
+      o3_for<kAhead>([&](auto ii) { job_load<0, decltype(ii)::value>(b[decltype(ii)::value]); });
+      T gsum = 0;
+      o3_for<16>([&](auto ii) {
+        constexpr int i = decltype(ii)::value, c = job_color(0, i);
+        o3_next();
+        if constexpr (i + kAhead < 16) job_load<0, i + kAhead>(b[(i + kAhead) % NB]);
+        const O3Row<T> &r = b[i % NB];
+        const T d = f[c] - job_sum<0, i, OVF>(r, lat, lat0, far);
+        if constexpr (i < 8) {
+          lat[G::child(c) + G::own] = T(0) + d / r.a[0];
+          __syncthreads();
+        } else {
+          gsum += d;
+        }
+      });
+      g3[q_of_m3(static_cast<uint32_t>(tid), 3)] = gsum;
+      __syncthreads();
+      const T r3 = level3<false, false>(g3[tid]);
+      e3[(lane << 3) | wave] = r3;  // by the cell's Morton index, that of its super-cell on level 4
+      o3_for<kAhead>([&](auto ii) { job_load<1, decltype(ii)::value>(b[decltype(ii)::value]); });
+      __syncthreads();
+      {
+        const T em = e3[tid];
+        o3_for<8>([&](auto cc) { lat[G::child(decltype(cc)::value) + G::own] += em; });
+      }
+      __syncthreads();
+      double v[4] = {0.0, 0.0, 0.0, 0.0};
+      o3_for<16>([&](auto ii) {
+        constexpr int i = decltype(ii)::value, c = job_color(1, i);
+        o3_next();
+        if constexpr (i + kAhead < 16) job_load<1, i + kAhead>(b[(i + kAhead) % NB]);
+        const O3Row<T> &r = b[i % NB];
+        const T s = job_sum<1, i, OVF>(r, lat, lat0, far);
+        T *own = lat + G::child(c) + G::own;
+        if constexpr (i < 8) {
+          const T u = *own + (f[c] - s) / r.a[0];
+          if constexpr (OVF) __syncthreads();
+          *own = u;
+          __syncthreads();
+        } else {
+          const double ud = static_cast<double>(*own), fd = static_cast<double>(f[c]);
+          v[0] += ud * static_cast<double>(s);
+          v[1] += fd * ud;
+          v[2] += ud * static_cast<double>(q0[c]);  // zero in the first step
+          v[3] += fd * static_cast<double>(p0(c));
+          q0[c] = half ? q0[c] : s;
+          p0(c) = half ? p0(c) : *own;
+        }
+      });
+      if (half == 0) {
+        first_scalars(v, Z);
+        o3_for<8>([&](auto cc) {
+          constexpr int c = decltype(cc)::value;
+          f[c] = f[c] - Z.a0 * q0[c];
+        });
+      } else {
+        T bt, a1;
+        second_scalars(v, Z, bt, a1);
+        o3_for<8>([&](auto cc) {
+          constexpr int c = decltype(cc)::value;
+          T e = Z.a0 * p0(c);
+          e += a1 * (lat[G::child(c) + G::own] + bt * p0(c));
+          A.e[c * G::N8 + tid] = e;
+        });
+      }
+    }
+  }
+};
+
+template <class T, int KT, bool OVF>
+__global__ void __launch_bounds__(kO3Threads) k_engine_oct(O3Args<T> A) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double *D = reinterpret_cast<double *>(smem);
+  T *S = reinterpret_cast<T *>(smem + sizeof(double) * O3Lay::kDoubles);
+  const int tid = static_cast<int>(threadIdx.x);
+  double ai[8];
+#pragma unroll
+  for (int k = 0; k < 8; k++) ai[k] = A.ainv[tid + k * kO3Threads];
+  for (int i = tid; i < O3Lay::units<T>(); i += kO3Threads) S[i] = T(0);  // the lattices' rings are read and never written
+#pragma unroll
+  for (int k = 0; k < 8; k++) D[O3Lay::kAinv + tid + k * kO3Threads] = ai[k];
+  __syncthreads();
+  const O3<T> E{A, D, S, tid, __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63};
+  if constexpr (KT == 4) E.template level4<OVF>();
+  else A.e[tid] = E.template level3<true, OVF>(A.g[tid]);
+}
+
+template <class T>
+const void *o3_kernel(int kt, bool ovf) {
+  if (kt == 4)
+    return ovf ? reinterpret_cast<const void *>(k_engine_oct<T, 4, true>)
+               : reinterpret_cast<const void *>(k_engine_oct<T, 4, false>);
+  return ovf ? reinterpret_cast<const void *>(k_engine_oct<T, 3, true>)
+             : reinterpret_cast<const void *>(k_engine_oct<T, 3, false>);
+}
+
+amg_status o3_lds_limits(int device) {
+  static std::once_flag once[64];
+  if (device < 0 || device >= 64) return AMG_ERR_DEVICE;
+  amg_status st = AMG_OK;
+  std::call_once(once[device], [&]() {
+    for (int kt : {3, 4})
+      for (bool ovf : {false, true})
+        for (bool dbl : {false, true}) {
+          const void *k = dbl ? o3_kernel<double>(kt, ovf) : o3_kernel<float>(kt, ovf);
+          const int b = static_cast<int>(dbl ? O3Lay::bytes<double>() : O3Lay::bytes<float>());
+          if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, b) != hipSuccess) st = AMG_ERR_DEVICE;
+        }
+  });
+  return st;
+}
+
+template <class T>
+void o3_launch(amg_hierarchy *h, const LevelWork<T> &w, const T *ax4, const T *ax3, const T *oval) {
+  const QuadLevel &Q = h->lev[h->oct_top];
+  const O3Args<T> A{h->ainv, ax4, ax3, w.g, w.e, Q.optr, Q.ocol, oval};
+  const size_t lds = O3Lay::bytes<T>();
+  const bool ovf = Q.ovf_nnz != 0;
+  if (Q.k == 4) {
+    if (ovf) k_engine_oct<T, 4, true><<<1, kO3Threads, lds, h->stream>>>(A);
+    else k_engine_oct<T, 4, false><<<1, kO3Threads, lds, h->stream>>>(A);
+  } else {
+    if (ovf) k_engine_oct<T, 3, true><<<1, kO3Threads, lds, h->stream>>>(A);
+    else k_engine_oct<T, 3, false><<<1, kO3Threads, lds, h->stream>>>(A);
+  }
+}
+
+}  // namespace
+
+// Selects the octree engine's top level: k = min(L, 4), where the coarsest level is k = 2 with 64 cells, the cycle has
+// one sweep and two inner steps, and the level below the top holds no couplings beyond one cell.
+amg_status plan_engine_oct(amg_hierarchy *h) {
+  h->oct_top = -1;
+  if (h->dim != 3 || h->opt.engine == 0 || h->nlev < 3 || h->L < 3 || h->lev[h->nlev - 1].k != 2 || h->nc != 64 ||
+      h->opt.sweeps != 1 || h->opt.inner_iters != 2)
+    return AMG_OK;
+  const int kt = h->L < 4 ? h->L : 4, top = 1 + (h->L - kt);
+  for (int l = top + 1; l + 1 < h->nlev; l++)
+    if (h->lev[l].ovf_nnz != 0 || h->lev[l].same_color_ovf) return AMG_OK;
+  int lds = 0;
+  QA_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device));
+  if (O3Lay::bytes<double>() > static_cast<size_t>(lds)) return AMG_OK;
+  QA_TRY(o3_lds_limits(h->device));
+  h->oct_top = top;
+  return AMG_OK;
+}
+
+void launch_engine_oct(amg_hierarchy *h, int precision) {
+  const int top = h->oct_top;
+  const bool four = h->lev[top].k == 4;
+  const QuadLevel &Q = h->lev[top], &Q3 = h->lev[four ? top + 1 : top];
+  if (precision) o3_launch<float>(h, h->w32[top], four ? Q.ax32 : nullptr, Q3.ax32, Q.oval32);
+  else o3_launch<double>(h, h->w64[top], four ? Q.ax64 : nullptr, Q3.ax64, Q.oval64);
+}
+
+}  // namespace qa

@@ -299,6 +299,7 @@ struct amg_hierarchy {
   int use_engine = 1;                 // 0 off, 1 on (specialised engine where eligible), 2 the step interpreter only
   // specialised engine (qa_engine.hip): configuration id per precision (-1 = the interpreter)
   int fe_cfg[2] = {-1, -1};
+  int oct_top = -1;                   // top level of the octree engine (qa_engine3.hip), -1 = not used
   int use_batch = 1;
   // whole-solve workgroup (batched serving of small systems), per precision
   void *wg_ops[2] = {nullptr, nullptr};
@@ -356,6 +357,8 @@ amg_status plan_engine(amg_hierarchy *h);
 amg_status plan_wg(amg_hierarchy *h);
 amg_status plan_engine_fast(amg_hierarchy *h);   // qa_engine.hip
 void launch_engine_fast(amg_hierarchy *h, int precision);
+amg_status plan_engine_oct(amg_hierarchy *h);    // qa_engine3.hip
+void launch_engine_oct(amg_hierarchy *h, int precision);
 amg_status precond_apply(amg_hierarchy *h, int precision, const double *r_p, double *z_p);
 amg_status level_smooth_internal(amg_hierarchy *h, int level, const double *f, double *x, int forward, int prec);
 amg_status level_spmv_internal(amg_hierarchy *h, int level, const double *x, double *y, int prec);

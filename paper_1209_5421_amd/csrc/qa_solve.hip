@@ -1214,7 +1214,7 @@ __device__ __forceinline__ void ring_phase(const RingRows<T, TS, RS, RG> &D,
 }
 
 // the four sums of a launch's workgroups (part: four doubles each, nb <= 256 of them), the same in every thread of every
-// workgroup that asks: the loads, to be issued with the caller's others, and the sums (all threads call both)
+// workgroup that asks: the loads, to be issued with the caller's others, then block_sum4 (all threads call both)
 __device__ __forceinline__ void fold_load(const double *__restrict__ part, int nb, double (&v)[4]) {
   const int t = static_cast<int>(threadIdx.x);
   const double2 *p = reinterpret_cast<const double2 *>(part) + 2 * (t < nb ? t : 0);
@@ -1222,20 +1222,6 @@ __device__ __forceinline__ void fold_load(const double *__restrict__ part, int n
   const bool in = t < nb;
   v[0] = in ? x.x : 0.0, v[1] = in ? x.y : 0.0, v[2] = in ? y.x : 0.0, v[3] = in ? y.y : 0.0;
 }
-template <int NT>
-__device__ __forceinline__ void block_sum4(double (&v)[4], double (*red)[8]) {  // red[4][8] in LDS
-  const int lane = static_cast<int>(threadIdx.x & 63), w = static_cast<int>(threadIdx.x >> 6);
-  const double k = wave_sum4(v);
-  if (lane < 4) red[sum4_of(lane)][w] = k;
-  __syncthreads();
-  double r = (lane & 7) < NT / 64 ? red[(lane >> 3) & 3][lane & 7] : 0.0;  // lanes 8 j .. 8 j + 7: the waves' v[j]
-  r += dpp_f64<0xb1>(r);
-  r += dpp_f64<0x4e>(r);
-  r += dpp_f64<0x141>(r);
-#pragma unroll
-  for (int j = 0; j < 4; j++) v[j] = readlane_f64(r, 8 * j);
-}
-
 // The whole first post-smoothing sweep (color phases 3, 2, 1, 0, the prolongation folded in as in k_cgs_post) of a
 // level without same-color couplings or overflow entries, in one launch: x + P e_c (x: the presmoothed values) staged
 // over the square and its rings, each phase on one ring less, the result to u (another vector: the neighbouring
@@ -2774,8 +2760,8 @@ static double engine_flops(const amg_hierarchy *h, int top, const std::vector<En
 
 amg_status plan_engine(amg_hierarchy *h) {
   h->engine_top[0] = h->engine_top[1] = -1;
-  // nothing between the fine level and the coarsest; octree levels run per step
-  if (h->nlev < 3 || h->dim != 2) return AMG_OK;
+  if (h->dim == 3) return plan_engine_oct(h);
+  if (h->nlev < 3) return AMG_OK;  // nothing between the fine level and the coarsest
   int lds = 0;
   QA_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device));
   h->lds_max = static_cast<size_t>(lds);
@@ -3651,6 +3637,10 @@ static void bhat_oct(amg_hierarchy *h, int l, const T *f, T *u) {
 
 template <class T>
 static void btilde_oct(amg_hierarchy *h, int l, const T *g, T *e) {
+  if (l == h->oct_top) {  // g and e are the level's own vectors
+    launch_engine_oct(h, std::is_same<T, float>::value ? 1 : 0);
+    return;
+  }
   const QuadLevel &Q = h->lev[l];
   LevelWork<T> &w = P<T>::W(h)[l];
   hipStream_t s = h->stream;

@@ -53,4 +53,20 @@ __device__ __forceinline__ double wave_sum4(const double (&v)[4]) {
   return rows_sum(k);
 }
 
+// four sums over a workgroup of NT threads (at most 512), the same in every thread (all call): each wavefront's sums as
+// above, then the wavefronts' added in pairs. red: 4 x 8 doubles of LDS, not in use before the next barrier but one.
+template <int NT>
+__device__ __forceinline__ void block_sum4(double (&v)[4], double (*red)[8]) {
+  const int lane = static_cast<int>(threadIdx.x & 63), w = static_cast<int>(threadIdx.x >> 6);
+  const double k = wave_sum4(v);
+  if (lane < 4) red[sum4_of(lane)][w] = k;
+  __syncthreads();
+  double r = (lane & 7) < NT / 64 ? red[(lane >> 3) & 3][lane & 7] : 0.0;  // lanes 8 j .. 8 j + 7: the waves' v[j]
+  r += dpp_f64<0xb1>(r);
+  r += dpp_f64<0x4e>(r);
+  r += dpp_f64<0x141>(r);
+#pragma unroll
+  for (int j = 0; j < 4; j++) v[j] = readlane_f64(r, 8 * j);
+}
+
 }  // namespace qa
