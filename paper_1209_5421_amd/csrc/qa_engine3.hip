@@ -12,14 +12,17 @@
 //    registers, and the rows stream from L2, each row's entries loaded one or two rows ahead of their use and across the
 //    barriers (kAhead); the presmoothing sweep starts from zero, so it neither loads nor reads the slots of colors not
 //    relaxed yet;
-//  - on level 3 a thread owns a row, wavefront c those of color c, its entries in registers;
+//  - on level 3 eight threads share the rows of a super-cell, each holding four of the 27 slots of all eight in registers,
+//    so that the 64 rows of a color phase are spread over every wavefront;
 //  - A p1 with (p1, A p1), (r, p1), (p1, q0) and (r, p0) replaces A (p1 + beta p0), as in the quadtree's engine: one
 //    reduction per inner step;
-//  - the FP64 coarsest solve takes eight columns per wavefront.
+//  - the FP64 coarsest solve takes eight columns per thread.
 // On the top level couplings beyond one cell are allowed (OVF): rows that have some are marked once, and coupled rows of
 // one color see the values from before their phase.
-// One launch takes 87 us (FP32) and 157 us (FP64) on level 4, where B~ of that level took 30 launches and about 390 us:
-// 28.0 -> 15.5 ms per FP32-preconditioned solve of the heat step with 1,020,100 unknowns, 6.1 -> 3.8 ms in FP64 with
+// One launch takes 82 us (FP32) and 134 us (FP64) on level 4, where B~ of that level took 30 launches and about 390 us. Of
+// the FP32 launch the sixteen color phases of level 4 take 1.0 us each (0.5 without the operator's loads: a CU reads
+// 35 to 50 bytes per clock from L2), a color phase of level 3 0.24 us (0.4 with the 64 rows in one wavefront).
+// 28.0 -> 15.2 ms per FP32-preconditioned solve of the heat step with 1,020,100 unknowns, 6.1 -> 3.5 ms in FP64 with
 // 8,820.
 
 #include <hip/hip_runtime.h>
@@ -78,13 +81,12 @@ struct O3Geo {
   static constexpr int child(int c) { return (c >> 2) * SZ + ((c >> 1) & 1) * SY + (c & 1); }
 };
 
-// LDS. In doubles: the coarsest inverse, its right-hand side, the wavefronts' partial solutions, the wavefront sums of
-// the reductions. In units of T: the lattices, the right-hand side of level 3 and its result (both 512), the residuals
-// of level 3 and, in FP64, p0 of level 4.
+// LDS. In doubles: the coarsest inverse (rows 66 apart, so that eight rows read at once use different banks), its
+// right-hand side, the wavefront sums of the reductions. In units of T: the two lattices and, in FP64, p0 of level 4.
 struct O3Lay {
-  static constexpr int kAinv = 0, kG2 = 4096, kPart = kG2 + 64, kRed = kPart + 512, kDoubles = kRed + 32;
-  static constexpr int kLat4 = 0, kLat3 = O3Geo<4>::cells, kG3 = kLat3 + O3Geo<3>::cells, kE3 = kG3 + 512,
-                       kRes = kE3 + 512, kP0 = kRes + 512;
+  static constexpr int kAinvRow = 66;
+  static constexpr int kAinv = 0, kG2 = 64 * kAinvRow, kRed = kG2 + 64, kDoubles = kRed + 32;
+  static constexpr int kLat4 = 0, kLat3 = O3Geo<4>::cells, kP0 = kLat3 + O3Geo<3>::cells;
   template <class T>
   static constexpr int units() {
     return kP0 + (sizeof(T) == 8 ? O3Geo<4>::n : 0);
@@ -126,21 +128,63 @@ __device__ __forceinline__ T o3_ovf(const O3Args<T> &A, T acc, uint32_t q, int c
   return acc;
 }
 
-// between two rows: nothing is loaded further ahead, and no lattice value is kept for the next (either would spill)
-__device__ __forceinline__ void o3_next() {
-  asm volatile("" ::: "memory");
+// between two rows: the finished row's sum is formed here, not later, nothing is loaded further ahead, and no lattice
+// value is kept for the next row (any of it would spill)
+template <class T>
+__device__ __forceinline__ void o3_done(T &sum) {
+  asm volatile("" : "+v"(sum) : : "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// a uniform address that the optimiser cannot identify: it would hoist the loads out of the loop over the inner steps, or
-// keep one step's entries for the next, and spill them
+// entry `at` (compile-time part) + lane offset of an operator, by a buffer load: the slot's distance is a scalar operand.
+// The lane's byte offset passes through o3_opaque for every row: the optimiser would otherwise hoist the loads out of the
+// loop over the inner steps, or keep one step's entries for the next, and spill them.
+__device__ __forceinline__ int o3_opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 template <class T>
-using Global = const __attribute__((address_space(1))) T *;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t o3_rsrc(const T *p, int count) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(p), 0, count * static_cast<int>(sizeof(T)), 0x00027000);
+}
 template <class T>
-__device__ __forceinline__ Global<T> o3_opaque(const T *p) {
-  Global<T> g = (Global<T>)p;
-  asm volatile("" : "+s"(g));
-  return g;
+__device__ __forceinline__ T o3_load(__amdgpu_buffer_rsrc_t r, int lane_bytes, int at) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane_bytes, at * 4, 0));
+  } else {
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane_bytes, at * 8, 0));
+  }
+}
+
+// a lane's value moved by a DPP lane pattern
+template <int Ctrl>
+__device__ __forceinline__ double o3_dpp(double x) {
+  return dpp_f64<Ctrl>(x);
+}
+template <int Ctrl>
+__device__ __forceinline__ float o3_dpp(float x) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), Ctrl, 0xf, 0xf, false));
+}
+// sum over the eight lanes 8 k .. 8 k + 7, the same in each
+template <class X>
+__device__ __forceinline__ X o3_sum8(X x) {
+  x += o3_dpp<0xb1>(x);   // quad_perm [1, 0, 3, 2]
+  x += o3_dpp<0x4e>(x);   // quad_perm [2, 3, 0, 1]
+  x += o3_dpp<0x141>(x);  // row_half_mirror
+  return x;
+}
+// eight sums over the eight lanes 8 k .. 8 k + 7, sum g in lane g: in each step a lane hands its partner the half of its
+// values that the partner keeps
+template <class T>
+__device__ __forceinline__ T o3_sum8_own(const T (&v)[8], int g) {
+  const bool b0 = g & 1, b1 = g & 2, b2 = g & 4;
+  T h[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) h[i] = (b2 ? v[4 + i] : v[i]) + o3_dpp<0x141>(b2 ? v[i] : v[4 + i]);
+  const T k0 = (b0 ? h[1] : h[0]) + o3_dpp<0xb1>(b0 ? h[0] : h[1]);
+  const T k1 = (b0 ? h[3] : h[2]) + o3_dpp<0xb1>(b0 ? h[2] : h[3]);
+  return (b1 ? k1 : k0) + o3_dpp<0x4e>(b1 ? k0 : k1);
 }
 
 template <class T>
@@ -160,7 +204,7 @@ struct O3 {
   const O3Args<T> &A;
   double *D;
   T *S;
-  int tid, wave, lane;
+  int tid;
 
   // (u, A u), (f, u), (u, q0), (f, p0) over the workgroup -> alpha0 (first) or beta and alpha1, uniform
   __device__ __forceinline__ void first_scalars(double (&v)[4], O3Scal<T> &Z) const {
@@ -177,83 +221,95 @@ struct O3 {
     a1 = static_cast<T>((stop || !(d1 > 0.0)) ? 0.0 : (v[1] + b * v[3]) / d1);
   }
 
-  // ---- level 3: thread = row c 64 + j ----
+  // ---- level 3: eight threads to a super-cell j = tid >> 3; thread g = tid & 7 of them owns row g 64 + j and holds the
+  // slots 4 g .. 4 g + 3 of all eight rows, so that a color phase is spread over every wavefront ----
 
-  // B~ with right-hand side f of the thread's row; returns the row's result
+  // B~ with right-hand side f of the thread's row; returns the row's result. (A thread's row is the level-4 super-cell
+  // of the same Morton index: right-hand side and result pass between the levels in registers.)
   template <bool TOP, bool OVF>
   __device__ __forceinline__ T level3(T f) const {
     using G = O3Geo<3>;
-    const int c = wave, j = lane;
-    const uint32_t q = static_cast<uint32_t>(tid);
-    T a[27];
-    const Global<T> ax = o3_opaque(A.ax3);
-    o3_for<27>([&](auto ss) {
-      constexpr int s = decltype(ss)::value;
-      a[s] = (ax + s * G::n)[tid];
-    });
-    T *lat = S + O3Lay::kLat3 + o3_place<3>(q);
+    const int t = o3_opaque(tid), j = t >> 3, g = t & 7;
+    const uint32_t q = static_cast<uint32_t>(g * G::N8 + j);
     const T *lat0 = S + O3Lay::kLat3;
+    T *lat = S + O3Lay::kLat3 + o3_place<3>(static_cast<uint32_t>(j));  // color 0's corner
+    T a[8][4];
+    const T *at[4];
+    {
+      const __amdgpu_buffer_rsrc_t r = o3_rsrc(A.ax3, 27 * G::n);
+      const int lb = (4 * g * G::n + j) * static_cast<int>(sizeof(T));  // slot 27 lies behind the operator: reads 0
+#pragma unroll
+      for (int c = 0; c < 8; c++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) a[c][i] = o3_load<T>(r, lb, i * G::n + c * G::N8);
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int s = 4 * g + i, p = s % 9, z = s / 9;
+        const int dx = ((0x106 >> p) & 1) - ((0x70 >> p) & 1), dy = ((0x1c >> p) & 1) - ((0x1c0 >> p) & 1);
+        const int dz = z == 1 ? 1 : (z == 2 ? -1 : 0);
+        at[i] = lat + (s < 27 ? (1 + dz) * G::SZ + (1 + dy) * G::SY + 1 + dx : static_cast<int>(G::own));
+      }
+    }
+    T *own = lat + ((g >> 2) * G::SZ + ((g >> 1) & 1) * G::SY + (g & 1)) + G::own;
+    const T dg = A.ax3[q];
     bool far = false;
     if constexpr (TOP && OVF) far = A.optr[q + 1] > A.optr[q];
-    T *res = S + O3Lay::kRes;
-    double *g2 = D + O3Lay::kG2, *part = D + O3Lay::kPart;
+    double *g2 = D + O3Lay::kG2;
     const int q2 = static_cast<int>(q_of_m3(static_cast<uint32_t>(j), 2));
-    auto sum = [&]() -> T {
-      T acc = 0;
-      o3_for<27>([&](auto ss) {
-        constexpr int s = decltype(ss)::value;
-        acc += a[s] * lat[G::off(s)];
-      });
+    auto part = [&](auto cc) -> T {  // this thread's four products of color c's row
+      constexpr int c = decltype(cc)::value;
+      T acc = a[c][0] * at[0][G::child(c)];
+#pragma unroll
+      for (int i = 1; i < 4; i++) acc += a[c][i] * at[i][G::child(c)];
+      return acc;
+    };
+    auto row = [&]() -> T {  // (A u) of the own row
+      T v[8];
+      o3_for<8>([&](auto cc) { v[decltype(cc)::value] = part(cc); });
+      T acc = o3_sum8_own(v, g);
       if constexpr (TOP && OVF)
         if (far) acc = o3_ovf<T, 3, false>(A, acc, q, 0, lat0);
       return acc;
+    };
+    auto phase = [&](auto cc, T &u) {  // x += (f - A x) / diag on color c's rows
+      constexpr int c = decltype(cc)::value;
+      T acc = o3_sum8(part(cc));
+      if (g == c) {
+        if constexpr (TOP && OVF)
+          if (far) acc = o3_ovf<T, 3, false>(A, acc, q, 0, lat0);
+        u += (f - acc) / dg;
+      }
+      if constexpr (TOP && OVF) __syncthreads();
+      if (g == c) *own = u;
+      __syncthreads();
     };
     O3Scal<T> Z;
     T q0 = 0, p0 = 0, e = 0;
 #pragma unroll 1
     for (int half = 0; half < 2; half++) {
       T u = 0;
-      lat[G::own] = T(0);
+      *own = T(0);  // colors not relaxed yet (and coupled rows of the phase's color) hold zero
       __syncthreads();
-#pragma unroll 1
-      for (int cc = 0; cc < 8; cc++) {  // from zero: colors not relaxed yet (and coupled rows of this one) hold zero
-        if (c == cc) u = T(0) + (f - sum()) / a[0];
-        if constexpr (TOP && OVF) __syncthreads();
-        if (c == cc) lat[G::own] = u;
-        __syncthreads();
-      }
-      res[tid] = f - sum();
+      o3_for<8>([&](auto cc) { phase(cc, u); });
+      const T r = o3_sum8(f - row());  // residual, summed over the children
+      if (g == 0) g2[q2] = static_cast<double>(r);
       __syncthreads();
-      if (c == 0) {
-        T acc = 0;
-        o3_for<8>([&](auto ii) { acc += res[o3_child(decltype(ii)::value) * 64 + j]; });
-        g2[q2] = static_cast<double>(acc);
-      }
-      __syncthreads();
-      {  // e2 = A_2^{-1} g2: wavefront w takes the columns 8 w .. 8 w + 7 of row `lane` (symmetric: read as a column)
+      {  // e2 = A_2^{-1} g2: thread g takes the columns 8 g .. 8 g + 7 of the super-cell's row
+        const double2 *Ai = reinterpret_cast<const double2 *>(D + O3Lay::kAinv + q2 * O3Lay::kAinvRow + 8 * g);
+        const double2 *gv = reinterpret_cast<const double2 *>(g2 + 8 * g);
         double acc[2] = {0.0, 0.0};
-        o3_for<8>([&](auto ii) {
-          constexpr int i = decltype(ii)::value;
-          acc[i & 1] += D[O3Lay::kAinv + (8 * c + i) * 64 + j] * g2[8 * c + i];
-        });
-        part[c * 64 + j] = acc[0] + acc[1];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const double2 x = Ai[i], y = gv[i];
+          acc[0] += x.x * y.x;
+          acc[1] += x.y * y.y;
+        }
+        u += static_cast<T>(o3_sum8(acc[0] + acc[1]));
+        *own = u;
       }
       __syncthreads();
-      {
-        double acc[2] = {0.0, 0.0};
-        o3_for<8>([&](auto ii) { acc[decltype(ii)::value & 1] += part[decltype(ii)::value * 64 + q2]; });
-        u += static_cast<T>(acc[0] + acc[1]);
-        lat[G::own] = u;
-      }
-      __syncthreads();
-#pragma unroll 1
-      for (int cc = 7; cc >= 0; cc--) {
-        if (c == cc) u += (f - sum()) / a[0];
-        if constexpr (TOP && OVF) __syncthreads();
-        if (c == cc) lat[G::own] = u;
-        __syncthreads();
-      }
-      const T y = sum();
+      o3_for<8>([&](auto cc) { phase(IC<7 - decltype(cc)::value>{}, u); });
+      const T y = row();
       const double ud = static_cast<double>(u), fd = static_cast<double>(f);
       double v[4] = {ud * static_cast<double>(y), fd * ud, 0.0, 0.0};
       if (half == 0) {
@@ -284,10 +340,12 @@ struct O3 {
   __device__ __forceinline__ void job_load(O3Row<T> &b) const {
     constexpr int c = job_color(STAGE, I);
     constexpr bool pre = STAGE == 0 && I < 8;
-    const Global<T> ax = o3_opaque(A.ax4);
+    const __amdgpu_buffer_rsrc_t r = o3_rsrc(A.ax4, 27 * O3Geo<4>::n);
+    const int lb = o3_opaque(tid * static_cast<int>(sizeof(T)));
     o3_for<27>([&](auto ss) {
       constexpr int s = decltype(ss)::value;
-      if constexpr (!pre || s == 0 || o3_color(c, s) < c) b.a[s] = (ax + (s * O3Geo<4>::n + c * O3Geo<4>::N8))[tid];
+      if constexpr (!pre || s == 0 || o3_color(c, s) < c)
+        b.a[s] = o3_load<T>(r, lb, s * O3Geo<4>::n + c * O3Geo<4>::N8);
     });
   }
   template <int STAGE, int I, bool OVF>
@@ -302,6 +360,13 @@ struct O3 {
     });
     if constexpr (OVF)
       if ((far >> c) & 1u) acc = o3_ovf<T, 4, pre>(A, acc, static_cast<uint32_t>(c * G::N8 + tid), c, lat0);
+    // the next rows' loads between this row's products: issued in one run, they hold a wavefront up for as long as the
+    // products take
+    o3_for<27>([&](auto) {
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // a load
+      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // two VALU instructions
+    });
+    o3_done(acc);
     return acc;
   }
 
@@ -312,7 +377,6 @@ struct O3 {
     constexpr int NB = kAhead + 1;
     const int corner = o3_place<4>(static_cast<uint32_t>(tid));  // color 0's
     T *lat0 = S + O3Lay::kLat4, *lat = lat0 + corner;
-    T *g3 = S + O3Lay::kG3, *e3 = S + O3Lay::kE3;
     T f[8], q0[8], p0r[sizeof(T) == 4 ? 8 : 1];
     auto p0 = [&](int c) -> T & {  // FP64: in LDS, to save registers
       if constexpr (sizeof(T) == 4) return p0r[c];
@@ -334,7 +398,6 @@ struct O3 {
       T gsum = 0;
       o3_for<16>([&](auto ii) {
         constexpr int i = decltype(ii)::value, c = job_color(0, i);
-        o3_next();
         if constexpr (i + kAhead < 16) job_load<0, i + kAhead>(b[(i + kAhead) % NB]);
         const O3Row<T> &r = b[i % NB];
         const T d = f[c] - job_sum<0, i, OVF>(r, lat, lat0, far);
@@ -345,21 +408,13 @@ struct O3 {
           gsum += d;
         }
       });
-      g3[q_of_m3(static_cast<uint32_t>(tid), 3)] = gsum;
-      __syncthreads();
-      const T r3 = level3<false, false>(g3[tid]);
-      e3[(lane << 3) | wave] = r3;  // by the cell's Morton index, that of its super-cell on level 4
+      const T em = level3<false, false>(gsum);
       o3_for<kAhead>([&](auto ii) { job_load<1, decltype(ii)::value>(b[decltype(ii)::value]); });
-      __syncthreads();
-      {
-        const T em = e3[tid];
-        o3_for<8>([&](auto cc) { lat[G::child(decltype(cc)::value) + G::own] += em; });
-      }
+      o3_for<8>([&](auto cc) { lat[G::child(decltype(cc)::value) + G::own] += em; });
       __syncthreads();
       double v[4] = {0.0, 0.0, 0.0, 0.0};
       o3_for<16>([&](auto ii) {
         constexpr int i = decltype(ii)::value, c = job_color(1, i);
-        o3_next();
         if constexpr (i + kAhead < 16) job_load<1, i + kAhead>(b[(i + kAhead) % NB]);
         const O3Row<T> &r = b[i % NB];
         const T s = job_sum<1, i, OVF>(r, lat, lat0, far);
@@ -408,13 +463,20 @@ __global__ void __launch_bounds__(kO3Threads) k_engine_oct(O3Args<T> A) {
   double ai[8];
 #pragma unroll
   for (int k = 0; k < 8; k++) ai[k] = A.ainv[tid + k * kO3Threads];
-  for (int i = tid; i < O3Lay::units<T>(); i += kO3Threads) S[i] = T(0);  // the lattices' rings are read and never written
+  for (int i = tid; i < O3Lay::units<T>(); i += kO3Threads) S[i] = T(0);  // the lattices' rings are read, never written
 #pragma unroll
-  for (int k = 0; k < 8; k++) D[O3Lay::kAinv + tid + k * kO3Threads] = ai[k];
+  for (int k = 0; k < 8; k++) {
+    const int i = tid + k * kO3Threads;
+    D[O3Lay::kAinv + (i >> 6) * O3Lay::kAinvRow + (i & 63)] = ai[k];
+  }
   __syncthreads();
-  const O3<T> E{A, D, S, tid, __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63};
-  if constexpr (KT == 4) E.template level4<OVF>();
-  else A.e[tid] = E.template level3<true, OVF>(A.g[tid]);
+  const O3<T> E{A, D, S, tid};
+  if constexpr (KT == 4) {
+    E.template level4<OVF>();
+  } else {
+    const int q = (tid & 7) * O3Geo<3>::N8 + (tid >> 3);
+    A.e[q] = E.template level3<true, OVF>(A.g[q]);
+  }
 }
 
 template <class T>
