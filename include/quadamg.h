@@ -57,17 +57,17 @@ typedef struct {
                             with LDS-resident operators, specialised at compile time to the level shape where the
                             levels allow it, and each larger quadtree level without same-color or overflow couplings
                             runs its presmoothing sweep with the restriction, and its first post-smoothing sweep, as
-                            one launch each (16 x 16 super-cell tiles; the same values as one launch per color
-                            phase); 2: the same, with the workgroup always through its generic step interpreter;
+                            one launch each (tiles of 8 x 8 or 16 x 16 super-cells; the same values as one launch
+                            per color phase); 2: the same, with the workgroup always through its generic step interpreter;
                             0: one kernel launch per step on every level */
-    int32_t batch;       /* 1 (default): amg_solve_batch runs this system, when it has at most 65,536 unknowns, as
-                            one workgroup of a whole-solve launch shared with the batch's other small systems;
-                            0: it runs as its own amg_solve */
+    int32_t batch;       /* 1 (default): amg_solve_batch runs this system, when it has at most 65,536 unknowns,
+                            together with the batch's other small systems, in shared launches; 0: it runs as its own
+                            amg_solve */
     int32_t smoother;    /* fine-level block smoother of Section 4.5: 0 (default) one forward (R_k) / backward
                             (R_k^t) substitution over each cell's unknowns per color phase; 1 the exact solve of
                             each cell's diagonal block (a dense Cholesky factor per cell made at setup) for cells of
-                            at most 32 unknowns, the substitution for larger ones. With 1 the system never takes the
-                            whole-solve workgroup of amg_solve_batch. */
+                            at most 32 unknowns, the substitution for larger ones. With 1 amg_solve_batch runs the
+                            system as its own amg_solve. */
     const double *box;   /* host {a1, b1, a2, b2}: the auxiliary box of eq. (5); NULL = bounding box of coords
                             (eq. 6). Points outside a given box are rejected. */
     void *stream;        /* hipStream_t used for every launch; NULL = default stream */
@@ -157,21 +157,24 @@ amg_status amg_set_stream(amg_hierarchy *h, void *stream);
 /* Solve `count` independent systems of one device concurrently (the serving form). h, b, x, tol are host arrays of
  * `count` entries; b[i] and x[i] are device vectors of hierarchy i's size, ready once that hierarchy's stream has
  * drained (the call synchronises each stream first); info is a host array of `count` entries or NULL. The
- * hierarchies must be distinct. Small systems (options.batch, at most 65,536 unknowns) are solved together in one
- * launch, on the stream of the first of them, with one persistent workgroup per system: outer flexible CG,
- * smoother, K-cycle and convergence test all on the device. Every other system is driven by its own host thread on
- * its hierarchy's stream, overlapping with the launch (systems whose hierarchies share a stream run in turn). The
- * call returns when every system is done. A system's result does not depend on the rest of the batch (bit-identical alone and in any mix); the
- * whole-solve workgroup and amg_solve differ only by rounding (different reduction trees). Returns the first
+ * hierarchies must be distinct. Small systems (options.batch, at most 65,536 unknowns) are solved together on the
+ * stream of the first of them: above 2,500 unknowns (with the small-level engine's specialised form, see
+ * amg_engine_info) in step, one launch per step of the iteration for all systems that are at it, each system's kernels
+ * those of amg_solve; the others as one persistent workgroup per system in one launch, outer flexible CG, smoother,
+ * K-cycle and convergence test all on the device. Every other system is driven by its own host thread on its
+ * hierarchy's stream, overlapping with the launches (systems whose hierarchies share a stream run in turn). The call
+ * returns when every system is done. A system's result does not depend on the rest of the batch (bit-identical alone
+ * and in any mix); a system in step has amg_solve's result bit for bit, a whole-solve workgroup's differs from it only
+ * by rounding (different reduction trees). Returns the first
  * non-OK status; every system is attempted. */
 amg_status amg_solve_batch(amg_hierarchy *const *h, const double *const *b, double *const *x, const double *tol,
                            int32_t count, amg_info *info);
 
 /* amg_solve_batch for callers that cannot allocate device memory (code under HIP graph capture, serving loops that
- * forbid allocation): the same whole-solve launches and results, with the per-call system descriptors and info words
+ * forbid allocation): the same launches and results, with the per-call system descriptors and info words
  * held in a device array of the library's own (about 400 KB per device, kept until the process ends) instead of
- * memory allocated per call. No hipMalloc, hipFree or other allocating call is made. Every system must take the
- * whole-solve route (options.batch = 1, the default fine smoother, at most 65,536 unknowns); count must not exceed
+ * memory allocated per call. No hipMalloc, hipFree or other allocating call is made. Every system must be one
+ * that amg_solve_batch solves together with others (options.batch = 1, the default fine smoother, at most 65,536 unknowns); count must not exceed
  * 256. Errors, before any device work: AMG_ERR_INVALID for those conditions or the arguments amg_solve_batch
  * rejects. All calls on one device share the array: calls that overlap in time on one device race and must be
  * serialised by the caller. */

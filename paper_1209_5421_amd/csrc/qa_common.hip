@@ -426,6 +426,7 @@ void amg_free(amg_hierarchy *h) {
   (void)hipSetDevice(h->device);
   (void)hipStreamSynchronize(h->stream);
   qa::release(h);
+  qa::free_batch_lists(h);
   delete h;
 }
 

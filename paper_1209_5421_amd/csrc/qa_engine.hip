@@ -50,6 +50,7 @@
 #include <vector>
 
 #include "qa_internal.hpp"
+#include "qa_launch.hpp"
 #include "qa_wave.hpp"
 
 namespace qa {
@@ -409,7 +410,7 @@ __device__ __forceinline__ void fe_recip(FeRows<T, TR> &R) {
 }
 
 template <class T, int KT>
-__global__ void __launch_bounds__(FeLayout<KT>::threads) k_engine_fast(FeArgs<T> A) {
+__device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
   using Lay = FeLayout<KT>;
   constexpr int NT = Lay::threads, TR = Lay::TR;
   // wavefronts of the levels: the top level from wavefront 0; k = 5 below it from 4; k = 4 below those in one; the
@@ -617,6 +618,10 @@ __global__ void __launch_bounds__(FeLayout<KT>::threads) k_engine_fast(FeArgs<T>
     }
   }
 }
+template <class T, int KT>
+__global__ void __launch_bounds__(FeLayout<KT>::threads) k_engine_fast(FeArgs<T> A) {
+  k_engine_fast_body<T, KT>(A);
+}
 
 // ---- host side ----
 
@@ -687,12 +692,12 @@ void fe_launch(amg_hierarchy *h, int pi) {
   const size_t lds = FeLayout<KT>::template bytes<T>();
   Timing &t = h->timing;
   const int kind = pi ? KK_ENGINE32 : KK_ENGINE64;
-  if (t.kind == kind && t.used + 2 <= t.ev.size()) {  // dispatch-stamped start / stop
+  if (!h->recording && t.kind == kind && t.used + 2 <= t.ev.size()) {  // dispatch-stamped start / stop
     hipExtLaunchKernelGGL(k_engine_fast<T, KT>, dim3(1), dim3(FeLayout<KT>::threads), lds, h->stream, t.ev[t.used],
                           t.ev[t.used + 1], 0, A);
     t.used += 2;
   } else {
-    k_engine_fast<T, KT><<<1, FeLayout<KT>::threads, lds, h->stream>>>(A);
+    QA_RUN(h, FeLayout<KT>::threads, 1, lds, k_engine_fast, QA_T(T, KT), A);
   }
 }
 

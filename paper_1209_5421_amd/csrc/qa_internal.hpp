@@ -252,6 +252,9 @@ struct Chunk {                  // a device allocation that several arrays are c
   size_t size = 0, used = 0;
 };
 
+struct LaunchList;
+struct BatchLists;
+
 }  // namespace qa
 
 struct amg_hierarchy {
@@ -307,6 +310,9 @@ struct amg_hierarchy {
   int wg_lds_top[2] = {-1, -1};
   int wg_ainv_lds[2] = {0, 0};
   size_t wg_lds[2] = {0, 0};
+  bool in_step[2] = {false, false};        // amg_solve_batch runs it in step with others (per precision; plan_wg)
+  qa::LaunchList *recording = nullptr;      // launches go to this list instead of the stream
+  qa::BatchLists *batch_lists = nullptr;    // the recorded pieces of its outer iteration, kept for their storage
   // all-directions outer iteration (outer_mmax < 0): kept directions p_j, q_j = A p_j, their device address table,
   // the inner products (z, q_j) of the current step and (p_j, q_j)
   std::vector<double *> dir_p, dir_q;
@@ -355,6 +361,7 @@ amg_status alloc_workspaces(amg_hierarchy *h);
 amg_status build_mhat(amg_hierarchy *h);
 amg_status plan_engine(amg_hierarchy *h);
 amg_status plan_wg(amg_hierarchy *h);
+void free_batch_lists(amg_hierarchy *h);
 amg_status plan_engine_fast(amg_hierarchy *h);   // qa_engine.hip
 void launch_engine_fast(amg_hierarchy *h, int precision);
 amg_status plan_engine_oct(amg_hierarchy *h);    // qa_engine3.hip

@@ -25,6 +25,7 @@
 #include <hip/hip_ext.h>
 
 #include "qa_internal.hpp"
+#include "qa_launch.hpp"
 #include "qa_wave.hpp"
 
 namespace qa {
@@ -43,6 +44,7 @@ struct Red {
   double *sc;
   int epi;
   int slot;
+  unsigned nb;  // workgroups of the launch
 };
 
 // sum over the workgroup (fixed order); valid in thread 0
@@ -127,7 +129,7 @@ template <int ND>
 __device__ inline void reduce_finish(double (&v)[ND], const Red &R) {
   block_sum<ND>(v);
   if (threadIdx.x == 0) {
-    if (gridDim.x == 1) {
+    if (R.nb == 1) {
       epilogue(v, R);
     } else {
 #pragma unroll
@@ -137,15 +139,19 @@ __device__ inline void reduce_finish(double (&v)[ND], const Red &R) {
 }
 
 template <int ND>
-__global__ void __launch_bounds__(kBlock) k_finish(unsigned nb, Red R) {
+__device__ __forceinline__ void k_finish_body(Red R) {
   double acc[ND];
 #pragma unroll
   for (int j = 0; j < ND; j++) acc[j] = 0.0;
-  for (unsigned b = threadIdx.x; b < nb; b += kBlock)
+  for (unsigned b = threadIdx.x; b < R.nb; b += kBlock)
 #pragma unroll
     for (int j = 0; j < ND; j++) acc[j] += R.partials[static_cast<size_t>(b) * ND + j];
   block_sum<ND>(acc);
   if (threadIdx.x == 0) epilogue(acc, R);
+}
+template <int ND>
+__global__ void __launch_bounds__(kBlock) k_finish(Red R) {
+  k_finish_body<ND>(R);
 }
 
 // r = g - a0 q0 of the first inner update of Algorithm 2.1 (one expression, so the separate and the folded forms
@@ -331,16 +337,26 @@ __device__ inline void fine_resid_body(const SellView<T> &S, const SliceSched &Z
 // residual of one color's rows, for a smoother phase whose color has couplings between its own cells (the fused
 // phase below then reads it from d)
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_fine_resid(SellView<T> S, SliceSched Z, const T *__restrict__ f,
-                                                        const T *__restrict__ x, T *__restrict__ d) {
+__device__ __forceinline__ void k_fine_resid_body(const SellView<T> &S, const SliceSched &Z, const T *__restrict__ f,
+                                                  const T *__restrict__ x, T *__restrict__ d) {
   fine_resid_body(S, Z, f, x, d);
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_fine_resid(SellView<T> S, SliceSched Z, const T *__restrict__ f,
+                                                       const T *__restrict__ x, T *__restrict__ d) {
+  k_fine_resid_body<T>(S, Z, f, x, d);
 }
 
 // residual of all rows (input of the restriction); a kernel of its own so its launches are timed separately
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_fine_resid_full(SellView<T> S, SliceSched Z, const T *__restrict__ f,
-                                                             const T *__restrict__ x, T *__restrict__ d) {
+__device__ __forceinline__ void k_fine_resid_full_body(const SellView<T> &S, const SliceSched &Z, const T *__restrict__ f,
+                                                       const T *__restrict__ x, T *__restrict__ d) {
   fine_resid_body(S, Z, f, x, d);
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_fine_resid_full(SellView<T> S, SliceSched Z, const T *__restrict__ f,
+                                                            const T *__restrict__ x, T *__restrict__ d) {
+  k_fine_resid_full_body<T>(S, Z, f, x, d);
 }
 
 // y = A x over the scheduled slices (level hook)
@@ -360,7 +376,7 @@ __global__ void __launch_bounds__(kBlock) k_fine_apply(SellView<T> S, SliceSched
 
 // L L^t v = v in place, L packed lower triangle (row i holds L_i0 .. L_ii), v with the given element stride
 template <class T>
-__device__ inline void block_solve(const T *Lf, int m, T *v, int stride) {
+__device__ __forceinline__ void block_solve(const T *Lf, int m, T *v, int stride) {
   for (int i = 0; i < m; i++) {
     const T *Li = Lf + i * (i + 1) / 2;
     T s = v[i * stride];
@@ -414,7 +430,7 @@ __device__ __forceinline__ void block_solve_reg(const T *Lf, int m, T *v) {
 // more registers than a thread holds without spilling)
 constexpr int kRegCell = 16;
 template <class T>
-__device__ inline void block_solve_small(const T *Lf, int m, T *v) {
+__device__ __forceinline__ void block_solve_small(const T *Lf, int m, T *v) {
   static_assert(kRegCell == 16, "register classes 4, 8, 16");
   if (m <= 4) block_solve_reg<T, 4>(Lf, m, v);
   else if (m <= 8) block_solve_reg<T, 8>(Lf, m, v);
@@ -438,7 +454,7 @@ __device__ __forceinline__ T wave_lane_value(T v, int k) {  // v of lane k (k un
 // (columns ascending forward, descending backward) and the results are identical; the dependent chain is 2 m
 // broadcast steps instead of m^2 dependent memory operations of one thread.
 template <class T>
-__device__ inline void block_solve_wave(const T *Lf, int m, T *v, int lane) {
+__device__ __forceinline__ void block_solve_wave(const T *Lf, int m, T *v, int lane) {
   static_assert(kBlockMax <= 64, "one row per lane");
   T y = lane < m ? v[lane] : T(0);
 #pragma unroll 2
@@ -530,7 +546,7 @@ struct FuseArgs {
 };
 
 template <class T, int SM, bool FWD, bool GIVEN>
-__global__ void __launch_bounds__(kBlock) k_fine_gs(SellView<T> S, FuseArgs<T> A) {
+__device__ __forceinline__ void k_fine_gs_body(const SellView<T> &S, const FuseArgs<T> &A) {
   constexpr int CMAX = SM ? kBlockMax : kBigCell;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ T s_r[kFuseRows];                   // residual (SM = 1: then the delta, in place)
@@ -731,6 +747,10 @@ __global__ void __launch_bounds__(kBlock) k_fine_gs(SellView<T> S, FuseArgs<T> A
     else if (A.big && !GIVEN) A.d[r0 + i] = s_r[i];
   }
 }
+template <class T, int SM, bool FWD, bool GIVEN>
+__global__ void __launch_bounds__(kBlock) k_fine_gs(SellView<T> S, FuseArgs<T> A) {
+  k_fine_gs_body<T, SM, FWD, GIVEN>(S, A);
+}
 
 // The same substitution for the big cells of one color, one workgroup per cell: rows are taken level by level of the
 // cell's dependency schedule (the rows of a level use only values of earlier levels), with a barrier between levels;
@@ -747,15 +767,14 @@ constexpr int kSubstLevels = 256;
 constexpr int kSubstDynBytes = 48 * 1024;
 
 template <class T, bool FWD>
-__global__ void __launch_bounds__(kSubstLanes) k_fine_subst_big(const int32_t *__restrict__ crow,
-                                                            const int32_t *__restrict__ icp,
-                                                            const int32_t *__restrict__ icc,
-                                                            const T *__restrict__ icv, const T *__restrict__ diag,
-                                                            const T *src, T *d, T *__restrict__ x,
-                                                            const int32_t *__restrict__ cells, int64_t b_begin,
-                                                            const int32_t *__restrict__ lofs,
-                                                            const int32_t *__restrict__ lptr,
-                                                            const int32_t *__restrict__ sched, int lds_rows) {
+__device__ __forceinline__ void k_fine_subst_big_body(const int32_t *__restrict__ crow,
+                                                      const int32_t *__restrict__ icp,
+                                                      const int32_t *__restrict__ icc, const T *__restrict__ icv,
+                                                      const T *__restrict__ diag, const T *src, T *d,
+                                                      T *__restrict__ x, const int32_t *__restrict__ cells,
+                                                      int64_t b_begin, const int32_t *__restrict__ lofs,
+                                                      const int32_t *__restrict__ lptr,
+                                                      const int32_t *__restrict__ sched, int lds_rows) {
   constexpr int R = kSubstRegRows, KM = kSubstRegCouplings;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t s_lp[kSubstLevels + 1];
@@ -863,12 +882,24 @@ __global__ void __launch_bounds__(kSubstLanes) k_fine_subst_big(const int32_t *_
     x[p] += v;
   }
 }
+template <class T, bool FWD>
+__global__ void __launch_bounds__(kSubstLanes) k_fine_subst_big(const int32_t *__restrict__ crow,
+                                                                const int32_t *__restrict__ icp,
+                                                                const int32_t *__restrict__ icc,
+                                                                const T *__restrict__ icv, const T *__restrict__ diag,
+                                                                const T *src, T *d, T *__restrict__ x,
+                                                                const int32_t *__restrict__ cells, int64_t b_begin,
+                                                                const int32_t *__restrict__ lofs,
+                                                                const int32_t *__restrict__ lptr,
+                                                                const int32_t *__restrict__ sched, int lds_rows) {
+  k_fine_subst_big_body<T, FWD>(crow, icp, icc, icv, diag, src, d, x, cells, b_begin, lofs, lptr, sched, lds_rows);
+}
 
 // g[q] = sum of d over the rows of level-L cell q (rows ascending); cells of more than `big` rows are left to
 // k_fine_restrict_big
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_fine_restrict(int64_t nL, const int32_t *__restrict__ crow,
-                                                           const T *__restrict__ d, T *__restrict__ g, int big) {
+__device__ __forceinline__ void k_fine_restrict_body(int64_t nL, const int32_t *__restrict__ crow,
+                                                     const T *__restrict__ d, T *__restrict__ g, int big) {
   const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= nL) return;
   const int32_t a = crow[q], b = crow[q + 1];
@@ -877,6 +908,11 @@ __global__ void __launch_bounds__(kBlock) k_fine_restrict(int64_t nL, const int3
   for (int32_t p = a; p < b; p++) acc += d[p];
   g[q] = acc;
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_fine_restrict(int64_t nL, const int32_t *__restrict__ crow,
+                                                          const T *__restrict__ d, T *__restrict__ g, int big) {
+  k_fine_restrict_body<T>(nL, crow, d, g, big);
+}
 
 // the same sum for the listed cells, one wavefront per cell: the wavefront stages the cell's d in LDS with coalesced
 // loads, 1,024 rows at a time, and lane 0 adds them in ascending order (the thread-per-cell order), so a cell of a
@@ -884,9 +920,9 @@ __global__ void __launch_bounds__(kBlock) k_fine_restrict(int64_t nL, const int3
 constexpr int kRestrictChunk = 1024;
 
 template <class T>
-__global__ void __launch_bounds__(64) k_fine_restrict_big(const int32_t *__restrict__ cells,
-                                                           const int32_t *__restrict__ crow,
-                                                           const T *__restrict__ d, T *__restrict__ g) {
+__device__ __forceinline__ void k_fine_restrict_big_body(const int32_t *__restrict__ cells,
+                                                         const int32_t *__restrict__ crow, const T *__restrict__ d,
+                                                         T *__restrict__ g) {
   __shared__ T s_d[kRestrictChunk];
   const int32_t q = cells[blockIdx.x];
   const int32_t a = crow[q], b = crow[q + 1];
@@ -911,18 +947,30 @@ __global__ void __launch_bounds__(64) k_fine_restrict_big(const int32_t *__restr
   }
   if (threadIdx.x == 0) g[q] = acc;
 }
+template <class T>
+__global__ void __launch_bounds__(64) k_fine_restrict_big(const int32_t *__restrict__ cells,
+                                                          const int32_t *__restrict__ crow, const T *__restrict__ d,
+                                                          T *__restrict__ g) {
+  k_fine_restrict_big_body<T>(cells, crow, d, g);
+}
 
 // u += P e on the fine level; snap (when not null) gets a copy of the new u
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_fine_prolong(int64_t n, const int32_t *__restrict__ agg_q,
-                                                          const T *__restrict__ e, Pending<T> pend,
-                                                          T *__restrict__ u, T *__restrict__ snap) {
+__device__ __forceinline__ void k_fine_prolong_body(int64_t n, const int32_t *__restrict__ agg_q,
+                                                    const T *__restrict__ e, Pending<T> pend, T *__restrict__ u,
+                                                    T *__restrict__ snap) {
   const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (p >= n) return;
   const T em = pend.apply(e, static_cast<uint32_t>(agg_q[p]));
   const T v = u[p] + em;
   u[p] = v;
   if (snap) snap[p] = v;
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_fine_prolong(int64_t n, const int32_t *__restrict__ agg_q,
+                                                         const T *__restrict__ e, Pending<T> pend, T *__restrict__ u,
+                                                         T *__restrict__ snap) {
+  k_fine_prolong_body<T>(n, agg_q, e, pend, u, snap);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -984,8 +1032,7 @@ __device__ inline void cgs_first2_row(const QView<T> &Q, int64_t q, FV fv, T *__
 }
 
 template <class T, bool UPD>
-__global__ void __launch_bounds__(kBlock) k_cgs_first2(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
-                                                        Upd1<T> U) {
+__device__ __forceinline__ void k_cgs_first2_body(const QView<T> &Q, const T *__restrict__ f, T *__restrict__ x, Upd1<T> U) {
   const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= Q.n) return;
   if constexpr (UPD) {
@@ -996,14 +1043,18 @@ __global__ void __launch_bounds__(kBlock) k_cgs_first2(QView<T> Q, const T *__re
     cgs_first2_row<T>(Q, q, [f](uint32_t i) { return f[i]; }, x);
   }
 }
+template <class T, bool UPD>
+__global__ void __launch_bounds__(kBlock) k_cgs_first2(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
+                                                       Upd1<T> U) {
+  k_cgs_first2_body<T, UPD>(Q, f, x, U);
+}
 
 // one color phase of the pointwise 4-color Gauss-Seidel: rows q = c n/4 + j, Morton m = 4 j + c.
 // delta == nullptr: update in place (valid when no coupling joins two cells of color c); else write delta only.
 // ZERO: the phase of a sweep from zero, where the color's rows hold zero before it: the values of coupled rows of the
 // color are not read, so the update is in place whatever the couplings.
 template <class T, bool ZERO>
-__global__ void __launch_bounds__(kBlock) k_cgs(QView<T> Q, const T *__restrict__ f, T *x, T *__restrict__ delta,
-                                                int c) {
+__device__ __forceinline__ void k_cgs_body(const QView<T> &Q, const T *__restrict__ f, T *x, T *__restrict__ delta, int c) {
   const int64_t n4 = Q.n >> 2;
   const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (j >= n4) return;
@@ -1018,12 +1069,17 @@ __global__ void __launch_bounds__(kBlock) k_cgs(QView<T> Q, const T *__restrict_
     else x[q] += dl;
   }
 }
+template <class T, bool ZERO>
+__global__ void __launch_bounds__(kBlock) k_cgs(QView<T> Q, const T *__restrict__ f, T *x, T *__restrict__ delta,
+                                                int c) {
+  k_cgs_body<T, ZERO>(Q, f, x, delta, c);
+}
 
 // the last color phase (c = 0) of the second B^ with the inner product (p1, q0) of Algorithm 2.1 for beta: thread j
 // relaxes row j and adds the products of rows j + c n/4 of all four colors (colors 1 to 3 are final already)
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_cgs0_beta(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
-                                                      const T *__restrict__ q0, Red R) {
+__device__ __forceinline__ void k_cgs0_beta_body(const QView<T> &Q, const T *__restrict__ f, T *__restrict__ x,
+                                                 const T *__restrict__ q0, Red R) {
   const int64_t n4 = Q.n >> 2;
   const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   double v[1] = {0.0};
@@ -1037,6 +1093,11 @@ __global__ void __launch_bounds__(kBlock) k_cgs0_beta(QView<T> Q, const T *__res
   }
   reduce_finish<1>(v, R);
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_cgs0_beta(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
+                                                      const T *__restrict__ q0, Red R) {
+  k_cgs0_beta_body<T>(Q, f, x, q0, R);
+}
 
 // A color phase of the first post-smoothing sweep with the prolongation u = x + P e_c folded in (x: the presmoothed
 // values): the backward sweep has only passed colors > C, so those are read from u and the others as x + (P e_c) formed
@@ -1044,9 +1105,9 @@ __global__ void __launch_bounds__(kBlock) k_cgs0_beta(QView<T> Q, const T *__res
 // of its own rows to u. As x is not written, coupled rows of one color all see the values from before the phase. With
 // BETA (C = 0, the last phase of the second B^) it also forms (p1, q0) for beta over the rows j + c n/4 of the colors.
 template <class T, int C, bool BETA>
-__global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__restrict__ f, const T *__restrict__ x, T *u,
-                                                     const T *__restrict__ ec, Pending<T> pend,
-                                                     const T *__restrict__ q0, Red R) {
+__device__ __forceinline__ void k_cgs_post_body(const QView<T> &Q, const T *__restrict__ f, const T *__restrict__ x, T *u,
+                                                const T *__restrict__ ec, Pending<T> pend, const T *__restrict__ q0,
+                                                Red R) {
   const int64_t n4 = Q.n >> 2;
   const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int sh = 2 * Q.k - 2;
@@ -1080,6 +1141,12 @@ __global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__rest
     }
   }
   if constexpr (BETA) reduce_finish<1>(v, R);
+}
+template <class T, int C, bool BETA>
+__global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__restrict__ f, const T *__restrict__ x,
+                                                     T *u, const T *__restrict__ ec, Pending<T> pend,
+                                                     const T *__restrict__ q0, Red R) {
+  k_cgs_post_body<T, C, BETA>(Q, f, x, u, ec, pend, q0, R);
 }
 
 // Tiles of the per-step path. Workgroup b owns a Morton-aligned square of TS x TS super-cells, j in
@@ -1233,9 +1300,9 @@ __device__ __forceinline__ void fold_load(const double *__restrict__ part, int n
 // This replaces a pass over the level per inner step (k_cspmv_dot, k_cspmv_dir) and two reductions. (In the first inner
 // step u is p0 itself, which is not read then.)
 template <class T, int SP, int TS>
-__global__ void __launch_bounds__((Tile<TS, SP ? 5 : 4>::NT))
-    k_cgs_post4(QView<T> Q, const T *__restrict__ f, const T *__restrict__ x, T *u, const T *__restrict__ ec,
-                Pending<T> pend, T *q0, const T *p0, double *__restrict__ part) {
+__device__ __forceinline__ void k_cgs_post4_body(const QView<T> &Q, const T *__restrict__ f, const T *__restrict__ x, T *u,
+                                                 const T *__restrict__ ec, Pending<T> pend, T *q0, const T *p0,
+                                                 double *__restrict__ part) {
   constexpr int RS = SP ? 5 : 4, G = RS - 4;  // G: rings of the last phase
   using TL = Tile<TS, RS>;
   constexpr int NT = TL::NT, W = TL::W;
@@ -1364,6 +1431,14 @@ __global__ void __launch_bounds__((Tile<TS, SP ? 5 : 4>::NT))
     u[c * n4 + j0 + static_cast<uint32_t>(w)] = sv[c][ly * W + lx];
   }
 }
+template <class T, int SP, int TS>
+__global__ void __launch_bounds__((Tile<TS, SP ? 5 : 4>::NT)) k_cgs_post4(QView<T> Q, const T *__restrict__ f,
+                                                                          const T *__restrict__ x, T *u,
+                                                                          const T *__restrict__ ec, Pending<T> pend,
+                                                                          T *q0, const T *p0,
+                                                                          double *__restrict__ part) {
+  k_cgs_post4_body<T, SP, TS>(Q, f, x, u, ec, pend, q0, p0, part);
+}
 
 // The whole presmoothing sweep from zero and the restriction (k_cgs_first2, the color phases 2 and 3, k_cres_restrict)
 // of a level without same-color couplings or overflow entries, in one launch: color 0 = f / diag staged over the
@@ -1372,8 +1447,8 @@ __global__ void __launch_bounds__((Tile<TS, SP ? 5 : 4>::NT))
 // side is the pending first inner update's r, formed on the fly, and the update's e and r are stored for the square;
 // alpha0 comes from the scalars or, where the update names partial sums, from those (workgroup 0 stores the scalars).
 template <class T, bool UPD, int TS>
-__global__ void __launch_bounds__((Tile<TS, 4>::NT))
-    k_cgs_pre4(QView<T> Q, const T *__restrict__ f, T *__restrict__ x, Upd1<T> U, T *__restrict__ gc) {
+__device__ __forceinline__ void k_cgs_pre4_body(const QView<T> &Q, const T *__restrict__ f, T *__restrict__ x, Upd1<T> U,
+                                                T *__restrict__ gc) {
   constexpr int RS = 4;
   using TL = Tile<TS, RS>;
   constexpr int NT = TL::NT, W = TL::W;
@@ -1498,19 +1573,29 @@ __global__ void __launch_bounds__((Tile<TS, 4>::NT))
     x[c * n4 + j0 + static_cast<uint32_t>(w)] = sv[c][ly * W + lx];
   }
 }
+template <class T, bool UPD, int TS>
+__global__ void __launch_bounds__((Tile<TS, 4>::NT)) k_cgs_pre4(QView<T> Q, const T *__restrict__ f,
+                                                                T *__restrict__ x, Upd1<T> U, T *__restrict__ gc) {
+  k_cgs_pre4_body<T, UPD, TS>(Q, f, x, U, gc);
+}
 
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_add_range(int64_t begin, int64_t count, const T *__restrict__ delta,
-                                                       T *__restrict__ x) {
+__device__ __forceinline__ void k_add_range_body(int64_t begin, int64_t count, const T *__restrict__ delta,
+                                                 T *__restrict__ x) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < count) x[begin + i] += delta[begin + i];
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_add_range(int64_t begin, int64_t count, const T *__restrict__ delta,
+                                                      T *__restrict__ x) {
+  k_add_range_body<T>(begin, count, delta, x);
 }
 
 // residual of the four children of coarse cell M, summed in the order 0, 1, 3, 2 (Section 4.3's explicit
 // restriction), written to the parent's color-major slot
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_cres_restrict(QView<T> Q, const T *__restrict__ f,
-                                                           const T *__restrict__ u, T *__restrict__ g) {
+__device__ __forceinline__ void k_cres_restrict_body(const QView<T> &Q, const T *__restrict__ f, const T *__restrict__ u,
+                                                     T *__restrict__ g) {
   const int64_t n4 = Q.n >> 2;
   const int64_t M = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (M >= n4) return;
@@ -1524,14 +1609,19 @@ __global__ void __launch_bounds__(kBlock) k_cres_restrict(QView<T> Q, const T *_
   }
   g[q_of_m(static_cast<uint32_t>(M), Q.k - 1)] = acc;
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_cres_restrict(QView<T> Q, const T *__restrict__ f,
+                                                          const T *__restrict__ u, T *__restrict__ g) {
+  k_cres_restrict_body<T>(Q, f, u, g);
+}
 
 // y = A x on a quadtree level with two inner products (x, y) and (w, x); grid-stride, fixed grid
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_cspmv_dot(QView<T> Q, const T *__restrict__ x, T *__restrict__ y,
-                                                       const T *__restrict__ w, Red R) {
+__device__ __forceinline__ void k_cspmv_dot_body(const QView<T> &Q, const T *__restrict__ x, T *__restrict__ y,
+                                                 const T *__restrict__ w, Red R) {
   double v[2] = {0.0, 0.0};
   for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < Q.n;
-       q += static_cast<int64_t>(gridDim.x) * kBlock) {
+       q += static_cast<int64_t>(R.nb) * kBlock) {
     const T yq = row_apply(Q, static_cast<uint32_t>(q), row_color(static_cast<uint32_t>(q), 2 * Q.k - 2), x);
     y[q] = yq;
     const double xq = static_cast<double>(x[q]);
@@ -1540,15 +1630,20 @@ __global__ void __launch_bounds__(kBlock) k_cspmv_dot(QView<T> Q, const T *__res
   }
   reduce_finish<2>(v, R);
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_cspmv_dot(QView<T> Q, const T *__restrict__ x, T *__restrict__ y,
+                                                      const T *__restrict__ w, Red R) {
+  k_cspmv_dot_body<T>(Q, x, y, w, R);
+}
 
 // the second inner step of Algorithm 2.1 from p1 alone: A p1 (not stored) with (p1, A p1), (r, p1), (p1, q0) and
 // (r, p0), from which pair_scalars has beta and alpha1: one reduction instead of one for beta and one for alpha1
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_cspmv_pair(QView<T> Q, const T *__restrict__ p1, const T *__restrict__ r,
-                                                        const T *__restrict__ q0, const T *__restrict__ p0, Red R) {
+__device__ __forceinline__ void k_cspmv_pair_body(const QView<T> &Q, const T *__restrict__ p1, const T *__restrict__ r,
+                                                  const T *__restrict__ q0, const T *__restrict__ p0, Red R) {
   double v[4] = {0.0, 0.0, 0.0, 0.0};
   for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < Q.n;
-       q += static_cast<int64_t>(gridDim.x) * kBlock) {
+       q += static_cast<int64_t>(R.nb) * kBlock) {
     const T yq = row_apply(Q, static_cast<uint32_t>(q), row_color(static_cast<uint32_t>(q), 2 * Q.k - 2), p1);
     const double u = static_cast<double>(p1[q]), f = static_cast<double>(r[q]);
     v[0] += u * static_cast<double>(yq);
@@ -1558,18 +1653,22 @@ __global__ void __launch_bounds__(kBlock) k_cspmv_pair(QView<T> Q, const T *__re
   }
   reduce_finish<4>(v, R);
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_cspmv_pair(QView<T> Q, const T *__restrict__ p1, const T *__restrict__ r,
+                                                       const T *__restrict__ q0, const T *__restrict__ p0, Red R) {
+  k_cspmv_pair_body<T>(Q, p1, r, q0, p0, R);
+}
 
 // the second inner step of Algorithm 2.1: A d with the direction d = p1 + beta p0 formed on the fly (never stored),
 // inner products (d, A d) and (r, d)
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_cspmv_dir(QView<T> Q, const double *__restrict__ sc,
-                                                       const T *__restrict__ p1, const T *__restrict__ p0,
-                                                       const T *__restrict__ r, Red R) {
+__device__ __forceinline__ void k_cspmv_dir_body(const QView<T> &Q, const double *__restrict__ sc, const T *__restrict__ p1,
+                                                 const T *__restrict__ p0, const T *__restrict__ r, Red R) {
   const T beta = static_cast<T>(sc[S_BETA]);
   auto dir = [p1, p0, beta](uint32_t i) { return p1[i] + beta * p0[i]; };
   double v[2] = {0.0, 0.0};
   for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < Q.n;
-       q += static_cast<int64_t>(gridDim.x) * kBlock) {
+       q += static_cast<int64_t>(R.nb) * kBlock) {
     const uint32_t qu = static_cast<uint32_t>(q);
     const T yq = row_apply_f<T>(Q, qu, row_color(qu, 2 * Q.k - 2), dir);
     const double dq = static_cast<double>(dir(qu));
@@ -1577,6 +1676,12 @@ __global__ void __launch_bounds__(kBlock) k_cspmv_dir(QView<T> Q, const double *
     v[1] += static_cast<double>(r[q]) * dq;
   }
   reduce_finish<2>(v, R);
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_cspmv_dir(QView<T> Q, const double *__restrict__ sc,
+                                                      const T *__restrict__ p1, const T *__restrict__ p0,
+                                                      const T *__restrict__ r, Red R) {
+  k_cspmv_dir_body<T>(Q, sc, p1, p0, r, R);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1811,7 +1916,7 @@ __global__ void __launch_bounds__(kBlock) k_cspmv_dot3(QView<T> Q, const T *__re
                                                        const T *__restrict__ w, Red R) {
   double v[2] = {0.0, 0.0};
   for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < Q.n;
-       q += static_cast<int64_t>(gridDim.x) * kBlock) {
+       q += static_cast<int64_t>(R.nb) * kBlock) {
     const T yq = row_apply3(Q, static_cast<uint32_t>(q), x);
     y[q] = yq;
     const double xq = static_cast<double>(x[q]);
@@ -1830,7 +1935,7 @@ __global__ void __launch_bounds__(kBlock) k_cspmv_dir3(QView<T> Q, const double 
   auto dir = [p1, p0, beta](uint32_t i) { return p1[i] + beta * p0[i]; };
   double v[2] = {0.0, 0.0};
   for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < Q.n;
-       q += static_cast<int64_t>(gridDim.x) * kBlock) {
+       q += static_cast<int64_t>(R.nb) * kBlock) {
     const uint32_t qu = static_cast<uint32_t>(q);
     const T yq = row_apply3_f<T>(Q, qu, dir);
     const double dq = static_cast<double>(dir(qu));
@@ -1851,45 +1956,65 @@ __global__ void __launch_bounds__(kBlock) k_capply3(QView<T> Q, const T *__restr
 // vector kernels of Algorithm 2.1 (n = 2); scalars are read from device memory
 
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_update1(int64_t n, const double *__restrict__ sc,
-                                                     const T *__restrict__ p0, const T *__restrict__ q0,
-                                                     const T *__restrict__ g, T *__restrict__ e, T *__restrict__ r) {
+__device__ __forceinline__ void k_update1_body(int64_t n, const double *__restrict__ sc, const T *__restrict__ p0,
+                                               const T *__restrict__ q0, const T *__restrict__ g, T *__restrict__ e,
+                                               T *__restrict__ r) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const T a = static_cast<T>(sc[S_A0]);
   e[i] = a * p0[i];
   r[i] = upd1_r(g[i], a, q0[i]);
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_update1(int64_t n, const double *__restrict__ sc,
+                                                    const T *__restrict__ p0, const T *__restrict__ q0,
+                                                    const T *__restrict__ g, T *__restrict__ e, T *__restrict__ r) {
+  k_update1_body<T>(n, sc, p0, q0, g, e, r);
+}
 
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_dot(int64_t n, const T *__restrict__ a, const T *__restrict__ b, Red R) {
+__device__ __forceinline__ void k_dot_body(int64_t n, const T *__restrict__ a, const T *__restrict__ b, Red R) {
   double v[1] = {0.0};
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kBlock)
+       i += static_cast<int64_t>(R.nb) * kBlock)
     v[0] += static_cast<double>(a[i]) * static_cast<double>(b[i]);
   reduce_finish<1>(v, R);
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_dot(int64_t n, const T *__restrict__ a, const T *__restrict__ b, Red R) {
+  k_dot_body<T>(n, a, b, R);
 }
 
 // e += a1 (p1 + beta p0): the last update of Algorithm 2.1 with the direction formed on the fly
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_update2(int64_t n, const double *__restrict__ sc, const T *__restrict__ p1,
-                                                     const T *__restrict__ p0, T *__restrict__ e) {
+__device__ __forceinline__ void k_update2_body(int64_t n, const double *__restrict__ sc, const T *__restrict__ p1,
+                                               const T *__restrict__ p0, T *__restrict__ e) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const T a1 = static_cast<T>(sc[S_A1]), beta = static_cast<T>(sc[S_BETA]);
   e[i] += a1 * (p1[i] + beta * p0[i]);
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_update2(int64_t n, const double *__restrict__ sc,
+                                                    const T *__restrict__ p1, const T *__restrict__ p0,
+                                                    T *__restrict__ e) {
+  k_update2_body<T>(n, sc, p1, p0, e);
+}
 
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_fill(int64_t n, T *__restrict__ v, T val) {
+__device__ __forceinline__ void k_fill_body(int64_t n, T *__restrict__ v, T val) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) v[i] = val;
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_fill(int64_t n, T *__restrict__ v, T val) {
+  k_fill_body<T>(n, v, val);
 }
 
 // e = A^{-1} g on the coarsest level (FP64 arithmetic whatever T is); one workgroup
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_dense_solve(int n, const double *__restrict__ ainv,
-                                                         const T *__restrict__ g, T *__restrict__ e) {
+__device__ __forceinline__ void k_dense_solve_body(int n, const double *__restrict__ ainv, const T *__restrict__ g,
+                                                   T *__restrict__ e) {
   __shared__ double sg[1024];
   for (int i = threadIdx.x; i < n; i += kBlock) sg[i] = static_cast<double>(g[i]);
   __syncthreads();
@@ -1899,14 +2024,18 @@ __global__ void __launch_bounds__(kBlock) k_dense_solve(int n, const double *__r
     e[i] = static_cast<T>(acc);
   }
 }
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_dense_solve(int n, const double *__restrict__ ainv,
+                                                        const T *__restrict__ g, T *__restrict__ e) {
+  k_dense_solve_body<T>(n, ainv, g, e);
+}
 
 // ---------------------------------------------------------------------------------------------------------------
 // outer flexible CG kernels (FP64, permuted numbering)
 
 // q = A p over all slices, with (p, q) and (r, p); one wavefront per slice
-__global__ void __launch_bounds__(kBlock) k_outer_spmv_dot(SellView<double> S, SliceSched Z,
-                                                            const double *__restrict__ p, double *__restrict__ q,
-                                                            const double *__restrict__ r, Red R) {
+__device__ __forceinline__ void k_outer_spmv_dot_body(const SellView<double> &S, const SliceSched &Z, const double *__restrict__ p,
+                                                      double *__restrict__ q, const double *__restrict__ r, Red R) {
   const int64_t s = sched_slice(Z);
   const int lane = threadIdx.x & 63;
   double v[2] = {0.0, 0.0};
@@ -1923,12 +2052,16 @@ __global__ void __launch_bounds__(kBlock) k_outer_spmv_dot(SellView<double> S, S
   }
   reduce_finish<2>(v, R);
 }
+__global__ void __launch_bounds__(kBlock) k_outer_spmv_dot(SellView<double> S, SliceSched Z,
+                                                           const double *__restrict__ p, double *__restrict__ q,
+                                                           const double *__restrict__ r, Red R) {
+  k_outer_spmv_dot_body(S, Z, p, q, r, R);
+}
 
 // t = b - A x with (t, t)
-__global__ void __launch_bounds__(kBlock) k_outer_true_resid(SellView<double> S, SliceSched Z,
-                                                              const double *__restrict__ b,
-                                                              const double *__restrict__ x, double *__restrict__ t,
-                                                              Red R) {
+__device__ __forceinline__ void k_outer_true_resid_body(const SellView<double> &S, const SliceSched &Z,
+                                                        const double *__restrict__ b, const double *__restrict__ x,
+                                                        double *__restrict__ t, Red R) {
   const int64_t s = sched_slice(Z);
   const int lane = threadIdx.x & 63;
   double v[1] = {0.0};
@@ -1945,15 +2078,21 @@ __global__ void __launch_bounds__(kBlock) k_outer_true_resid(SellView<double> S,
   }
   reduce_finish<1>(v, R);
 }
+__global__ void __launch_bounds__(kBlock) k_outer_true_resid(SellView<double> S, SliceSched Z,
+                                                             const double *__restrict__ b,
+                                                             const double *__restrict__ x, double *__restrict__ t,
+                                                             Red R) {
+  k_outer_true_resid_body(S, Z, b, x, t, R);
+}
 
 // x += alpha p, r -= alpha q, with (r, r)
-__global__ void __launch_bounds__(kBlock) k_outer_update(int64_t n, const double *__restrict__ sc,
-                                                          const double *__restrict__ p, const double *__restrict__ q,
-                                                          double *__restrict__ x, double *__restrict__ r, Red R) {
+__device__ __forceinline__ void k_outer_update_body(int64_t n, const double *__restrict__ sc,
+                                                    const double *__restrict__ p, const double *__restrict__ q,
+                                                    double *__restrict__ x, double *__restrict__ r, Red R) {
   const double a = sc[O_ALPHA];
   double v[1] = {0.0};
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kBlock) {
+       i += static_cast<int64_t>(R.nb) * kBlock) {
     x[i] += a * p[i];
     const double ri = r[i] - a * q[i];
     r[i] = ri;
@@ -1961,16 +2100,27 @@ __global__ void __launch_bounds__(kBlock) k_outer_update(int64_t n, const double
   }
   reduce_finish<1>(v, R);
 }
+__global__ void __launch_bounds__(kBlock) k_outer_update(int64_t n, const double *__restrict__ sc,
+                                                         const double *__restrict__ p, const double *__restrict__ q,
+                                                         double *__restrict__ x, double *__restrict__ r, Red R) {
+  k_outer_update_body(n, sc, p, q, x, r, R);
+}
 
 // p = z + beta pprev (beta from the scalar block when use_beta)
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_outer_dir(int64_t n, const double *__restrict__ sc,
-                                                       const T *__restrict__ z, const double *__restrict__ pprev,
-                                                       double *__restrict__ p, int use_beta) {
+__device__ __forceinline__ void k_outer_dir_body(int64_t n, const double *__restrict__ sc, const T *__restrict__ z,
+                                                 const double *__restrict__ pprev, double *__restrict__ p,
+                                                 int use_beta) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double zi = static_cast<double>(z[i]);
   p[i] = use_beta ? zi + sc[O_BETA] * pprev[i] : zi;
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_outer_dir(int64_t n, const double *__restrict__ sc,
+                                                      const T *__restrict__ z, const double *__restrict__ pprev,
+                                                      double *__restrict__ p, int use_beta) {
+  k_outer_dir_body<T>(n, sc, z, pprev, p, use_beta);
 }
 
 // p = z + sum_j beta_j P_j over all m stored directions, beta_j = -(z, Q_j) / (P_j, Q_j) (Algorithm 2.1, Step 2, as
@@ -1987,34 +2137,38 @@ __global__ void __launch_bounds__(kBlock) k_outer_dir_all(int64_t n, const doubl
   p[i] = pi;
 }
 
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_dot_mixed(int64_t n, const T *__restrict__ a, const double *__restrict__ b,
-                                                       Red R) {
-  double v[1] = {0.0};
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kBlock)
-    v[0] += static_cast<double>(a[i]) * b[i];
-  reduce_finish<1>(v, R);
-}
-
 template <class S, class D>
-__global__ void __launch_bounds__(kBlock) k_gather(int64_t n, const int32_t *__restrict__ perm,
-                                                    const S *__restrict__ src, D *__restrict__ dst) {
+__device__ __forceinline__ void k_gather_body(int64_t n, const int32_t *__restrict__ perm, const S *__restrict__ src,
+                                              D *__restrict__ dst) {
   const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (p < n) dst[p] = static_cast<D>(src[perm[p]]);
 }
-
 template <class S, class D>
-__global__ void __launch_bounds__(kBlock) k_scatter_back(int64_t n, const int32_t *__restrict__ perm,
-                                                          const S *__restrict__ src, D *__restrict__ dst) {
-  const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p < n) dst[perm[p]] = static_cast<D>(src[p]);
+__global__ void __launch_bounds__(kBlock) k_gather(int64_t n, const int32_t *__restrict__ perm,
+                                                   const S *__restrict__ src, D *__restrict__ dst) {
+  k_gather_body<S, D>(n, perm, src, dst);
 }
 
 template <class S, class D>
-__global__ void __launch_bounds__(kBlock) k_cast(int64_t n, const S *__restrict__ src, D *__restrict__ dst) {
+__device__ __forceinline__ void k_scatter_back_body(int64_t n, const int32_t *__restrict__ perm,
+                                                    const S *__restrict__ src, D *__restrict__ dst) {
+  const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (p < n) dst[perm[p]] = static_cast<D>(src[p]);
+}
+template <class S, class D>
+__global__ void __launch_bounds__(kBlock) k_scatter_back(int64_t n, const int32_t *__restrict__ perm,
+                                                         const S *__restrict__ src, D *__restrict__ dst) {
+  k_scatter_back_body<S, D>(n, perm, src, dst);
+}
+
+template <class S, class D>
+__device__ __forceinline__ void k_cast_body(int64_t n, const S *__restrict__ src, D *__restrict__ dst) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = static_cast<D>(src[i]);
+}
+template <class S, class D>
+__global__ void __launch_bounds__(kBlock) k_cast(int64_t n, const S *__restrict__ src, D *__restrict__ dst) {
+  k_cast_body<S, D>(n, src, dst);
 }
 
 // lexicographic <-> color-major numbering of a quadtree level (tests and level hooks)
@@ -2066,14 +2220,14 @@ template <class T>
 static SellView<T> sview(const FineLevel &F, const T *val) {
   return SellView<T>{F.slice_ptr, F.slice_row0, F.s_row, F.s_col, val};
 }
-static Red red(amg_hierarchy *h, int l, int epi, int slot = 0) {
-  return Red{h->partials, h->scal + static_cast<size_t>(l) * kScalars, epi, slot};
+static Red red(amg_hierarchy *h, int l, unsigned nb, int epi, int slot = 0) {
+  return Red{h->partials, h->scal + static_cast<size_t>(l) * kScalars, epi, slot, nb};
 }
 
 // second stage of a multi-workgroup reduction (no-op for a single-workgroup launch)
 template <int ND>
-static void finish(amg_hierarchy *h, unsigned nb, const Red &R) {
-  if (nb > 1) k_finish<ND><<<1, kBlock, 0, h->stream>>>(nb, R);
+static void finish(amg_hierarchy *h, const Red &R) {
+  if (R.nb > 1) QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(ND), R);
 }
 
 // Schedule of a fine-level pass over colors [c0, c1); the XCD-aware order from 256 slices (16,384 rows) up.
@@ -2108,25 +2262,21 @@ static unsigned sched_grid(const SliceSched &Z) {
   return static_cast<unsigned>(8 * ((most + 3) / 4));
 }
 
-// Launch `kern` on the hierarchy's stream with kBlock threads per workgroup. When its family is the one being timed,
-// the launch goes through hipExtLaunchKernelGGL with a start/stop event pair: the runtime stamps both events from
-// the dispatch packet itself, so the interval is the kernel's own execution window (the same span a kernel-trace
-// profiler reports), not the gap between two markers queued around it.
-template <typename F, typename... Args>
-static void launch_timed_lds(amg_hierarchy *h, int kind, F kern, unsigned grid, size_t lds, Args... args) {
+// QA_RUN of a kernel of the family `KIND`. When that family is the one being timed, the launch goes through
+// hipExtLaunchKernelGGL with a start/stop event pair: the runtime stamps both events from the dispatch packet itself,
+// so the interval is the kernel's own execution window (the same span a kernel-trace profiler reports), not the gap
+// between two markers queued around it.
+#define QA_RUN_TIMED(h, KIND, NT, GRID, LDS, K, TA, ...)                                                       \
+  launch_timed<NT>(h, KIND, K TA, [] __device__(const auto &...a) { K##_body TA(a...); }, GRID, LDS, __VA_ARGS__)
+template <int NT, class K, class F, class... A>
+static void launch_timed(amg_hierarchy *h, int kind, K kern, F body, unsigned grid, size_t lds, A... a) {
   Timing &t = h->timing;
-  if (kind >= 0 && t.kind == kind && t.used + 2 <= t.ev.size()) {
-    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, h->stream, t.ev[t.used], t.ev[t.used + 1], 0,
-                          args...);
+  if (!h->recording && kind >= 0 && t.kind == kind && t.used + 2 <= t.ev.size()) {
+    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, h->stream, t.ev[t.used], t.ev[t.used + 1], 0, a...);
     t.used += 2;
   } else {
-    kern<<<grid, kBlock, lds, h->stream>>>(args...);
+    launch<NT>(h, kern, body, grid, lds, a...);
   }
-}
-
-template <class F, class... Args>
-static void launch_timed(amg_hierarchy *h, int kind, F kern, unsigned grid, Args... args) {
-  launch_timed_lds(h, kind, kern, grid, 0, args...);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -2211,6 +2361,7 @@ __device__ inline void eng_reduce(double (&v)[ND], double *red) {
     for (int w = 0; w < kEngWaves; w++) acc += red[j * kEngWaves + w];
     v[j] = acc;  // every thread sums the same values in the same order
   }
+  __syncthreads();  // before red is written again
 }
 
 // The same sum delivered to thread 0 only, for steps whose result thread 0 stores: waves at or past `waves` hold
@@ -2977,12 +3128,20 @@ static void launch_engine(amg_hierarchy *h, int top) {
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Whole-solve workgroup: the serving form for small systems. One workgroup runs a complete solve of one system
+// Whole-solve workgroup: the serving form for the smallest systems (plan_wg). One workgroup runs a complete solve of one system
 // (outer flexible CG, fine-level block smoother, the coarse cycle through the step interpreter, the convergence
 // test) with no host round trip; a batch of systems is one launch with one workgroup per system, so the result of
 // a system does not depend on what else is in the batch.
 
-constexpr int64_t kWgMaxRows = 65536;
+constexpr int64_t kWgMaxRows = 65536;   // of a system that shares its launches with others
+// Such a system is a whole-solve workgroup up to kWgSolveMax unknowns and where the hierarchy has no specialised engine;
+// otherwise its launches are shared with the batch's others (solve_many). Measured, FP32 preconditioner, one system
+// and 64 alike, workgroups against launches in step: 784 unknowns 1.08 and 1.26 against 1.67 and 1.84 ms; 2,500 unknowns
+// 1.85 and 2.36 against 1.75 and 2.10; 3,844 unknowns 2.99 and 4.09 against 2.15 and 2.68; 10,000 unknowns (one) 4.98
+// against 1.99; 63,504 unknowns 38.5 and 55.0 against 3.3 and 13.1. The general engine's plan (1.3 KB of arguments)
+// limits a launch to 12 systems, and its 1024 threads to one at a time on a CU: 64 systems of 4,900 unknowns took 4.6
+// against 12.0.
+constexpr int64_t kWgSolveMax = 2500;
 
 template <class T>
 struct WgSys {
@@ -3229,10 +3388,11 @@ __global__ void __launch_bounds__(kEngThreads) k_solve_wg(const WgSys<T> *system
   }
 }
 
-// Plan of the whole-solve workgroup for one precision: all quadtree levels run through the step interpreter, the
-// deepest ones from LDS.
+// How amg_solve_batch runs a system, per precision: in step with others, or in a whole-solve workgroup, whose plan this
+// is: all quadtree levels run through the step interpreter, the deepest ones from LDS.
 amg_status plan_wg(amg_hierarchy *h) {
   h->wg_nops[0] = h->wg_nops[1] = 0;
+  h->in_step[0] = h->in_step[1] = false;
   // the whole-solve workgroup carries the substitution smoother and at most one kept direction only
   if (h->nlev < 3 || h->n > kWgMaxRows || h->opt.smoother || h->opt.outer_mmax < 0 || h->dim != 2) return AMG_OK;
   if (h->lds_max == 0) {
@@ -3248,6 +3408,8 @@ amg_status plan_wg(amg_hierarchy *h) {
   emit_btilde(ops, EmitCtx{h->nlev - 1, h->opt.sweeps, h->opt.inner_iters, mhat, same1.data()}, 0, false);
   if (ops.size() > static_cast<size_t>(kEngMaxOps) || h->nlev - 1 > kEngMaxLevels) return AMG_OK;
   for (int pi = 0; pi < 2; pi++) {
+    h->in_step[pi] = h->fe_cfg[pi] >= 0 && h->n > kWgSolveMax;
+    if (h->in_step[pi]) continue;
     const size_t ts = pi == 0 ? sizeof(double) : sizeof(float);
     const size_t extra = mhat ? static_cast<size_t>(kMhatPart) * ts : 0;
     size_t bytes = static_cast<size_t>(h->nc) * 2 * ts + extra;
@@ -3302,7 +3464,7 @@ static Pending<T> coarse_solve_or_cycle(amg_hierarchy *h, int l, bool fold) {
   LevelWork<T> &w = P<T>::W(h)[l];
   const int pi = std::is_same<T, float>::value ? 1 : 0;
   if (l == h->nlev - 1) {
-    k_dense_solve<T><<<1, kBlock, 0, h->stream>>>(static_cast<int>(h->nc), h->ainv, w.g, w.e);
+    QA_RUN(h, kBlock, 1, 0, k_dense_solve, QA_T(T), static_cast<int>(h->nc), h->ainv, w.g, w.e);
   } else if (h->dim == 3) {
     btilde_oct<T>(h, l, w.g, w.e);
   } else if (h->use_engine && l == h->engine_top[pi]) {
@@ -3323,13 +3485,13 @@ static void gs_phase_coarse(amg_hierarchy *h, int l, const T *f, T *u, int c, bo
   const QuadLevel &Q = h->lev[l];
   const int64_t n4 = Q.n >> 2;
   if (Q.same_color_ovf && zero) {
-    k_cgs<T, true><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, nullptr, c);
+    QA_RUN(h, kBlock, nblk(n4), 0, k_cgs, QA_T(T, true), qview<T>(Q), f, u, nullptr, c);
   } else if (Q.same_color_ovf) {
     T *dl = P<T>::W(h)[l].d;
-    k_cgs<T, false><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, dl, c);
-    k_add_range<T><<<nblk(n4), kBlock, 0, h->stream>>>(c * n4, n4, dl, u);
+    QA_RUN(h, kBlock, nblk(n4), 0, k_cgs, QA_T(T, false), qview<T>(Q), f, u, dl, c);
+    QA_RUN(h, kBlock, nblk(n4), 0, k_add_range, QA_T(T), c * n4, n4, dl, u);
   } else {
-    k_cgs<T, false><<<nblk(n4), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, nullptr, c);
+    QA_RUN(h, kBlock, nblk(n4), 0, k_cgs, QA_T(T, false), qview<T>(Q), f, u, nullptr, c);
   }
 }
 
@@ -3341,7 +3503,6 @@ template <class T>
 static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T> &upd = Upd1<T>{},
                         const T *beta_q0 = nullptr, int sp = 0) {
   const QuadLevel &Q = h->lev[l];
-  hipStream_t s = h->stream;
   const int sweeps = h->opt.sweeps;
   const bool U = upd.sc != nullptr;
   const int64_t n4 = Q.n >> 2;
@@ -3357,35 +3518,37 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
   if (tiled_pre) {
     const QView<T> V = qview<T>(Q);
     if (U) {
-      if (small) k_cgs_pre4<T, true, 8><<<grid, Tile<8, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
-      else k_cgs_pre4<T, true, 16><<<grid, Tile<16, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
+      if (small) QA_RUN(h, (Tile<8, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, true, 8), V, f, v, upd, wc.g);
+      else QA_RUN(h, (Tile<16, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, true, 16), V, f, v, upd, wc.g);
     } else {
-      if (small) k_cgs_pre4<T, false, 8><<<grid, Tile<8, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
-      else k_cgs_pre4<T, false, 16><<<grid, Tile<16, 4>::NT, 0, s>>>(V, f, v, upd, wc.g);
+      if (small) QA_RUN(h, (Tile<8, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, false, 8), V, f, v, upd, wc.g);
+      else QA_RUN(h, (Tile<16, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, false, 16), V, f, v, upd, wc.g);
     }
   }
   for (int sw = 0; sw < (tiled_pre ? 0 : sweeps); sw++)
     for (int c = 0; c < 4; c++) {
       if (sw == 0 && c == 0) {
-        if (U) k_cgs_first2<T, true><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
-        else k_cgs_first2<T, false><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), f, v, upd);
+        if (U) QA_RUN(h, kBlock, nblk(Q.n), 0, k_cgs_first2, QA_T(T, true), qview<T>(Q), f, v, upd);
+        else QA_RUN(h, kBlock, nblk(Q.n), 0, k_cgs_first2, QA_T(T, false), qview<T>(Q), f, v, upd);
         c = 1;
       } else {
         gs_phase_coarse<T>(h, l, f, v, c, sw == 0);
       }
     }
-  if (!tiled_pre) k_cres_restrict<T><<<nblk(Q.n >> 2), kBlock, 0, s>>>(qview<T>(Q), f, v, wc.g);
+  if (!tiled_pre) QA_RUN(h, kBlock, nblk(Q.n >> 2), 0, k_cres_restrict, QA_T(T), qview<T>(Q), f, v, wc.g);
   const Pending<T> pend = coarse_solve_or_cycle<T>(h, l + 1, tiles);
-  const Red rb = red(h, l, EPI_BETA);
+  const Red rb = red(h, l, nblk(n4), EPI_BETA);
   if (tiles) {
     const QView<T> V = qview<T>(Q);
     double *part = tile_part<T>(h, l);
     auto post = [&](auto spc) {
       constexpr int SP = decltype(spc)::value;
       if (small)
-        k_cgs_post4<T, SP, 8><<<grid, Tile<8, SP ? 5 : 4>::NT, 0, s>>>(V, f, v, u, wc.e, pend, w.q0, w.p0, part);
+        QA_RUN(h, (Tile<8, SP ? 5 : 4>::NT), grid, 0, k_cgs_post4, QA_T(T, SP, 8), V, f, v, u, wc.e, pend, w.q0,
+               w.p0, part);
       else
-        k_cgs_post4<T, SP, 16><<<grid, Tile<16, SP ? 5 : 4>::NT, 0, s>>>(V, f, v, u, wc.e, pend, w.q0, w.p0, part);
+        QA_RUN(h, (Tile<16, SP ? 5 : 4>::NT), grid, 0, k_cgs_post4, QA_T(T, SP, 16), V, f, v, u, wc.e, pend, w.q0,
+               w.p0, part);
     };
     if (sp == 1) post(std::integral_constant<int, 1>{});
     else if (sp == 2) post(std::integral_constant<int, 2>{});
@@ -3397,19 +3560,20 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
       if (sw == 0) {
         const QView<T> V = qview<T>(Q);
         switch (c) {
-          case 3: k_cgs_post<T, 3, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb); break;
-          case 2: k_cgs_post<T, 2, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb); break;
-          case 1: k_cgs_post<T, 1, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb); break;
+          case 3: QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 3, false), V, f, v, u, wc.e, pend, beta_q0, rb); break;
+          case 2: QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 2, false), V, f, v, u, wc.e, pend, beta_q0, rb); break;
+          case 1: QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 1, false), V, f, v, u, wc.e, pend, beta_q0, rb); break;
           default:
-            if (beta_here) k_cgs_post<T, 0, true><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb);
-            else k_cgs_post<T, 0, false><<<nblk(n4), kBlock, 0, s>>>(V, f, v, u, wc.e, pend, beta_q0, rb);
+            if (beta_here) QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 0, true), V, f, v, u, wc.e, pend,
+                                  beta_q0, rb);
+            else QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 0, false), V, f, v, u, wc.e, pend, beta_q0, rb);
         }
       } else if (beta_here) {
-        k_cgs0_beta<T><<<nblk(n4), kBlock, 0, s>>>(qview<T>(Q), f, u, beta_q0, rb);
+        QA_RUN(h, kBlock, nblk(n4), 0, k_cgs0_beta, QA_T(T), qview<T>(Q), f, u, beta_q0, rb);
       } else {
         gs_phase_coarse<T>(h, l, f, u, c, false);
       }
-      if (beta_here) finish<1>(h, nblk(n4), rb);
+      if (beta_here) finish<1>(h, rb);
     }
 }
 
@@ -3418,18 +3582,17 @@ static void fine_resid(amg_hierarchy *h, const T *f, const T *x, T *d, int c0, i
   const SliceSched Z = slice_sched(h->fine, c0, c1);
   const unsigned grid = sched_grid(Z);
   if (grid == 0) return;
-  if (kind == P<T>::kResid)
-    launch_timed(h, kind, k_fine_resid_full<T>, grid, sview<T>(h->fine, P<T>::sval(h->fine)), Z, f, x, d);
-  else
-    launch_timed(h, kind, k_fine_resid<T>, grid, sview<T>(h->fine, P<T>::sval(h->fine)), Z, f, x, d);
+  const SellView<T> A = sview<T>(h->fine, P<T>::sval(h->fine));
+  if (kind == P<T>::kResid) QA_RUN_TIMED(h, kind, kBlock, grid, 0, k_fine_resid_full, QA_T(T), A, Z, f, x, d);
+  else QA_RUN_TIMED(h, kind, kBlock, grid, 0, k_fine_resid, QA_T(T), A, Z, f, x, d);
 }
 
 template <class T, int SM, bool FWD, bool GIVEN>
 static void fine_gs_launch(amg_hierarchy *h, unsigned grid, FuseArgs<T> A) {
   A.ent_cap = std::min(h->fine.win_ent_max, kFuseDynBytes / fuse_ent_bytes<T, SM>());
   const size_t lds = (static_cast<size_t>(A.ent_cap) * fuse_ent_bytes<T, SM>() + 15) / 16 * 16;
-  launch_timed_lds(h, P<T>::kGs, k_fine_gs<T, SM, FWD, GIVEN>, grid, lds, sview<T>(h->fine, P<T>::sval(h->fine)),
-                   A);
+  QA_RUN_TIMED(h, P<T>::kGs, kBlock, grid, lds, k_fine_gs, QA_T(T, SM, FWD, GIVEN),
+               sview<T>(h->fine, P<T>::sval(h->fine)), A);
 }
 
 // One color phase of the fine smoother: the fused residual and cell solves (k_fine_gs), then the cells left to the
@@ -3488,13 +3651,13 @@ static void fine_phase(amg_hierarchy *h, const T *f, T *u, T *d, int c, bool fwd
     const int lds_rows = std::min(F.big_max_rows, kSubstDynBytes / static_cast<int>(sizeof(T)));
     const size_t lds = (static_cast<size_t>(lds_rows) * sizeof(T) + 15) / 16 * 16;
     if (fwd)
-      k_fine_subst_big<T, true><<<static_cast<unsigned>(nb), kSubstLanes, lds, h->stream>>>(
-          F.crow, F.ic_ptr, F.ic_col, P<T>::icv(F), P<T>::diag(F), src, d, u, F.big_cells, b0, F.big_lofs[dir],
-          F.big_lptr[dir], F.big_sched[dir], lds_rows);
+      QA_RUN(h, kSubstLanes, static_cast<unsigned>(nb), lds, k_fine_subst_big, QA_T(T, true), F.crow, F.ic_ptr,
+             F.ic_col, P<T>::icv(F), P<T>::diag(F), src, d, u, F.big_cells, b0, F.big_lofs[dir], F.big_lptr[dir],
+             F.big_sched[dir], lds_rows);
     else
-      k_fine_subst_big<T, false><<<static_cast<unsigned>(nb), kSubstLanes, lds, h->stream>>>(
-          F.crow, F.ic_ptr, F.ic_col, P<T>::icv(F), P<T>::diag(F), src, d, u, F.big_cells, b0, F.big_lofs[dir],
-          F.big_lptr[dir], F.big_sched[dir], lds_rows);
+      QA_RUN(h, kSubstLanes, static_cast<unsigned>(nb), lds, k_fine_subst_big, QA_T(T, false), F.crow, F.ic_ptr,
+             F.ic_col, P<T>::icv(F), P<T>::diag(F), src, d, u, F.big_cells, b0, F.big_lofs[dir], F.big_lptr[dir],
+             F.big_sched[dir], lds_rows);
   }
 }
 
@@ -3502,9 +3665,8 @@ static void fine_phase(amg_hierarchy *h, const T *f, T *u, T *d, int c, bool fwd
 template <class T>
 static void bhat_fine(amg_hierarchy *h, const T *f, T *u) {
   const FineLevel &F = h->fine;
-  hipStream_t s = h->stream;
   LevelWork<T> &w = P<T>::W(h)[0];
-  k_fill<T><<<nblk(F.n), kBlock, 0, s>>>(F.n, u, T(0));
+  QA_RUN(h, kBlock, nblk(F.n), 0, k_fill, QA_T(T), F.n, u, T(0));
   const int sweeps = h->opt.sweeps;
   const int nc = F.ncolor;
   // one sweep each way: the pre-smoothing's color rows are zero before their phase, and the post-smoothing's hold
@@ -3517,10 +3679,11 @@ static void bhat_fine(amg_hierarchy *h, const T *f, T *u) {
   fine_resid<T>(h, f, u, w.d, 0, F.ncolor, P<T>::kResid);
   const int64_t nL = static_cast<int64_t>(1) << (h->dim * h->L);
   const int big = h->opt.smoother ? kBlockMax : kBigCell;  // the big-cell list's threshold
-  k_fine_restrict<T><<<nblk(nL), kBlock, 0, s>>>(nL, F.crow, w.d, wc.g, F.nbig ? big : INT32_MAX);
-  if (F.nbig) k_fine_restrict_big<T><<<static_cast<unsigned>(F.nbig), 64, 0, s>>>(F.big_cells, F.crow, w.d, wc.g);
+  QA_RUN(h, kBlock, nblk(nL), 0, k_fine_restrict, QA_T(T), nL, F.crow, w.d, wc.g, F.nbig ? big : INT32_MAX);
+  if (F.nbig) QA_RUN(h, 64, static_cast<unsigned>(F.nbig), 0, k_fine_restrict_big, QA_T(T), F.big_cells, F.crow, w.d,
+                     wc.g);
   const Pending<T> pend = coarse_solve_or_cycle<T>(h, 1, false);
-  k_fine_prolong<T><<<nblk(F.n), kBlock, 0, s>>>(F.n, F.agg_q, wc.e, pend, u, one ? w.r : nullptr);
+  QA_RUN(h, kBlock, nblk(F.n), 0, k_fine_prolong, QA_T(T), F.n, F.agg_q, wc.e, pend, u, one ? w.r : nullptr);
   for (int sw = 0; sw < sweeps; sw++)
     for (int c = nc - 1; c >= 0; c--) fine_phase<T>(h, f, u, w.d, c, false, false, one ? kOldSnap : kOldNone);
 }
@@ -3531,7 +3694,6 @@ template <class T>
 static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2, bool fold) {
   const QuadLevel &Q = h->lev[l];
   LevelWork<T> &w = P<T>::W(h)[l];
-  hipStream_t s = h->stream;
   double *sc = h->scal + static_cast<size_t>(l) * kScalars;
   const bool two = h->opt.inner_iters >= 2;
   if (level_tiled(h, l) && h->opt.sweeps == 1) {  // two launches per B^
@@ -3539,24 +3701,24 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
     const unsigned nb = static_cast<unsigned>(tile_grid(Q));
     const bool few = nb <= kFoldBlocks;
     bhat_coarse<T>(h, l, g, w.p0, Upd1<T>{}, nullptr, 1);
-    if (!two || !few) k_finish<4><<<1, kBlock, 0, s>>>(nb, Red{part, sc, EPI_ALPHA0, 0});
+    if (!two || !few) QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(4), Red{part, sc, EPI_ALPHA0, 0, nb});
     if (!two) {
-      k_update1<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p0, w.q0, g, e, w.r);
+      QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
       return false;
     }
     bhat_coarse<T>(h, l, w.r, w.p1,
                    Upd1<T>{sc, g, w.q0, w.p0, e, w.r, few ? part : nullptr, few ? static_cast<int>(nb) : 0}, nullptr, 2);
     if (few && fold && defer_update2) return true;
-    k_finish<4><<<1, kBlock, 0, s>>>(
-        nb, Red{part, sc, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64, 0});
-    if (!defer_update2) k_update2<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p1, w.p0, e);
+    QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(4),
+           Red{part, sc, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64, 0, nb});
+    if (!defer_update2) QA_RUN(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
     return false;
   }
   bhat_coarse<T>(h, l, g, w.p0);
-  k_cspmv_dot<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p0, w.q0, g, red(h, l, EPI_ALPHA0));
-  finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA0));
+  QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_dot, QA_T(T), qview<T>(Q), w.p0, w.q0, g, red(h, l, nred(Q.n), EPI_ALPHA0));
+  finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA0));
   if (!two) {
-    k_update1<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p0, w.q0, g, e, w.r);
+    QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
     return false;
   }
   // the first inner update folds into the second B^'s first relaxation. With the engine on, beta and alpha1 come from
@@ -3564,21 +3726,21 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
   // relaxation where its sweeps allow, then A d.
   const Upd1<T> upd{sc, g, w.q0, w.p0, e, w.r, nullptr, 0};
   if (h->use_engine != 0) {
-    const Red rp = red(h, l, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64);
+    const Red rp = red(h, l, nred(Q.n), std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64);
     bhat_coarse<T>(h, l, w.r, w.p1, upd);
-    k_cspmv_pair<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p1, w.r, w.q0, w.p0, rp);
-    finish<4>(h, nred(Q.n), rp);
+    QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_pair, QA_T(T), qview<T>(Q), w.p1, w.r, w.q0, w.p0, rp);
+    finish<4>(h, rp);
   } else {
     const bool fold_beta = !Q.same_color_ovf || h->opt.sweeps == 1;
     bhat_coarse<T>(h, l, w.r, w.p1, upd, fold_beta ? w.q0 : nullptr);
     if (!fold_beta) {
-      k_dot<T><<<nred(Q.n), kBlock, 0, s>>>(Q.n, w.p1, w.q0, red(h, l, EPI_BETA));
-      finish<1>(h, nred(Q.n), red(h, l, EPI_BETA));
+      QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
+      finish<1>(h, red(h, l, nred(Q.n), EPI_BETA));
     }
-    k_cspmv_dir<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, EPI_ALPHA1));
-    finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA1));
+    QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_dir, QA_T(T), qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
+    finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA1));
   }
-  if (!defer_update2) k_update2<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p1, w.p0, e);
+  if (!defer_update2) QA_RUN(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
   return false;
 }
 
@@ -3592,7 +3754,7 @@ static void gs_phase_oct(amg_hierarchy *h, int l, const T *f, T *u, int c) {
   if (Q.same_color_ovf) {
     T *dl = P<T>::W(h)[l].d;
     k_cgs3<T><<<nblk(n8), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, dl, c);
-    k_add_range<T><<<nblk(n8), kBlock, 0, h->stream>>>(c * n8, n8, dl, u);
+    QA_RUN(h, kBlock, nblk(n8), 0, k_add_range, QA_T(T), c * n8, n8, dl, u);
   } else {
     k_cgs3<T><<<nblk(n8), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, nullptr, c);
   }
@@ -3622,12 +3784,12 @@ static void bhat_oct(amg_hierarchy *h, int l, const T *f, T *u) {
     }
     return;
   }
-  k_fill<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, u, T(0));
+  QA_RUN(h, kBlock, nblk(Q.n), 0, k_fill, QA_T(T), Q.n, u, T(0));
   for (int sw = 0; sw < h->opt.sweeps; sw++)
     for (int c = 0; c < 8; c++) gs_phase_oct<T>(h, l, f, u, c);
   k_cres_restrict3<T><<<nblk(Q.n >> 3), kBlock, 0, s>>>(qview<T>(Q), f, u, wc.g);
   if (l + 1 == h->nlev - 1)
-    k_dense_solve<T><<<1, kBlock, 0, s>>>(static_cast<int>(h->nc), h->ainv, wc.g, wc.e);
+    QA_RUN(h, kBlock, 1, 0, k_dense_solve, QA_T(T), static_cast<int>(h->nc), h->ainv, wc.g, wc.e);
   else
     btilde_oct<T>(h, l + 1, wc.g, wc.e);
   k_cprolong3<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, wc.e, u);
@@ -3646,32 +3808,31 @@ static void btilde_oct(amg_hierarchy *h, int l, const T *g, T *e) {
   hipStream_t s = h->stream;
   const double *sc = h->scal + static_cast<size_t>(l) * kScalars;
   bhat_oct<T>(h, l, g, w.p0);
-  k_cspmv_dot3<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p0, w.q0, g, red(h, l, EPI_ALPHA0));
-  finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA0));
-  k_update1<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p0, w.q0, g, e, w.r);
+  k_cspmv_dot3<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p0, w.q0, g, red(h, l, nred(Q.n), EPI_ALPHA0));
+  finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA0));
+  QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
   if (h->opt.inner_iters < 2) return;
   bhat_oct<T>(h, l, w.r, w.p1);
-  k_dot<T><<<nred(Q.n), kBlock, 0, s>>>(Q.n, w.p1, w.q0, red(h, l, EPI_BETA));
-  finish<1>(h, nred(Q.n), red(h, l, EPI_BETA));
-  k_cspmv_dir3<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, EPI_ALPHA1));
-  finish<2>(h, nred(Q.n), red(h, l, EPI_ALPHA1));
-  k_update2<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.n, sc, w.p1, w.p0, e);
+  QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
+  finish<1>(h, red(h, l, nred(Q.n), EPI_BETA));
+  k_cspmv_dir3<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
+  finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA1));
+  QA_RUN(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
 }
 
 // z = B^_F[r] in the requested precision (r, z: FP64, permuted numbering)
 amg_status precond_apply(amg_hierarchy *h, int precision, const double *r, double *z) {
   const int64_t n = h->n;
-  hipStream_t s = h->stream;
   if (h->nlev == 1) {
-    k_dense_solve<double><<<1, kBlock, 0, s>>>(static_cast<int>(h->nc), h->ainv, r, z);
+    QA_RUN(h, kBlock, 1, 0, k_dense_solve, QA_T(double), static_cast<int>(h->nc), h->ainv, r, z);
     QA_LAUNCH_CHECK();
     return AMG_OK;
   }
   if (precision == 1) {
     LevelWork<float> &w = h->w32[0];
-    k_cast<double, float><<<nblk(n), kBlock, 0, s>>>(n, r, w.f);
+    QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(double, float), n, r, w.f);
     bhat_fine<float>(h, w.f, w.u);
-    k_cast<float, double><<<nblk(n), kBlock, 0, s>>>(n, w.u, z);
+    QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(float, double), n, w.u, z);
   } else {
     bhat_fine<double>(h, r, z);
   }
@@ -3781,66 +3942,110 @@ static amg_status outer_dirs_reserve(amg_hierarchy *h, int count) {
   return AMG_OK;
 }
 
+// Pieces of the outer iteration, launched or recorded. L0 = nlev is the outer scalar block.
+
+// b in the permuted numbering with (b, b), x = 0, r = b
+static void outer_start(amg_hierarchy *h, const double *b) {
+  const int64_t n = h->n;
+  const Red R = red(h, h->nlev, nred(n), EPI_STORE, O_BB);
+  QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, double), n, h->fine.perm, b, h->bp);
+  QA_RUN(h, kBlock, nred(n), 0, k_dot, QA_T(double), n, h->bp, h->bp, R);
+  finish<1>(h, R);
+  QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, h->xp, 0.0);
+  QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(double, double), n, h->bp, h->rp);
+}
+
+// q = A p, alpha, x += alpha p, r -= alpha q with (r, r)
+static void outer_step(amg_hierarchy *h, double *p, double *q) {
+  const int64_t n = h->n;
+  const int L0 = h->nlev;
+  const double *osc = h->scal + static_cast<size_t>(L0) * kScalars;
+  const SliceSched Z = slice_sched(h->fine, 0, h->fine.ncolor);
+  const Red ra = red(h, L0, sched_grid(Z), EPI_OUT_ALPHA), rr = red(h, L0, nred(n), EPI_STORE, O_RR);
+  QA_RUN_TIMED(h, KK_SPMV64, kBlock, ra.nb, 0, k_outer_spmv_dot, , sview<double>(h->fine, h->fine.s_val64), Z, p, q,
+               h->rp, ra);
+  finish<2>(h, ra);
+  QA_RUN(h, kBlock, rr.nb, 0, k_outer_update, , n, osc, p, q, h->xp, h->rp, rr);
+  finish<1>(h, rr);
+}
+
+// one iteration with at most one kept direction
+static amg_status outer_iterate(amg_hierarchy *h, double *p, double *q, const double *pprev, const double *qprev,
+                                bool use_beta) {
+  const int64_t n = h->n;
+  const int L0 = h->nlev;
+  const double *osc = h->scal + static_cast<size_t>(L0) * kScalars;
+  QA_TRY(precond_apply(h, h->precision, h->rp, h->zp));
+  if (use_beta) {
+    const Red R = red(h, L0, nred(n), EPI_OUT_BETA);
+    QA_RUN(h, kBlock, R.nb, 0, k_dot, QA_T(double), n, h->zp, qprev, R);
+    finish<1>(h, R);
+  }
+  QA_RUN(h, kBlock, nblk(n), 0, k_outer_dir, QA_T(double), n, osc, h->zp, pprev, p, use_beta ? 1 : 0);
+  outer_step(h, p, q);
+  return AMG_OK;
+}
+
+// t = b - A x with (t, t)
+static void outer_true_resid(amg_hierarchy *h) {
+  const SliceSched Z = slice_sched(h->fine, 0, h->fine.ncolor);
+  const Red R = red(h, h->nlev, sched_grid(Z), EPI_STORE, O_TT);
+  QA_RUN(h, kBlock, R.nb, 0, k_outer_true_resid, , sview<double>(h->fine, h->fine.s_val64), Z, h->bp, h->xp, h->tp, R);
+  finish<1>(h, R);
+}
+
+// the residual vector is the true residual just formed
+static void outer_restart(amg_hierarchy *h) {
+  QA_RUN(h, kBlock, nblk(h->n), 0, k_cast, QA_T(double, double), h->n, h->tp, h->rp);
+}
+
+// true residual and the solution in the caller's numbering
+static void outer_end(amg_hierarchy *h, double *x) {
+  outer_true_resid(h);
+  QA_RUN(h, kBlock, nblk(h->n), 0, k_scatter_back, QA_T(double, double), h->n, h->fine.perm, h->xp, x);
+}
+
 static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, double tol, amg_info *info) {
   const auto t0 = std::chrono::steady_clock::now();
   const int64_t n = h->n;
-  const FineLevel &F = h->fine;
   hipStream_t s = h->stream;
-  const int L0 = h->nlev;  // outer scalar block
-  const double *osc = h->scal + static_cast<size_t>(L0) * kScalars;
-  const SliceSched Zall = slice_sched(F, 0, F.ncolor);
-  const unsigned nsl_blocks = sched_grid(Zall);
-  SellView<double> A64 = sview<double>(F, F.s_val64);
+  const double *osc = h->scal + static_cast<size_t>(h->nlev) * kScalars;
   amg_info inf{};
   inf.setup_ms = h->setup_ms;
 
-  k_gather<double, double><<<nblk(n), kBlock, 0, s>>>(n, F.perm, b, h->bp);
-  k_dot<double><<<nred(n), kBlock, 0, s>>>(n, h->bp, h->bp, red(h, L0, EPI_STORE, O_BB));
-  finish<1>(h, nred(n), red(h, L0, EPI_STORE, O_BB));
-  k_fill<double><<<nblk(n), kBlock, 0, s>>>(n, h->xp, 0.0);
+  outer_start(h, b);
   QA_LAUNCH_CHECK();
   QA_TRY(read_scalars(h, O_BB, 1));
   const double bn = std::sqrt(h->host_scal[O_BB]);
   if (bn == 0.0) {
-    k_fill<double><<<nblk(n), kBlock, 0, s>>>(n, x, 0.0);
+    QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, x, 0.0);
     QA_HIP(hipStreamSynchronize(s));
     inf.solve_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     if (info) *info = inf;
     return AMG_OK;
   }
-  QA_HIP(hipMemcpyAsync(h->rp, h->bp, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
   amg_status st = AMG_ERR_NOCONV;
   int it = 0;
   bool have_prev = false;
   double *p = h->pp, *q = h->qp, *pprev = h->pprev, *qprev = h->qprev;
-  const int prec = h->precision;
   const bool all_dirs = h->opt.outer_mmax < 0;
   int stored = 0;  // all-directions form: directions kept since the start or the last restart
   while (it < h->opt.max_iters) {
-    QA_TRY(precond_apply(h, prec, h->rp, h->zp));
     if (all_dirs) {
+      QA_TRY(precond_apply(h, h->precision, h->rp, h->zp));
       QA_TRY(outer_dirs_reserve(h, stored + 1));
       p = h->dir_p[stored];
       q = h->dir_q[stored];
       for (int j = 0; j < stored; j++) {
-        const Red R{h->partials, h->dir_zq, EPI_STORE, j};
-        k_dot<double><<<nred(n), kBlock, 0, s>>>(n, h->zp, h->dir_q[j], R);
-        finish<1>(h, nred(n), R);
+        const Red R{h->partials, h->dir_zq, EPI_STORE, j, nred(n)};
+        QA_RUN(h, kBlock, R.nb, 0, k_dot, QA_T(double), n, h->zp, h->dir_q[j], R);
+        finish<1>(h, R);
       }
       k_outer_dir_all<<<nblk(n), kBlock, 0, s>>>(n, h->zp, h->dir_pp, h->dir_zq, h->dir_d, stored, p);
+      outer_step(h, p, q);
     } else {
-      const bool use_beta = have_prev && h->opt.outer_mmax == 1;
-      if (use_beta) {
-        k_dot<double><<<nred(n), kBlock, 0, s>>>(n, h->zp, qprev, red(h, L0, EPI_OUT_BETA));
-        finish<1>(h, nred(n), red(h, L0, EPI_OUT_BETA));
-      }
-      k_outer_dir<double><<<nblk(n), kBlock, 0, s>>>(n, osc, h->zp, pprev, p, use_beta ? 1 : 0);
+      QA_TRY(outer_iterate(h, p, q, pprev, qprev, have_prev && h->opt.outer_mmax == 1));
     }
-    launch_timed(h, KK_SPMV64, k_outer_spmv_dot, nsl_blocks, A64, Zall, static_cast<const double *>(p), q,
-                 static_cast<const double *>(h->rp), red(h, L0, EPI_OUT_ALPHA));
-    finish<2>(h, nsl_blocks, red(h, L0, EPI_OUT_ALPHA));
-    k_outer_update<<<nred(n), kBlock, 0, s>>>(n, osc, p, q, h->xp, h->rp, red(h, L0, EPI_STORE, O_RR));
-    finish<1>(h, nred(n), red(h, L0, EPI_STORE, O_RR));
     QA_LAUNCH_CHECK();
     QA_TRY(read_scalars(h, 0, O_BB));
     if (h->host_scal[O_BREAK] != 0.0) {
@@ -3857,24 +4062,20 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
       std::swap(q, qprev);
     }
     if (std::sqrt(h->host_scal[O_RR]) <= tol * bn) {
-      k_outer_true_resid<<<nsl_blocks, kBlock, 0, s>>>(A64, Zall, h->bp, h->xp, h->tp,
-                                                        red(h, L0, EPI_STORE, O_TT));
-      finish<1>(h, nsl_blocks, red(h, L0, EPI_STORE, O_TT));
+      outer_true_resid(h);
       QA_LAUNCH_CHECK();
       QA_TRY(read_scalars(h, O_TT, 1));
       if (std::sqrt(h->host_scal[O_TT]) <= tol * bn) {
         st = AMG_OK;
         break;
       }
-      QA_HIP(hipMemcpyAsync(h->rp, h->tp, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
+      outer_restart(h);
       have_prev = false;
       stored = 0;
       inf.restarts++;
     }
   }
-  k_outer_true_resid<<<nsl_blocks, kBlock, 0, s>>>(A64, Zall, h->bp, h->xp, h->tp, red(h, L0, EPI_STORE, O_TT));
-  finish<1>(h, nsl_blocks, red(h, L0, EPI_STORE, O_TT));
-  k_scatter_back<double, double><<<nblk(n), kBlock, 0, s>>>(n, F.perm, h->xp, x);
+  outer_end(h, x);
   QA_LAUNCH_CHECK();
   QA_TRY(read_scalars(h, O_TT, 1));
   inf.iters = it;
@@ -3882,6 +4083,174 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
   inf.solve_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   if (info) *info = inf;
   return st;
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Several systems in step. A small system's iteration is a chain of short launches that leave most of the chip idle, so
+// a batch runs one chain for all: every system records its pieces of the outer iteration once, and each launch takes
+// the systems that are at that step (run_lists). A system runs the kernels, grids and reductions of amg_solve, so its
+// result is amg_solve's bit for bit, whatever else is in the batch. After each iteration the scalars of all systems go
+// to pinned host memory by one launch, and the host drops those that are done.
+// A whole-solve workgroup is bound by one CU's gathers (about 50 clocks per 64-lane gather) and by latency: eight systems
+// of 10,000 to 63,504 unknowns (FP32 preconditioner) took 37.2 ms so, 2.6 ms per iteration of the largest; in step they
+// take 6.0, bound by the launches' chain (about 70 in an iteration).
+
+enum { LL_START = 0, LL_ITER = 1, LL_CHECK = 5, LL_RESTART = 6, LL_END = 7, LL_ZERO = 8, LL_COUNT = 9 };
+struct BatchLists {
+  LaunchList list[LL_COUNT];  // LL_ITER + 2 * parity + (a kept direction)
+};
+
+void free_batch_lists(amg_hierarchy *h) {
+  delete h->batch_lists;
+  h->batch_lists = nullptr;
+}
+
+// the outer iteration's scalars to pinned host memory
+__device__ __forceinline__ void k_report_body(const double *sc, double *host) {
+  if (threadIdx.x <= O_BB) host[threadIdx.x] = sc[threadIdx.x];
+}
+__global__ void __launch_bounds__(64) k_report(const double *sc, double *host) { k_report_body(sc, host); }
+
+struct BatchSys {
+  amg_hierarchy *h;
+  const double *b;
+  double *x;
+  double tol, bn;
+  int iters, restarts, want;  // want: the list to run next, or -1
+  bool prev;                  // a direction is kept
+  int par;                    // which pair of direction vectors is the new one
+  amg_status st;
+};
+
+// list `what` of a system, recorded when it is first needed in a call
+static amg_status batch_list(BatchSys &Y, int what, LaunchList *&list) {
+  amg_hierarchy *h = Y.h;
+  list = &h->batch_lists->list[what];
+  if (!list->steps.empty()) return AMG_OK;
+  struct Scope {  // recording ends on every path
+    amg_hierarchy *h;
+    ~Scope() { h->recording = nullptr; }
+  } scope{h};
+  h->recording = list;
+  amg_status st = AMG_OK;
+  bool report = true;
+  if (what == LL_START) {
+    outer_start(h, Y.b);
+  } else if (what == LL_CHECK) {
+    outer_true_resid(h);
+  } else if (what == LL_RESTART) {
+    outer_restart(h);
+    report = false;
+  } else if (what == LL_END) {
+    outer_end(h, Y.x);
+  } else if (what == LL_ZERO) {
+    QA_RUN(h, kBlock, nblk(h->n), 0, k_fill, QA_T(double), h->n, Y.x, 0.0);
+    report = false;
+  } else {
+    double *P[2] = {h->pp, h->pprev}, *Q[2] = {h->qp, h->qprev};
+    const int i = (what - LL_ITER) >> 1;
+    st = outer_iterate(h, P[i], Q[i], P[1 - i], Q[1 - i], ((what - LL_ITER) & 1) != 0);
+  }
+  if (report)
+    QA_RUN(h, 64, 1, 0, k_report, , static_cast<const double *>(h->scal + static_cast<size_t>(h->nlev) * kScalars),
+           h->host_scal);
+  return st;
+}
+
+// run the wanted lists of all systems that have one
+static amg_status batch_run(BatchSys *Y, int m, ListCursor *cur, const unsigned char **args, const LaunchStep **steps,
+                            hipStream_t s) {
+  int k = 0;
+  for (int i = 0; i < m; i++) {
+    if (Y[i].want < 0) continue;
+    LaunchList *list = nullptr;
+    QA_TRY(batch_list(Y[i], Y[i].want, list));
+    cur[k++] = ListCursor{list, 0};
+  }
+  QA_HIP(run_lists(cur, args, steps, k, s));
+  QA_HIP(hipStreamSynchronize(s));
+  return AMG_OK;
+}
+
+// Solve the m systems Y on stream s; cur, args, steps: room for m entries each.
+static amg_status solve_many_lists(BatchSys *Y, int m, ListCursor *cur, const unsigned char **args, const LaunchStep **steps,
+                             hipStream_t s) {
+  for (int i = 0; i < m; i++) {
+    amg_hierarchy *h = Y[i].h;
+    if (!h->batch_lists) h->batch_lists = new BatchLists;
+    for (LaunchList &l : h->batch_lists->list) l.clear();
+    Y[i].want = LL_START;
+  }
+  auto run = [&]() { return batch_run(Y, m, cur, args, steps, s); };
+  QA_TRY(run());
+  for (int i = 0; i < m; i++) {
+    BatchSys &S = Y[i];
+    S.bn = std::sqrt(S.h->host_scal[O_BB]);
+    S.st = S.bn == 0.0 ? AMG_OK : AMG_ERR_NOCONV;
+    S.want = S.bn == 0.0 || S.h->opt.max_iters <= 0 ? -1 : LL_ITER;
+  }
+  auto any = [&]() {
+    for (int i = 0; i < m; i++)
+      if (Y[i].want >= 0) return true;
+    return false;
+  };
+  while (any()) {
+    QA_TRY(run());
+    bool check = false;
+    for (int i = 0; i < m; i++) {
+      BatchSys &S = Y[i];
+      if (S.want < 0) continue;
+      const double *sc = S.h->host_scal;
+      if (sc[O_BREAK] != 0.0) {
+        S.st = AMG_ERR_BREAKDOWN;
+        S.want = -1;
+        continue;
+      }
+      S.iters++;
+      S.prev = true;
+      S.par ^= 1;
+      S.want = std::sqrt(sc[O_RR]) <= S.tol * S.bn ? LL_CHECK : LL_ITER;
+      if (S.want == LL_CHECK) check = true;
+    }
+    if (check) {  // the true residual of those at the tolerance; the others pause
+      for (int i = 0; i < m; i++)
+        if (Y[i].want == LL_ITER) Y[i].want = -2;
+      QA_TRY(run());
+      bool restart = false;
+      for (int i = 0; i < m; i++) {
+        BatchSys &S = Y[i];
+        if (S.want != LL_CHECK) continue;
+        if (std::sqrt(S.h->host_scal[O_TT]) <= S.tol * S.bn) {
+          S.st = AMG_OK;
+          S.want = -1;
+        } else {
+          S.want = LL_RESTART;
+          S.prev = false;
+          S.restarts++;
+          restart = true;
+        }
+      }
+      if (restart) QA_TRY(run());
+      for (int i = 0; i < m; i++)
+        if (Y[i].want != -1) Y[i].want = LL_ITER;
+    }
+    for (int i = 0; i < m; i++) {
+      BatchSys &S = Y[i];
+      if (S.want < 0) continue;
+      if (S.iters >= S.h->opt.max_iters) S.want = -1;
+      else S.want = LL_ITER + 2 * S.par + (S.prev && S.h->opt.outer_mmax == 1 ? 1 : 0);
+    }
+  }
+  for (int i = 0; i < m; i++) Y[i].want = Y[i].bn == 0.0 ? LL_ZERO : LL_END;
+  return run();
+}
+static amg_status solve_many(BatchSys *Y, int m, ListCursor *cur, const unsigned char **args, const LaunchStep **steps,
+                             hipStream_t s) {
+  try {
+    return solve_many_lists(Y, m, cur, args, steps, s);
+  } catch (const std::bad_alloc &) {  // the lists' storage
+    return AMG_ERR_NOMEM;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -3895,11 +4264,11 @@ static amg_status level_smooth_t(amg_hierarchy *h, int level, const double *f, d
     const FineLevel &F = h->fine;
     const int64_t n = F.n;
     T *ff = W[0].f, *xx = W[0].u;
-    k_gather<double, T><<<nblk(n), kBlock, 0, s>>>(n, F.perm, f, ff);
-    k_gather<double, T><<<nblk(n), kBlock, 0, s>>>(n, F.perm, x, xx);
+    QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, f, ff);
+    QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, x, xx);
     const int nc = h->fine.ncolor;
     for (int c = 0; c < nc; c++) fine_phase<T>(h, ff, xx, W[0].d, forward ? c : nc - 1 - c, forward != 0, false);
-    k_scatter_back<T, double><<<nblk(n), kBlock, 0, s>>>(n, F.perm, xx, x);
+    QA_RUN(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(T, double), n, F.perm, xx, x);
   } else {
     const QuadLevel &Q = h->lev[level];
     const int dim = h->dim, nc = 1 << dim;
@@ -3929,10 +4298,10 @@ static amg_status level_spmv_t(amg_hierarchy *h, int level, const double *x, dou
     const FineLevel &F = h->fine;
     const int64_t n = F.n;
     T *xx = W[0].f, *yy = W[0].u;
-    k_gather<double, T><<<nblk(n), kBlock, 0, s>>>(n, F.perm, x, xx);
+    QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, x, xx);
     const SliceSched Z = slice_sched(F, 0, F.ncolor);
     k_fine_apply<T><<<sched_grid(Z), kBlock, 0, s>>>(sview<T>(F, P<T>::sval(F)), Z, xx, yy);
-    k_scatter_back<T, double><<<nblk(n), kBlock, 0, s>>>(n, F.perm, yy, y);
+    QA_RUN(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(T, double), n, F.perm, yy, y);
     QA_LAUNCH_CHECK();
     QA_HIP(hipStreamSynchronize(s));
     return AMG_OK;
@@ -3945,8 +4314,8 @@ static amg_status level_spmv_t(amg_hierarchy *h, int level, const double *x, dou
     k_capply3<T><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), xx, yy);
   } else {
     // reuse the dot kernel's SpMV (the inner products are discarded into the scratch slot of level 0)
-    k_cspmv_dot<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), xx, yy, xx, red(h, h->nlev, EPI_STORE, 15));
-    finish<2>(h, nred(Q.n), red(h, h->nlev, EPI_STORE, 15));
+    QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_dot, QA_T(T), qview<T>(Q), xx, yy, xx, red(h, h->nlev, nred(Q.n), EPI_STORE, 15));
+    finish<2>(h, red(h, h->nlev, nred(Q.n), EPI_STORE, 15));
   }
   k_lex_to_q<T, double><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, yy, y, 1, dim);
   QA_LAUNCH_CHECK();
@@ -3975,9 +4344,9 @@ extern "C" amg_status amg_apply_precond(amg_hierarchy *h, const double *r, doubl
   QA_HIP(hipSetDevice(h->device));
   const int64_t n = h->n;
   hipStream_t s = h->stream;
-  k_gather<double, double><<<nblk(n), kBlock, 0, s>>>(n, h->fine.perm, r, h->tp);
+  QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, double), n, h->fine.perm, r, h->tp);
   QA_TRY(precond_apply(h, precision, h->tp, h->zp));
-  k_scatter_back<double, double><<<nblk(n), kBlock, 0, s>>>(n, h->fine.perm, h->zp, z);
+  QA_RUN(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(double, double), n, h->fine.perm, h->zp, z);
   QA_LAUNCH_CHECK();
   QA_HIP(hipStreamSynchronize(s));
   return AMG_OK;
@@ -4103,6 +4472,48 @@ static amg_status check_batch_args(amg_hierarchy *const *hs, const double *const
   return AMG_OK;
 }
 
+// A batch's systems by route: ids[0], ids[1] the whole-solve workgroups of either precision, ids[2] the systems that run
+// in step. Host memory of the call; with the lists' cursors, room for all systems.
+struct BatchWork {
+  int *ids[3];
+  int count[3];
+  BatchSys *sys;
+  ListCursor *cur;
+  const unsigned char **args;
+  const LaunchStep **steps;
+};
+static int batch_route(const amg_hierarchy *h) {  // 0 to 2 as above, -1: amg_solve
+  const int pi = h->precision;
+  if (!h->use_batch) return -1;
+  return h->in_step[pi] ? 2 : (h->wg_nops[pi] > 0 ? pi : -1);
+}
+
+// the systems of W.ids[2], their results into st / inf
+static amg_status batch_in_step(amg_hierarchy *const *hs, const double *const *b, double *const *x, const double *tol,
+                                const BatchWork &W, std::chrono::steady_clock::time_point t0, amg_status *st,
+                                amg_info *inf) {
+  const int m = W.count[2];
+  if (m == 0) return AMG_OK;
+  QA_HIP(hipSetDevice(hs[W.ids[2][0]]->device));
+  for (int j = 0; j < m; j++) {
+    const int i = W.ids[2][j];
+    W.sys[j] = BatchSys{hs[i], b[i], x[i], tol[i], 0.0, 0, 0, -1, false, 0, AMG_OK};
+  }
+  QA_TRY(solve_many(W.sys, m, W.cur, W.args, W.steps, hs[W.ids[2][0]]->stream));
+  const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+  for (int j = 0; j < m; j++) {
+    const int i = W.ids[2][j];
+    const BatchSys &S = W.sys[j];
+    st[i] = S.st;
+    inf[i].iters = S.iters;
+    inf[i].restarts = S.restarts;
+    inf[i].relres = S.bn == 0.0 ? 0.0 : std::sqrt(S.h->host_scal[O_TT]) / S.bn;
+    inf[i].setup_ms = S.h->setup_ms;
+    inf[i].solve_ms = ms;
+  }
+  return AMG_OK;
+}
+
 // ---------------------------------------------------------------------------------------------------------------
 // Batch solve without allocation. The system descriptors and info words of the whole-solve launches live in a
 // file-scope device array instead of memory allocated per call. The array's name is only a host-side handle: its
@@ -4135,7 +4546,11 @@ struct NoAllocStage {
   WgSys<double> sys64[kNoAllocMaxSystems];
   WgSys<float> sys32[kNoAllocMaxSystems];
   double out[4 * kNoAllocMaxSystems];
-  int ids[2][kNoAllocMaxSystems];
+  int ids[3][kNoAllocMaxSystems];
+  BatchSys sys[kNoAllocMaxSystems];
+  ListCursor cur[kNoAllocMaxSystems];
+  const unsigned char *args[kNoAllocMaxSystems];
+  const LaunchStep *steps[kNoAllocMaxSystems];
   amg_status st[kNoAllocMaxSystems];
   amg_info inf[kNoAllocMaxSystems];
 };
@@ -4154,12 +4569,17 @@ extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *co
     QA_HIP(hipSetDevice(hs[i]->device));
     QA_HIP(hipStreamSynchronize(hs[i]->stream));
   }
-  std::vector<int> small[2], large;
+  std::vector<int> ids[3], large;
   for (int32_t i = 0; i < count; i++) {
-    const int pi = hs[i]->precision;
-    if (hs[i]->use_batch && hs[i]->wg_nops[pi] > 0) small[pi].push_back(i);
+    const int route = batch_route(hs[i]);
+    if (route >= 0) ids[route].push_back(i);
     else large.push_back(i);
   }
+  const size_t m = ids[2].size();
+  std::vector<BatchSys> sys(m);
+  std::vector<ListCursor> cur(m);
+  std::vector<const unsigned char *> args(m);
+  std::vector<const LaunchStep *> steps(m);
   std::vector<amg_status> st(count, AMG_OK);
   std::vector<amg_info> inf(count);
   std::vector<std::thread> threads;
@@ -4168,21 +4588,31 @@ extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *co
       if (hipSetDevice(hs[i]->device) != hipSuccess) { st[i] = AMG_ERR_DEVICE; return; }
       st[i] = amg_solve(hs[i], b[i], x[i], tol[i], &inf[i]);
     });
-  amg_status launch_st = AMG_OK;
-  for (int pi = 0; pi < 2 && launch_st == AMG_OK; pi++) {
-    if (small[pi].empty()) continue;
-    std::vector<double> out;
-    launch_st = pi == 0 ? launch_wg_batch<double>(hs, b, x, tol, small[pi], out)
-                        : launch_wg_batch<float>(hs, b, x, tol, small[pi], out);
-    if (launch_st != AMG_OK) break;
-    wg_results(hs, small[pi].data(), static_cast<int>(small[pi].size()), out.data(),
-               std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count(), st.data(),
-               inf.data());
-  }
+  // the whole-solve workgroups, beside the systems that run in step where there are both
+  amg_status wg_st = AMG_OK, step_st = AMG_OK;
+  auto whole = [&]() {
+    for (int pi = 0; pi < 2 && wg_st == AMG_OK; pi++) {
+      if (ids[pi].empty()) continue;
+      std::vector<double> out;
+      wg_st = pi == 0 ? launch_wg_batch<double>(hs, b, x, tol, ids[pi], out)
+                      : launch_wg_batch<float>(hs, b, x, tol, ids[pi], out);
+      if (wg_st != AMG_OK) break;
+      wg_results(hs, ids[pi].data(), static_cast<int>(ids[pi].size()), out.data(),
+                 std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count(), st.data(),
+                 inf.data());
+    }
+  };
+  if (m > 0 && ids[0].size() + ids[1].size() > 0) threads.emplace_back(whole);
+  else whole();
+  const BatchWork W{{ids[0].data(), ids[1].data(), ids[2].data()}, {0, 0, static_cast<int>(m)},
+                    sys.data(), cur.data(), args.data(), steps.data()};
+  step_st = batch_in_step(hs, b, x, tol, W, t0, st.data(), inf.data());
   for (auto &t : threads) t.join();
-  amg_status first = launch_st;
+  amg_status first = wg_st != AMG_OK ? wg_st : step_st;
   for (int32_t i = 0; i < count; i++) {
-    if (launch_st != AMG_OK && std::find(large.begin(), large.end(), i) == large.end()) st[i] = launch_st;
+    const int route = batch_route(hs[i]);
+    if (route == 2 && step_st != AMG_OK) st[i] = step_st;
+    if ((route == 0 || route == 1) && wg_st != AMG_OK) st[i] = wg_st;
     inf[i].status = st[i];
     if (info) info[i] = inf[i];
     if (first == AMG_OK && st[i] != AMG_OK) first = st[i];
@@ -4195,16 +4625,14 @@ extern "C" amg_status amg_solve_batch_noalloc(amg_hierarchy *const *hs, const do
   QA_TRY(check_batch_args(hs, b, x, tol, count));
   if (count > kNoAllocMaxSystems) return AMG_ERR_INVALID;
   if (count == 0) return AMG_OK;
-  for (int32_t i = 0; i < count; i++) {
-    const int pi = hs[i]->precision;
-    if (!(hs[i]->use_batch && hs[i]->wg_nops[pi] > 0)) return AMG_ERR_INVALID;  // only whole-solve systems
-  }
+  for (int32_t i = 0; i < count; i++)
+    if (batch_route(hs[i]) < 0) return AMG_ERR_INVALID;
   std::lock_guard<std::mutex> lock(g_noalloc_mu);
   NoAllocStage &G = g_stage;
-  int nsmall[2] = {0, 0};
+  BatchWork W{{G.ids[0], G.ids[1], G.ids[2]}, {0, 0, 0}, G.sys, G.cur, G.args, G.steps};
   for (int32_t i = 0; i < count; i++) {
-    const int pi = hs[i]->precision;
-    G.ids[pi][nsmall[pi]++] = i;
+    const int route = batch_route(hs[i]);
+    W.ids[route][W.count[route]++] = i;
     G.st[i] = AMG_OK;
     G.inf[i] = amg_info{};
   }
@@ -4214,19 +4642,22 @@ extern "C" amg_status amg_solve_batch_noalloc(amg_hierarchy *const *hs, const do
   if (!base) return AMG_ERR_DEVICE;
   for (int32_t i = 0; i < count; i++) QA_HIP(hipStreamSynchronize(hs[i]->stream));
   // the FP64 group's descriptors first, the FP32 group's after them: disjoint parts of the array
-  const size_t off[2] = {0, wg_batch_bytes<double>(nsmall[0])};
+  const size_t off[2] = {0, wg_batch_bytes<double>(W.count[0])};
   amg_status first = AMG_OK;
   for (int pi = 0; pi < 2 && first == AMG_OK; pi++) {
-    if (nsmall[pi] == 0) continue;
-    first = pi == 0 ? launch_wg_batch_in<double>(hs, b, x, tol, G.ids[0], nsmall[0], base + off[0], G.sys64, G.out)
-                    : launch_wg_batch_in<float>(hs, b, x, tol, G.ids[1], nsmall[1], base + off[1], G.sys32, G.out);
+    if (W.count[pi] == 0) continue;
+    first = pi == 0
+                ? launch_wg_batch_in<double>(hs, b, x, tol, G.ids[0], W.count[0], base + off[0], G.sys64, G.out)
+                : launch_wg_batch_in<float>(hs, b, x, tol, G.ids[1], W.count[1], base + off[1], G.sys32, G.out);
     if (first == AMG_OK)
-      wg_results(hs, G.ids[pi], nsmall[pi], G.out,
+      wg_results(hs, G.ids[pi], W.count[pi], G.out,
                  std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count(), G.st,
                  G.inf);
   }
+  if (first == AMG_OK) first = batch_in_step(hs, b, x, tol, W, t0, G.st, G.inf);
+  const amg_status run_st = first;
   for (int32_t i = 0; i < count; i++) {
-    if (first != AMG_OK) G.st[i] = first;
+    if (run_st != AMG_OK) G.st[i] = run_st;
     G.inf[i].status = G.st[i];
     if (info) info[i] = G.inf[i];
     if (first == AMG_OK && G.st[i] != AMG_OK) first = G.st[i];
