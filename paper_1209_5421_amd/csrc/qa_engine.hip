@@ -141,31 +141,12 @@ __device__ __forceinline__ void for_16(F f) {
   f(IC<8>{}); f(IC<9>{}); f(IC<10>{}); f(IC<11>{}); f(IC<12>{}); f(IC<13>{}); f(IC<14>{}); f(IC<15>{});
 }
 
-__device__ __forceinline__ float fe_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fe_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
 // the thread index, opaque to the optimiser: places derived from it on the lower levels are formed when such a level
 // begins rather than kept in registers across the launch
 __device__ __forceinline__ int fe_tid() {
   int t;
   asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(static_cast<int>(threadIdx.x)));
   return t;
-}
-
-// n / d from rd = 1 / d rounded to nearest: q = n rd, then q + (n - q d) rd with fused multiply-adds (Markstein, IBM
-// Journal of Research and Development 34, 1990)
-template <class T>
-__device__ __forceinline__ T fe_div(T n, T d, T rd) {
-  const T q = n * rd;
-  return fe_fma(fe_fma(-q, d, n), rd, q);
-}
-
-// lane n's double in every lane of each row of 16 lanes (row_newbcast)
-template <int N>
-__device__ __forceinline__ double fe_bcast(double x) {
-  const long u = __builtin_bit_cast(long, x);
-  const long r = __builtin_amdgcn_update_dpp(0L, u, 0x150 + N, 0xf, 0xf, true);
-  return __builtin_bit_cast(double, r);
 }
 
 // Order between the sub-steps of the one-wavefront B~: a wavefront's LDS accesses are performed in issue order, so
@@ -251,7 +232,7 @@ __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T 
         if constexpr (TOP && p)
           if (half == 0) R.rd[t][c] = T(1) / R.a[t][c][0];
         const T acc = fe_row<T, K, c, p>(R.a[t][c], R.u[t], pl + t * second);
-        const T dl = fe_div(R.f[t][c] - acc, R.a[t][c][0], R.rd[t][c]);
+        const T dl = quotient(R.f[t][c] - acc, R.a[t][c][0], R.rd[t][c]);
         if constexpr (p) R.u[t][c] = dl;
         else R.u[t][c] += dl;
         pl[t * second + c * G::PP + own] = R.u[t][c];
@@ -265,7 +246,7 @@ __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T 
       for (int t = 0; t < TR; t++) {
         if constexpr (TOP)
           if (half == 0) R.rd[t][0] = T(1) / R.a[t][0][0];
-        R.u[t][0] = fe_div(R.f[t][0], R.a[t][0][0], R.rd[t][0]);
+        R.u[t][0] = quotient(R.f[t][0], R.a[t][0][0], R.rd[t][0]);
         A[t * second + own] = R.u[t][0];
       }
     fe_sync<WAVE>();
@@ -308,7 +289,7 @@ __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T 
           }
           acc += R.a[t][3][s] * x;
         });
-        R.u[t][3] += fe_div(R.f[t][3] - acc, R.a[t][3][0], R.rd[t][3]);
+        R.u[t][3] += quotient(R.f[t][3] - acc, R.a[t][3][0], R.rd[t][3]);
         T *ql = B + t * second + own;
         for_colors([&](auto cc) {
           constexpr int c = decltype(cc)::value;
@@ -528,8 +509,8 @@ __device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
               constexpr int n = decltype(nn)::value;
               if constexpr (n % 2 == 0) {
                 const double2 x = Ai[(n / 2) * 64];
-                acc[n % 4] += x.x * fe_bcast<n>(gr);
-                acc[n % 4 + 1] += x.y * fe_bcast<n + 1>(gr);
+                acc[n % 4] += x.x * bcast_of<n, 16>(gr);
+                acc[n % 4 + 1] += x.y * bcast_of<n + 1, 16>(gr);
               }
             });
             const double mine = (acc[0] + acc[1]) + (acc[2] + acc[3]);
@@ -548,7 +529,7 @@ __device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
           double acc[4] = {0.0, 0.0, 0.0, 0.0};
           for_16([&](auto nn) {
             constexpr int n = decltype(nn)::value;
-            acc[n % 4] += hget(nn) * fe_bcast<n>(gr);
+            acc[n % 4] += hget(nn) * bcast_of<n, 16>(gr);
           });
           ps[64 * part + lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
         }

@@ -6,6 +6,33 @@
 
 namespace qa {
 
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// n / d from rd = 1 / d rounded to nearest: q = n rd, then q + (n - q d) rd with fused multiply-adds (Markstein, IBM
+// Journal of Research and Development 34, 1990)
+template <class T>
+__device__ __forceinline__ T quotient(T n, T d, T rd) {
+  const T q = n * rd;
+  return fma_of(fma_of(-q, d, n), rd, q);
+}
+
+// lane N's value in every lane of each row of 16 lanes (row_newbcast); with G = 8, lane N's of each half row
+template <int N, int G>
+__device__ __forceinline__ float bcast_of(float x) {
+  const int u = __builtin_bit_cast(int, x);
+  int r = __builtin_amdgcn_update_dpp(0, u, 0x150 + N, 0xf, 0xf, true);
+  if constexpr (G == 8) r = __builtin_amdgcn_update_dpp(r, u, 0x158 + N, 0xf, 0xc, false);
+  return __builtin_bit_cast(float, r);
+}
+template <int N, int G>
+__device__ __forceinline__ double bcast_of(double x) {
+  const long u = __builtin_bit_cast(long, x);
+  long r = __builtin_amdgcn_update_dpp(0L, u, 0x150 + N, 0xf, 0xf, true);
+  if constexpr (G == 8) r = __builtin_amdgcn_update_dpp(r, u, 0x158 + N, 0xf, 0xc, false);
+  return __builtin_bit_cast(double, r);
+}
+
 // a lane's double moved by a DPP lane pattern (two 32-bit moves)
 template <int Ctrl>
 __device__ __forceinline__ double dpp_f64(double x) {
