@@ -45,6 +45,7 @@ struct Red {
   int epi;
   int slot;
   unsigned nb;  // workgroups of the launch
+  double *host;  // not null: the outer scalars (sc) also go to this pinned host memory
 };
 
 // sum over the workgroup (fixed order); valid in thread 0
@@ -118,6 +119,14 @@ __device__ inline void epilogue(const double *acc, const Red &R) {
       break;
     default:
       sc[R.slot] = acc[0];
+  }
+  if (R.host) {
+    double v[O_BB + 1];
+#pragma unroll
+    for (int j = 0; j <= O_BB; j++) v[j] = sc[j];
+#pragma unroll
+    for (int j = 0; j <= O_BB; j++) R.host[j] = v[j];
+    __threadfence_system();
   }
 }
 
@@ -2166,17 +2175,17 @@ __global__ void __launch_bounds__(kBlock) k_update1(int64_t n, const double *__r
   k_update1_body<T>(n, sc, p0, q0, g, e, r);
 }
 
-template <class T>
-__device__ __forceinline__ void k_dot_body(int64_t n, const T *__restrict__ a, const T *__restrict__ b, Red R) {
+template <class T, class S>
+__device__ __forceinline__ void k_dot_body(int64_t n, const T *__restrict__ a, const S *__restrict__ b, Red R) {
   double v[1] = {0.0};
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
        i += static_cast<int64_t>(R.nb) * kBlock)
     v[0] += static_cast<double>(a[i]) * static_cast<double>(b[i]);
   reduce_finish<1>(v, R);
 }
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_dot(int64_t n, const T *__restrict__ a, const T *__restrict__ b, Red R) {
-  k_dot_body<T>(n, a, b, R);
+template <class T, class S>
+__global__ void __launch_bounds__(kBlock) k_dot(int64_t n, const T *__restrict__ a, const S *__restrict__ b, Red R) {
+  k_dot_body<T, S>(n, a, b, R);
 }
 
 // e += a1 (p1 + beta p0): the last update of Algorithm 2.1 with the direction formed on the fly
@@ -2279,10 +2288,22 @@ __global__ void __launch_bounds__(kBlock) k_outer_true_resid(SellView<double> S,
   k_outer_true_resid_body(S, Z, b, x, t, R);
 }
 
+// The next B^_F starts from the residual r in the preconditioner's precision, f (null in FP64, which reads r itself), and
+// from u = 0; the kernels that form r write both. Each launch costs an iteration 3 to 5 us: with the
+// conversions, the zeroing and the scalars' way to the host as launches and a copy of their own, a solve took 1.58 ms
+// instead of 1.47 (4,096 unknowns, FP64), 4.09 instead of 3.97 (100,000, FP32) and 8.91 instead of 8.73 (1M, FP32).
+template <class T>
+__device__ __forceinline__ void bhat_input(int64_t i, double r, T *__restrict__ f, T *__restrict__ u) {
+  if constexpr (!std::is_same<T, double>::value) f[i] = static_cast<T>(r);
+  u[i] = T(0);
+}
+
 // x += alpha p, r -= alpha q, with (r, r)
+template <class T>
 __device__ __forceinline__ void k_outer_update_body(int64_t n, const double *__restrict__ sc,
                                                     const double *__restrict__ p, const double *__restrict__ q,
-                                                    double *__restrict__ x, double *__restrict__ r, Red R) {
+                                                    double *__restrict__ x, double *__restrict__ r, T *__restrict__ f,
+                                                    T *__restrict__ u, Red R) {
   const double a = sc[O_ALPHA];
   double v[1] = {0.0};
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
@@ -2290,14 +2311,33 @@ __device__ __forceinline__ void k_outer_update_body(int64_t n, const double *__r
     x[i] += a * p[i];
     const double ri = r[i] - a * q[i];
     r[i] = ri;
+    bhat_input<T>(i, ri, f, u);
     v[0] += ri * ri;
   }
   reduce_finish<1>(v, R);
 }
+template <class T>
 __global__ void __launch_bounds__(kBlock) k_outer_update(int64_t n, const double *__restrict__ sc,
                                                          const double *__restrict__ p, const double *__restrict__ q,
-                                                         double *__restrict__ x, double *__restrict__ r, Red R) {
-  k_outer_update_body(n, sc, p, q, x, r, R);
+                                                         double *__restrict__ x, double *__restrict__ r,
+                                                         T *__restrict__ f, T *__restrict__ u, Red R) {
+  k_outer_update_body<T>(n, sc, p, q, x, r, f, u, R);
+}
+
+// r = src
+template <class T>
+__device__ __forceinline__ void k_outer_resid_body(int64_t n, const double *__restrict__ src, double *__restrict__ r,
+                                                   T *__restrict__ f, T *__restrict__ u) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double ri = src[i];
+  r[i] = ri;
+  bhat_input<T>(i, ri, f, u);
+}
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_outer_resid(int64_t n, const double *__restrict__ src,
+                                                        double *__restrict__ r, T *__restrict__ f, T *__restrict__ u) {
+  k_outer_resid_body<T>(n, src, r, f, u);
 }
 
 // p = z + beta pprev (beta from the scalar block when use_beta)
@@ -2415,7 +2455,13 @@ static SellView<T> sview(const FineLevel &F, const T *val) {
   return SellView<T>{F.slice_ptr, F.slice_row0, F.s_row, F.s_col, val};
 }
 static Red red(amg_hierarchy *h, int l, unsigned nb, int epi, int slot = 0) {
-  return Red{h->partials, h->scal + static_cast<size_t>(l) * kScalars, epi, slot, nb};
+  return Red{h->partials, h->scal + static_cast<size_t>(l) * kScalars, epi, slot, nb, nullptr};
+}
+// of an outer scalar, after which the host reads them
+static Red red_report(amg_hierarchy *h, unsigned nb, int slot) {
+  Red R = red(h, h->nlev, nb, EPI_STORE, slot);
+  R.host = h->host_scal;
+  return R;
 }
 
 // second stage of a multi-workgroup reduction (no-op for a single-workgroup launch)
@@ -3865,12 +3911,11 @@ static void fine_phase(amg_hierarchy *h, const T *f, T *u, T *d, int c, bool fwd
   }
 }
 
-// B^_F on the fine level (f, u in permuted numbering)
+// B^_F on the fine level (f, u in permuted numbering; u = 0 on entry)
 template <class T>
 static void bhat_fine(amg_hierarchy *h, const T *f, T *u) {
   const FineLevel &F = h->fine;
   LevelWork<T> &w = P<T>::W(h)[0];
-  QA_RUN(h, kBlock, nblk(F.n), 0, k_fill, QA_T(T), F.n, u, T(0));
   const int sweeps = h->opt.sweeps;
   const int nc = F.ncolor;
   // one sweep each way: the pre-smoothing's color rows are zero before their phase, and the post-smoothing's hold
@@ -3905,7 +3950,7 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
     const unsigned nb = static_cast<unsigned>(tile_grid(Q));
     const bool few = nb <= kFoldBlocks;
     bhat_coarse<T>(h, l, g, w.p0, Upd1<T>{}, nullptr, 1);
-    if (!two || !few) QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(4), Red{part, sc, EPI_ALPHA0, 0, nb});
+    if (!two || !few) QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(4), Red{part, sc, EPI_ALPHA0, 0, nb, nullptr});
     if (!two) {
       QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
       return false;
@@ -3914,7 +3959,7 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
                    Upd1<T>{sc, g, w.q0, w.p0, e, w.r, few ? part : nullptr, few ? static_cast<int>(nb) : 0}, nullptr, 2);
     if (few && fold && defer_update2) return true;
     QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(4),
-           Red{part, sc, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64, 0, nb});
+           Red{part, sc, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64, 0, nb, nullptr});
     if (!defer_update2) QA_RUN(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
     return false;
   }
@@ -3938,7 +3983,7 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
     const bool fold_beta = !Q.same_color_ovf || h->opt.sweeps == 1;
     bhat_coarse<T>(h, l, w.r, w.p1, upd, fold_beta ? w.q0 : nullptr);
     if (!fold_beta) {
-      QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
+      QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T, T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
       finish<1>(h, red(h, l, nred(Q.n), EPI_BETA));
     }
     QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_dir, QA_T(T), qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
@@ -4017,7 +4062,7 @@ static void btilde_oct(amg_hierarchy *h, int l, const T *g, T *e) {
   QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
   if (h->opt.inner_iters < 2) return;
   bhat_oct<T>(h, l, w.r, w.p1);
-  QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
+  QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T, T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
   finish<1>(h, red(h, l, nred(Q.n), EPI_BETA));
   k_cspmv_dir3<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
   finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA1));
@@ -4035,9 +4080,11 @@ amg_status precond_apply(amg_hierarchy *h, int precision, const double *r, doubl
   if (precision == 1) {
     LevelWork<float> &w = h->w32[0];
     QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(double, float), n, r, w.f);
+    QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(float), n, w.u, 0.f);
     bhat_fine<float>(h, w.f, w.u);
     QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(float, double), n, w.u, z);
   } else {
+    QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, z, 0.0);
     bhat_fine<double>(h, r, z);
   }
   QA_LAUNCH_CHECK();
@@ -4116,9 +4163,9 @@ double kernel_bytes(const amg_hierarchy *h, int kind) {
   return 0.0;
 }
 
-static amg_status read_scalars(amg_hierarchy *h, int first, int count) {
-  const double *src = h->scal + static_cast<size_t>(h->nlev) * kScalars + first;
-  QA_HIP(hipMemcpyAsync(h->host_scal + first, src, sizeof(double) * count, hipMemcpyDeviceToHost, h->stream));
+// the outer scalars that the last reduction reported
+static amg_status read_scalars(amg_hierarchy *h) {
+  QA_LAUNCH_CHECK();
   QA_HIP(hipStreamSynchronize(h->stream));
   return AMG_OK;
 }
@@ -4148,15 +4195,24 @@ static amg_status outer_dirs_reserve(amg_hierarchy *h, int count) {
 
 // Pieces of the outer iteration, launched or recorded. L0 = nlev is the outer scalar block.
 
+// r = src, and what B^_F starts from
+static void outer_resid(amg_hierarchy *h, const double *src) {
+  if (h->precision == 1)
+    QA_RUN(h, kBlock, nblk(h->n), 0, k_outer_resid, QA_T(float), h->n, src, h->rp, h->w32[0].f, h->w32[0].u);
+  else
+    QA_RUN(h, kBlock, nblk(h->n), 0, k_outer_resid, QA_T(double), h->n, src, h->rp, static_cast<double *>(nullptr),
+           h->zp);
+}
+
 // b in the permuted numbering with (b, b), x = 0, r = b
 static void outer_start(amg_hierarchy *h, const double *b) {
   const int64_t n = h->n;
-  const Red R = red(h, h->nlev, nred(n), EPI_STORE, O_BB);
+  const Red R = red_report(h, nred(n), O_BB);
   QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, double), n, h->fine.perm, b, h->bp);
-  QA_RUN(h, kBlock, nred(n), 0, k_dot, QA_T(double), n, h->bp, h->bp, R);
+  QA_RUN(h, kBlock, nred(n), 0, k_dot, QA_T(double, double), n, h->bp, h->bp, R);
   finish<1>(h, R);
   QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, h->xp, 0.0);
-  QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(double, double), n, h->bp, h->rp);
+  outer_resid(h, h->bp);
 }
 
 // q = A p, alpha, x += alpha p, r -= alpha q with (r, r)
@@ -4165,27 +4221,44 @@ static void outer_step(amg_hierarchy *h, double *p, double *q) {
   const int L0 = h->nlev;
   const double *osc = h->scal + static_cast<size_t>(L0) * kScalars;
   const SliceSched Z = slice_sched(h->fine, 0, h->fine.ncolor);
-  const Red ra = red(h, L0, sched_grid(Z), EPI_OUT_ALPHA), rr = red(h, L0, nred(n), EPI_STORE, O_RR);
+  const Red ra = red(h, L0, sched_grid(Z), EPI_OUT_ALPHA), rr = red_report(h, nred(n), O_RR);
   QA_RUN_TIMED(h, KK_SPMV64, kBlock, ra.nb, 0, k_outer_spmv_dot, , sview<double>(h->fine, h->fine.s_val64), Z, p, q,
                h->rp, ra);
   finish<2>(h, ra);
-  QA_RUN(h, kBlock, rr.nb, 0, k_outer_update, , n, osc, p, q, h->xp, h->rp, rr);
+  if (h->precision == 1)
+    QA_RUN(h, kBlock, rr.nb, 0, k_outer_update, QA_T(float), n, osc, p, q, h->xp, h->rp, h->w32[0].f, h->w32[0].u, rr);
+  else
+    QA_RUN(h, kBlock, rr.nb, 0, k_outer_update, QA_T(double), n, osc, p, q, h->xp, h->rp,
+           static_cast<double *>(nullptr), h->zp, rr);
   finish<1>(h, rr);
 }
 
-// one iteration with at most one kept direction
-static amg_status outer_iterate(amg_hierarchy *h, double *p, double *q, const double *pprev, const double *qprev,
-                                bool use_beta) {
+// p = z + beta pprev, beta from (z, qprev)
+template <class T>
+static void outer_dir(amg_hierarchy *h, const T *z, double *p, const double *pprev, const double *qprev,
+                      bool use_beta) {
   const int64_t n = h->n;
-  const int L0 = h->nlev;
-  const double *osc = h->scal + static_cast<size_t>(L0) * kScalars;
-  QA_TRY(precond_apply(h, h->precision, h->rp, h->zp));
+  const double *osc = h->scal + static_cast<size_t>(h->nlev) * kScalars;
   if (use_beta) {
-    const Red R = red(h, L0, nred(n), EPI_OUT_BETA);
-    QA_RUN(h, kBlock, R.nb, 0, k_dot, QA_T(double), n, h->zp, qprev, R);
+    const Red R = red(h, h->nlev, nred(n), EPI_OUT_BETA);
+    QA_RUN(h, kBlock, R.nb, 0, k_dot, QA_T(T, double), n, z, qprev, R);
     finish<1>(h, R);
   }
-  QA_RUN(h, kBlock, nblk(n), 0, k_outer_dir, QA_T(double), n, osc, h->zp, pprev, p, use_beta ? 1 : 0);
+  QA_RUN(h, kBlock, nblk(n), 0, k_outer_dir, QA_T(T), n, osc, z, pprev, p, use_beta ? 1 : 0);
+}
+
+// one iteration with at most one kept direction; r, f and u are prepared
+static amg_status outer_iterate(amg_hierarchy *h, double *p, double *q, const double *pprev, const double *qprev,
+                                bool use_beta) {
+  if (h->nlev > 1 && h->precision == 1) {
+    LevelWork<float> &w = h->w32[0];
+    bhat_fine<float>(h, w.f, w.u);
+    outer_dir<float>(h, w.u, p, pprev, qprev, use_beta);
+  } else {
+    if (h->nlev > 1) bhat_fine<double>(h, h->rp, h->zp);
+    else QA_TRY(precond_apply(h, 0, h->rp, h->zp));
+    outer_dir<double>(h, h->zp, p, pprev, qprev, use_beta);
+  }
   outer_step(h, p, q);
   return AMG_OK;
 }
@@ -4193,15 +4266,13 @@ static amg_status outer_iterate(amg_hierarchy *h, double *p, double *q, const do
 // t = b - A x with (t, t)
 static void outer_true_resid(amg_hierarchy *h) {
   const SliceSched Z = slice_sched(h->fine, 0, h->fine.ncolor);
-  const Red R = red(h, h->nlev, sched_grid(Z), EPI_STORE, O_TT);
+  const Red R = red_report(h, sched_grid(Z), O_TT);
   QA_RUN(h, kBlock, R.nb, 0, k_outer_true_resid, , sview<double>(h->fine, h->fine.s_val64), Z, h->bp, h->xp, h->tp, R);
   finish<1>(h, R);
 }
 
 // the residual vector is the true residual just formed
-static void outer_restart(amg_hierarchy *h) {
-  QA_RUN(h, kBlock, nblk(h->n), 0, k_cast, QA_T(double, double), h->n, h->tp, h->rp);
-}
+static void outer_restart(amg_hierarchy *h) { outer_resid(h, h->tp); }
 
 // true residual and the solution in the caller's numbering
 static void outer_end(amg_hierarchy *h, double *x) {
@@ -4218,8 +4289,7 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
   inf.setup_ms = h->setup_ms;
 
   outer_start(h, b);
-  QA_LAUNCH_CHECK();
-  QA_TRY(read_scalars(h, O_BB, 1));
+  QA_TRY(read_scalars(h));
   const double bn = std::sqrt(h->host_scal[O_BB]);
   if (bn == 0.0) {
     QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, x, 0.0);
@@ -4241,8 +4311,8 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
       p = h->dir_p[stored];
       q = h->dir_q[stored];
       for (int j = 0; j < stored; j++) {
-        const Red R{h->partials, h->dir_zq, EPI_STORE, j, nred(n)};
-        QA_RUN(h, kBlock, R.nb, 0, k_dot, QA_T(double), n, h->zp, h->dir_q[j], R);
+        const Red R{h->partials, h->dir_zq, EPI_STORE, j, nred(n), nullptr};
+        QA_RUN(h, kBlock, R.nb, 0, k_dot, QA_T(double, double), n, h->zp, h->dir_q[j], R);
         finish<1>(h, R);
       }
       k_outer_dir_all<<<nblk(n), kBlock, 0, s>>>(n, h->zp, h->dir_pp, h->dir_zq, h->dir_d, stored, p);
@@ -4250,8 +4320,7 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
     } else {
       QA_TRY(outer_iterate(h, p, q, pprev, qprev, have_prev && h->opt.outer_mmax == 1));
     }
-    QA_LAUNCH_CHECK();
-    QA_TRY(read_scalars(h, 0, O_BB));
+    QA_TRY(read_scalars(h));
     if (h->host_scal[O_BREAK] != 0.0) {
       st = AMG_ERR_BREAKDOWN;
       break;
@@ -4267,8 +4336,7 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
     }
     if (std::sqrt(h->host_scal[O_RR]) <= tol * bn) {
       outer_true_resid(h);
-      QA_LAUNCH_CHECK();
-      QA_TRY(read_scalars(h, O_TT, 1));
+      QA_TRY(read_scalars(h));
       if (std::sqrt(h->host_scal[O_TT]) <= tol * bn) {
         st = AMG_OK;
         break;
@@ -4280,8 +4348,7 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
     }
   }
   outer_end(h, x);
-  QA_LAUNCH_CHECK();
-  QA_TRY(read_scalars(h, O_TT, 1));
+  QA_TRY(read_scalars(h));
   inf.iters = it;
   inf.relres = std::sqrt(h->host_scal[O_TT]) / bn;
   inf.solve_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -4293,11 +4360,11 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
 // Several systems in step. A small system's iteration is a chain of short launches that leave most of the chip idle, so
 // a batch runs one chain for all: every system records its pieces of the outer iteration once, and each launch takes
 // the systems that are at that step (run_lists). A system runs the kernels, grids and reductions of amg_solve, so its
-// result is amg_solve's bit for bit, whatever else is in the batch. After each iteration the scalars of all systems go
-// to pinned host memory by one launch, and the host drops those that are done.
+// result is amg_solve's bit for bit, whatever else is in the batch. After each iteration the host reads the systems'
+// scalars from pinned memory and drops those that are done.
 // A whole-solve workgroup is bound by one CU's gathers (about 50 clocks per 64-lane gather) and by latency: eight systems
 // of 10,000 to 63,504 unknowns (FP32 preconditioner) took 37.2 ms so, 2.6 ms per iteration of the largest; in step they
-// take 6.0, bound by the launches' chain (about 70 in an iteration).
+// take 5.4, bound by the launches' chain (about 60 in an iteration).
 
 enum { LL_START = 0, LL_ITER = 1, LL_CHECK = 5, LL_RESTART = 6, LL_END = 7, LL_ZERO = 8, LL_COUNT = 9 };
 struct BatchLists {
@@ -4308,12 +4375,6 @@ void free_batch_lists(amg_hierarchy *h) {
   delete h->batch_lists;
   h->batch_lists = nullptr;
 }
-
-// the outer iteration's scalars to pinned host memory
-__device__ __forceinline__ void k_report_body(const double *sc, double *host) {
-  if (threadIdx.x <= O_BB) host[threadIdx.x] = sc[threadIdx.x];
-}
-__global__ void __launch_bounds__(64) k_report(const double *sc, double *host) { k_report_body(sc, host); }
 
 struct BatchSys {
   amg_hierarchy *h;
@@ -4337,27 +4398,21 @@ static amg_status batch_list(BatchSys &Y, int what, LaunchList *&list) {
   } scope{h};
   h->recording = list;
   amg_status st = AMG_OK;
-  bool report = true;
   if (what == LL_START) {
     outer_start(h, Y.b);
   } else if (what == LL_CHECK) {
     outer_true_resid(h);
   } else if (what == LL_RESTART) {
     outer_restart(h);
-    report = false;
   } else if (what == LL_END) {
     outer_end(h, Y.x);
   } else if (what == LL_ZERO) {
     QA_RUN(h, kBlock, nblk(h->n), 0, k_fill, QA_T(double), h->n, Y.x, 0.0);
-    report = false;
   } else {
     double *P[2] = {h->pp, h->pprev}, *Q[2] = {h->qp, h->qprev};
     const int i = (what - LL_ITER) >> 1;
     st = outer_iterate(h, P[i], Q[i], P[1 - i], Q[1 - i], ((what - LL_ITER) & 1) != 0);
   }
-  if (report)
-    QA_RUN(h, 64, 1, 0, k_report, , static_cast<const double *>(h->scal + static_cast<size_t>(h->nlev) * kScalars),
-           h->host_scal);
   return st;
 }
 
