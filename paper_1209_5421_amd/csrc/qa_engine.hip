@@ -29,7 +29,7 @@
 //  - A p1 is formed for the second inner step instead of A (p1 + beta p0): with (p0, q0), (g, p0), (p1, q0),
 //    (p1, A p1), (r, p1) and (r, p0) Algorithm 2.1's beta and alpha1 follow, so a level needs one reduction per inner
 //    step. The error of one FP32 preconditioner application against FP64, geometric mean over 120 systems of 256 to
-//    1,044,484 unknowns, is 1.39e-6 this way and 1.43e-6 with A (p1 + beta p0);
+//    1,044,484 unknowns, is 1.31e-6 this way and 1.43e-6 with A (p1 + beta p0);
 //  - the whole of B~ on the 256-cell level k = 4, with the coarsest solve below it, runs in a single wavefront: its
 //    steps are ordered by the wavefront's in-order LDS accesses, with no workgroup barrier between them.
 //  - the FP64 coarsest solve is shared by four wavefronts, the three others holding their columns of the inverse in
