@@ -4505,11 +4505,16 @@ static amg_status solve_many_lists(BatchSys *Y, int m, ListCursor *cur, const un
 }
 static amg_status solve_many(BatchSys *Y, int m, ListCursor *cur, const unsigned char **args, const LaunchStep **steps,
                              hipStream_t s) {
+  amg_status st;
   try {
-    return solve_many_lists(Y, m, cur, args, steps, s);
+    st = solve_many_lists(Y, m, cur, args, steps, s);
   } catch (const std::bad_alloc &) {  // the lists' storage
-    return AMG_ERR_NOMEM;
+    st = AMG_ERR_NOMEM;
   }
+  for (int i = 0; i < m; i++)  // the storage stays, the calls and the caller's vectors in them do not
+    if (Y[i].h->batch_lists)
+      for (LaunchList &l : Y[i].h->batch_lists->list) l.clear();
+  return st;
 }
 
 // ---------------------------------------------------------------------------------------------------------------
