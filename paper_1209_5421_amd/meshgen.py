@@ -520,6 +520,7 @@ def cube_mesh(m: int, seed: int = SEED_MESH, jitter: float = 0.15):
     only along them)."""
     h = 1.0 / m
     g = np.arange(m + 1, dtype=np.float64) * h
+    g[m] = 1.0  # m (1 / m) rounds below 1 for some m (49, 98, 103, ...)
     z, y, x = np.meshgrid(g, g, g, indexing="ij")
     pts = np.stack([x.ravel(), y.ravel(), z.ravel()], 1)
     rng = np.random.default_rng(seed)
