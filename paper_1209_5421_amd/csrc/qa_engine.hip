@@ -25,7 +25,8 @@
 //    are zero); the prolongation is folded into the first post-smoothing phase, which reads u + P e_c of its
 //    neighbours formed from the presmoothing planes and the coarse correction's plane and writes a second set of
 //    planes; quotients by the diagonal take Markstein's correction of numerator x reciprocal (the correctly rounded
-//    quotient for a correctly rounded reciprocal) in three instructions;
+//    quotient for a correctly rounded reciprocal) in three instructions; a system with a diagonal too small for its
+//    reciprocal takes k_engine_div, the same with divisions;
 //  - A p1 is formed for the second inner step instead of A (p1 + beta p0): with (p0, q0), (g, p0), (p1, q0),
 //    (p1, A p1), (r, p1) and (r, p0) Algorithm 2.1's beta and alpha1 follow, so a level needs one reduction per inner
 //    step. The error of one FP32 preconditioner application against FP64, geometric mean over 120 systems of 256 to
@@ -215,14 +216,18 @@ __device__ __forceinline__ T fe_row(const T (&a)[9], const T (&own)[4], const T 
 // the level's pre- and post-smoothing planes and the correction's plane at the thread's place (less one row and one
 // column); a thread's second super-cell lies 16 rows on. `act`: the thread belongs to the level (all threads call,
 // or, for a level of one wavefront, its threads). TOP: the reciprocals of the diagonals are formed on the way, each
-// when its rows are first needed. put(t, g) hands the restricted residual to the next level, child(half) runs that.
-template <class T, int K, int TR, int W, bool WAVE, bool TOP, class Put, class Child, class Out>
+// when its rows are first needed. DIV: divisions in place of reciprocals. put(t, g) hands the restricted residual to the next level, child(half) runs that.
+template <class T, int K, int TR, int W, bool WAVE, bool TOP, bool DIV, class Put, class Child, class Out>
 __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T *E, bool act, int wl, double *red,
                                           Put put, Child child, Out out) {
   using G = FeGeo<K>;
   constexpr int own = G::P + 1, second = 16 * G::P;
   double d0 = 0.0, rd0 = 0.0;
   T a0 = 0;
+  auto quot = [](T n, T d, T rd) -> T {
+    if constexpr (DIV) return n / d;
+    else return quotient(n, d, rd);
+  };
   auto relax = [&](auto cc, auto pre, T *pl, int half) {  // x += (f - A x) / diag on the color's rows
     constexpr int c = decltype(cc)::value;
     constexpr bool p = decltype(pre)::value != 0;
@@ -232,7 +237,7 @@ __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T 
         if constexpr (TOP && p)
           if (half == 0) R.rd[t][c] = T(1) / R.a[t][c][0];
         const T acc = fe_row<T, K, c, p>(R.a[t][c], R.u[t], pl + t * second);
-        const T dl = quotient(R.f[t][c] - acc, R.a[t][c][0], R.rd[t][c]);
+        const T dl = quot(R.f[t][c] - acc, R.a[t][c][0], R.rd[t][c]);
         if constexpr (p) R.u[t][c] = dl;
         else R.u[t][c] += dl;
         pl[t * second + c * G::PP + own] = R.u[t][c];
@@ -246,7 +251,7 @@ __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T 
       for (int t = 0; t < TR; t++) {
         if constexpr (TOP)
           if (half == 0) R.rd[t][0] = T(1) / R.a[t][0][0];
-        R.u[t][0] = quotient(R.f[t][0], R.a[t][0][0], R.rd[t][0]);
+        R.u[t][0] = quot(R.f[t][0], R.a[t][0][0], R.rd[t][0]);
         A[t * second + own] = R.u[t][0];
       }
     fe_sync<WAVE>();
@@ -289,7 +294,7 @@ __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T 
           }
           acc += R.a[t][3][s] * x;
         });
-        R.u[t][3] += quotient(R.f[t][3] - acc, R.a[t][3][0], R.rd[t][3]);
+        R.u[t][3] += quot(R.f[t][3] - acc, R.a[t][3][0], R.rd[t][3]);
         T *ql = B + t * second + own;
         for_colors([&](auto cc) {
           constexpr int c = decltype(cc)::value;
@@ -390,7 +395,7 @@ __device__ __forceinline__ void fe_recip(FeRows<T, TR> &R) {
     });
 }
 
-template <class T, int KT>
+template <class T, int KT, bool DIV = false>
 __device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
   using Lay = FeLayout<KT>;
   constexpr int NT = Lay::threads, TR = Lay::TR;
@@ -497,7 +502,7 @@ __device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
     const int pl = place(lane, G::P);
     double *g3 = D + Lay::kG3, *ps = D + Lay::kPart;
     if (act) {
-      fe_btilde<T, 4, 1, 1, true, decltype(top)::value != 0>(
+      fe_btilde<T, 4, 1, 1, true, decltype(top)::value != 0, DIV>(
           Y, S4 + pl, S4 + 4 * G::PP + pl, S4 + 8 * G::PP + pl, true, 0, nullptr,
           [&](int, T acc) { g3[q3] = static_cast<double>(acc); },
           [&](int) {
@@ -552,7 +557,7 @@ __device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
       T *S5 = S + Lay::planes(5);
       T *g4 = S5 + 9 * G::PP;
       const int pl = place(j & (G::N4 - 1), G::P), e4 = parent_place(j4, G::P);
-      fe_btilde<T, 5, 1, 4, false, decltype(top)::value != 0>(
+      fe_btilde<T, 5, 1, 4, false, decltype(top)::value != 0, DIV>(
           Y, S5 + pl, S5 + 4 * G::PP + pl, S5 + 8 * G::PP + pl, act, wave - w5, D + Lay::kRed,
           [&](int, T acc) { g4[(j & 3) * FeGeo<4>::N4 + (j >> 2)] = acc; },
           [&](int half) {
@@ -578,7 +583,7 @@ __device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
       T *S6 = S + Lay::planes(6);
       T *g5 = S6 + 9 * G::PP;
       const int pl = place(jt, G::P);
-      fe_btilde<T, 6, 2, 8, false, true>(
+      fe_btilde<T, 6, 2, 8, false, true, DIV>(
           R, S6 + pl, S6 + 4 * G::PP + pl, S6 + 8 * G::PP + pl, true, wave, D + Lay::kRed + 4 * kFeRedWaves,
           [&](int t, T acc) { g5[(jt & 3) * FeGeo<5>::N4 + (jt >> 2) + t * (step / 4)] = acc; },
           [&](int half) {
@@ -602,6 +607,14 @@ __device__ __forceinline__ void k_engine_fast_body(FeArgs<T> A) {
 template <class T, int KT>
 __global__ void __launch_bounds__(FeLayout<KT>::threads) k_engine_fast(FeArgs<T> A) {
   k_engine_fast_body<T, KT>(A);
+}
+template <class T, int KT>
+__device__ __forceinline__ void k_engine_div_body(FeArgs<T> A) {
+  k_engine_fast_body<T, KT, true>(A);
+}
+template <class T, int KT>
+__global__ void __launch_bounds__(FeLayout<KT>::threads) k_engine_div(FeArgs<T> A) {
+  k_engine_div_body<T, KT>(A);
 }
 
 // ---- host side ----
@@ -627,13 +640,17 @@ size_t fe_cfg_bytes(int id) {
   }
 }
 
-const void *fe_kernel(int id) {
+template <class T, int KT>
+const void *fe_kernel_of(bool div) {
+  return div ? reinterpret_cast<const void *>(k_engine_div<T, KT>) : reinterpret_cast<const void *>(k_engine_fast<T, KT>);
+}
+const void *fe_kernel(int id, bool div) {
   switch (id) {
-    case 0: return reinterpret_cast<const void *>(k_engine_fast<float, 6>);
-    case 1: return reinterpret_cast<const void *>(k_engine_fast<float, 5>);
-    case 2: return reinterpret_cast<const void *>(k_engine_fast<float, 4>);
-    case 3: return reinterpret_cast<const void *>(k_engine_fast<double, 5>);
-    default: return reinterpret_cast<const void *>(k_engine_fast<double, 4>);
+    case 0: return fe_kernel_of<float, 6>(div);
+    case 1: return fe_kernel_of<float, 5>(div);
+    case 2: return fe_kernel_of<float, 4>(div);
+    case 3: return fe_kernel_of<double, 5>(div);
+    default: return fe_kernel_of<double, 4>(div);
   }
 }
 
@@ -642,8 +659,8 @@ amg_status fe_lds_limits(int device, size_t lds_max) {
   if (device < 0 || device >= 64) return AMG_ERR_DEVICE;
   amg_status st = AMG_OK;
   std::call_once(once[device], [&]() {
-    for (int id = 0; id < 5; id++)
-      if (hipFuncSetAttribute(fe_kernel(id), hipFuncAttributeMaxDynamicSharedMemorySize,
+    for (int id = 0; id < 10; id++)
+      if (hipFuncSetAttribute(fe_kernel(id % 5, id >= 5), hipFuncAttributeMaxDynamicSharedMemorySize,
                               static_cast<int>(lds_max)) != hipSuccess)
         st = AMG_ERR_DEVICE;
   });
@@ -674,9 +691,11 @@ void fe_launch(amg_hierarchy *h, int pi) {
   Timing &t = h->timing;
   const int kind = pi ? KK_ENGINE32 : KK_ENGINE64;
   if (!h->recording && t.kind == kind && t.used + 2 <= t.ev.size()) {  // dispatch-stamped start / stop
-    hipExtLaunchKernelGGL(k_engine_fast<T, KT>, dim3(1), dim3(FeLayout<KT>::threads), lds, h->stream, t.ev[t.used],
-                          t.ev[t.used + 1], 0, A);
+    hipExtLaunchKernelGGL(h->tiny_diag[pi] ? k_engine_div<T, KT> : k_engine_fast<T, KT>, dim3(1),
+                          dim3(FeLayout<KT>::threads), lds, h->stream, t.ev[t.used], t.ev[t.used + 1], 0, A);
     t.used += 2;
+  } else if (h->tiny_diag[pi]) {
+    QA_RUN(h, FeLayout<KT>::threads, 1, lds, k_engine_div, QA_T(T, KT), A);
   } else {
     QA_RUN(h, FeLayout<KT>::threads, 1, lds, k_engine_fast, QA_T(T, KT), A);
   }

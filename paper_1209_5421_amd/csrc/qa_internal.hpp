@@ -286,6 +286,7 @@ struct amg_hierarchy {
   std::vector<qa::Chunk> chunks;        // shared chunks that small arrays are carved from
   size_t chunk_unit = 8u << 20;         // size of a shared chunk (set from the size estimate at setup)
   double setup_ms = 0.0;
+  bool tiny_diag[2] = {false, false};   // some diagonal below the smallest normal number, per precision (0 = FP64)
   int stale = 0;                        // a values update failed after it began to overwrite: solves are refused
   qa::Timing timing;
   // persistent small-level engine: top level index per precision (0 = FP64, 1 = FP32), -1 = not used

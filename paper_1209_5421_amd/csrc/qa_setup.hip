@@ -12,6 +12,7 @@
 // This file is compiled with -ffp-contract=off: the cell index must be the IEEE sequence subtract, divide,
 // multiply, floor, and the Galerkin sums are plain additions taken in a fixed order (cells, then rows ascending,
 // then entries in the caller's order; children in the order of Section 4.3's restriction formula).
+#include <cfloat>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -20,7 +21,14 @@
 
 namespace qa {
 
-enum { F_INVALID = 1, F_NOT_SPD = 2, F_SAMECOLOR = 4 };
+enum { F_INVALID = 1, F_NOT_SPD = 2, F_SAMECOLOR = 4, F_TINY64 = 8, F_TINY32 = 16 };
+
+// flags of a diagonal entry: not positive, or smaller than the smallest normal number of either precision (the
+// reciprocals of `quotient` may then be infinite)
+__device__ inline int diag_flags(double d) {
+  if (!(d > 0.0)) return F_NOT_SPD;
+  return (d < DBL_MIN ? F_TINY64 : 0) | (static_cast<float>(d) < FLT_MIN ? F_TINY32 : 0);
+}
 
 struct Box3 {  // {a1, b1, a2, b2, a3, b3} of an octree's auxiliary box
   double v[6];
@@ -56,7 +64,7 @@ __global__ void __launch_bounds__(kBlock) k_validate(int64_t n, int64_t nnz, con
       if (c < 0 || c >= n) f |= F_INVALID;
       else if (c == i) dg += va[e];
     }
-    if (!(dg > 0.0)) f |= F_NOT_SPD;
+    f |= diag_flags(dg);
   }
   if (f) atomicOr(flag, f);
 }
@@ -87,7 +95,7 @@ __global__ void __launch_bounds__(kBlock) k_same_pattern(int64_t n, int64_t nnz,
       if (c < 0 || c >= n || iperm[c] != ci[o0 + (e - r0)]) f |= F_INVALID;
       else if (c == i) dg += va_in[e];
     }
-    if (!f && !(dg > 0.0)) f |= F_NOT_SPD;
+    if (!f) f |= diag_flags(dg);
   }
   if (f) atomicOr(flag, f);
 }
@@ -584,7 +592,7 @@ __global__ void __launch_bounds__(kBlock) k_galerkin_fine(int L, int64_t nL, con
 #pragma unroll
   for (int j = 0; j < 9; j++) ax[j * nL + q] = acc[j];
   ovf_cnt[q] = cnt;
-  if (!emp && !(acc[0] > 0.0)) atomicOr(flag, F_NOT_SPD);
+  if (const int df = emp ? 0 : diag_flags(acc[0])) atomicOr(flag, df);
 }
 
 __global__ void __launch_bounds__(kBlock) k_galerkin_fine_ovf(int L, int64_t nL, const int32_t *__restrict__ crow,
@@ -691,7 +699,7 @@ __global__ void __launch_bounds__(kBlock) k_galerkin_coarse(CoarseSrc F, double 
 #pragma unroll
   for (int j = 0; j < 9; j++) ax[j * nc + qc] = acc[j];
   ovf_cnt[qc] = cnt;
-  if (!all_empty && !(acc[0] > 0.0)) atomicOr(flag, F_NOT_SPD);
+  if (const int df = all_empty ? 0 : diag_flags(acc[0])) atomicOr(flag, df);
 }
 
 __global__ void __launch_bounds__(kBlock) k_galerkin_coarse_ovf(CoarseSrc F, const int32_t *__restrict__ optr,
@@ -804,7 +812,7 @@ __global__ void __launch_bounds__(kBlock) k_validate3(int64_t n, int64_t nnz, co
       if (c < 0 || c >= n) f |= F_INVALID;
       else if (c == i) dg += va[e];
     }
-    if (!(dg > 0.0)) f |= F_NOT_SPD;
+    f |= diag_flags(dg);
   }
   if (f) atomicOr(flag, f);
 }
@@ -899,7 +907,7 @@ __global__ void __launch_bounds__(kBlock) k_galerkin_fine3(int L, int64_t nL, co
 #pragma unroll
   for (int j = 0; j < 27; j++) ax[j * nL + q] = acc[j];
   ovf_cnt[q] = cnt;
-  if (!emp && !(acc[0] > 0.0)) atomicOr(flag, F_NOT_SPD);
+  if (const int df = emp ? 0 : diag_flags(acc[0])) atomicOr(flag, df);
 }
 
 __global__ void __launch_bounds__(kBlock) k_galerkin_fine3_ovf(int L, int64_t nL, const int32_t *__restrict__ crow,
@@ -997,7 +1005,7 @@ __global__ void __launch_bounds__(kBlock) k_galerkin_coarse3(CoarseSrc F, double
 #pragma unroll
   for (int j = 0; j < 27; j++) ax[j * nc + qc] = acc[j];
   ovf_cnt[qc] = cnt;
-  if (!all_empty && !(acc[0] > 0.0)) atomicOr(flag, F_NOT_SPD);
+  if (const int df = all_empty ? 0 : diag_flags(acc[0])) atomicOr(flag, df);
 }
 
 __global__ void __launch_bounds__(kBlock) k_galerkin_coarse3_ovf(CoarseSrc F, const int32_t *__restrict__ optr,
@@ -1226,6 +1234,11 @@ static amg_status read_flag(amg_hierarchy *h, int &f) {
   ReadBatch rb(h);
   QA_TRY(rb.add(&f, h->dflag, sizeof(int)));
   return rb.finish();
+}
+
+static void note_tiny(amg_hierarchy *h, int f) {
+  h->tiny_diag[0] = (f & F_TINY64) != 0;
+  h->tiny_diag[1] = (f & F_TINY32) != 0;
 }
 
 static amg_status sell_values(amg_hierarchy *h);
@@ -1858,6 +1871,7 @@ static amg_status setup_impl(amg_hierarchy *h, const double *coords, const int64
     h->fine.big_max_rows = fl[3];
   }
   if (f & F_NOT_SPD) return AMG_ERR_NOT_SPD;
+  note_tiny(h, f);
   QA_TRY(alloc_workspaces(h));
   QA_TRY(build_mhat(h));
   QA_TRY(plan_engine(h));
@@ -1902,6 +1916,7 @@ static amg_status update_impl(amg_hierarchy *h, const int64_t *row_ptr, const in
   }
   QA_TRY(read_flag(h, f));
   if (f & F_NOT_SPD) return AMG_ERR_NOT_SPD;
+  note_tiny(h, f);
   QA_TRY(build_mhat(h));
   QA_HIP(hipStreamSynchronize(s));
   h->stale = 0;

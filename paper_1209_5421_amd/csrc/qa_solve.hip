@@ -3841,7 +3841,8 @@ static void fine_gs_run(amg_hierarchy *h, unsigned grid, FuseArgs<T> A) {
 constexpr int64_t kGsWideWindows = 256;
 template <class T, int SM, bool FWD, bool GIVEN>
 static void fine_gs_launch(amg_hierarchy *h, unsigned grid, const FuseArgs<T> &A) {
-  if (A.nwin <= kGsWideWindows) fine_gs_run<T, SM, FWD, GIVEN, 512>(h, grid, A);
+  const bool tiny = h->tiny_diag[std::is_same<T, float>::value ? 1 : 0];  // the groups of lanes take reciprocals
+  if (A.nwin <= kGsWideWindows && !tiny) fine_gs_run<T, SM, FWD, GIVEN, 512>(h, grid, A);
   else fine_gs_run<T, SM, FWD, GIVEN, 256>(h, grid, A);
 }
 

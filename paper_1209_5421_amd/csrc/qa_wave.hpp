@@ -6,13 +6,14 @@
 
 namespace qa {
 
-__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__host__ __device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__host__ __device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // n / d from rd = 1 / d rounded to nearest: q = n rd, then q + (n - q d) rd with fused multiply-adds (Markstein, IBM
-// Journal of Research and Development 34, 1990)
+// Journal of Research and Development 34, 1990). For d from the smallest normal number up; below about a quarter of that
+// rd is infinite, and systems with such diagonals (amg_hierarchy::tiny_diag) take the division.
 template <class T>
-__device__ __forceinline__ T quotient(T n, T d, T rd) {
+__host__ __device__ __forceinline__ T quotient(T n, T d, T rd) {
   const T q = n * rd;
   return fma_of(fma_of(-q, d, n), rd, q);
 }
