@@ -58,6 +58,7 @@ N_CU = 256
 C5_RATE = 112.2
 MALL_BYTES = 256 << 20           # Infinity Cache: operands smaller than this may be served from it
 ROW_VISIT_BYTES = 250.0          # algorithmic bytes per visit of a tree-level row (9 FP32 values, its vectors)
+OCT_ROW_VISIT_BYTES = 540.0      # of an octree level's row: four passes over 27 values instead of 9
 
 
 def coarse_row_visits(levels, top):
@@ -432,6 +433,8 @@ def main():
 
     solve_ms = float(np.median([i["solve_ms"] for i in infos]))
 
+    oct_tree = prob.coords.shape[1] == 3
+
     def entry(kind):
         launches, kern_ms, per_launch, nsteps = timed[kind]
         avg_ms = kern_ms / max(launches, 1)
@@ -441,16 +444,17 @@ def main():
             eng = engine["fp32_precond" if kind == "engine32" else "fp64"]
             top = eng["top_level"]
             rows = coarse_row_visits(levels, top) if top >= 0 else 0
-            nbytes = rows * ROW_VISIT_BYTES
+            row_bytes = OCT_ROW_VISIT_BYTES if oct_tree else ROW_VISIT_BYTES
+            nbytes = rows * row_bytes
             gbs = nbytes / (avg_ms * 1e-3) / 1e9 if launches else None
-            name = ROOFLINE_KERNELS[kind]
+            name = ROOFLINE_KERNELS[kind].replace("fast", "oct") if oct_tree else ROOFLINE_KERNELS[kind]
             if top >= 0:  # the specialised engine's instance: <precision, top level k>
                 name = f"{name[:-1]}, {levels[top]['k']}>"
             return {"bound": "hbm", "kernel": name, "achieved": gbs, "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": (gbs / HBM_PEAK_GBS) if gbs else None,
                     "traffic": traffic_from_profiles(kind, args.workload),
                     "launches": launches, "avg_us": avg_ms * 1e3, "algorithmic_bytes_per_launch": nbytes,
-                    "row_visits_per_launch": rows, "bytes_per_row_visit": ROW_VISIT_BYTES,
+                    "row_visits_per_launch": rows, "bytes_per_row_visit": row_bytes,
                     "share_of_solve": (kern_ms / max(nsteps, 1)) / solve_ms if nsteps else None,
                     "operands_fit_infinity_cache": True,
                     "limit": "latency of one workgroup's chain of dependent steps (operands in LDS and L2)"}

@@ -241,9 +241,9 @@ amg_status amg_level_spmv(amg_hierarchy *h, int32_t level, const double *x, doub
 amg_status amg_kernel_timing_enable(amg_hierarchy *h, const char *name);
 amg_status amg_kernel_timing_read(amg_hierarchy *h, int64_t *launches, double *total_ms, double *bytes_per_launch);
 
-/* Configuration of the persistent small-level workgroup for a precision: the hierarchy level index of its top
- * (-1 = not used), the first level index whose operators stay on chip for a launch (registers or LDS), the number of
- * its steps and its dynamic LDS bytes. */
+/* Configuration of the persistent small-level workgroup (of the octree's, for amg_setup3d's hierarchies) for a precision:
+ * the hierarchy level index of its top (-1 = not used), the first level index whose operators stay on chip while the level
+ * is worked on (registers or LDS), the number of its steps and its dynamic LDS bytes. */
 amg_status amg_engine_info(const amg_hierarchy *h, int32_t precision, int32_t *top_level, int32_t *lds_level,
                            int32_t *steps, size_t *lds_bytes);
 

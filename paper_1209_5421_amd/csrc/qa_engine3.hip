@@ -26,6 +26,7 @@
 // 8,820.
 
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 
 #include <mutex>
 #include <type_traits>
@@ -510,13 +511,29 @@ void o3_launch(amg_hierarchy *h, const LevelWork<T> &w, const T *ax4, const T *a
   const O3Args<T> A{h->ainv, ax4, ax3, w.g, w.e, Q.optr, Q.ocol, oval};
   const size_t lds = O3Lay::bytes<T>();
   const bool ovf = Q.ovf_nnz != 0;
-  if (Q.k == 4) {
-    if (ovf) k_engine_oct<T, 4, true><<<1, kO3Threads, lds, h->stream>>>(A);
-    else k_engine_oct<T, 4, false><<<1, kO3Threads, lds, h->stream>>>(A);
+  const auto kernel = Q.k == 4 ? (ovf ? k_engine_oct<T, 4, true> : k_engine_oct<T, 4, false>)
+                               : (ovf ? k_engine_oct<T, 3, true> : k_engine_oct<T, 3, false>);
+  Timing &t = h->timing;
+  if (t.kind == (sizeof(T) == 4 ? KK_ENGINE32 : KK_ENGINE64) && t.used + 2 <= t.ev.size()) {
+    hipExtLaunchKernelGGL(kernel, dim3(1), dim3(kO3Threads), lds, h->stream, t.ev[t.used], t.ev[t.used + 1], 0, A);
+    t.used += 2;
   } else {
-    if (ovf) k_engine_oct<T, 3, true><<<1, kO3Threads, lds, h->stream>>>(A);
-    else k_engine_oct<T, 3, false><<<1, kO3Threads, lds, h->stream>>>(A);
+    kernel<<<1, kO3Threads, lds, h->stream>>>(A);
   }
+}
+
+// steps of one launch (a step ends with a barrier): per inner step of a level eight presmoothing phases, the restriction,
+// the next level's steps (one for the coarsest solve), eight post-smoothing phases and the reduction
+constexpr int o3_steps(int kt) { return 2 * (18 + (kt == 3 ? 1 : o3_steps(kt - 1))); }
+
+// algorithmic floating-point operations of one launch: each add, multiply or divide counts one (a fused multiply-add
+// two), once per value; a row of 27 slots is 54
+double o3_flops(int kt) {
+  const double n = static_cast<double>(1 << (3 * kt)), n8 = n / 8;
+  const double child = kt == 3 ? 2.0 * 64 * 64 : o3_flops(kt - 1);
+  // color 0 from zero, seven phases, residuals and their sums, prolongation, eight phases, A u and two inner products
+  const double step = n8 + 7 * n8 * 57 + n * 56 + child + n + 8 * n8 * 57 + n * 58;
+  return 2 * step + 3 * n + 2 * n + 2 * n + 4 * n;  // first update, beta, direction, last update
 }
 
 }  // namespace
@@ -536,6 +553,13 @@ amg_status plan_engine_oct(amg_hierarchy *h) {
   if (O3Lay::bytes<double>() > static_cast<size_t>(lds)) return AMG_OK;
   QA_TRY(o3_lds_limits(h->device));
   h->oct_top = top;
+  for (int pi = 0; pi < 2; pi++) {
+    h->engine_top[pi] = top;
+    h->engine_lds_top[pi] = kt == 4 ? top + 1 : top;  // the 512-cell level's rows lie in registers during its visits
+    h->engine_nops[pi] = o3_steps(kt);
+    h->engine_lds[pi] = pi ? O3Lay::bytes<float>() : O3Lay::bytes<double>();
+    h->engine_flops[pi] = o3_flops(kt);
+  }
   return AMG_OK;
 }
 

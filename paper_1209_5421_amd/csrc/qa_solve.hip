@@ -4979,7 +4979,7 @@ extern "C" amg_status amg_engine_info(const amg_hierarchy *h, int32_t precision,
                                       int32_t *lds_level, int32_t *steps, size_t *lds_bytes) {
   if (!h || (precision != 0 && precision != 1)) return AMG_ERR_INVALID;
   const int pi = precision;
-  if (top_level) *top_level = h->use_engine ? h->engine_top[pi] : -1;
+  if (top_level) *top_level = h->use_engine || h->dim == 3 ? h->engine_top[pi] : -1;  // 3D: set where it runs
   if (lds_level) *lds_level = h->engine_lds_top[pi];
   if (steps) *steps = h->engine_nops[pi];
   if (lds_bytes) *lds_bytes = h->engine_lds[pi];
