@@ -4512,6 +4512,7 @@ static amg_status solve_many(BatchSys *Y, int m, ListCursor *cur, const unsigned
   } catch (const std::bad_alloc &) {  // the lists' storage
     st = AMG_ERR_NOMEM;
   }
+  if (st != AMG_OK) (void)hipStreamSynchronize(s);  // launches before the failed one still use the caller's vectors
   for (int i = 0; i < m; i++)  // the storage stays, the calls and the caller's vectors in them do not
     if (Y[i].h->batch_lists)
       for (LaunchList &l : Y[i].h->batch_lists->list) l.clear();

@@ -1,0 +1,159 @@
+// amg_solve_batch's host side on the CPU: the program defines the HIP runtime calls that the library makes (they take
+// the place of the runtime's), so every launch, copy and wait of a call is seen, can be made to fail, and moves no data
+// but the convergence scalars. The hierarchies hold the shapes that planning and launching read and no values.
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <new>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include "qa_internal.hpp"
+
+namespace {
+
+std::mutex g_mu;
+std::map<hipStream_t, long> g_pending;       // launches on a stream since it was last waited for
+std::vector<amg_hierarchy *> g_hs;
+long g_launches = 0, g_fail_at = -1;         // the launch that fails, counted from 0 (-1: none)
+hipError_t g_error = hipSuccess;             // what hipGetLastError returns next
+
+struct Config {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t s;
+};
+thread_local Config g_config;
+
+hipError_t launched(hipStream_t s) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  if (g_launches++ == g_fail_at) return g_error = hipErrorLaunchFailure;
+  g_pending[s]++;
+  return hipSuccess;
+}
+
+}  // namespace
+
+extern "C" {
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+  g_config = Config{grid, block, lds, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *s) {
+  *grid = g_config.grid, *block = g_config.block, *lds = g_config.lds, *s = g_config.s;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t s) { return launched(s); }
+hipError_t hipGetLastError() {
+  std::lock_guard<std::mutex> lock(g_mu);
+  const hipError_t e = g_error;
+  g_error = hipSuccess;
+  return e;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  g_pending[s] = 0;
+  for (amg_hierarchy *h : g_hs) {  // |b| = 1, and every residual zero: converged after one iteration
+    for (int i = 0; i < 9; i++) h->host_scal[i] = 0.0;
+    h->host_scal[8] = 1.0;
+  }
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { return *v = 160 * 1024, hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipFuncGetAttributes(hipFuncAttributes *a, const void *) { return *a = hipFuncAttributes{}, hipSuccess; }
+hipError_t hipMemPoolCreate(hipMemPool_t *p, const hipMemPoolProps *) {
+  return *p = reinterpret_cast<hipMemPool_t>(1), hipSuccess;
+}
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipMallocFromPoolAsync(void **p, size_t n, hipMemPool_t, hipStream_t) {
+  return (*p = std::calloc(n, 1)) ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFreeAsync(void *p, hipStream_t) { return std::free(p), hipSuccess; }
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t) {
+  return std::memcpy(dst, src, n), hipSuccess;
+}
+hipError_t hipMemsetAsync(void *dst, int v, size_t n, hipStream_t) { return std::memset(dst, v, n), hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) {
+  static double scratch[1 << 17];
+  return *p = scratch, hipSuccess;
+}
+}
+
+namespace {
+
+// a hierarchy of n unknowns on quadtree levels k = 5, 4, 3 (1,024 < n <= 4,096), FP32 preconditioner, on its own stream
+amg_hierarchy *make(int64_t n) {
+  amg_hierarchy *h = new amg_hierarchy;
+  amg_default_options(&h->opt);
+  h->stream = reinterpret_cast<hipStream_t>(0x1000 + 16 * g_hs.size());
+  h->n = h->fine.n = n;
+  h->L = 5, h->kc = 3, h->nlev = 4, h->nc = 64;
+  h->precision = 1;
+  h->lev.resize(4);
+  for (int l = 1; l < 4; l++) h->lev[l].k = 6 - l, h->lev[l].n = int64_t(1) << (2 * (6 - l));
+  qa::FineLevel &F = h->fine;
+  F.nnz = 7 * n;
+  F.nslices = (n + 63) / 64;
+  F.nwin = 16;
+  for (int c = 0; c <= 4; c++) {
+    F.color_row[c] = n * c / 4;
+    F.color_slice[c] = F.nslices * c / 4;
+    F.color_win[c] = 4 * c;
+  }
+  F.win_ent_max = 100;
+  h->use_engine = 1;
+  h->host_scal = static_cast<double *>(std::calloc(qa::kScalars, sizeof(double)));
+  if (qa::alloc_workspaces(h) != AMG_OK || qa::plan_engine(h) != AMG_OK || qa::plan_wg(h) != AMG_OK) std::exit(3);
+  g_hs.push_back(h);
+  return h;
+}
+
+amg_status call(bool noalloc, std::vector<amg_info> &info) {
+  const int m = static_cast<int>(g_hs.size());
+  static double b[4096], x[4096];
+  std::vector<const double *> bs(m, b);
+  std::vector<double *> xs(m, x);
+  std::vector<double> tol(m, 1e-8);
+  info.assign(m, amg_info{});
+  return (noalloc ? amg_solve_batch_noalloc : amg_solve_batch)(g_hs.data(), bs.data(), xs.data(), tol.data(), m,
+                                                               info.data());
+}
+
+// a launch fails at each place of a call in turn: the call says so and leaves nothing queued
+int drain(bool noalloc) {
+  make(3000), make(3500), make(4000);
+  std::vector<amg_info> info;
+  g_launches = 0;
+  if (call(noalloc, info) != AMG_OK) return 4;
+  const long total = g_launches;
+  long bad = 0, queued = 0;
+  for (long at = 0; at < total; at++) {
+    g_launches = 0, g_fail_at = at;
+    const amg_status st = call(noalloc, info);
+    g_fail_at = -1;
+    if (st != AMG_ERR_DEVICE) bad++;
+    for (const auto &p : g_pending) queued += p.second;
+    g_pending.clear();
+    if (call(noalloc, info) != AMG_OK) bad++;  // the next call is whole
+  }
+  std::printf("launches %ld bad %ld queued %ld\n", total, bad, queued);
+  return 0;
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "drain") return drain(false);
+  if (what == "drain-noalloc") return drain(true);
+  return 2;
+}

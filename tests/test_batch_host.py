@@ -1,0 +1,25 @@
+"""The host side of amg_solve_batch without a GPU (tests/host/batch_calls.hip: the program's own HIP runtime calls)."""
+import os
+
+import pytest
+
+from paper_1209_5421_amd import amg
+from tests import host_program
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    lib = os.path.dirname(amg.LIB_PATH)
+    return host_program.build("batch_calls.hip", tmp_path_factory.mktemp("host"),
+                              [f"-L{lib}", "-lquadamg", f"-Wl,-rpath,{lib}", "-lpthread"])
+
+
+def result(exe, *args):
+    out = host_program.run(exe, *args).split()
+    return dict(zip(out[::2], map(int, out[1::2])))
+
+
+@pytest.mark.parametrize("mode", ["drain", "drain-noalloc"])
+def test_a_failed_launch_leaves_nothing_queued(exe, mode):
+    r = result(exe, mode)
+    assert r["launches"] > 20 and r["bad"] == 0 and r["queued"] == 0
