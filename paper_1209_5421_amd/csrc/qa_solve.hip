@@ -4854,7 +4854,7 @@ extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *co
       if (hipSetDevice(hs[i]->device) != hipSuccess) { st[i] = AMG_ERR_DEVICE; return; }
       st[i] = amg_solve(hs[i], b[i], x[i], tol[i], &inf[i]);
     });
-  // the whole-solve workgroups, beside the systems that run in step where there are both
+  // the whole-solve workgroups and, beside them where there are both, the systems that run in step
   amg_status wg_st = AMG_OK, step_st = AMG_OK;
   auto whole = [&]() {
     for (int pi = 0; pi < 2 && wg_st == AMG_OK; pi++) {
@@ -4868,11 +4868,16 @@ extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *co
                  inf.data());
     }
   };
-  if (m > 0 && ids[0].size() + ids[1].size() > 0) threads.emplace_back(whole);
-  else whole();
   const BatchWork W{{ids[0].data(), ids[1].data(), ids[2].data()}, {0, 0, static_cast<int>(m)},
                     sys.data(), cur.data(), args.data(), steps.data()};
-  step_st = batch_in_step(hs, b, x, tol, W, t0, st.data(), inf.data());
+  auto in_step = [&]() { step_st = batch_in_step(hs, b, x, tol, W, t0, st.data(), inf.data()); };
+  // the whole-solve launches take device memory, from the caller's allocator where it gave one: on the caller's thread
+  if (ids[0].size() + ids[1].size() > 0) {
+    if (m > 0) threads.emplace_back(in_step);
+    whole();
+  } else {
+    in_step();
+  }
   for (auto &t : threads) t.join();
   amg_status first = wg_st != AMG_OK ? wg_st : step_st;
   for (int32_t i = 0; i < count; i++) {

@@ -90,10 +90,24 @@ hipError_t hipGetSymbolAddress(void **p, const void *) {
 
 namespace {
 
+// the caller's allocator: blocks taken on another thread than the caller's
+const std::thread::id g_caller = std::this_thread::get_id();
+std::atomic<long> g_blocks{0}, g_foreign{0};
+void *own_alloc(size_t n, void *) {
+  g_blocks++;
+  if (std::this_thread::get_id() != g_caller) g_foreign++;
+  return std::calloc(n, 1);
+}
+void own_free(void *p, void *) {
+  if (std::this_thread::get_id() != g_caller) g_foreign++;
+  std::free(p);
+}
+
 // a hierarchy of n unknowns on quadtree levels k = 5, 4, 3 (1,024 < n <= 4,096), FP32 preconditioner, on its own stream
-amg_hierarchy *make(int64_t n) {
+amg_hierarchy *make(int64_t n, bool allocator = false) {
   amg_hierarchy *h = new amg_hierarchy;
   amg_default_options(&h->opt);
+  if (allocator) h->opt.alloc = own_alloc, h->opt.dealloc = own_free;
   h->stream = reinterpret_cast<hipStream_t>(0x1000 + 16 * g_hs.size());
   h->n = h->fine.n = n;
   h->L = 5, h->kc = 3, h->nlev = 4, h->nc = 64;
@@ -149,11 +163,22 @@ int drain(bool noalloc) {
   return 0;
 }
 
+// a whole-solve system with the caller's allocator beside one that runs in step
+int allocator() {
+  make(2000, true), make(3000);
+  std::vector<amg_info> info;
+  const long before = g_blocks;
+  const amg_status st = call(false, info);
+  std::printf("status %d blocks %ld foreign %ld\n", static_cast<int>(st), g_blocks - before, g_foreign.load());
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "drain") return drain(false);
   if (what == "drain-noalloc") return drain(true);
+  if (what == "allocator") return allocator();
   return 2;
 }

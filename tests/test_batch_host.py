@@ -23,3 +23,9 @@ def result(exe, *args):
 def test_a_failed_launch_leaves_nothing_queued(exe, mode):
     r = result(exe, mode)
     assert r["launches"] > 20 and r["bad"] == 0 and r["queued"] == 0
+
+
+def test_the_callers_allocator_is_called_on_the_callers_thread(exe):
+    """It may depend on the thread (torch's current stream does), and amg_solve_batch called it on that thread before it
+    ran two routes side by side."""
+    assert result(exe, "allocator") == {"status": 0, "blocks": 1, "foreign": 0}
