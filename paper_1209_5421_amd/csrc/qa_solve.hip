@@ -18,6 +18,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <thread>
 #include <type_traits>
@@ -4701,10 +4702,10 @@ static amg_status launch_wg_batch(amg_hierarchy *const *hs, const double *const 
                                   const double *tol, const std::vector<int> &ids, std::vector<double> &out) {
   QA_HIP(hipSetDevice(hs[ids[0]]->device));
   hipStream_t s = hs[ids[0]]->stream;
-  void *buf = tmp_alloc(hs[ids[0]], s, wg_batch_bytes<T>(ids.size()));
-  if (!buf) return AMG_ERR_NOMEM;
   std::vector<WgSys<T>> sys(ids.size());
   out.assign(4 * ids.size(), 0.0);
+  void *buf = tmp_alloc(hs[ids[0]], s, wg_batch_bytes<T>(ids.size()));
+  if (!buf) return AMG_ERR_NOMEM;
   const amg_status st =
       launch_wg_batch_in<T>(hs, b, x, tol, ids.data(), static_cast<int>(ids.size()), buf, sys.data(), out.data());
   tmp_free(hs[ids[0]], s, buf);  // on every path
@@ -4825,10 +4826,38 @@ static std::mutex g_noalloc_mu;
 
 }  // namespace qa
 
-extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *const *b, double *const *x,
-                                      const double *tol, int32_t count, amg_info *info) {
-  QA_TRY(check_batch_args(hs, b, x, tol, count));
-  if (count == 0) return AMG_OK;
+namespace qa {
+
+// Routes of a batch run beside each other. A route for which no thread can be had runs on the caller's; a route's
+// exception is its status; all have ended before the caller's next step.
+struct Routes {
+  std::vector<std::thread> threads;
+  template <class F>
+  static amg_status guarded(F f) {
+    try {
+      return f();
+    } catch (const std::exception &) {  // host memory
+      return AMG_ERR_NOMEM;
+    }
+  }
+  template <class F>
+  void beside(amg_status &st, F f) {
+    auto body = [&st, f]() { st = guarded(f); };
+    try {
+      threads.emplace_back(body);
+    } catch (const std::exception &) {
+      body();
+    }
+  }
+  void join() {
+    for (std::thread &t : threads) t.join();
+    threads.clear();
+  }
+  ~Routes() { join(); }
+};
+
+static amg_status solve_batch(amg_hierarchy *const *hs, const double *const *b, double *const *x, const double *tol,
+                              int32_t count, amg_info *info) {
   const auto t0 = std::chrono::steady_clock::now();
   // inputs are complete once each hierarchy's stream has drained
   for (int32_t i = 0; i < count; i++) {
@@ -4848,37 +4877,38 @@ extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *co
   std::vector<const LaunchStep *> steps(m);
   std::vector<amg_status> st(count, AMG_OK);
   std::vector<amg_info> inf(count);
-  std::vector<std::thread> threads;
-  for (int i : large)
-    threads.emplace_back([&, i]() {
-      if (hipSetDevice(hs[i]->device) != hipSuccess) { st[i] = AMG_ERR_DEVICE; return; }
-      st[i] = amg_solve(hs[i], b[i], x[i], tol[i], &inf[i]);
-    });
   // the whole-solve workgroups and, beside them where there are both, the systems that run in step
   amg_status wg_st = AMG_OK, step_st = AMG_OK;
-  auto whole = [&]() {
-    for (int pi = 0; pi < 2 && wg_st == AMG_OK; pi++) {
+  Routes routes;
+  routes.threads.reserve(large.size() + 1);
+  for (int i : large)
+    routes.beside(st[i], [&, i]() -> amg_status {
+      QA_HIP(hipSetDevice(hs[i]->device));
+      return amg_solve(hs[i], b[i], x[i], tol[i], &inf[i]);
+    });
+  auto whole = [&]() -> amg_status {
+    for (int pi = 0; pi < 2; pi++) {
       if (ids[pi].empty()) continue;
       std::vector<double> out;
-      wg_st = pi == 0 ? launch_wg_batch<double>(hs, b, x, tol, ids[pi], out)
-                      : launch_wg_batch<float>(hs, b, x, tol, ids[pi], out);
-      if (wg_st != AMG_OK) break;
+      QA_TRY(pi == 0 ? launch_wg_batch<double>(hs, b, x, tol, ids[pi], out)
+                     : launch_wg_batch<float>(hs, b, x, tol, ids[pi], out));
       wg_results(hs, ids[pi].data(), static_cast<int>(ids[pi].size()), out.data(),
                  std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count(), st.data(),
                  inf.data());
     }
+    return AMG_OK;
   };
   const BatchWork W{{ids[0].data(), ids[1].data(), ids[2].data()}, {0, 0, static_cast<int>(m)},
                     sys.data(), cur.data(), args.data(), steps.data()};
-  auto in_step = [&]() { step_st = batch_in_step(hs, b, x, tol, W, t0, st.data(), inf.data()); };
+  auto in_step = [&]() { return batch_in_step(hs, b, x, tol, W, t0, st.data(), inf.data()); };
   // the whole-solve launches take device memory, from the caller's allocator where it gave one: on the caller's thread
   if (ids[0].size() + ids[1].size() > 0) {
-    if (m > 0) threads.emplace_back(in_step);
-    whole();
+    if (m > 0) routes.beside(step_st, in_step);
+    wg_st = Routes::guarded(whole);
   } else {
-    in_step();
+    step_st = Routes::guarded(in_step);
   }
-  for (auto &t : threads) t.join();
+  routes.join();
   amg_status first = wg_st != AMG_OK ? wg_st : step_st;
   for (int32_t i = 0; i < count; i++) {
     const int route = batch_route(hs[i]);
@@ -4889,6 +4919,15 @@ extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *co
     if (first == AMG_OK && st[i] != AMG_OK) first = st[i];
   }
   return first;
+}
+
+}  // namespace qa
+
+extern "C" amg_status amg_solve_batch(amg_hierarchy *const *hs, const double *const *b, double *const *x,
+                                      const double *tol, int32_t count, amg_info *info) {
+  QA_TRY(check_batch_args(hs, b, x, tol, count));
+  if (count == 0) return AMG_OK;
+  return Routes::guarded([&]() { return solve_batch(hs, b, x, tol, count, info); });
 }
 
 extern "C" amg_status amg_solve_batch_noalloc(amg_hierarchy *const *hs, const double *const *b, double *const *x,

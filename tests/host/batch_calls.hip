@@ -3,7 +3,11 @@
 // but the convergence scalars. The hierarchies hold the shapes that planning and launching read and no values.
 #include <hip/hip_runtime.h>
 
+#include <dlfcn.h>
+#include <pthread.h>
+
 #include <atomic>
+#include <cerrno>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -31,6 +35,9 @@ struct Config {
 };
 thread_local Config g_config;
 
+std::atomic<bool> g_no_threads{false};
+std::atomic<long> g_new{0}, g_new_fail_at{-1};  // allocations since g_new was cleared, and the one that fails
+
 hipError_t launched(hipStream_t s) {
   std::lock_guard<std::mutex> lock(g_mu);
   if (g_launches++ == g_fail_at) return g_error = hipErrorLaunchFailure;
@@ -40,7 +47,20 @@ hipError_t launched(hipStream_t s) {
 
 }  // namespace
 
+void *operator new(size_t n) {
+  if (g_new++ == g_new_fail_at) throw std::bad_alloc();
+  if (void *p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 extern "C" {
+int pthread_create(pthread_t *t, const pthread_attr_t *a, void *(*f)(void *), void *arg) {
+  using Create = int (*)(pthread_t *, const pthread_attr_t *, void *(*)(void *), void *);
+  static const Create real = reinterpret_cast<Create>(dlsym(RTLD_NEXT, "pthread_create"));
+  return g_no_threads ? EAGAIN : real(t, a, f, arg);
+}
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
   g_config = Config{grid, block, lds, s};
   return hipSuccess;
@@ -173,6 +193,54 @@ int allocator() {
   return 0;
 }
 
+// every route at once: two in-step systems, a whole-solve one, one that runs as its own amg_solve
+void every_route() {
+  make(3000), make(3500), make(2000);
+  make(4000)->use_batch = 0;
+}
+
+// no thread can be started: the routes run one after another
+int no_threads() {
+  every_route();
+  std::vector<amg_info> info;
+  g_no_threads = true;
+  const amg_status st = call(false, info);
+  g_no_threads = false;
+  long ok = 0;
+  for (const amg_info &i : info) ok += i.status == AMG_OK;
+  std::printf("status %d ok %ld\n", static_cast<int>(st), ok);
+  return 0;
+}
+
+// each allocation of host memory of a call fails in turn
+int no_memory(bool noalloc) {
+  if (noalloc) make(3000), make(3500), make(2000);
+  else every_route();
+  std::vector<amg_info> info;
+  if (call(noalloc, info) != AMG_OK) return 4;
+  long bad = 0, queued = 0, refused = 0, at = 0;
+  for (;; at++) {
+    const int m = static_cast<int>(g_hs.size());
+    static double b[4096], x[4096], tol[8];
+    static const double *bs[8];
+    static double *xs[8];
+    static amg_info inf[8];
+    for (int i = 0; i < m; i++) bs[i] = b, xs[i] = x, tol[i] = 1e-8;
+    g_new = 0, g_new_fail_at = at;
+    const amg_status st = (noalloc ? amg_solve_batch_noalloc : amg_solve_batch)(g_hs.data(), bs, xs, tol, m, inf);
+    const bool reached = g_new > at;
+    g_new_fail_at = -1;
+    if (st != AMG_OK && st != AMG_ERR_NOMEM) bad++;
+    if (st == AMG_ERR_NOMEM) refused++;
+    for (const auto &p : g_pending) queued += p.second;
+    g_pending.clear();
+    if (call(noalloc, info) != AMG_OK) bad++;
+    if (!reached) break;  // the call made fewer allocations than this
+  }
+  std::printf("allocations %ld bad %ld refused %ld queued %ld\n", at, bad, refused, queued);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -180,5 +248,8 @@ int main(int argc, char **argv) {
   if (what == "drain") return drain(false);
   if (what == "drain-noalloc") return drain(true);
   if (what == "allocator") return allocator();
+  if (what == "no-threads") return no_threads();
+  if (what == "no-memory") return no_memory(false);
+  if (what == "no-memory-noalloc") return no_memory(true);
   return 2;
 }

@@ -11,7 +11,7 @@ from tests import host_program
 def exe(tmp_path_factory):
     lib = os.path.dirname(amg.LIB_PATH)
     return host_program.build("batch_calls.hip", tmp_path_factory.mktemp("host"),
-                              [f"-L{lib}", "-lquadamg", f"-Wl,-rpath,{lib}", "-lpthread"])
+                              [f"-L{lib}", "-lquadamg", f"-Wl,-rpath,{lib}", "-lpthread", "-ldl", "-rdynamic"])
 
 
 def result(exe, *args):
@@ -29,3 +29,15 @@ def test_the_callers_allocator_is_called_on_the_callers_thread(exe):
     """It may depend on the thread (torch's current stream does), and amg_solve_batch called it on that thread before it
     ran two routes side by side."""
     assert result(exe, "allocator") == {"status": 0, "blocks": 1, "foreign": 0}
+
+
+def test_a_call_that_gets_no_thread_runs_its_routes_in_turn(exe):
+    assert result(exe, "no-threads") == {"status": 0, "ok": 4}
+
+
+@pytest.mark.parametrize("mode", ["no-memory", "no-memory-noalloc"])
+def test_no_exception_leaves_a_call(exe, mode):
+    """Each host allocation of a call fails in turn: the call answers AMG_ERR_NOMEM or does without, leaves nothing
+    queued, and the next call is whole."""
+    r = result(exe, mode)
+    assert r["bad"] == 0 and r["queued"] == 0
