@@ -34,6 +34,7 @@
 #include <vector>
 
 #include "qa_internal.hpp"
+#include "qa_launch.hpp"
 #include "qa_wave.hpp"
 
 namespace qa {
@@ -513,6 +514,7 @@ void o3_launch(amg_hierarchy *h, const LevelWork<T> &w, const T *ax4, const T *a
   const bool ovf = Q.ovf_nnz != 0;
   const auto kernel = Q.k == 4 ? (ovf ? k_engine_oct<T, 4, true> : k_engine_oct<T, 4, false>)
                                : (ovf ? k_engine_oct<T, 3, true> : k_engine_oct<T, 3, false>);
+  if (refuse_recording(h)) return;
   Timing &t = h->timing;
   if (t.kind == (sizeof(T) == 4 ? KK_ENGINE32 : KK_ENGINE64) && t.used + 2 <= t.ev.size()) {
     hipExtLaunchKernelGGL(kernel, dim3(1), dim3(kO3Threads), lds, h->stream, t.ev[t.used], t.ev[t.used + 1], 0, A);

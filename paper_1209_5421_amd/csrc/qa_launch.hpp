@@ -79,7 +79,8 @@ struct LaunchStep {
 struct LaunchList {
   std::vector<LaunchStep> steps;
   std::vector<unsigned char> bytes;
-  void clear() { steps.clear(), bytes.clear(); }
+  bool refused = false;  // it met a kernel that cannot be recorded
+  void clear() { steps.clear(), bytes.clear(), refused = false; }
 };
 
 // dynamic LDS beyond the default limit has to be asked for, once per device: all that the kernel's static arrays leave
@@ -137,13 +138,28 @@ void record(LaunchList &list, F body, unsigned grid, size_t lds, A... a) {
 }
 
 // Launch kernel K<TA> of NT threads for hierarchy h, or record the call of its body K_body<TA>. TA: QA_T(...) or empty.
+// QA_ONCE launches a kernel that no recorded list needs (it has no form for several systems): a list that meets one is
+// refused, so that nothing runs ahead of the list's own steps. QA_RUN_IF takes the one or the other by a constant.
 #define QA_T(...) <__VA_ARGS__>
-#define QA_RUN(h, NT, GRID, LDS, K, TA, ...)                                                            \
-  ::qa::launch<NT>(h, K TA, [] __device__(const auto &...a) { K##_body TA(a...); }, GRID, LDS, __VA_ARGS__)
-template <int NT, class H, class K, class F, class... A>
+#define QA_RUN_IF(COND, h, NT, GRID, LDS, K, TA, ...)                                                           \
+  ::qa::launch<NT, (COND)>(h, K TA, [] __device__(const auto &...a) { K##_body TA(a...); }, GRID, LDS, __VA_ARGS__)
+#define QA_RUN(h, NT, GRID, LDS, K, TA, ...)                                                                  \
+  ::qa::launch<NT, true>(h, K TA, [] __device__(const auto &...a) { K##_body TA(a...); }, GRID, LDS, __VA_ARGS__)
+#define QA_ONCE(h, NT, GRID, LDS, K, TA, ...) ::qa::launch_once<NT>(h, K TA, GRID, LDS, __VA_ARGS__)
+template <class H>
+bool refuse_recording(H *h) {
+  if (h->recording) h->recording->refused = true;
+  return h->recording != nullptr;
+}
+template <int NT, class H, class K, class... A>
+void launch_once(H *h, K kern, unsigned grid, size_t lds, A... a) {
+  if (!refuse_recording(h)) kern<<<grid, NT, lds, h->stream>>>(a...);
+}
+template <int NT, bool SHARED, class H, class K, class F, class... A>
 void launch(H *h, K kern, F body, unsigned grid, size_t lds, A... a) {
-  if (h->recording) record<NT>(*h->recording, body, grid, lds, a...);
-  else kern<<<grid, NT, lds, h->stream>>>(a...);
+  if constexpr (SHARED)
+    if (h->recording) return record<NT>(*h->recording, body, grid, lds, a...);
+  launch_once<NT>(h, kern, grid, lds, a...);
 }
 
 // Run count lists on one stream, each in its own order. The system with the most steps left names the next kernel, and

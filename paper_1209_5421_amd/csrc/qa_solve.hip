@@ -358,14 +358,9 @@ __device__ inline void fine_resid_body(const SellView<T> &S, const SliceSched &Z
 // residual of one color's rows, for a smoother phase whose color has couplings between its own cells (the fused
 // phase below then reads it from d)
 template <class T>
-__device__ __forceinline__ void k_fine_resid_body(const SellView<T> &S, const SliceSched &Z, const T *__restrict__ f,
-                                                  const T *__restrict__ x, T *__restrict__ d) {
-  fine_resid_body(S, Z, f, x, d);
-}
-template <class T>
 __global__ void __launch_bounds__(kBlock) k_fine_resid(SellView<T> S, SliceSched Z, const T *__restrict__ f,
                                                        const T *__restrict__ x, T *__restrict__ d) {
-  k_fine_resid_body<T>(S, Z, f, x, d);
+  fine_resid_body(S, Z, f, x, d);
 }
 
 // residual of all rows (input of the restriction); a kernel of its own so its launches are timed separately
@@ -1282,8 +1277,8 @@ __global__ void __launch_bounds__(kBlock) k_cgs(QView<T> Q, const T *__restrict_
 // the last color phase (c = 0) of the second B^ with the inner product (p1, q0) of Algorithm 2.1 for beta: thread j
 // relaxes row j and adds the products of rows j + c n/4 of all four colors (colors 1 to 3 are final already)
 template <class T>
-__device__ __forceinline__ void k_cgs0_beta_body(const QView<T> &Q, const T *__restrict__ f, T *__restrict__ x,
-                                                 const T *__restrict__ q0, Red R) {
+__global__ void __launch_bounds__(kBlock) k_cgs0_beta(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
+                                                      const T *__restrict__ q0, Red R) {
   const int64_t n4 = Q.n >> 2;
   const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   double v[1] = {0.0};
@@ -1296,11 +1291,6 @@ __device__ __forceinline__ void k_cgs0_beta_body(const QView<T> &Q, const T *__r
     for (int c = 1; c < 4; c++) v[0] += static_cast<double>(x[c * n4 + j]) * static_cast<double>(q0[c * n4 + j]);
   }
   reduce_finish<1>(v, R);
-}
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_cgs0_beta(QView<T> Q, const T *__restrict__ f, T *__restrict__ x,
-                                                      const T *__restrict__ q0, Red R) {
-  k_cgs0_beta_body<T>(Q, f, x, q0, R);
 }
 
 // A color phase of the first post-smoothing sweep with the prolongation u = x + P e_c folded in (x: the presmoothed
@@ -1784,15 +1774,10 @@ __global__ void __launch_bounds__((Tile<TS, 4>::NT)) k_cgs_pre4(QView<T> Q, cons
 }
 
 template <class T>
-__device__ __forceinline__ void k_add_range_body(int64_t begin, int64_t count, const T *__restrict__ delta,
-                                                 T *__restrict__ x) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < count) x[begin + i] += delta[begin + i];
-}
-template <class T>
 __global__ void __launch_bounds__(kBlock) k_add_range(int64_t begin, int64_t count, const T *__restrict__ delta,
                                                       T *__restrict__ x) {
-  k_add_range_body<T>(begin, count, delta, x);
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < count) x[begin + i] += delta[begin + i];
 }
 
 // residual of the four children of coarse cell M, summed in the order 0, 1, 3, 2 (Section 4.3's explicit
@@ -1866,8 +1851,9 @@ __global__ void __launch_bounds__(kBlock) k_cspmv_pair(QView<T> Q, const T *__re
 // the second inner step of Algorithm 2.1: A d with the direction d = p1 + beta p0 formed on the fly (never stored),
 // inner products (d, A d) and (r, d)
 template <class T>
-__device__ __forceinline__ void k_cspmv_dir_body(const QView<T> &Q, const double *__restrict__ sc, const T *__restrict__ p1,
-                                                 const T *__restrict__ p0, const T *__restrict__ r, Red R) {
+__global__ void __launch_bounds__(kBlock) k_cspmv_dir(QView<T> Q, const double *__restrict__ sc,
+                                                      const T *__restrict__ p1, const T *__restrict__ p0,
+                                                      const T *__restrict__ r, Red R) {
   const T beta = static_cast<T>(sc[S_BETA]);
   auto dir = [p1, p0, beta](uint32_t i) { return p1[i] + beta * p0[i]; };
   double v[2] = {0.0, 0.0};
@@ -1880,12 +1866,6 @@ __device__ __forceinline__ void k_cspmv_dir_body(const QView<T> &Q, const double
     v[1] += static_cast<double>(r[q]) * dq;
   }
   reduce_finish<2>(v, R);
-}
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_cspmv_dir(QView<T> Q, const double *__restrict__ sc,
-                                                      const T *__restrict__ p1, const T *__restrict__ p0,
-                                                      const T *__restrict__ r, Red R) {
-  k_cspmv_dir_body<T>(Q, sc, p1, p0, r, R);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -2160,20 +2140,14 @@ __global__ void __launch_bounds__(kBlock) k_capply3(QView<T> Q, const T *__restr
 // vector kernels of Algorithm 2.1 (n = 2); scalars are read from device memory
 
 template <class T>
-__device__ __forceinline__ void k_update1_body(int64_t n, const double *__restrict__ sc, const T *__restrict__ p0,
-                                               const T *__restrict__ q0, const T *__restrict__ g, T *__restrict__ e,
-                                               T *__restrict__ r) {
+__global__ void __launch_bounds__(kBlock) k_update1(int64_t n, const double *__restrict__ sc,
+                                                    const T *__restrict__ p0, const T *__restrict__ q0,
+                                                    const T *__restrict__ g, T *__restrict__ e, T *__restrict__ r) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const T a = static_cast<T>(sc[S_A0]);
   e[i] = a * p0[i];
   r[i] = upd1_r(g[i], a, q0[i]);
-}
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_update1(int64_t n, const double *__restrict__ sc,
-                                                    const T *__restrict__ p0, const T *__restrict__ q0,
-                                                    const T *__restrict__ g, T *__restrict__ e, T *__restrict__ r) {
-  k_update1_body<T>(n, sc, p0, q0, g, e, r);
 }
 
 template <class T, class S>
@@ -2191,18 +2165,13 @@ __global__ void __launch_bounds__(kBlock) k_dot(int64_t n, const T *__restrict__
 
 // e += a1 (p1 + beta p0): the last update of Algorithm 2.1 with the direction formed on the fly
 template <class T>
-__device__ __forceinline__ void k_update2_body(int64_t n, const double *__restrict__ sc, const T *__restrict__ p1,
-                                               const T *__restrict__ p0, T *__restrict__ e) {
+__global__ void __launch_bounds__(kBlock) k_update2(int64_t n, const double *__restrict__ sc,
+                                                    const T *__restrict__ p1, const T *__restrict__ p0,
+                                                    T *__restrict__ e) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const T a1 = static_cast<T>(sc[S_A1]), beta = static_cast<T>(sc[S_BETA]);
   e[i] += a1 * (p1[i] + beta * p0[i]);
-}
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_update2(int64_t n, const double *__restrict__ sc,
-                                                    const T *__restrict__ p1, const T *__restrict__ p0,
-                                                    T *__restrict__ e) {
-  k_update2_body<T>(n, sc, p1, p0, e);
 }
 
 template <class T>
@@ -2217,8 +2186,8 @@ __global__ void __launch_bounds__(kBlock) k_fill(int64_t n, T *__restrict__ v, T
 
 // e = A^{-1} g on the coarsest level (FP64 arithmetic whatever T is); one workgroup
 template <class T>
-__device__ __forceinline__ void k_dense_solve_body(int n, const double *__restrict__ ainv, const T *__restrict__ g,
-                                                   T *__restrict__ e) {
+__global__ void __launch_bounds__(kBlock) k_dense_solve(int n, const double *__restrict__ ainv,
+                                                        const T *__restrict__ g, T *__restrict__ e) {
   __shared__ double sg[1024];
   for (int i = threadIdx.x; i < n; i += kBlock) sg[i] = static_cast<double>(g[i]);
   __syncthreads();
@@ -2227,11 +2196,6 @@ __device__ __forceinline__ void k_dense_solve_body(int n, const double *__restri
     for (int j = 0; j < n; j++) acc += ainv[static_cast<size_t>(i) * n + j] * sg[j];
     e[i] = static_cast<T>(acc);
   }
-}
-template <class T>
-__global__ void __launch_bounds__(kBlock) k_dense_solve(int n, const double *__restrict__ ainv,
-                                                        const T *__restrict__ g, T *__restrict__ e) {
-  k_dense_solve_body<T>(n, ainv, g, e);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -2397,13 +2361,9 @@ __global__ void __launch_bounds__(kBlock) k_scatter_back(int64_t n, const int32_
 }
 
 template <class S, class D>
-__device__ __forceinline__ void k_cast_body(int64_t n, const S *__restrict__ src, D *__restrict__ dst) {
+__global__ void __launch_bounds__(kBlock) k_cast(int64_t n, const S *__restrict__ src, D *__restrict__ dst) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = static_cast<D>(src[i]);
-}
-template <class S, class D>
-__global__ void __launch_bounds__(kBlock) k_cast(int64_t n, const S *__restrict__ src, D *__restrict__ dst) {
-  k_cast_body<S, D>(n, src, dst);
 }
 
 // lexicographic <-> color-major numbering of a quadtree level (tests and level hooks)
@@ -2507,17 +2467,22 @@ static unsigned sched_grid(const SliceSched &Z) {
 // hipExtLaunchKernelGGL with a start/stop event pair: the runtime stamps both events from the dispatch packet itself,
 // so the interval is the kernel's own execution window (the same span a kernel-trace profiler reports), not the gap
 // between two markers queued around it.
-#define QA_RUN_TIMED(h, KIND, NT, GRID, LDS, K, TA, ...)                                                       \
-  launch_timed<NT>(h, KIND, K TA, [] __device__(const auto &...a) { K##_body TA(a...); }, GRID, LDS, __VA_ARGS__)
-template <int NT, class K, class F, class... A>
-static void launch_timed(amg_hierarchy *h, int kind, K kern, F body, unsigned grid, size_t lds, A... a) {
+#define QA_RUN_TIMED(h, KIND, NT, GRID, LDS, K, TA, ...) \
+  launch_timed<NT, true>(h, KIND, K TA, [] __device__(const auto &...a) { K##_body TA(a...); }, GRID, LDS, __VA_ARGS__)
+#define QA_RUN_TIMED_IF(COND, h, KIND, NT, GRID, LDS, K, TA, ...)                                                      \
+  launch_timed<NT, (COND)>(h, KIND, K TA, [] __device__(const auto &...a) { K##_body TA(a...); }, GRID, LDS, \
+                           __VA_ARGS__)
+template <int NT, class K, class... A>
+static bool launch_stamped(amg_hierarchy *h, int kind, K kern, unsigned grid, size_t lds, A... a) {
   Timing &t = h->timing;
-  if (!h->recording && kind >= 0 && t.kind == kind && t.used + 2 <= t.ev.size()) {
-    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, h->stream, t.ev[t.used], t.ev[t.used + 1], 0, a...);
-    t.used += 2;
-  } else {
-    launch<NT>(h, kern, body, grid, lds, a...);
-  }
+  if (h->recording || t.kind != kind || t.used + 2 > t.ev.size()) return false;
+  hipExtLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, h->stream, t.ev[t.used], t.ev[t.used + 1], 0, a...);
+  t.used += 2;
+  return true;
+}
+template <int NT, bool SHARED, class K, class F, class... A>
+static void launch_timed(amg_hierarchy *h, int kind, K kern, F body, unsigned grid, size_t lds, A... a) {
+  if (!launch_stamped<NT>(h, kind, kern, grid, lds, a...)) launch<NT, SHARED>(h, kern, body, grid, lds, a...);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -3357,15 +3322,8 @@ static void launch_engine(amg_hierarchy *h, int top) {
   std::vector<LevelWork<T>> &W = P<T>::W(h);
   E.g_in = W[top].g;
   E.e_out = W[top].e;
-  Timing &t = h->timing;
-  const int kind = pi ? KK_ENGINE32 : KK_ENGINE64;
-  if (t.kind == kind && t.used + 2 <= t.ev.size()) {  // dispatch-stamped start / stop, as launch_timed
-    hipExtLaunchKernelGGL(k_engine<T>, dim3(1), dim3(kEngThreads), h->engine_lds[pi], h->stream, t.ev[t.used],
-                          t.ev[t.used + 1], 0, E);
-    t.used += 2;
-  } else {
-    k_engine<T><<<1, kEngThreads, h->engine_lds[pi], h->stream>>>(E);
-  }
+  if (!launch_stamped<kEngThreads>(h, pi ? KK_ENGINE32 : KK_ENGINE64, k_engine<T>, 1, h->engine_lds[pi], E))
+    QA_ONCE(h, kEngThreads, 1, h->engine_lds[pi], k_engine, QA_T(T), E);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -3705,7 +3663,7 @@ static Pending<T> coarse_solve_or_cycle(amg_hierarchy *h, int l, bool fold) {
   LevelWork<T> &w = P<T>::W(h)[l];
   const int pi = std::is_same<T, float>::value ? 1 : 0;
   if (l == h->nlev - 1) {
-    QA_RUN(h, kBlock, 1, 0, k_dense_solve, QA_T(T), static_cast<int>(h->nc), h->ainv, w.g, w.e);
+    QA_ONCE(h, kBlock, 1, 0, k_dense_solve, QA_T(T), static_cast<int>(h->nc), h->ainv, w.g, w.e);
   } else if (h->dim == 3) {
     btilde_oct<T>(h, l, w.g, w.e);
   } else if (h->use_engine && l == h->engine_top[pi]) {
@@ -3729,8 +3687,8 @@ static void gs_phase_coarse(amg_hierarchy *h, int l, const T *f, T *u, int c, bo
     QA_RUN(h, kBlock, nblk(n4), 0, k_cgs, QA_T(T, true), qview<T>(Q), f, u, nullptr, c);
   } else if (Q.same_color_ovf) {
     T *dl = P<T>::W(h)[l].d;
-    QA_RUN(h, kBlock, nblk(n4), 0, k_cgs, QA_T(T, false), qview<T>(Q), f, u, dl, c);
-    QA_RUN(h, kBlock, nblk(n4), 0, k_add_range, QA_T(T), c * n4, n4, dl, u);
+    QA_ONCE(h, kBlock, nblk(n4), 0, k_cgs, QA_T(T, false), qview<T>(Q), f, u, dl, c);
+    QA_ONCE(h, kBlock, nblk(n4), 0, k_add_range, QA_T(T), c * n4, n4, dl, u);
   } else {
     QA_RUN(h, kBlock, nblk(n4), 0, k_cgs, QA_T(T, false), qview<T>(Q), f, u, nullptr, c);
   }
@@ -3760,10 +3718,10 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
     const QView<T> V = qview<T>(Q);
     if (U) {
       if (small) QA_RUN(h, (Tile<8, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, true, 8), V, f, v, upd, wc.g);
-      else QA_RUN(h, (Tile<16, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, true, 16), V, f, v, upd, wc.g);
+      else QA_ONCE(h, (Tile<16, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, true, 16), V, f, v, upd, wc.g);
     } else {
       if (small) QA_RUN(h, (Tile<8, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, false, 8), V, f, v, upd, wc.g);
-      else QA_RUN(h, (Tile<16, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, false, 16), V, f, v, upd, wc.g);
+      else QA_ONCE(h, (Tile<16, 4>::NT), grid, 0, k_cgs_pre4, QA_T(T, false, 16), V, f, v, upd, wc.g);
     }
   }
   for (int sw = 0; sw < (tiled_pre ? 0 : sweeps); sw++)
@@ -3785,11 +3743,11 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
     auto post = [&](auto spc) {
       constexpr int SP = decltype(spc)::value;
       if (small)
-        QA_RUN(h, (Tile<8, SP ? 5 : 4>::NT), grid, 0, k_cgs_post4, QA_T(T, SP, 8), V, f, v, u, wc.e, pend, w.q0,
-               w.p0, part);
+        QA_RUN_IF(SP > 0, h, (Tile<8, SP ? 5 : 4>::NT), grid, 0, k_cgs_post4, QA_T(T, SP, 8), V, f, v, u, wc.e, pend,
+                  w.q0, w.p0, part);
       else
-        QA_RUN(h, (Tile<16, SP ? 5 : 4>::NT), grid, 0, k_cgs_post4, QA_T(T, SP, 16), V, f, v, u, wc.e, pend, w.q0,
-               w.p0, part);
+        QA_ONCE(h, (Tile<16, SP ? 5 : 4>::NT), grid, 0, k_cgs_post4, QA_T(T, SP, 16), V, f, v, u, wc.e, pend, w.q0,
+                w.p0, part);
     };
     if (sp == 1) post(std::integral_constant<int, 1>{});
     else if (sp == 2) post(std::integral_constant<int, 2>{});
@@ -3805,12 +3763,12 @@ static void bhat_coarse(amg_hierarchy *h, int l, const T *f, T *u, const Upd1<T>
           case 2: QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 2, false), V, f, v, u, wc.e, pend, beta_q0, rb); break;
           case 1: QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 1, false), V, f, v, u, wc.e, pend, beta_q0, rb); break;
           default:
-            if (beta_here) QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 0, true), V, f, v, u, wc.e, pend,
-                                  beta_q0, rb);
+            if (beta_here) QA_ONCE(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 0, true), V, f, v, u, wc.e, pend,
+                                   beta_q0, rb);
             else QA_RUN(h, kBlock, nblk(n4), 0, k_cgs_post, QA_T(T, 0, false), V, f, v, u, wc.e, pend, beta_q0, rb);
         }
       } else if (beta_here) {
-        QA_RUN(h, kBlock, nblk(n4), 0, k_cgs0_beta, QA_T(T), qview<T>(Q), f, u, beta_q0, rb);
+        QA_ONCE(h, kBlock, nblk(n4), 0, k_cgs0_beta, QA_T(T), qview<T>(Q), f, u, beta_q0, rb);
       } else {
         gs_phase_coarse<T>(h, l, f, u, c, false);
       }
@@ -3825,15 +3783,17 @@ static void fine_resid(amg_hierarchy *h, const T *f, const T *x, T *d, int c0, i
   if (grid == 0) return;
   const SellView<T> A = sview<T>(h->fine, P<T>::sval(h->fine));
   if (kind == P<T>::kResid) QA_RUN_TIMED(h, kind, kBlock, grid, 0, k_fine_resid_full, QA_T(T), A, Z, f, x, d);
-  else QA_RUN_TIMED(h, kind, kBlock, grid, 0, k_fine_resid, QA_T(T), A, Z, f, x, d);
+  else QA_ONCE(h, kBlock, grid, 0, k_fine_resid, QA_T(T), A, Z, f, x, d);
 }
 
 template <class T, int SM, bool FWD, bool GIVEN, int NT>
 static void fine_gs_run(amg_hierarchy *h, unsigned grid, FuseArgs<T> A) {
   A.ent_cap = std::min(h->fine.win_ent_max, kFuseDynBytes / fuse_ent_bytes<T, SM>());
   const size_t lds = (static_cast<size_t>(A.ent_cap) * fuse_ent_bytes<T, SM>() + 15) / 16 * 16;
-  QA_RUN_TIMED(h, P<T>::kGs, NT, grid, lds, k_fine_gs, QA_T(T, SM, FWD, GIVEN, NT),
-               sview<T>(h->fine, P<T>::sval(h->fine)), A);
+  const SellView<T> S = sview<T>(h->fine, P<T>::sval(h->fine));
+  // recorded: the substitution smoother with one sweep, whose residual is given in the first phase of all only
+  constexpr bool shared = SM == 0 && (FWD || !GIVEN);
+  QA_RUN_TIMED_IF(shared, h, P<T>::kGs, NT, grid, lds, k_fine_gs, QA_T(T, SM, FWD, GIVEN, NT), S, A);
 }
 // Threads of a phase: eight wavefronts, which solve 64 cells at once by groups of eight lanes, while every window has a
 // CU of its own; four beyond, with a thread per cell. Measured, wide against narrow: 4,096 unknowns (5 windows, FP64)
@@ -3952,9 +3912,9 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
     const unsigned nb = static_cast<unsigned>(tile_grid(Q));
     const bool few = nb <= kFoldBlocks;
     bhat_coarse<T>(h, l, g, w.p0, Upd1<T>{}, nullptr, 1);
-    if (!two || !few) QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(4), Red{part, sc, EPI_ALPHA0, 0, nb, nullptr});
+    if (!two || !few) QA_ONCE(h, kBlock, 1, 0, k_finish, QA_T(4), Red{part, sc, EPI_ALPHA0, 0, nb, nullptr});
     if (!two) {
-      QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
+      QA_ONCE(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
       return false;
     }
     bhat_coarse<T>(h, l, w.r, w.p1,
@@ -3962,14 +3922,14 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
     if (few && fold && defer_update2) return true;
     QA_RUN(h, kBlock, 1, 0, k_finish, QA_T(4),
            Red{part, sc, std::is_same<T, float>::value ? EPI_PAIR32 : EPI_PAIR64, 0, nb, nullptr});
-    if (!defer_update2) QA_RUN(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
+    if (!defer_update2) QA_ONCE(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
     return false;
   }
   bhat_coarse<T>(h, l, g, w.p0);
   QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_dot, QA_T(T), qview<T>(Q), w.p0, w.q0, g, red(h, l, nred(Q.n), EPI_ALPHA0));
   finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA0));
   if (!two) {
-    QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
+    QA_ONCE(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
     return false;
   }
   // the first inner update folds into the second B^'s first relaxation. With the engine on, beta and alpha1 come from
@@ -3985,13 +3945,13 @@ static bool btilde(amg_hierarchy *h, int l, const T *g, T *e, bool defer_update2
     const bool fold_beta = !Q.same_color_ovf || h->opt.sweeps == 1;
     bhat_coarse<T>(h, l, w.r, w.p1, upd, fold_beta ? w.q0 : nullptr);
     if (!fold_beta) {
-      QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T, T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
+      QA_ONCE(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T, T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
       finish<1>(h, red(h, l, nred(Q.n), EPI_BETA));
     }
-    QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_dir, QA_T(T), qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
+    QA_ONCE(h, kBlock, nred(Q.n), 0, k_cspmv_dir, QA_T(T), qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
     finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA1));
   }
-  if (!defer_update2) QA_RUN(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
+  if (!defer_update2) QA_ONCE(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
   return false;
 }
 
@@ -4004,10 +3964,10 @@ static void gs_phase_oct(amg_hierarchy *h, int l, const T *f, T *u, int c) {
   const int64_t n8 = Q.n >> 3;
   if (Q.same_color_ovf) {
     T *dl = P<T>::W(h)[l].d;
-    k_cgs3<T><<<nblk(n8), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, dl, c);
-    QA_RUN(h, kBlock, nblk(n8), 0, k_add_range, QA_T(T), c * n8, n8, dl, u);
+    QA_ONCE(h, kBlock, nblk(n8), 0, k_cgs3, QA_T(T), qview<T>(Q), f, u, dl, c);
+    QA_ONCE(h, kBlock, nblk(n8), 0, k_add_range, QA_T(T), c * n8, n8, dl, u);
   } else {
-    k_cgs3<T><<<nblk(n8), kBlock, 0, h->stream>>>(qview<T>(Q), f, u, nullptr, c);
+    QA_ONCE(h, kBlock, nblk(n8), 0, k_cgs3, QA_T(T), qview<T>(Q), f, u, nullptr, c);
   }
 }
 
@@ -4025,25 +3985,25 @@ static void bhat_oct(amg_hierarchy *h, int l, const T *f, T *u) {
     const int nc = whole ? static_cast<int>(h->nc) : 0, sw = h->opt.sweeps;
     const size_t lds = bhat3_lds_bytes<T>(Q.n, nc);
     if (whole && lds <= static_cast<size_t>(bhat3_lds_limit(h->device))) {
-      k_bhat3_lds<T><<<1, kOctSweepThreads, lds, s>>>(qview<T>(Q), f, u, h->ainv, nc, sw, dl ? 1 : 0);
+      QA_ONCE(h, kOctSweepThreads, 1, lds, k_bhat3_lds, QA_T(T), qview<T>(Q), f, u, h->ainv, nc, sw, dl ? 1 : 0);
     } else if (whole) {
-      k_bhat3_small<T, 0><<<1, kOctSweepThreads, 0, s>>>(qview<T>(Q), f, u, dl, wc.g, wc.e, h->ainv, nc, sw);
+      QA_ONCE(h, kOctSweepThreads, 1, 0, k_bhat3_small, QA_T(T, 0), qview<T>(Q), f, u, dl, wc.g, wc.e, h->ainv, nc, sw);
     } else {
-      k_bhat3_small<T, 1><<<1, kOctSweepThreads, 0, s>>>(qview<T>(Q), f, u, dl, wc.g, wc.e, nullptr, 0, sw);
+      QA_ONCE(h, kOctSweepThreads, 1, 0, k_bhat3_small, QA_T(T, 1), qview<T>(Q), f, u, dl, wc.g, wc.e, nullptr, 0, sw);
       btilde_oct<T>(h, l + 1, wc.g, wc.e);
-      k_bhat3_small<T, 2><<<1, kOctSweepThreads, 0, s>>>(qview<T>(Q), f, u, dl, wc.g, wc.e, nullptr, 0, sw);
+      QA_ONCE(h, kOctSweepThreads, 1, 0, k_bhat3_small, QA_T(T, 2), qview<T>(Q), f, u, dl, wc.g, wc.e, nullptr, 0, sw);
     }
     return;
   }
-  QA_RUN(h, kBlock, nblk(Q.n), 0, k_fill, QA_T(T), Q.n, u, T(0));
+  QA_ONCE(h, kBlock, nblk(Q.n), 0, k_fill, QA_T(T), Q.n, u, T(0));
   for (int sw = 0; sw < h->opt.sweeps; sw++)
     for (int c = 0; c < 8; c++) gs_phase_oct<T>(h, l, f, u, c);
-  k_cres_restrict3<T><<<nblk(Q.n >> 3), kBlock, 0, s>>>(qview<T>(Q), f, u, wc.g);
+  QA_ONCE(h, kBlock, nblk(Q.n >> 3), 0, k_cres_restrict3, QA_T(T), qview<T>(Q), f, u, wc.g);
   if (l + 1 == h->nlev - 1)
-    QA_RUN(h, kBlock, 1, 0, k_dense_solve, QA_T(T), static_cast<int>(h->nc), h->ainv, wc.g, wc.e);
+    QA_ONCE(h, kBlock, 1, 0, k_dense_solve, QA_T(T), static_cast<int>(h->nc), h->ainv, wc.g, wc.e);
   else
     btilde_oct<T>(h, l + 1, wc.g, wc.e);
-  k_cprolong3<T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, wc.e, u);
+  QA_ONCE(h, kBlock, nblk(Q.n), 0, k_cprolong3, QA_T(T), Q.k, Q.n, wc.e, u);
   for (int sw = 0; sw < h->opt.sweeps; sw++)
     for (int c = 7; c >= 0; c--) gs_phase_oct<T>(h, l, f, u, c);
 }
@@ -4059,34 +4019,34 @@ static void btilde_oct(amg_hierarchy *h, int l, const T *g, T *e) {
   hipStream_t s = h->stream;
   const double *sc = h->scal + static_cast<size_t>(l) * kScalars;
   bhat_oct<T>(h, l, g, w.p0);
-  k_cspmv_dot3<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), w.p0, w.q0, g, red(h, l, nred(Q.n), EPI_ALPHA0));
+  QA_ONCE(h, kBlock, nred(Q.n), 0, k_cspmv_dot3, QA_T(T), qview<T>(Q), w.p0, w.q0, g, red(h, l, nred(Q.n), EPI_ALPHA0));
   finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA0));
-  QA_RUN(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
+  QA_ONCE(h, kBlock, nblk(Q.n), 0, k_update1, QA_T(T), Q.n, sc, w.p0, w.q0, g, e, w.r);
   if (h->opt.inner_iters < 2) return;
   bhat_oct<T>(h, l, w.r, w.p1);
-  QA_RUN(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T, T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
+  QA_ONCE(h, kBlock, nred(Q.n), 0, k_dot, QA_T(T, T), Q.n, w.p1, w.q0, red(h, l, nred(Q.n), EPI_BETA));
   finish<1>(h, red(h, l, nred(Q.n), EPI_BETA));
-  k_cspmv_dir3<T><<<nred(Q.n), kBlock, 0, s>>>(qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
+  QA_ONCE(h, kBlock, nred(Q.n), 0, k_cspmv_dir3, QA_T(T), qview<T>(Q), sc, w.p1, w.p0, w.r, red(h, l, nred(Q.n), EPI_ALPHA1));
   finish<2>(h, red(h, l, nred(Q.n), EPI_ALPHA1));
-  QA_RUN(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
+  QA_ONCE(h, kBlock, nblk(Q.n), 0, k_update2, QA_T(T), Q.n, sc, w.p1, w.p0, e);
 }
 
 // z = B^_F[r] in the requested precision (r, z: FP64, permuted numbering)
 amg_status precond_apply(amg_hierarchy *h, int precision, const double *r, double *z) {
   const int64_t n = h->n;
   if (h->nlev == 1) {
-    QA_RUN(h, kBlock, 1, 0, k_dense_solve, QA_T(double), static_cast<int>(h->nc), h->ainv, r, z);
+    QA_ONCE(h, kBlock, 1, 0, k_dense_solve, QA_T(double), static_cast<int>(h->nc), h->ainv, r, z);
     QA_LAUNCH_CHECK();
     return AMG_OK;
   }
   if (precision == 1) {
     LevelWork<float> &w = h->w32[0];
-    QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(double, float), n, r, w.f);
-    QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(float), n, w.u, 0.f);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_cast, QA_T(double, float), n, r, w.f);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_fill, QA_T(float), n, w.u, 0.f);
     bhat_fine<float>(h, w.f, w.u);
-    QA_RUN(h, kBlock, nblk(n), 0, k_cast, QA_T(float, double), n, w.u, z);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_cast, QA_T(float, double), n, w.u, z);
   } else {
-    QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, z, 0.0);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, z, 0.0);
     bhat_fine<double>(h, r, z);
   }
   QA_LAUNCH_CHECK();
@@ -4294,7 +4254,7 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
   QA_TRY(read_scalars(h));
   const double bn = std::sqrt(h->host_scal[O_BB]);
   if (bn == 0.0) {
-    QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, x, 0.0);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, x, 0.0);
     QA_HIP(hipStreamSynchronize(s));
     inf.solve_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     if (info) *info = inf;
@@ -4314,10 +4274,10 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
       q = h->dir_q[stored];
       for (int j = 0; j < stored; j++) {
         const Red R{h->partials, h->dir_zq, EPI_STORE, j, nred(n), nullptr};
-        QA_RUN(h, kBlock, R.nb, 0, k_dot, QA_T(double, double), n, h->zp, h->dir_q[j], R);
+        QA_ONCE(h, kBlock, R.nb, 0, k_dot, QA_T(double, double), n, h->zp, h->dir_q[j], R);
         finish<1>(h, R);
       }
-      k_outer_dir_all<<<nblk(n), kBlock, 0, s>>>(n, h->zp, h->dir_pp, h->dir_zq, h->dir_d, stored, p);
+      QA_ONCE(h, kBlock, nblk(n), 0, k_outer_dir_all, , n, h->zp, h->dir_pp, h->dir_zq, h->dir_d, stored, p);
       outer_step(h, p, q);
     } else {
       QA_TRY(outer_iterate(h, p, q, pprev, qprev, have_prev && h->opt.outer_mmax == 1));
@@ -4415,7 +4375,7 @@ static amg_status batch_list(BatchSys &Y, int what, LaunchList *&list) {
     const int i = (what - LL_ITER) >> 1;
     st = outer_iterate(h, P[i], Q[i], P[1 - i], Q[1 - i], ((what - LL_ITER) & 1) != 0);
   }
-  return st;
+  return st == AMG_OK && list->refused ? AMG_ERR_INVALID : st;
 }
 
 // run the wanted lists of all systems that have one
@@ -4531,22 +4491,22 @@ static amg_status level_smooth_t(amg_hierarchy *h, int level, const double *f, d
     const FineLevel &F = h->fine;
     const int64_t n = F.n;
     T *ff = W[0].f, *xx = W[0].u;
-    QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, f, ff);
-    QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, x, xx);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, f, ff);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, x, xx);
     const int nc = h->fine.ncolor;
     for (int c = 0; c < nc; c++) fine_phase<T>(h, ff, xx, W[0].d, forward ? c : nc - 1 - c, forward != 0, false);
-    QA_RUN(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(T, double), n, F.perm, xx, x);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(T, double), n, F.perm, xx, x);
   } else {
     const QuadLevel &Q = h->lev[level];
     const int dim = h->dim, nc = 1 << dim;
     T *ff = W[level].r, *xx = W[level].p0;
-    k_lex_to_q<double, T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, f, ff, 0, dim);
-    k_lex_to_q<double, T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, x, xx, 0, dim);
+    QA_ONCE(h, kBlock, nblk(Q.n), 0, k_lex_to_q, QA_T(double, T), Q.k, Q.n, f, ff, 0, dim);
+    QA_ONCE(h, kBlock, nblk(Q.n), 0, k_lex_to_q, QA_T(double, T), Q.k, Q.n, x, xx, 0, dim);
     for (int c = 0; c < nc; c++) {
       if (dim == 3) gs_phase_oct<T>(h, level, ff, xx, forward ? c : nc - 1 - c);
       else gs_phase_coarse<T>(h, level, ff, xx, forward ? c : nc - 1 - c, false);
     }
-    k_lex_to_q<T, double><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, xx, x, 1, dim);
+    QA_ONCE(h, kBlock, nblk(Q.n), 0, k_lex_to_q, QA_T(T, double), Q.k, Q.n, xx, x, 1, dim);
   }
   QA_LAUNCH_CHECK();
   QA_HIP(hipStreamSynchronize(s));
@@ -4565,10 +4525,10 @@ static amg_status level_spmv_t(amg_hierarchy *h, int level, const double *x, dou
     const FineLevel &F = h->fine;
     const int64_t n = F.n;
     T *xx = W[0].f, *yy = W[0].u;
-    QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, x, xx);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_gather, QA_T(double, T), n, F.perm, x, xx);
     const SliceSched Z = slice_sched(F, 0, F.ncolor);
-    k_fine_apply<T><<<sched_grid(Z), kBlock, 0, s>>>(sview<T>(F, P<T>::sval(F)), Z, xx, yy);
-    QA_RUN(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(T, double), n, F.perm, yy, y);
+    QA_ONCE(h, kBlock, sched_grid(Z), 0, k_fine_apply, QA_T(T), sview<T>(F, P<T>::sval(F)), Z, xx, yy);
+    QA_ONCE(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(T, double), n, F.perm, yy, y);
     QA_LAUNCH_CHECK();
     QA_HIP(hipStreamSynchronize(s));
     return AMG_OK;
@@ -4576,15 +4536,15 @@ static amg_status level_spmv_t(amg_hierarchy *h, int level, const double *x, dou
   const QuadLevel &Q = h->lev[level];
   const int dim = h->dim;
   T *xx = W[level].g, *yy = W[level].e;
-  k_lex_to_q<double, T><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, x, xx, 0, dim);
+  QA_ONCE(h, kBlock, nblk(Q.n), 0, k_lex_to_q, QA_T(double, T), Q.k, Q.n, x, xx, 0, dim);
   if (dim == 3) {
-    k_capply3<T><<<nblk(Q.n), kBlock, 0, s>>>(qview<T>(Q), xx, yy);
+    QA_ONCE(h, kBlock, nblk(Q.n), 0, k_capply3, QA_T(T), qview<T>(Q), xx, yy);
   } else {
     // reuse the dot kernel's SpMV (the inner products are discarded into the scratch slot of level 0)
-    QA_RUN(h, kBlock, nred(Q.n), 0, k_cspmv_dot, QA_T(T), qview<T>(Q), xx, yy, xx, red(h, h->nlev, nred(Q.n), EPI_STORE, 15));
+    QA_ONCE(h, kBlock, nred(Q.n), 0, k_cspmv_dot, QA_T(T), qview<T>(Q), xx, yy, xx, red(h, h->nlev, nred(Q.n), EPI_STORE, 15));
     finish<2>(h, red(h, h->nlev, nred(Q.n), EPI_STORE, 15));
   }
-  k_lex_to_q<T, double><<<nblk(Q.n), kBlock, 0, s>>>(Q.k, Q.n, yy, y, 1, dim);
+  QA_ONCE(h, kBlock, nblk(Q.n), 0, k_lex_to_q, QA_T(T, double), Q.k, Q.n, yy, y, 1, dim);
   QA_LAUNCH_CHECK();
   QA_HIP(hipStreamSynchronize(s));
   return AMG_OK;
@@ -4611,9 +4571,9 @@ extern "C" amg_status amg_apply_precond(amg_hierarchy *h, const double *r, doubl
   QA_HIP(hipSetDevice(h->device));
   const int64_t n = h->n;
   hipStream_t s = h->stream;
-  QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, double), n, h->fine.perm, r, h->tp);
+  QA_ONCE(h, kBlock, nblk(n), 0, k_gather, QA_T(double, double), n, h->fine.perm, r, h->tp);
   QA_TRY(precond_apply(h, precision, h->tp, h->zp));
-  QA_RUN(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(double, double), n, h->fine.perm, h->zp, z);
+  QA_ONCE(h, kBlock, nblk(n), 0, k_scatter_back, QA_T(double, double), n, h->fine.perm, h->zp, z);
   QA_LAUNCH_CHECK();
   QA_HIP(hipStreamSynchronize(s));
   return AMG_OK;

@@ -241,6 +241,20 @@ int no_memory(bool noalloc) {
   return 0;
 }
 
+// an in-step system whose iteration needs a kernel with no form for several systems: the call says so, and none of the
+// iteration's kernels runs ahead of the others (the start's list alone is launched)
+int refused(bool engine) {
+  amg_hierarchy *h = make(3000);
+  std::vector<amg_info> info;
+  if (call(false, info) != AMG_OK) return 4;
+  if (engine) h->fe_cfg[1] = -1;  // the general engine
+  else h->opt.smoother = 1;       // exact blocks
+  g_launches = 0;
+  const amg_status st = call(false, info);
+  std::printf("status %d launches %ld\n", static_cast<int>(st), g_launches);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -251,5 +265,7 @@ int main(int argc, char **argv) {
   if (what == "no-threads") return no_threads();
   if (what == "no-memory") return no_memory(false);
   if (what == "no-memory-noalloc") return no_memory(true);
+  if (what == "refused-engine") return refused(true);
+  if (what == "refused-smoother") return refused(false);
   return 2;
 }

@@ -41,3 +41,10 @@ def test_no_exception_leaves_a_call(exe, mode):
     queued, and the next call is whole."""
     r = result(exe, mode)
     assert r["bad"] == 0 and r["queued"] == 0
+
+
+@pytest.mark.parametrize("mode", ["refused-engine", "refused-smoother"])
+def test_a_list_with_a_kernel_that_cannot_be_shared_is_refused(exe, mode):
+    """(Planning keeps such systems out.) Launched beside the recording, the kernel would run before the list's others."""
+    r = result(exe, mode)
+    assert r["status"] == amg.INVALID and 0 < r["launches"] <= 6
