@@ -117,10 +117,10 @@ struct FeRows {
 
 template <class T>
 struct FeArgs {
-  const double *ainv;        // coarsest inverse, 64 x 64, storage numbering (bitwise symmetric: Y^t Y in one order)
-  const T *ax[3];            // 9 x n operator of each engine level from the top down (global)
-  const T *g;                // the top level's right-hand side and result (global)
-  T *e;
+  Ptr<const double> ainv;       // coarsest inverse, 64 x 64, storage numbering (bitwise symmetric: Y^t Y in one order)
+  Ptr<const T> ax[3];           // 9 x n operator of each engine level from the top down (global)
+  Ptr<const T> g;               // the top level's right-hand side and result (global)
+  Ptr<T> e;
 };
 
 template <class F>
@@ -703,30 +703,32 @@ void fe_launch(amg_hierarchy *h, int pi) {
 
 }  // namespace
 
-amg_status plan_engine_fast(amg_hierarchy *h) {
-  h->fe_cfg[0] = h->fe_cfg[1] = -1;
+// The configuration a precision's small levels have the shape of, or -1: the top is the largest level the registers allow,
+// k = min(L, 6) in FP32, min(L, 5) in FP64.
+int engine_fast_config(const amg_hierarchy *h, int pi) {
   if (h->use_engine != 1 || h->nlev < 3 || h->L < 4 || h->lev[h->nlev - 1].k != 3 || h->nc != kFeCoarse ||
       h->opt.sweeps != 1 || h->opt.inner_iters != 2)
-    return AMG_OK;
-  if (h->lds_max == 0) {
-    int lds = 0;
-    QA_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device));
-    h->lds_max = static_cast<size_t>(lds);
-  }
+    return -1;
   for (int id = 0; id < 5; id++) {
     const FeCfg c = kFeCfgs[id];
-    // the top is the largest level the count allows: k = min(L, 6) in FP32, min(L, 5) in FP64
-    if (std::min(h->L, c.pi ? 6 : 5) != c.kt) continue;
-    const int top = 1 + (h->L - c.kt);  // hierarchy index of level k = kt
-    bool ok = fe_cfg_bytes(id) <= h->lds_max;
-    for (int l = top; l + 1 < h->nlev && ok; l++)
-      if (h->lev[l].ovf_nnz != 0 || h->lev[l].same_color_ovf) ok = false;
-    if (!ok) continue;
-    h->fe_cfg[c.pi] = id;
-    h->engine_top[c.pi] = top;
-    h->engine_lds_top[c.pi] = top;
-    h->engine_lds[c.pi] = fe_cfg_bytes(id);
-    h->engine_nops[c.pi] = fe_steps(c.kt);
+    if (c.pi != pi || std::min(h->L, pi ? 6 : 5) != c.kt) continue;
+    if (fe_cfg_bytes(id) > h->lds_max) return -1;
+    for (int l = 1 + (h->L - c.kt); l + 1 < h->nlev; l++)
+      if (h->lev[l].ovf_nnz != 0 || h->lev[l].same_color_ovf) return -1;
+    return id;
+  }
+  return -1;
+}
+
+amg_status plan_engine_fast(amg_hierarchy *h) {
+  for (int pi = 0; pi < 2; pi++) {
+    const int id = h->fe_cfg[pi] = engine_fast_config(h, pi);
+    if (id < 0) continue;
+    const int kt = kFeCfgs[id].kt, top = 1 + (h->L - kt);  // hierarchy index of level k = kt
+    h->engine_top[pi] = top;
+    h->engine_lds_top[pi] = top;
+    h->engine_lds[pi] = fe_cfg_bytes(id);
+    h->engine_nops[pi] = fe_steps(kt);
   }
   if (h->fe_cfg[0] >= 0 || h->fe_cfg[1] >= 0) QA_TRY(fe_lds_limits(h->device, h->lds_max));
   return AMG_OK;

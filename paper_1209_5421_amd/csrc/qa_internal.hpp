@@ -254,6 +254,10 @@ struct Chunk {                  // a device allocation that several arrays are c
 
 struct LaunchList;
 struct BatchLists;
+struct BatchIo {                // the caller's vectors of a batch call in step, on the device
+  const double *b;
+  double *x;
+};
 
 }  // namespace qa
 
@@ -313,7 +317,8 @@ struct amg_hierarchy {
   size_t wg_lds[2] = {0, 0};
   bool in_step[2] = {false, false};        // amg_solve_batch runs it in step with others (per precision; plan_wg)
   qa::LaunchList *recording = nullptr;      // launches go to this list instead of the stream
-  qa::BatchLists *batch_lists = nullptr;    // the recorded pieces of its outer iteration, kept for their storage
+  qa::BatchLists *batch_lists[2] = {nullptr, nullptr};  // the recorded pieces of its outer iteration, per precision
+  qa::BatchIo *batch_io = nullptr;
   // all-directions outer iteration (outer_mmax < 0): kept directions p_j, q_j = A p_j, their device address table,
   // the inner products (z, q_j) of the current step and (p_j, q_j)
   std::vector<double *> dir_p, dir_q;
@@ -362,8 +367,10 @@ amg_status alloc_workspaces(amg_hierarchy *h);
 amg_status build_mhat(amg_hierarchy *h);
 amg_status plan_engine(amg_hierarchy *h);
 amg_status plan_wg(amg_hierarchy *h);
+amg_status record_batch(amg_hierarchy *h, int precision);
 void free_batch_lists(amg_hierarchy *h);
-amg_status plan_engine_fast(amg_hierarchy *h);   // qa_engine.hip
+int engine_fast_config(const amg_hierarchy *h, int precision);  // qa_engine.hip
+amg_status plan_engine_fast(amg_hierarchy *h);
 void launch_engine_fast(amg_hierarchy *h, int precision);
 amg_status plan_engine_oct(amg_hierarchy *h);    // qa_engine3.hip
 void launch_engine_oct(amg_hierarchy *h, int precision);

@@ -6,12 +6,33 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <type_traits>
 #include <vector>
 
 namespace qa {
+
+// A pointer read from memory is taken to point anywhere (flat loads, which occupy the LDS path as well); of a kernel's own
+// arguments it is known that they point to global memory. global_pointer says so for a pointer of a recorded call, and the
+// classes that kernels take hold Ptrs, which say so where they are read: made on the host, never to name LDS.
+template <class X>
+__host__ __device__ __forceinline__ X *global_pointer(X *p) {
+#ifdef __HIP_DEVICE_COMPILE__
+  // by way of an integer: the cast to the global address space and back alone is folded away
+  return (X *)(__attribute__((address_space(1))) X *)reinterpret_cast<uintptr_t>(p);
+#else
+  return p;
+#endif
+}
+template <class X>
+struct Ptr {
+  X *p;
+  Ptr() = default;
+  __host__ __device__ Ptr(X *q) : p(q) {}
+  __host__ __device__ operator X *() const { return global_pointer(p); }
+};
 
 // arguments of one kernel call
 template <class... A>
@@ -21,7 +42,8 @@ struct KArgs<H> {
   H head;
   template <class F, class... B>
   __device__ __forceinline__ void call(F f, const B &...b) const {
-    f(b..., head);
+    if constexpr (std::is_pointer<H>::value) f(b..., global_pointer(head));
+    else f(b..., head);
   }
 };
 template <class H, class... R>
@@ -30,7 +52,8 @@ struct KArgs<H, R...> {
   KArgs<R...> rest;
   template <class F, class... B>
   __device__ __forceinline__ void call(F f, const B &...b) const {
-    rest.call(f, b..., head);
+    if constexpr (std::is_pointer<H>::value) rest.call(f, b..., global_pointer(head));
+    else rest.call(f, b..., head);
   }
 };
 template <class H>
@@ -50,35 +73,57 @@ struct KCall {
   __device__ __forceinline__ void run() const { args.call(body); }
 };
 
-// The calls of up to many_cap systems, passed by value: at most 16,000 bytes of kernel arguments, and no device memory
-// for them. (With at most 4,000, 64 systems of 3,844 unknowns took 6.2 ms for the 2.6 that they take so, and 64 of
-// 63,504 took 16.7 for 13.1; 32,000 gave no more.) A call's workgroups are blockIdx.x < grid; a launch takes the largest grid, rounded up to a multiple of
-// eight so that workgroup b of every system runs on XCD b mod 8.
+// The calls of up to kManySystems systems. Up to many_cap of them go by value, in at most 16,000 bytes of kernel
+// arguments: a workgroup then has its call's arguments after one wait. More systems' launches name where the arguments lie
+// in device memory (each hierarchy's own, written when it was planned): with a second launch behind the first, and a third,
+// a step of 256 systems took four launches, each far from filling the chip: 256 systems of 2,601 unknowns 7.0 ms (FP32
+// preconditioner) instead of 3.0, of 10,000 in FP64 22.2 instead of 13.1, where a whole-solve workgroup each takes 3.3 and
+// 13.9. (All launches by address: 64 systems of 63,504 unknowns 13.5 ms instead of 13.2.)
+// A call's workgroups are blockIdx.x < grid. From kAlignGrid workgroups on, the launch's grid is rounded up to a multiple of
+// eight, so that workgroup b of every system runs on XCD b mod 8; smaller grids are left as they are, since the empty
+// places would leave XCDs idle (rounded too, the 256 systems of 2,601 unknowns, of 3 to 12 workgroups a step, took 4.2 ms).
+constexpr int kManySystems = 256;
+constexpr unsigned kAlignGrid = 64;
 template <class P>
 constexpr int many_cap() {
   return std::max<int>(1, std::min<int>(64, 16000 / static_cast<int>(sizeof(P) + 4)));
 }
 template <class P>
 struct Many {
-  P call[many_cap<P>()];
-  unsigned grid[many_cap<P>()];
+  unsigned grid[kManySystems];
+  unsigned by_value;
+  // the calls by value, or where they are
+  alignas(16) unsigned char call[std::max(many_cap<P>() * sizeof(P), kManySystems * sizeof(const P *))];
 };
 template <int NT, class P>
-__global__ void __launch_bounds__(NT) k_many(Many<P> m) {
-  if (blockIdx.x >= m.grid[blockIdx.y]) return;
-  m.call[blockIdx.y].run();
+__global__ void __launch_bounds__(NT) k_many(Many<P>) {
+  // read where the arguments lie (a copy of them would be indexed in scratch memory); constant for the launch in either
+  // place, so scalar loads
+  using Byte = const __attribute__((address_space(4))) unsigned char;
+  using Word = const __attribute__((address_space(4))) unsigned;
+  using Place = const __attribute__((address_space(4))) unsigned long long;
+  Byte *m = (Byte *)__builtin_amdgcn_kernarg_segment_ptr();
+  const unsigned y = blockIdx.y;
+  if (blockIdx.x >= *(Word *)(m + offsetof(Many<P>, grid) + 4 * y)) return;
+  Byte *call = m + offsetof(Many<P>, call);
+  if (*(Word *)(m + offsetof(Many<P>, by_value))) call += y * sizeof(P);
+  else call = (Byte *)*(Place *)(call + 8 * y);
+  ((const P *)call)->run();
 }
 
-// Recorded calls: a step's arguments lie at `at` in the list's bytes.
+// Recorded calls: a step's arguments lie at `at` in the list's bytes, while it is recorded, and then in its copies on the
+// host and on the device.
+struct LaunchList;
 struct LaunchStep {
-  // one launch for the steps of `count` systems, given their arguments, grids and LDS
-  hipError_t (*run)(const unsigned char *const *args, const LaunchStep *const *steps, int count, hipStream_t s);
+  // one launch for the steps of `count` systems, each of a list
+  hipError_t (*run)(const LaunchList *const *lists, const LaunchStep *const *steps, int count, hipStream_t s);
   unsigned grid, lds;
   size_t at;
 };
 struct LaunchList {
   std::vector<LaunchStep> steps;
   std::vector<unsigned char> bytes;
+  const unsigned char *host = nullptr, *dev = nullptr;
   bool refused = false;  // it met a kernel that cannot be recorded
   void clear() { steps.clear(), bytes.clear(), refused = false; }
 };
@@ -101,23 +146,27 @@ inline hipError_t lds_limit(const void *kernel, std::once_flag *once, hipError_t
 }
 
 template <int NT, class P>
-hipError_t run_many(const unsigned char *const *args, const LaunchStep *const *steps, int count, hipStream_t s) {
-  constexpr int cap = many_cap<P>();
+hipError_t run_many(const LaunchList *const *lists, const LaunchStep *const *steps, int count, hipStream_t s) {
   static std::once_flag once[64];
   static hipError_t err[64];
-  for (int i = 0; i < count; i += cap) {
-    alignas(Many<P>) unsigned char buf[sizeof(Many<P>)];  // a body has no default constructor
-    Many<P> &m = *reinterpret_cast<Many<P> *>(buf);
-    const int k = std::min(cap, count - i);
+  for (int i = 0; i < count; i += kManySystems) {
+    Many<P> m;
+    const int k = std::min(kManySystems, count - i);
+    m.by_value = k <= many_cap<P>();
     unsigned grid = 1, lds = 0;
-    for (int j = 0; j < cap; j++) {  // places past the last system: no workgroup runs them
-      const int l = i + std::min(j, k - 1);
-      std::memcpy(static_cast<void *>(&m.call[j]), args[l], sizeof(P));
-      m.grid[j] = j < k ? steps[l]->grid : 0;
-      grid = std::max(grid, m.grid[j]);
-      lds = std::max(lds, steps[l]->lds);
+    for (int j = 0; j < k; j++) {
+      const LaunchStep &t = *steps[i + j];
+      if (m.by_value) {
+        std::memcpy(m.call + j * sizeof(P), lists[i + j]->host + t.at, sizeof(P));
+      } else {
+        const unsigned char *at = lists[i + j]->dev + t.at;
+        std::memcpy(m.call + j * sizeof(at), &at, sizeof(at));
+      }
+      m.grid[j] = t.grid;
+      grid = std::max(grid, t.grid);
+      lds = std::max(lds, t.lds);
     }
-    if (grid > 1) grid = (grid + 7) / 8 * 8;
+    if (grid >= kAlignGrid) grid = (grid + 7) / 8 * 8;
     if (lds > 48 * 1024) {
       const hipError_t e = lds_limit(reinterpret_cast<const void *>(k_many<NT, P>), once, err);
       if (e != hipSuccess) return e;
@@ -132,6 +181,7 @@ void record(LaunchList &list, F body, unsigned grid, size_t lds, A... a) {
   using P = KCall<F, A...>;
   static_assert(std::is_trivially_copyable<P>::value, "arguments are copied as bytes");
   const P p{body, kargs(a...)};
+  list.bytes.resize((list.bytes.size() + 15) / 16 * 16);
   list.steps.push_back(LaunchStep{run_many<NT, P>, grid, static_cast<unsigned>(lds), list.bytes.size()});
   const unsigned char *b = reinterpret_cast<const unsigned char *>(&p);
   list.bytes.insert(list.bytes.end(), b, b + sizeof(P));
@@ -171,8 +221,8 @@ struct ListCursor {
   size_t next;
   size_t left() const { return list->steps.size() - next; }
 };
-// args, steps: room for `count` pointers
-inline hipError_t run_lists(ListCursor *c, const unsigned char **args, const LaunchStep **steps, int count,
+// lists, steps: room for `count` pointers
+inline hipError_t run_lists(ListCursor *c, const LaunchList **lists, const LaunchStep **steps, int count,
                             hipStream_t s) {
   for (;;) {
     int lead = 0;
@@ -185,11 +235,11 @@ inline hipError_t run_lists(ListCursor *c, const unsigned char **args, const Lau
       if (c[i].left() == 0) continue;
       const LaunchStep &t = c[i].list->steps[c[i].next];
       if (t.run != run) continue;
-      args[k] = c[i].list->bytes.data() + t.at;
+      lists[k] = c[i].list;
       steps[k++] = &t;
       c[i].next++;
     }
-    const hipError_t e = run(args, steps, k, s);
+    const hipError_t e = run(lists, steps, k, s);
     if (e != hipSuccess) return e;
   }
 }

@@ -1916,8 +1916,11 @@ static amg_status update_impl(amg_hierarchy *h, const int64_t *row_ptr, const in
   }
   QA_TRY(read_flag(h, f));
   if (f & F_NOT_SPD) return AMG_ERR_NOT_SPD;
+  const bool tiny[2] = {h->tiny_diag[0], h->tiny_diag[1]};
   note_tiny(h, f);
   QA_TRY(build_mhat(h));
+  for (int pi = 0; pi < 2; pi++)  // other kernels run
+    if (h->in_step[pi] && tiny[pi] != h->tiny_diag[pi]) QA_TRY(record_batch(h, pi));
   QA_HIP(hipStreamSynchronize(s));
   h->stale = 0;
   return AMG_OK;
@@ -2020,6 +2023,7 @@ static amg_status setup_dim(int dim, int64_t n, const double *coords, const int6
   if (st != AMG_OK) {
     (void)hipStreamSynchronize(h->stream);
     release(h);
+    free_batch_lists(h);
     delete h;
     return st;
   }

@@ -41,12 +41,12 @@ enum {
 enum Epi { EPI_ALPHA0, EPI_BETA, EPI_ALPHA1, EPI_PAIR32, EPI_PAIR64, EPI_OUT_ALPHA, EPI_OUT_BETA, EPI_STORE };
 
 struct Red {
-  double *partials;
-  double *sc;
+  Ptr<double> partials;
+  Ptr<double> sc;
   int epi;
   int slot;
   unsigned nb;  // workgroups of the launch
-  double *host;  // not null: the outer scalars (sc) also go to this pinned host memory
+  Ptr<double> host;  // not null: the outer scalars (sc) also go to this pinned host memory
 };
 
 // sum over the workgroup (fixed order); valid in thread 0
@@ -175,10 +175,10 @@ __device__ __forceinline__ T upd1_r(T g, T a0, T q0) {
 // that kernel writes e and r and reads its right-hand side r formed on the fly
 template <class T>
 struct Upd1 {
-  double *sc;
-  const T *g, *q0, *p0;
-  T *e, *r;
-  const double *part;  // partial sums (p0, q0), (g, p0) not yet added up (tiled levels), four doubles to a workgroup
+  Ptr<double> sc;
+  Ptr<const T> g, q0, p0;
+  Ptr<T> e, r;
+  Ptr<const double> part;  // partial sums (p0, q0), (g, p0) not yet added up (tiled levels), four doubles to a workgroup
   int nb;              // of nb workgroups; null: the scalars hold alpha0
   __device__ T a0() const { return static_cast<T>(sc[S_A0]); }
   // alpha0 from the sums v; `store`: this thread keeps the scalars for the kernels behind
@@ -200,9 +200,9 @@ struct Upd1 {
 // With `part`, beta and alpha1 come from partial sums that a tiled level left (nb workgroups, four doubles each).
 template <class T>
 struct Pending {
-  const double *sc;
-  const T *p1, *p0;
-  const double *part;
+  Ptr<const double> sc;
+  Ptr<const T> p1, p0;
+  Ptr<const double> part;
   int nb;
   __device__ void pair(const double (&v)[4], T &a1, T &beta) const {
     double b, a;
@@ -224,11 +224,11 @@ struct Pending {
 
 template <class T>
 struct SellView {
-  const int64_t *ptr;
-  const int32_t *row0;    // first position of each slice
-  const int32_t *srow;    // position -> row
-  const int32_t *col;
-  const T *val;
+  Ptr<const int64_t> ptr;
+  Ptr<const int32_t> row0;    // first position of each slice
+  Ptr<const int32_t> srow;    // position -> row
+  Ptr<const int32_t> col;
+  Ptr<const T> val;
 };
 
 // (A x)_row for the row of `lane` in a slice of width w starting at entry `off`: the loop is unrolled by four with the
@@ -644,20 +644,20 @@ __device__ __forceinline__ T subst_lanes(int a, int m, int i, T r, T dg, int k0,
 
 template <class T>
 struct FuseArgs {
-  const int32_t *win_q, *win_row, *crow;
-  const int64_t *win_slice, *win_ent;
+  Ptr<const int32_t> win_q, win_row, crow;
+  Ptr<const int64_t> win_slice, win_ent;
   int64_t win0, nwin;            // this color's windows
   int xcd;                       // 1: XCD-aware window order (grid = 8 x the largest per-XCD share)
   int big;                       // the color has cells left to k_fine_subst_big: write their residual to d
   int ent_cap;                   // factor values / couplings the dynamic LDS holds
   int split;                     // 1: the residual reads the color's own rows [clo, chi) from alt (zero when null)
   int32_t clo, chi;
-  const T *alt;
-  const T *f, *src;              // src: the given residual (GIVEN)
-  T *u, *d;
-  const T *diag, *icv, *fac;
-  const int32_t *icp, *icc;
-  const int64_t *boff;
+  Ptr<const T> alt;
+  Ptr<const T> f, src;              // src: the given residual (GIVEN)
+  Ptr<T> u, d;
+  Ptr<const T> diag, icv, fac;
+  Ptr<const int32_t> icp, icc;
+  Ptr<const int64_t> boff;
 };
 
 template <class T, int SM, bool FWD, bool GIVEN, int NT>
@@ -1179,10 +1179,10 @@ template <class T>
 struct QView {
   int k;
   int64_t n;
-  const T *ax;       // 9 x n slot-major
-  const int32_t *optr;  // null when the level has no overflow
-  const int32_t *ocol;
-  const T *oval;
+  Ptr<const T> ax;       // 9 x n slot-major
+  Ptr<const int32_t> optr;  // null when the level has no overflow
+  Ptr<const int32_t> ocol;
+  Ptr<const T> oval;
 };
 
 // (A x)_q for row q = c n/4 + j of a quadtree level (slots in order 0..8, then overflow entries). A slot whose
@@ -1516,7 +1516,8 @@ __device__ __forceinline__ void k_cgs_post4_body(const QView<T> &Q, const T *__r
   int sl[TL::stage_slots];
   bool sin[TL::stage_slots];
   T sx[TL::stage_slots][4], se[TL::stage_slots], s1[TL::stage_slots], s0[TL::stage_slots];
-  const T *p1p = pend.sc ? pend.p1 : ec, *p0p = pend.sc ? pend.p0 : ec;
+  const T *p1p = ec, *p0p = ec;
+  if (pend.sc) p1p = pend.p1, p0p = pend.p0;
 #pragma unroll
   for (int i = 0; i < TL::stage_slots; i++) {
     const int r = t + i * NT;
@@ -1918,13 +1919,13 @@ __global__ void __launch_bounds__(kBlock) k_cgs3(QView<T> Q, const T *__restrict
 constexpr int kOctSweepThreads = 1024;
 constexpr int64_t kOctSweepMax = 8 * 2048;  // levels of at most this many cells sweep in one workgroup
 template <class T, bool FWD, class Apply>
-__device__ inline void oct_sweep(const QView<T> &Q, const T *__restrict__ f, T *x, T *delta, Apply apply) {
-  const int64_t n8 = Q.n >> 3;
+__device__ inline void oct_sweep(int64_t n, const T *ax, const T *__restrict__ f, T *x, T *delta, Apply apply) {
+  const int64_t n8 = n >> 3;
   for (int cc = 0; cc < 8; cc++) {
     const int c = FWD ? cc : 7 - cc;
     for (int64_t j = threadIdx.x; j < n8; j += kOctSweepThreads) {
       const uint32_t q = static_cast<uint32_t>(c * n8 + j);
-      const T dl = (f[q] - apply(q, x)) / Q.ax[q];
+      const T dl = (f[q] - apply(q, x)) / ax[q];
       if (delta) delta[q] = dl;
       else x[q] += dl;
     }
@@ -1966,7 +1967,7 @@ __global__ void __launch_bounds__(kOctSweepThreads) k_bhat3_small(QView<T> Q, co
   if (PART != 2) {
     for (int64_t q = tid; q < n; q += kOctSweepThreads) u[q] = T(0);
     __syncthreads();
-    for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, true>(Q, f, u, dl, ap);
+    for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, true>(n, Q.ax, f, u, dl, ap);
     for (int64_t M = tid; M < n8; M += kOctSweepThreads) oct_restrict<T>(Q, f, u, gc, M, ap);
     if (PART == 1) return;
     __syncthreads();
@@ -1981,7 +1982,7 @@ __global__ void __launch_bounds__(kOctSweepThreads) k_bhat3_small(QView<T> Q, co
   }
   for (int64_t q = tid; q < n; q += kOctSweepThreads) u[q] += ec[q_of_m3(static_cast<uint32_t>(q & (n8 - 1)), Q.k - 1)];
   __syncthreads();
-  for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, false>(Q, f, u, dl, ap);
+  for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, false>(n, Q.ax, f, u, dl, ap);
 }
 
 // residual of the eight children of coarse cell M, summed in child3_order (Section 4.3's restriction order on each
@@ -2033,8 +2034,6 @@ __global__ void __launch_bounds__(kOctSweepThreads) k_bhat3_lds(QView<T> Q, cons
     }
   }
   __syncthreads();
-  QView<T> QL = Q;
-  QL.ax = s_ax;
   // row_apply3's sum (slots 0..26, then the overflow entries) with the neighbours from the table
   auto ap = [&](uint32_t q, const T *x) {
     T acc = 0;
@@ -2043,8 +2042,8 @@ __global__ void __launch_bounds__(kOctSweepThreads) k_bhat3_lds(QView<T> Q, cons
       for (int32_t e = Q.optr[q]; e < Q.optr[q + 1]; e++) acc += Q.oval[e] * x[static_cast<uint32_t>(Q.ocol[e])];
     return acc;
   };
-  for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, true>(QL, s_f, s_u, use_delta ? s_dl : nullptr, ap);
-  for (int64_t M = tid; M < n8; M += kOctSweepThreads) oct_restrict<T>(QL, s_f, s_u, s_gt, M, ap);
+  for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, true>(n, s_ax, s_f, s_u, use_delta ? s_dl : nullptr, ap);
+  for (int64_t M = tid; M < n8; M += kOctSweepThreads) oct_restrict<T>(Q, s_f, s_u, s_gt, M, ap);
   __syncthreads();
   for (int i = tid; i < nc; i += kOctSweepThreads) s_g[i] = static_cast<double>(s_gt[i]);
   __syncthreads();
@@ -2057,7 +2056,7 @@ __global__ void __launch_bounds__(kOctSweepThreads) k_bhat3_lds(QView<T> Q, cons
   for (int64_t q = tid; q < n; q += kOctSweepThreads)
     s_u[q] += s_e[q_of_m3(static_cast<uint32_t>(q & (n8 - 1)), Q.k - 1)];
   __syncthreads();
-  for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, false>(QL, s_f, s_u, use_delta ? s_dl : nullptr, ap);
+  for (int sw = 0; sw < sweeps; sw++) oct_sweep<T, false>(n, s_ax, s_f, s_u, use_delta ? s_dl : nullptr, ap);
   for (int64_t q = tid; q < n; q += kOctSweepThreads) u[q] = s_u[q];
 }
 
@@ -2358,6 +2357,34 @@ template <class S, class D>
 __global__ void __launch_bounds__(kBlock) k_scatter_back(int64_t n, const int32_t *__restrict__ perm,
                                                          const S *__restrict__ src, D *__restrict__ dst) {
   k_scatter_back_body<S, D>(n, perm, src, dst);
+}
+
+// the ends of a batch call in step, whose caller's vectors are named on the device: b permuted, x from the permuted
+// solution (xp) or zero (null xp)
+struct BatchIoTable {
+  BatchIo *at[kManySystems];
+  BatchIo io[kManySystems];
+};
+__global__ void __launch_bounds__(kManySystems) k_batch_io(BatchIoTable T, int count) {
+  const int i = static_cast<int>(threadIdx.x);
+  if (i < count) *T.at[i] = T.io[i];
+}
+__device__ __forceinline__ void k_batch_b_body(int64_t n, const int32_t *__restrict__ perm, const BatchIo *io,
+                                               double *__restrict__ bp) {
+  k_gather_body<double, double>(n, perm, global_pointer(io->b), bp);
+}
+__global__ void __launch_bounds__(kBlock) k_batch_b(int64_t n, const int32_t *__restrict__ perm, const BatchIo *io,
+                                                    double *__restrict__ bp) {
+  k_batch_b_body(n, perm, io, bp);
+}
+__device__ __forceinline__ void k_batch_x_body(int64_t n, const int32_t *__restrict__ perm,
+                                               const double *__restrict__ xp, const BatchIo *io) {
+  if (xp) k_scatter_back_body<double, double>(n, perm, xp, global_pointer(io->x));
+  else k_fill_body<double>(n, global_pointer(io->x), 0.0);
+}
+__global__ void __launch_bounds__(kBlock) k_batch_x(int64_t n, const int32_t *__restrict__ perm,
+                                                    const double *__restrict__ xp, const BatchIo *io) {
+  k_batch_x_body(n, perm, xp, io);
 }
 
 template <class S, class D>
@@ -3170,6 +3197,8 @@ amg_status plan_engine(amg_hierarchy *h) {
           bytes += vb;
         }
     }
+    h->engine_flops[pi] = engine_flops(h, top, ops);
+    if (engine_fast_config(h, pi) >= 0) continue;  // nothing reads the list then
     EngOp *d = static_cast<EngOp *>(dalloc(h, sizeof(EngOp) * ops.size()));
     if (!d) return AMG_ERR_NOMEM;
     QA_HIP(hipMemcpyAsync(d, ops.data(), sizeof(EngOp) * ops.size(), hipMemcpyHostToDevice, h->stream));
@@ -3181,7 +3210,6 @@ amg_status plan_engine(amg_hierarchy *h) {
     h->engine_lds[pi] = bytes + ainv_bytes;
     h->engine_ops[pi] = d;
     h->engine_nops[pi] = static_cast<int>(ops.size());
-    h->engine_flops[pi] = engine_flops(h, top, ops);
   }
   QA_TRY(engine_lds_limits(h));
   // the specialised engine replaces the interpreter where the levels have its shape
@@ -3607,8 +3635,12 @@ amg_status plan_wg(amg_hierarchy *h) {
   emit_btilde(ops, EmitCtx{h->nlev - 1, h->opt.sweeps, h->opt.inner_iters, mhat, same1.data()}, 0, false);
   if (ops.size() > static_cast<size_t>(kEngMaxOps) || h->nlev - 1 > kEngMaxLevels) return AMG_OK;
   for (int pi = 0; pi < 2; pi++) {
-    h->in_step[pi] = h->fe_cfg[pi] >= 0 && h->n > kWgSolveMax;
-    if (h->in_step[pi]) continue;
+    if (h->fe_cfg[pi] >= 0 && h->n > kWgSolveMax) {
+      const amg_status st = record_batch(h, pi);
+      h->in_step[pi] = st == AMG_OK;
+      if (h->in_step[pi]) continue;
+      if (st != AMG_ERR_INVALID) return st;
+    }
     const size_t ts = pi == 0 ? sizeof(double) : sizeof(float);
     const size_t extra = mhat ? static_cast<size_t>(kMhatPart) * ts : 0;
     size_t bytes = static_cast<size_t>(h->nc) * 2 * ts + extra;
@@ -4166,11 +4198,12 @@ static void outer_resid(amg_hierarchy *h, const double *src) {
            h->zp);
 }
 
-// b in the permuted numbering with (b, b), x = 0, r = b
+// b in the permuted numbering with (b, b), x = 0, r = b (recorded: the caller's b and x are batch_io's)
 static void outer_start(amg_hierarchy *h, const double *b) {
   const int64_t n = h->n;
   const Red R = red_report(h, nred(n), O_BB);
-  QA_RUN(h, kBlock, nblk(n), 0, k_gather, QA_T(double, double), n, h->fine.perm, b, h->bp);
+  if (h->recording) QA_RUN(h, kBlock, nblk(n), 0, k_batch_b, , n, h->fine.perm, h->batch_io, h->bp);
+  else QA_ONCE(h, kBlock, nblk(n), 0, k_gather, QA_T(double, double), n, h->fine.perm, b, h->bp);
   QA_RUN(h, kBlock, nred(n), 0, k_dot, QA_T(double, double), n, h->bp, h->bp, R);
   finish<1>(h, R);
   QA_RUN(h, kBlock, nblk(n), 0, k_fill, QA_T(double), n, h->xp, 0.0);
@@ -4239,7 +4272,8 @@ static void outer_restart(amg_hierarchy *h) { outer_resid(h, h->tp); }
 // true residual and the solution in the caller's numbering
 static void outer_end(amg_hierarchy *h, double *x) {
   outer_true_resid(h);
-  QA_RUN(h, kBlock, nblk(h->n), 0, k_scatter_back, QA_T(double, double), h->n, h->fine.perm, h->xp, x);
+  if (h->recording) QA_RUN(h, kBlock, nblk(h->n), 0, k_batch_x, , h->n, h->fine.perm, h->xp, h->batch_io);
+  else QA_ONCE(h, kBlock, nblk(h->n), 0, k_scatter_back, QA_T(double, double), h->n, h->fine.perm, h->xp, x);
 }
 
 static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, double tol, amg_info *info) {
@@ -4331,11 +4365,16 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
 enum { LL_START = 0, LL_ITER = 1, LL_CHECK = 5, LL_RESTART = 6, LL_END = 7, LL_ZERO = 8, LL_COUNT = 9 };
 struct BatchLists {
   LaunchList list[LL_COUNT];  // LL_ITER + 2 * parity + (a kept direction)
+  std::vector<unsigned char> bytes;  // the lists' arguments, one list after the other
+  unsigned char *dev = nullptr;      // on the device
+  size_t size = 0;                   // the device array's
 };
 
 void free_batch_lists(amg_hierarchy *h) {
-  delete h->batch_lists;
-  h->batch_lists = nullptr;
+  for (BatchLists *&B : h->batch_lists) {
+    delete B;
+    B = nullptr;
+  }
 }
 
 struct BatchSys {
@@ -4349,60 +4388,94 @@ struct BatchSys {
   amg_status st;
 };
 
-// list `what` of a system, recorded when it is first needed in a call
-static amg_status batch_list(BatchSys &Y, int what, LaunchList *&list) {
-  amg_hierarchy *h = Y.h;
-  list = &h->batch_lists->list[what];
-  if (!list->steps.empty()) return AMG_OK;
-  struct Scope {  // recording ends on every path
-    amg_hierarchy *h;
-    ~Scope() { h->recording = nullptr; }
-  } scope{h};
-  h->recording = list;
+// one piece of the outer iteration into its list
+static amg_status record_list(amg_hierarchy *h, int what, LaunchList &list) {
+  list.clear();
+  h->recording = &list;
   amg_status st = AMG_OK;
   if (what == LL_START) {
-    outer_start(h, Y.b);
+    outer_start(h, nullptr);
   } else if (what == LL_CHECK) {
     outer_true_resid(h);
   } else if (what == LL_RESTART) {
     outer_restart(h);
   } else if (what == LL_END) {
-    outer_end(h, Y.x);
+    outer_end(h, nullptr);
   } else if (what == LL_ZERO) {
-    QA_RUN(h, kBlock, nblk(h->n), 0, k_fill, QA_T(double), h->n, Y.x, 0.0);
+    QA_RUN(h, kBlock, nblk(h->n), 0, k_batch_x, , h->n, h->fine.perm, static_cast<const double *>(nullptr), h->batch_io);
   } else {
     double *P[2] = {h->pp, h->pprev}, *Q[2] = {h->qp, h->qprev};
     const int i = (what - LL_ITER) >> 1;
     st = outer_iterate(h, P[i], Q[i], P[1 - i], Q[1 - i], ((what - LL_ITER) & 1) != 0);
   }
-  return st == AMG_OK && list->refused ? AMG_ERR_INVALID : st;
+  return st == AMG_OK && list.refused ? AMG_ERR_INVALID : st;
+}
+
+// Record a system's pieces in a precision and put their arguments on the device (ready once the stream has drained). They
+// name the hierarchy's own vectors only and hold until it is freed or needs other kernels (a values update that changes
+// tiny_diag: the same sizes). AMG_ERR_INVALID: a piece needs a kernel that cannot be shared.
+amg_status record_batch(amg_hierarchy *h, int pi) {
+  struct Scope {  // recording ends on every path
+    amg_hierarchy *h;
+    int precision;
+    ~Scope() { h->recording = nullptr, h->precision = precision; }
+  } scope{h, h->precision};
+  try {
+    if (!h->batch_lists[pi]) h->batch_lists[pi] = new BatchLists;
+    if (!h->batch_io) h->batch_io = dalloc_n<BatchIo>(h, 1);
+    if (!h->batch_io) return AMG_ERR_NOMEM;
+    BatchLists &B = *h->batch_lists[pi];
+    h->precision = pi;
+    size_t size = 0;
+    for (int w = 0; w < LL_COUNT; w++) {
+      QA_TRY(record_list(h, w, B.list[w]));
+      size += (B.list[w].bytes.size() + 15) / 16 * 16;
+    }
+    if (size > B.size) {
+      B.dev = dalloc_n<unsigned char>(h, static_cast<int64_t>(size));
+      if (!B.dev) return AMG_ERR_NOMEM;
+      B.size = size;
+    }
+    B.bytes.assign(size, 0);
+    size_t at = 0;
+    for (LaunchList &l : B.list) {
+      std::memcpy(B.bytes.data() + at, l.bytes.data(), l.bytes.size());
+      l.host = B.bytes.data() + at;
+      l.dev = B.dev + at;
+      at += (l.bytes.size() + 15) / 16 * 16;
+      std::vector<unsigned char>().swap(l.bytes);
+    }
+    QA_HIP(hipMemcpyAsync(B.dev, B.bytes.data(), size, hipMemcpyHostToDevice, h->stream));
+  } catch (const std::bad_alloc &) {  // the lists' storage
+    return AMG_ERR_NOMEM;
+  }
+  return AMG_OK;
 }
 
 // run the wanted lists of all systems that have one
-static amg_status batch_run(BatchSys *Y, int m, ListCursor *cur, const unsigned char **args, const LaunchStep **steps,
+static amg_status batch_run(BatchSys *Y, int m, ListCursor *cur, const LaunchList **lists, const LaunchStep **steps,
                             hipStream_t s) {
   int k = 0;
   for (int i = 0; i < m; i++) {
     if (Y[i].want < 0) continue;
-    LaunchList *list = nullptr;
-    QA_TRY(batch_list(Y[i], Y[i].want, list));
-    cur[k++] = ListCursor{list, 0};
+    cur[k++] = ListCursor{&Y[i].h->batch_lists[Y[i].h->precision]->list[Y[i].want], 0};
   }
-  QA_HIP(run_lists(cur, args, steps, k, s));
+  QA_HIP(run_lists(cur, lists, steps, k, s));
   QA_HIP(hipStreamSynchronize(s));
   return AMG_OK;
 }
 
-// Solve the m systems Y on stream s; cur, args, steps: room for m entries each.
-static amg_status solve_many_lists(BatchSys *Y, int m, ListCursor *cur, const unsigned char **args, const LaunchStep **steps,
+// Solve the m systems Y on stream s; cur, lists, steps: room for m entries each.
+static amg_status solve_many_lists(BatchSys *Y, int m, ListCursor *cur, const LaunchList **lists, const LaunchStep **steps,
                              hipStream_t s) {
-  for (int i = 0; i < m; i++) {
-    amg_hierarchy *h = Y[i].h;
-    if (!h->batch_lists) h->batch_lists = new BatchLists;
-    for (LaunchList &l : h->batch_lists->list) l.clear();
-    Y[i].want = LL_START;
+  for (int i = 0; i < m; i += kManySystems) {  // where the caller's vectors are
+    BatchIoTable T;
+    const int k = std::min(kManySystems, m - i);
+    for (int j = 0; j < k; j++) T.at[j] = Y[i + j].h->batch_io, T.io[j] = BatchIo{Y[i + j].b, Y[i + j].x};
+    k_batch_io<<<1, kManySystems, 0, s>>>(T, k);
   }
-  auto run = [&]() { return batch_run(Y, m, cur, args, steps, s); };
+  for (int i = 0; i < m; i++) Y[i].want = LL_START;
+  auto run = [&]() { return batch_run(Y, m, cur, lists, steps, s); };
   QA_TRY(run());
   for (int i = 0; i < m; i++) {
     BatchSys &S = Y[i];
@@ -4465,18 +4538,10 @@ static amg_status solve_many_lists(BatchSys *Y, int m, ListCursor *cur, const un
   for (int i = 0; i < m; i++) Y[i].want = Y[i].bn == 0.0 ? LL_ZERO : LL_END;
   return run();
 }
-static amg_status solve_many(BatchSys *Y, int m, ListCursor *cur, const unsigned char **args, const LaunchStep **steps,
+static amg_status solve_many(BatchSys *Y, int m, ListCursor *cur, const LaunchList **lists, const LaunchStep **steps,
                              hipStream_t s) {
-  amg_status st;
-  try {
-    st = solve_many_lists(Y, m, cur, args, steps, s);
-  } catch (const std::bad_alloc &) {  // the lists' storage
-    st = AMG_ERR_NOMEM;
-  }
+  const amg_status st = solve_many_lists(Y, m, cur, lists, steps, s);
   if (st != AMG_OK) (void)hipStreamSynchronize(s);  // launches before the failed one still use the caller's vectors
-  for (int i = 0; i < m; i++)  // the storage stays, the calls and the caller's vectors in them do not
-    if (Y[i].h->batch_lists)
-      for (LaunchList &l : Y[i].h->batch_lists->list) l.clear();
   return st;
 }
 
@@ -4706,7 +4771,7 @@ struct BatchWork {
   int count[3];
   BatchSys *sys;
   ListCursor *cur;
-  const unsigned char **args;
+  const LaunchList **lists;
   const LaunchStep **steps;
 };
 static int batch_route(const amg_hierarchy *h) {  // 0 to 2 as above, -1: amg_solve
@@ -4726,7 +4791,7 @@ static amg_status batch_in_step(amg_hierarchy *const *hs, const double *const *b
     const int i = W.ids[2][j];
     W.sys[j] = BatchSys{hs[i], b[i], x[i], tol[i], 0.0, 0, 0, -1, false, 0, AMG_OK};
   }
-  QA_TRY(solve_many(W.sys, m, W.cur, W.args, W.steps, hs[W.ids[2][0]]->stream));
+  QA_TRY(solve_many(W.sys, m, W.cur, W.lists, W.steps, hs[W.ids[2][0]]->stream));
   const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   for (int j = 0; j < m; j++) {
     const int i = W.ids[2][j];
@@ -4776,7 +4841,7 @@ struct NoAllocStage {
   int ids[3][kNoAllocMaxSystems];
   BatchSys sys[kNoAllocMaxSystems];
   ListCursor cur[kNoAllocMaxSystems];
-  const unsigned char *args[kNoAllocMaxSystems];
+  const LaunchList *lists[kNoAllocMaxSystems];
   const LaunchStep *steps[kNoAllocMaxSystems];
   amg_status st[kNoAllocMaxSystems];
   amg_info inf[kNoAllocMaxSystems];
@@ -4833,7 +4898,7 @@ static amg_status solve_batch(amg_hierarchy *const *hs, const double *const *b, 
   const size_t m = ids[2].size();
   std::vector<BatchSys> sys(m);
   std::vector<ListCursor> cur(m);
-  std::vector<const unsigned char *> args(m);
+  std::vector<const LaunchList *> lists(m);
   std::vector<const LaunchStep *> steps(m);
   std::vector<amg_status> st(count, AMG_OK);
   std::vector<amg_info> inf(count);
@@ -4859,7 +4924,7 @@ static amg_status solve_batch(amg_hierarchy *const *hs, const double *const *b, 
     return AMG_OK;
   };
   const BatchWork W{{ids[0].data(), ids[1].data(), ids[2].data()}, {0, 0, static_cast<int>(m)},
-                    sys.data(), cur.data(), args.data(), steps.data()};
+                    sys.data(), cur.data(), lists.data(), steps.data()};
   auto in_step = [&]() { return batch_in_step(hs, b, x, tol, W, t0, st.data(), inf.data()); };
   // the whole-solve launches take device memory, from the caller's allocator where it gave one: on the caller's thread
   if (ids[0].size() + ids[1].size() > 0) {
@@ -4899,7 +4964,7 @@ extern "C" amg_status amg_solve_batch_noalloc(amg_hierarchy *const *hs, const do
     if (batch_route(hs[i]) < 0) return AMG_ERR_INVALID;
   std::lock_guard<std::mutex> lock(g_noalloc_mu);
   NoAllocStage &G = g_stage;
-  BatchWork W{{G.ids[0], G.ids[1], G.ids[2]}, {0, 0, 0}, G.sys, G.cur, G.args, G.steps};
+  BatchWork W{{G.ids[0], G.ids[1], G.ids[2]}, {0, 0, 0}, G.sys, G.cur, G.lists, G.steps};
   for (int32_t i = 0; i < count; i++) {
     const int route = batch_route(hs[i]);
     W.ids[route][W.count[route]++] = i;

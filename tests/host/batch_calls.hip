@@ -241,17 +241,21 @@ int no_memory(bool noalloc) {
   return 0;
 }
 
-// an in-step system whose iteration needs a kernel with no form for several systems: the call says so, and none of the
-// iteration's kernels runs ahead of the others (the start's list alone is launched)
+// a system that planning would let run in step, whose iteration needs a kernel with no form for several systems (the
+// general engine; the per-step path of the engine's levels): the recording is refused, nothing is launched by it, and the
+// system becomes a whole-solve workgroup, one launch of a call
 int refused(bool engine) {
   amg_hierarchy *h = make(3000);
-  std::vector<amg_info> info;
-  if (call(false, info) != AMG_OK) return 4;
-  if (engine) h->fe_cfg[1] = -1;  // the general engine
-  else h->opt.smoother = 1;       // exact blocks
+  if (!h->in_step[1]) return 4;
+  if (engine) h->use_engine = 0;
+  else h->engine_top[1] = h->nlev;
   g_launches = 0;
+  if (qa::plan_wg(h) != AMG_OK) return 5;
+  const long planning = g_launches;
+  std::vector<amg_info> info;
   const amg_status st = call(false, info);
-  std::printf("status %d launches %ld\n", static_cast<int>(st), g_launches);
+  std::printf("planning %ld in_step %d status %d launches %ld\n", planning, h->in_step[1] ? 1 : 0, static_cast<int>(st),
+              g_launches - planning);
   return 0;
 }
 
@@ -266,6 +270,6 @@ int main(int argc, char **argv) {
   if (what == "no-memory") return no_memory(false);
   if (what == "no-memory-noalloc") return no_memory(true);
   if (what == "refused-engine") return refused(true);
-  if (what == "refused-smoother") return refused(false);
+  if (what == "refused-top") return refused(false);
   return 2;
 }
