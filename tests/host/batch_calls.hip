@@ -148,6 +148,7 @@ amg_hierarchy *make(int64_t n, bool allocator = false) {
   h->host_scal = static_cast<double *>(std::calloc(qa::kScalars, sizeof(double)));
   if (qa::alloc_workspaces(h) != AMG_OK || qa::plan_engine(h) != AMG_OK || qa::plan_wg(h) != AMG_OK) std::exit(3);
   g_hs.push_back(h);
+  g_pending[h->stream] = 0;
   return h;
 }
 
@@ -259,6 +260,19 @@ int refused(bool engine) {
   return 0;
 }
 
+// host memory that the first call without allocation takes
+int heap_noalloc() {
+  make(3000), make(3500), make(2000);
+  static double b[4096], x[4096], tol[3] = {1e-8, 1e-8, 1e-8};
+  static const double *bs[3] = {b, b, b};
+  static double *xs[3] = {x, x, x};
+  static amg_info info[3];
+  g_new = 0;
+  const amg_status st = amg_solve_batch_noalloc(g_hs.data(), bs, xs, tol, 3, info);
+  std::printf("status %d allocations %ld\n", static_cast<int>(st), g_new.load());
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -271,5 +285,6 @@ int main(int argc, char **argv) {
   if (what == "no-memory-noalloc") return no_memory(true);
   if (what == "refused-engine") return refused(true);
   if (what == "refused-top") return refused(false);
+  if (what == "heap-noalloc") return heap_noalloc();
   return 2;
 }

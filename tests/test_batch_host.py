@@ -47,3 +47,8 @@ def test_no_exception_leaves_a_call(exe, mode):
 def test_a_list_with_a_kernel_that_cannot_be_shared_is_refused(exe, mode):
     """(Planning's rules keep such systems out.) Launched beside the recording, the kernel would run at once."""
     assert result(exe, mode) == {"planning": 0, "in_step": 0, "status": 0, "launches": 1}
+
+
+def test_a_call_without_allocation_takes_no_host_memory_either(exe):
+    """Not in its first call: what it launches is recorded when the systems are planned."""
+    assert result(exe, "heap-noalloc") == {"status": 0, "allocations": 0}
