@@ -875,7 +875,8 @@ __device__ __forceinline__ void k_fine_gs_body(const SellView<T> &S, const FuseA
     const bool on = i < m;
     const int p = a + (on ? i : 0);
     T x;
-    if constexpr (SM) x = block_solve_lanes<T, G>(s_x + s_cf[j], m, i, on ? s_r[p] : T(0));
+    // (a group without a cell reads and discards a value: not behind the last cell's factor, where the LDS may end)
+    if constexpr (SM) x = block_solve_lanes<T, G>(m > 0 ? s_x + s_cf[j] : s_r, m, i, on ? s_r[p] : T(0));
     else
       x = subst_lanes<T, FWD, G>(a, m, i, on ? s_r[p] : T(0), on ? s_dg[p] : T(1), on ? s_ep[p] : 0,
                                  on ? s_ep[p + 1] : 0, s_col, s_val);
