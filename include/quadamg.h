@@ -54,12 +54,12 @@ typedef struct {
                             first use and kept by the hierarchy) */
     int32_t max_iters;   /* outer iteration cap (default 1000) */
     int32_t engine;      /* 1 (default): the small coarse levels of the cycle run inside one persistent workgroup
-                            with LDS-resident operators, specialised at compile time to the level shape where the
+                            with their operators on chip, specialised at compile time to the level shape where the
                             levels allow it, and each larger quadtree level without same-color or overflow couplings
                             runs its presmoothing sweep with the restriction, and its first post-smoothing sweep, as
                             one launch each (tiles of 8 x 8 or 16 x 16 super-cells; the same values as one launch
-                            per color phase); 2: the same, with the workgroup always through its generic step interpreter;
-                            0: one kernel launch per step on every level */
+                            per color phase); 2: the same, with the workgroup always through its generic step
+                            interpreter; 0: one kernel launch per step on every level */
     int32_t batch;       /* 1 (default): amg_solve_batch runs this system, when it has at most 65,536 unknowns,
                             together with the batch's other small systems, in shared launches; 0: it runs as its own
                             amg_solve */
@@ -109,10 +109,10 @@ amg_status amg_setup(int64_t n, const double *coords, const int64_t *row_ptr, co
  * for the Gauss-Seidel smoother, and the same cycle and outer iteration as amg_setup. The coarsest level is the first
  * k with 8^k <= coarse_max. coords: device, n x 3 interleaved (x, y, z). opt may be NULL; opt->box must be NULL (the
  * box argument replaces it). With options.engine on, the octree levels from 4,096 cells down run inside one persistent
- * workgroup (default coarse_max, sweeps and inner_iters); the others, and all with it off, run one kernel launch per step
- * (option batch has no effect). amg_solve, amg_apply_precond, amg_update_values, amg_export_level (27 slots per row, lexicographic id
- * t1 + 2^k t2 + 4^k t3), amg_level_smooth, amg_level_spmv and amg_free take the hierarchy as for amg_setup. Errors
- * as amg_setup. */
+ * workgroup (default coarse_max, sweeps and inner_iters); the others, and all with it off, run one kernel launch per
+ * step (option batch has no effect). amg_solve, amg_apply_precond, amg_update_values, amg_export_level (27 slots per
+ * row, lexicographic id t1 + 2^k t2 + 4^k t3), amg_level_smooth, amg_level_spmv and amg_free take the hierarchy as for
+ * amg_setup. Errors as amg_setup. */
 amg_status amg_setup3d(int64_t n, const double *coords, const int64_t *row_ptr, const int32_t *col_idx,
                        const double *vals, int64_t nnz, const double *box, const amg_options *opt,
                        amg_hierarchy **out);
@@ -159,25 +159,25 @@ amg_status amg_set_stream(amg_hierarchy *h, void *stream);
  * drained (the call synchronises each stream first); info is a host array of `count` entries or NULL. The
  * hierarchies must be distinct. Small systems (options.batch, at most 65,536 unknowns) are solved together on the
  * stream of the first of them: above 2,500 unknowns (with the small-level engine's specialised form, see
- * amg_engine_info) in step, one launch per step of the iteration for all systems that are at it, each system's kernels
- * those of amg_solve; the others as one persistent workgroup per system in one launch, outer flexible CG, smoother,
- * K-cycle and convergence test all on the device. Every other system is driven by its own host thread on its
- * hierarchy's stream, overlapping with the launches (systems whose hierarchies share a stream run in turn). The call
- * returns when every system is done. A system's result does not depend on the rest of the batch (bit-identical alone
- * and in any mix); a system in step has amg_solve's result bit for bit, a whole-solve workgroup's differs from it only
- * by rounding (different reduction trees). Returns the first
- * non-OK status; every system is attempted. */
+ * amg_engine_info) in step, one launch per step of the iteration for up to 256 systems that are at it, each system's
+ * kernels those of amg_solve, recorded at its setup; the others as one persistent workgroup per system in one launch,
+ * outer flexible CG, smoother, K-cycle and convergence test all on the device. Every other system is driven by its own
+ * host thread on its hierarchy's stream, overlapping with the launches (systems whose hierarchies share a stream run in
+ * turn; where no thread can be had, the caller's drives them). The call returns when every system is done. A system's
+ * result does not depend on the rest of the batch (bit-identical alone and in any mix); a system in step has
+ * amg_solve's result bit for bit, a whole-solve workgroup's differs from it only by rounding (different reduction
+ * trees). Returns the first non-OK status; every system is attempted. */
 amg_status amg_solve_batch(amg_hierarchy *const *h, const double *const *b, double *const *x, const double *tol,
                            int32_t count, amg_info *info);
 
-/* amg_solve_batch for callers that cannot allocate (code under HIP graph capture, serving loops that forbid allocation):
- * the same launches and results, with the per-call system descriptors and info words of the whole-solve workgroups held in
- * a device array of the library's own (about 400 KB per device, kept until the process ends) and the launches of systems
- * in step recorded when they were set up. No hipMalloc, hipFree or other allocating call is made, and no host memory is
- * taken. Every system must be one that amg_solve_batch solves together with others (options.batch = 1, the default fine
- * smoother, at most 65,536 unknowns); count must not exceed 256. Errors, before any device work: AMG_ERR_INVALID for those
- * conditions or the arguments amg_solve_batch rejects. All calls on one device share the array: calls that overlap in time
- * on one device race and must be serialised by the caller. */
+/* amg_solve_batch for callers that cannot allocate (code under HIP graph capture, serving loops that forbid
+ * allocation): the same launches and results, with the per-call system descriptors and info words of the whole-solve
+ * workgroups held in a device array of the library's own (about 400 KB per device, kept until the process ends) and
+ * the launches of systems in step recorded when they were set up. No hipMalloc, hipFree or other allocating call is
+ * made, and no host memory is taken. Every system must be one that amg_solve_batch solves together with others
+ * (options.batch = 1, the default fine smoother, at most 65,536 unknowns); count must not exceed 256. Errors, before
+ * any device work: AMG_ERR_INVALID for those conditions or the arguments amg_solve_batch rejects. All calls on one
+ * device share the array: calls that overlap in time on one device race and must be serialised by the caller. */
 amg_status amg_solve_batch_noalloc(amg_hierarchy *const *h, const double *const *b, double *const *x,
                                    const double *tol, int32_t count, amg_info *info);
 
@@ -233,7 +233,7 @@ amg_status amg_level_spmv(amg_hierarchy *h, int32_t level, const double *x, doub
 /* Kernel timing of one named kernel family for roofline measurement: while enabled, every launch of that
  * kernel on h's stream is bracketed by HIP events; amg_kernel_timing_read returns the number of launches and
  * their summed device time since the last enable. name: "spmv64" (outer FP64 sliced-ELL SpMV), "gs_fine32",
- * "gs_fine64" (fine-level smoother residual pass), "resid_fine32", "resid_fine64", "engine32", "engine64" (the
+ * "gs_fine64" (fine-level color phases), "resid_fine32", "resid_fine64", "engine32", "engine64" (the
  * persistent small-level workgroup of that precision). name NULL disables. bytes_per_launch is the kernel's
  * algorithmic HBM bytes per launch; for the engine kinds it is its algorithmic floating-point operations per
  * launch instead (the engine works out of LDS and L2). Timing one family takes up to 4,096 launches; later
@@ -241,9 +241,9 @@ amg_status amg_level_spmv(amg_hierarchy *h, int32_t level, const double *x, doub
 amg_status amg_kernel_timing_enable(amg_hierarchy *h, const char *name);
 amg_status amg_kernel_timing_read(amg_hierarchy *h, int64_t *launches, double *total_ms, double *bytes_per_launch);
 
-/* Configuration of the persistent small-level workgroup (of the octree's, for amg_setup3d's hierarchies) for a precision:
- * the hierarchy level index of its top (-1 = not used), the first level index whose operators stay on chip while the level
- * is worked on (registers or LDS), the number of its steps and its dynamic LDS bytes. */
+/* Configuration of the persistent small-level workgroup (of the octree's, for amg_setup3d's hierarchies) for a
+ * precision: the hierarchy level index of its top (-1 = not used), the first level index whose operators stay on chip
+ * while the level is worked on (registers or LDS), the number of its steps and its dynamic LDS bytes. */
 amg_status amg_engine_info(const amg_hierarchy *h, int32_t precision, int32_t *top_level, int32_t *lds_level,
                            int32_t *steps, size_t *lds_bytes);
 

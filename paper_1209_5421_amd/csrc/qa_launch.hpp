@@ -14,9 +14,9 @@
 
 namespace qa {
 
-// A pointer read from memory is taken to point anywhere (flat loads, which occupy the LDS path as well); of a kernel's own
-// arguments it is known that they point to global memory. global_pointer says so for a pointer of a recorded call, and the
-// classes that kernels take hold Ptrs, which say so where they are read: made on the host, never to name LDS.
+// A pointer read from memory is taken to point anywhere (flat loads, which occupy the LDS path as well); of a kernel's
+// own arguments it is known that they point to global memory. global_pointer says so for a pointer of a recorded call,
+// and the classes that kernels take hold Ptrs, which say so where they are read: made on the host, never to name LDS.
 template <class X>
 __host__ __device__ __forceinline__ X *global_pointer(X *p) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -74,14 +74,14 @@ struct KCall {
 };
 
 // The calls of up to kManySystems systems. Up to many_cap of them go by value, in at most 16,000 bytes of kernel
-// arguments: a workgroup then has its call's arguments after one wait. More systems' launches name where the arguments lie
-// in device memory (each hierarchy's own, written when it was planned): with a second launch behind the first, and a third,
-// a step of 256 systems took four launches, each far from filling the chip: 256 systems of 2,601 unknowns 7.0 ms (FP32
-// preconditioner) instead of 3.0, of 10,000 in FP64 22.2 instead of 13.1, where a whole-solve workgroup each takes 3.3 and
-// 13.9. (All launches by address: 64 systems of 63,504 unknowns 13.5 ms instead of 13.2.)
-// A call's workgroups are blockIdx.x < grid. From kAlignGrid workgroups on, the launch's grid is rounded up to a multiple of
-// eight, so that workgroup b of every system runs on XCD b mod 8; smaller grids are left as they are, since the empty
-// places would leave XCDs idle (rounded too, the 256 systems of 2,601 unknowns, of 3 to 12 workgroups a step, took 4.2 ms).
+// arguments: a workgroup then has its call's arguments after one wait. A launch for more systems names where the arguments
+// lie in device memory, each hierarchy's own, written at its setup. By value alone a step of 256 systems took four
+// launches or more, one behind the other and each far from filling the chip: 7.0 ms instead of 3.0 for systems of 2,601
+// unknowns (FP32 preconditioner), 22.2 instead of 13.1 for 10,000 (FP64); a whole-solve workgroup each takes 3.3 and 13.9.
+// By address alone 64 systems of 63,504 unknowns took 13.5 ms instead of 13.2.
+// A call's workgroups are blockIdx.x < grid. From kAlignGrid workgroups on, the launch's grid is rounded up to a multiple
+// of eight, so that workgroup b of every system runs on XCD b mod 8; smaller grids are left as they are, since the empty
+// places would leave XCDs idle (rounded too, the 256 systems of 2,601, of 3 to 12 workgroups a step, took 4.2 ms).
 constexpr int kManySystems = 256;
 constexpr unsigned kAlignGrid = 64;
 template <class P>
@@ -111,8 +111,8 @@ __global__ void __launch_bounds__(NT) k_many(Many<P>) {
   ((const P *)call)->run();
 }
 
-// Recorded calls: a step's arguments lie at `at` in the list's bytes, while it is recorded, and then in its copies on the
-// host and on the device.
+// Recorded calls: a step's arguments lie at `at` in the list's bytes, while it is recorded, and then in its copies on
+// the host and on the device.
 struct LaunchList;
 struct LaunchStep {
   // one launch for the steps of `count` systems, each of a list

@@ -1964,7 +1964,7 @@ extern "C" amg_status amg_estimate_bytes(int64_t n, int64_t nnz, const amg_optio
   // exact-block smoother: a packed factor of m (m + 1) / 2 FP64 + FP32 values per cell of m <= kBlockMax unknowns
   // (at most (kBlockMax + 1) / 2 values per unknown) and the cell offsets
   if (o.smoother == 1 && nlev > 1) b += static_cast<double>(n) * (kBlockMax + 1) * 6 + std::ldexp(1.0, 2 * L) * 16;
-  b += 1 << 20;  // scalars, partial sums, alignment slack
+  b += 1 << 20;  // scalars, partial sums, the recorded launches of a small system, alignment slack
   // arrays are carved from shared chunks of about b / 8 bytes (see chunk_unit_for): allow a chunk and a half unused
   b += 1.5 * static_cast<double>(chunk_unit_for(static_cast<size_t>(b)));
   *bytes = static_cast<size_t>(b);

@@ -3,14 +3,14 @@
 //
 // Kernels are templated on the storage/arithmetic type T (double for the plain solve, float for the
 // preconditioner of the mixed form); every inner product accumulates in double with a fixed reduction tree
-// (wavefront shuffles, then the four waves of a workgroup, then the workgroup partials summed in order by the last
-// workgroup to finish), so results depend only on the system size, never on scheduling.
+// (wavefront shuffles, then the waves of a workgroup, then the workgroups' partial sums in a fixed order, by k_finish or,
+// where they are few, by the kernel that needs them), so results depend only on the system size, never on scheduling.
 //
 // Fine level: sliced ELL (64-row slices = one wavefront, column-major, so every load of a slice row step is one
-// coalesced 256/512-byte access). The colored block Gauss-Seidel phase (Section 4.5) is split in two kernels: the
-// residual of the color's rows (sliced-ELL pass), then one thread per cell doing the forward/backward
-// substitution over the cell's unknowns with the in-cell couplings. The kernel boundary between the two is what
-// makes every residual of a color see the iterate at phase start.
+// coalesced 256/512-byte access). A colored block Gauss-Seidel phase (Section 4.5) is one launch, k_fine_gs: a workgroup
+// takes a window of whole cells of the color, forms the residual of its rows (sliced-ELL pass) and solves its cells, by
+// substitution or with their factors; k_fine_subst_big follows for the cells of more than 32 unknowns. Every residual
+// of a phase sees the iterate at its start: where the color's own rows couple across cells they are read from a copy.
 //
 // Quadtree levels: values only (9 per row, slot-major so each slot is a coalesced stream), neighbour indices
 // recomputed from the color-major Morton index; overflow couplings from a small CSR.
@@ -1358,8 +1358,9 @@ __global__ void __launch_bounds__(kBlock) k_cgs_post(QView<T> Q, const T *__rest
 // A launch is bound by its latency: dispatch, one round of loads, four LDS phases, the stores. B~ of a level takes four
 // launches (two tiles per B^, A u and the inner products in the second, their partial sums added up by the kernel that
 // needs them) where tiles, products and reductions of their own took nine: 47 -> 22 us per visit of the 16,384-cell
-// level in FP32 (4.9 / 5.4 us per presmoothing tile, 5.7 / 5.9 us with the products, against 6.2 + 4.7 + 4.3 us), 8.92
-// instead of 10.41 ms per FP32-preconditioned solve of 1,044,484 unknowns, 8.95 instead of 11.58 ms in FP64 on 301,401.
+// level in FP32 (4.9 / 5.4 us per presmoothing tile, 5.7 / 5.9 us with the products, against 6.2 + 4.7 + 4.3 us). Taken
+// alone that brought an FP32-preconditioned solve of 1,044,484 unknowns from 10.41 to 8.92 ms, one in FP64 of 301,401
+// from 11.58 to 8.95 ms.
 template <int TS, int RS>
 struct Tile {
   static constexpr int NT = TS == 16 ? 512 : 256;  // threads: at most two row slots per thread and phase, so that a
@@ -2258,9 +2259,9 @@ __global__ void __launch_bounds__(kBlock) k_outer_true_resid(SellView<double> S,
 }
 
 // The next B^_F starts from the residual r in the preconditioner's precision, f (null in FP64, which reads r itself), and
-// from u = 0; the kernels that form r write both. Each launch costs an iteration 3 to 5 us: with the
-// conversions, the zeroing and the scalars' way to the host as launches and a copy of their own, a solve took 1.58 ms
-// instead of 1.47 (4,096 unknowns, FP64), 4.09 instead of 3.97 (100,000, FP32) and 8.91 instead of 8.73 (1M, FP32).
+// from u = 0; the kernels that form r write both. Each launch costs an iteration 3 to 5 us: with the conversions, the
+// zeroing and the scalars' way to the host as launches and a copy of their own, a solve took 1.58 ms instead of 1.47
+// (4,096 unknowns, FP64), 4.09 instead of 3.97 (100,000, FP32) and 8.91 instead of 8.73 (1M, FP32).
 template <class T>
 __device__ __forceinline__ void bhat_input(int64_t i, double r, T *__restrict__ f, T *__restrict__ u) {
   if constexpr (!std::is_same<T, double>::value) f[i] = static_cast<T>(r);
@@ -3360,19 +3361,24 @@ static void launch_engine(amg_hierarchy *h, int top) {
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Whole-solve workgroup: the serving form for the smallest systems (plan_wg). One workgroup runs a complete solve of one system
-// (outer flexible CG, fine-level block smoother, the coarse cycle through the step interpreter, the convergence
+// Whole-solve workgroup: the serving form for the smallest systems (plan_wg). One workgroup runs a complete solve of one
+// system (outer flexible CG, fine-level block smoother, the coarse cycle through the step interpreter, the convergence
 // test) with no host round trip; a batch of systems is one launch with one workgroup per system, so the result of
 // a system does not depend on what else is in the batch.
 
 constexpr int64_t kWgMaxRows = 65536;   // of a system that shares its launches with others
 // Such a system is a whole-solve workgroup up to kWgSolveMax unknowns and where the hierarchy has no specialised engine;
-// otherwise its launches are shared with the batch's others (solve_many). Measured, FP32 preconditioner, one system
-// and 64 alike, workgroups against launches in step: 784 unknowns 1.08 and 1.26 against 1.67 and 1.84 ms; 2,500 unknowns
-// 1.85 and 2.36 against 1.75 and 2.10; 3,844 unknowns 2.99 and 4.09 against 2.15 and 2.68; 10,000 unknowns (one) 4.98
-// against 1.99; 63,504 unknowns 38.5 and 55.0 against 3.3 and 13.1. The general engine's plan (1.3 KB of arguments)
-// limits a launch to 12 systems, and its 1024 threads to one at a time on a CU: 64 systems of 4,900 unknowns took 4.6
-// against 12.0.
+// otherwise its launches are shared with the batch's others (solve_many). Measured for 1 / 64 / 256 systems alike, ms as
+// workgroups against launches in step:
+//   unknowns   FP32 preconditioner                       FP64
+//        784   1.10 / 1.26 / 2.04  1.47 / 1.61 / 2.05    1.23 / 1.48 / 2.11  1.51 / 1.56 / 2.19
+//      2,500   1.89 / 2.35 / 3.29  1.50 / 1.82 / 3.11    2.42 / 3.10 / 4.43  1.55 / 1.91 / 3.81
+//      3,136   2.29 / 2.89 / 4.02  1.66 / 2.00 / 3.76    2.89 / 3.76 / 5.26  1.68 / 2.09 / 4.42
+// so the line lies between 784 and 2,500 unknowns; meshes of 1,444 and 2,025 have far couplings on the engine's levels and
+// take the workgroup either way. Of 256 systems of 10,000 (FP64) the workgroups take 13.9 ms against 13.1, of 19,044 33.9
+// against 34.2, and FP32 23.8 against 20.1; 64 systems of 63,504 take 55 against 13.2. The general engine's plan (1.3 KB
+// of arguments) limits a launch by value to 12 systems, and its 1024 threads to one at a time on a CU: 64 systems of 4,900
+// unknowns took 4.6 ms as workgroups and 12.0 in step with it.
 constexpr int64_t kWgSolveMax = 2500;
 
 template <class T>
@@ -3680,7 +3686,8 @@ static bool level_tiled(const amg_hierarchy *h, int l) {
 // Super-cells of a level up to which its tiles have 8 instead of 16 to a side. Small squares spread a level over more
 // CUs but stage and relax more ring rows (2.7 rows relaxed per row kept with the products, against 1.7). Measured in
 // FP32: 6.5 us instead of 7.6 per post-smoothing tile on 16,384 super-cells (256 workgroups), but 15.6 instead of
-// 10.5 us on 65,536.
+// 10.5 us on 65,536. With the line at 4,096 / 16,384 / 65,536 a solve of 66,049 unknowns takes 3.02 / 2.92 / 3.00 ms in
+// FP32 and 4.05 / 3.93 / 3.99 in FP64, one of 264,196 takes 5.46 / 5.32 / 5.56 and 7.50 / 7.34 / 7.73.
 constexpr int64_t kTileSmall = 16384;
 static int64_t tile_grid(const QuadLevel &Q) { return (Q.n >> 2) / ((Q.n >> 2) <= kTileSmall ? 64 : 256); }
 // B~ of a tiled level with one sweep forms A u and its inner products in the last tile of each B^; the partial sums of
@@ -4359,13 +4366,13 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
 
 // ---------------------------------------------------------------------------------------------------------------
 // Several systems in step. A small system's iteration is a chain of short launches that leave most of the chip idle, so
-// a batch runs one chain for all: every system records its pieces of the outer iteration once, and each launch takes
-// the systems that are at that step (run_lists). A system runs the kernels, grids and reductions of amg_solve, so its
-// result is amg_solve's bit for bit, whatever else is in the batch. After each iteration the host reads the systems'
-// scalars from pinned memory and drops those that are done.
+// a batch runs one chain for all: a hierarchy's setup records the pieces of its outer iteration (record_batch), and each
+// launch takes the systems, up to kManySystems of them, that are at that step (run_lists). A system runs the kernels,
+// grids and reductions of amg_solve, so its result is amg_solve's bit for bit, whatever else is in the batch. After each
+// iteration the host reads the systems' scalars from pinned memory and drops those that are done.
 // A whole-solve workgroup is bound by one CU's gathers (about 50 clocks per 64-lane gather) and by latency: eight systems
 // of 10,000 to 63,504 unknowns (FP32 preconditioner) took 37.2 ms so, 2.6 ms per iteration of the largest; in step they
-// take 5.4, bound by the launches' chain (about 60 in an iteration).
+// take 5.4, bound by the launches' chain (about 60 in an iteration). Recording costs a setup about 10 us.
 
 enum { LL_START = 0, LL_ITER = 1, LL_CHECK = 5, LL_RESTART = 6, LL_END = 7, LL_ZERO = 8, LL_COUNT = 9 };
 struct BatchLists {
@@ -4471,8 +4478,8 @@ static amg_status batch_run(BatchSys *Y, int m, ListCursor *cur, const LaunchLis
 }
 
 // Solve the m systems Y on stream s; cur, lists, steps: room for m entries each.
-static amg_status solve_many_lists(BatchSys *Y, int m, ListCursor *cur, const LaunchList **lists, const LaunchStep **steps,
-                             hipStream_t s) {
+static amg_status solve_many_lists(BatchSys *Y, int m, ListCursor *cur, const LaunchList **lists,
+                                   const LaunchStep **steps, hipStream_t s) {
   for (int i = 0; i < m; i += kManySystems) {  // where the caller's vectors are
     BatchIoTable T;
     const int k = std::min(kManySystems, m - i);
