@@ -37,7 +37,7 @@
 //    registers that no level of theirs uses.
 // Before, with operators and vectors of the levels below the top in LDS, neighbours by index arithmetic, two
 // reductions per second inner step and the coarsest solve in one wavefront, a launch took 71.6 us (FP32, k = 6) and
-// 27.3 us (FP64, k = 5); now 31.3 and 15.1 us. Of the FP32 launch's 39 us with a clock read after every step, the
+// 27.3 us (FP64, k = 5); now 31.8 and 15.3 us. Of the FP32 launch's 39 us with a clock read after every step, the
 // prologue takes 4, the 4,096-cell level 9, the 1,024-cell level 9 and the eight B^ of the 256-cell level 17, where a
 // color phase is 0.1 us (one LDS round trip, nine products), the coarsest solve 0.45 and a reduction 0.25 us.
 
@@ -216,7 +216,8 @@ __device__ __forceinline__ T fe_row(const T (&a)[9], const T (&own)[4], const T 
 // the level's pre- and post-smoothing planes and the correction's plane at the thread's place (less one row and one
 // column); a thread's second super-cell lies 16 rows on. `act`: the thread belongs to the level (all threads call,
 // or, for a level of one wavefront, its threads). TOP: the reciprocals of the diagonals are formed on the way, each
-// when its rows are first needed. DIV: divisions in place of reciprocals. put(t, g) hands the restricted residual to the next level, child(half) runs that.
+// when its rows are first needed. DIV: divisions in place of reciprocals. put(t, g) hands the restricted residual to the
+// next level, child(half) runs that.
 template <class T, int K, int TR, int W, bool WAVE, bool TOP, bool DIV, class Put, class Child, class Out>
 __device__ __forceinline__ void fe_btilde(FeRows<T, TR> &R, T *A, T *B, const T *E, bool act, int wl, double *red,
                                           Put put, Child child, Out out) {
@@ -642,7 +643,8 @@ size_t fe_cfg_bytes(int id) {
 
 template <class T, int KT>
 const void *fe_kernel_of(bool div) {
-  return div ? reinterpret_cast<const void *>(k_engine_div<T, KT>) : reinterpret_cast<const void *>(k_engine_fast<T, KT>);
+  return div ? reinterpret_cast<const void *>(k_engine_div<T, KT>)
+             : reinterpret_cast<const void *>(k_engine_fast<T, KT>);
 }
 const void *fe_kernel(int id, bool div) {
   switch (id) {
@@ -703,8 +705,8 @@ void fe_launch(amg_hierarchy *h, int pi) {
 
 }  // namespace
 
-// The configuration a precision's small levels have the shape of, or -1: the top is the largest level the registers allow,
-// k = min(L, 6) in FP32, min(L, 5) in FP64.
+// The configuration a precision's small levels have the shape of, or -1: the top is the largest level the registers
+// allow, k = min(L, 6) in FP32, min(L, 5) in FP64.
 int engine_fast_config(const amg_hierarchy *h, int pi) {
   if (h->use_engine != 1 || h->nlev < 3 || h->L < 4 || h->lev[h->nlev - 1].k != 3 || h->nc != kFeCoarse ||
       h->opt.sweeps != 1 || h->opt.inner_iters != 2)

@@ -19,8 +19,8 @@
 //  - the FP64 coarsest solve takes eight columns per thread.
 // On the top level couplings beyond one cell are allowed (OVF): rows that have some are marked once, and coupled rows of
 // one color see the values from before their phase.
-// One launch takes 82 us (FP32) and 134 us (FP64) on level 4, where B~ of that level took 30 launches and about 390 us. Of
-// the FP32 launch the sixteen color phases of level 4 take 1.0 us each (0.5 without the operator's loads: a CU reads
+// One launch takes 84 us (FP32) and 139 us (FP64) on level 4, where B~ of that level took 30 launches and about 390 us.
+// Of the FP32 launch the sixteen color phases of level 4 take 1.0 us each (0.5 without the operator's loads: a CU reads
 // 35 to 50 bytes per clock from L2), a color phase of level 3 0.24 us (0.4 with the 64 rows in one wavefront).
 // Taken alone the kernel brought an FP32-preconditioned solve of the heat step with 1,020,100 unknowns from 28.0 to
 // 15.2 ms, one in FP64 with 8,820 from 6.1 to 3.5 ms.
