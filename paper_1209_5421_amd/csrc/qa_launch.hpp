@@ -79,6 +79,8 @@ struct KCall {
 // launches or more, one behind the other and each far from filling the chip: 7.0 ms instead of 3.0 for systems of 2,601
 // unknowns (FP32 preconditioner), 22.2 instead of 13.1 for 10,000 (FP64); a whole-solve workgroup each takes 3.3 and 13.9.
 // By address alone 64 systems of 63,504 unknowns took 13.5 ms instead of 13.2.
+// A system's one word says its grid and which of the two it is: with the choice in a word of its own a workgroup waited
+// twice before its arguments (2,601 unknowns: 64 systems 1.82 instead of 1.70 ms, 128 systems 2.20 instead of 2.09).
 // A call's workgroups are blockIdx.x < grid. From kAlignGrid workgroups on, the launch's grid is rounded up to a multiple
 // of eight, so that workgroup b of every system runs on XCD b mod 8; smaller grids are left as they are, since the empty
 // places would leave XCDs idle (rounded too, the 256 systems of 2,601, of 3 to 12 workgroups a step, took 4.2 ms).
@@ -90,10 +92,12 @@ constexpr int many_cap() {
 }
 template <class P>
 struct Many {
-  unsigned grid[kManySystems];
-  unsigned by_value;
-  // the calls by value, or where they are
-  alignas(16) unsigned char call[std::max(many_cap<P>() * sizeof(P), kManySystems * sizeof(const P *))];
+  static constexpr int cap = many_cap<P>();
+  static constexpr size_t calls = (4 * cap + 15) / 16 * 16;  // where the calls begin, by value,
+  static constexpr size_t places = 4 * kManySystems;         // or their addresses
+  static constexpr unsigned by_address = 1u << 31;
+  // a word for each system, its grid and by_address; then the calls or their addresses
+  alignas(16) unsigned char bytes[std::max(calls + cap * sizeof(P), places + kManySystems * sizeof(const P *))];
 };
 template <int NT, class P>
 __global__ void __launch_bounds__(NT) k_many(Many<P>) {
@@ -103,11 +107,10 @@ __global__ void __launch_bounds__(NT) k_many(Many<P>) {
   using Word = const __attribute__((address_space(4))) unsigned;
   using Place = const __attribute__((address_space(4))) unsigned long long;
   Byte *m = (Byte *)__builtin_amdgcn_kernarg_segment_ptr();
-  const unsigned y = blockIdx.y;
-  if (blockIdx.x >= *(Word *)(m + offsetof(Many<P>, grid) + 4 * y)) return;
-  Byte *call = m + offsetof(Many<P>, call);
-  if (*(Word *)(m + offsetof(Many<P>, by_value))) call += y * sizeof(P);
-  else call = (Byte *)*(Place *)(call + 8 * y);
+  const unsigned y = blockIdx.y, w = *(Word *)(m + 4 * y);
+  if (blockIdx.x >= (w & ~Many<P>::by_address)) return;
+  Byte *call = m + Many<P>::calls + y * sizeof(P);
+  if (w & Many<P>::by_address) call = (Byte *)*(Place *)(m + Many<P>::places + 8 * y);
   ((const P *)call)->run();
 }
 
@@ -152,17 +155,18 @@ hipError_t run_many(const LaunchList *const *lists, const LaunchStep *const *ste
   for (int i = 0; i < count; i += kManySystems) {
     Many<P> m;
     const int k = std::min(kManySystems, count - i);
-    m.by_value = k <= many_cap<P>();
+    const bool by_value = k <= Many<P>::cap;
     unsigned grid = 1, lds = 0;
     for (int j = 0; j < k; j++) {
       const LaunchStep &t = *steps[i + j];
-      if (m.by_value) {
-        std::memcpy(m.call + j * sizeof(P), lists[i + j]->host + t.at, sizeof(P));
+      const unsigned word = t.grid | (by_value ? 0 : Many<P>::by_address);
+      std::memcpy(m.bytes + 4 * j, &word, 4);
+      if (by_value) {
+        std::memcpy(m.bytes + Many<P>::calls + j * sizeof(P), lists[i + j]->host + t.at, sizeof(P));
       } else {
         const unsigned char *at = lists[i + j]->dev + t.at;
-        std::memcpy(m.call + j * sizeof(at), &at, sizeof(at));
+        std::memcpy(m.bytes + Many<P>::places + j * sizeof(at), &at, sizeof(at));
       }
-      m.grid[j] = t.grid;
       grid = std::max(grid, t.grid);
       lds = std::max(lds, t.lds);
     }
