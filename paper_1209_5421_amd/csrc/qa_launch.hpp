@@ -77,7 +77,7 @@ struct KCall {
 // arguments: a workgroup then has its call's arguments after one wait. A launch for more systems names where the arguments
 // lie in device memory, each hierarchy's own, written at its setup. By value alone a step of 256 systems took four
 // launches or more, one behind the other and each far from filling the chip: 7.0 ms instead of 3.0 for systems of 2,601
-// unknowns (FP32 preconditioner), 22.2 instead of 13.1 for 10,000 (FP64); a whole-solve workgroup each takes 3.3 and 13.9.
+// unknowns (FP32 preconditioner), 22.3 instead of 13.7 for 10,000 (FP64); a whole-solve workgroup each takes 3.4 and 13.9.
 // By address alone 64 systems of 63,504 unknowns took 13.5 ms instead of 13.2.
 // A system's one word says its grid and which of the two it is: with the choice in a word of its own a workgroup waited
 // twice before its arguments (2,601 unknowns: 64 systems 1.82 instead of 1.70 ms, 128 systems 2.20 instead of 2.09).

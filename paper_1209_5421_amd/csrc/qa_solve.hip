@@ -3371,12 +3371,12 @@ constexpr int64_t kWgMaxRows = 65536;   // of a system that shares its launches 
 // otherwise its launches are shared with the batch's others (solve_many). Measured for 1 / 64 / 256 systems alike, ms as
 // workgroups against launches in step:
 //   unknowns   FP32 preconditioner                       FP64
-//        784   1.10 / 1.26 / 2.04  1.47 / 1.61 / 2.05    1.23 / 1.48 / 2.11  1.51 / 1.56 / 2.19
-//      2,500   1.89 / 2.35 / 3.29  1.50 / 1.82 / 3.11    2.42 / 3.10 / 4.43  1.55 / 1.91 / 3.81
-//      3,136   2.29 / 2.89 / 4.02  1.66 / 2.00 / 3.76    2.89 / 3.76 / 5.26  1.68 / 2.09 / 4.42
+//        784   1.10 / 1.26 / 2.04  1.43 / 1.56 / 2.03    1.22 / 1.48 / 2.05  1.44 / 1.63 / 2.08
+//      2,500   1.89 / 2.38 / 3.30  1.55 / 1.74 / 3.00    2.41 / 3.10 / 4.36  1.53 / 1.86 / 3.58
+//      3,136   2.29 / 2.92 / 4.01  1.61 / 1.94 / 3.63    2.88 / 3.76 / 5.18  1.65 / 2.07 / 4.22
 // so the line lies between 784 and 2,500 unknowns; meshes of 1,444 and 2,025 have far couplings on the engine's levels and
-// take the workgroup either way. Of 256 systems of 10,000 (FP64) the workgroups take 13.9 ms against 13.1, of 19,044 33.9
-// against 34.2, and FP32 23.8 against 20.1; 64 systems of 63,504 take 55 against 13.2. The general engine's plan (1.3 KB
+// take the workgroup either way. 256 systems of 10,000 (FP64) take 13.9 ms against 13.7, of 19,044 34.2 against 34.1, and
+// with FP32 24.1 against 19.9; 64 systems of 63,504 take 55.1 against 13.1, in FP64 68.1 against 20.1. The general engine's plan (1.3 KB
 // of arguments) limits a launch by value to 12 systems, and its 1024 threads to one at a time on a CU: 64 systems of 4,900
 // unknowns took 4.6 ms as workgroups and 12.0 in step with it.
 constexpr int64_t kWgSolveMax = 2500;
@@ -4372,7 +4372,7 @@ static amg_status solve_impl(amg_hierarchy *h, const double *b, double *x, doubl
 // iteration the host reads the systems' scalars from pinned memory and drops those that are done.
 // A whole-solve workgroup is bound by one CU's gathers (about 50 clocks per 64-lane gather) and by latency: eight systems
 // of 10,000 to 63,504 unknowns (FP32 preconditioner) took 37.2 ms so, 2.6 ms per iteration of the largest; in step they
-// take 5.4, bound by the launches' chain (about 60 in an iteration). Recording costs a setup about 10 us.
+// take 5.6, bound by the launches' chain (about 60 in an iteration). Recording costs a setup about 10 us.
 
 enum { LL_START = 0, LL_ITER = 1, LL_CHECK = 5, LL_RESTART = 6, LL_END = 7, LL_ZERO = 8, LL_COUNT = 9 };
 struct BatchLists {
