@@ -32,3 +32,20 @@ def test_many_systems_equal_amg_solve(count, noalloc):
         y, one = h.solve(b)
         assert info["iters"] == one["iters"] and info["relres"] == one["relres"] and torch.equal(x, y), i
         h.close()
+
+
+# every count up to 64, so that each kernel meets its own limit of calls by value and the counts on either side of it
+@pytest.mark.parametrize("precision", [0, 1])
+def test_every_count_equals_amg_solve(precision):
+    from paper_1209_5421_amd import amg
+    print(f"[batch counts] precision {precision}", flush=True)
+    p = mg.jittered_problem(53, rhs_seed=53, fast=True)
+    hs = [amg.Hierarchy.from_problem(p, precision=precision) for _ in range(64)]
+    bs = [T(p.b) * (1.0 + i) for i in range(64)]
+    ref = [h.solve(b)[0] for h, b in zip(hs, bs)]
+    for count in range(1, 65):
+        xs = [torch.full_like(b, float("nan")) for b in bs[:count]]
+        code, _ = amg.solve_batch(hs[:count], bs[:count], xs, [1e-8] * count)
+        assert code == 0 and all(torch.equal(x, y) for x, y in zip(xs, ref)), count
+    for h in hs:
+        h.close()
